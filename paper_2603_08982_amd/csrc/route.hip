@@ -6,8 +6,10 @@
 // "Sort, prefix-sum the costs, cut at the budget" is done without a sort: the cut is the
 // first block, in (score desc, index asc) order, whose inclusive cumulative cost exceeds
 // the budget. Each block gets a unique 64-bit key that is monotone in that order; an
-// 8-pass, most-significant-byte-first radix descent over cost histograms finds the key K*
-// of the cut exactly (integer arithmetic only), and block (a,b) is routed iff key > K*.
+// most-significant-digit-first radix descent over cost histograms finds the key K* of the cut
+// exactly (integer arithmetic only), and block (a,b) is routed iff key > K*. A head with many
+// blocks is cut by many workgroups: they build one 12-bit histogram of it, collect the blocks of
+// the digit that crosses the budget, and one workgroup descends through those few alone.
 //
 // The adaptive per-query-cluster budgets (a reading of the top-p allocation the paper
 // inherits and does not define) use the same descent over integer mass weights.
@@ -52,23 +54,27 @@ struct CutState {
 // Walks n_items items in descending key order (keys unique) and returns the key of the first
 // one whose inclusive cumulative weight exceeds rem, or 0 if every item fits. visit(it, key,
 // weight) returns false for items that do not take part. Called by all threads of the block
-// (THREADS >= 256, a multiple of 64).
+// (THREADS >= 256, a multiple of 64). With open_bits < 64 the items share the key bits above
+// those, `prefix`.
 // Items are visited four at a time per thread, all their loads issued before the first
 // histogram update; the digit of the cut is found by a 256-wide scan of the histogram from
 // the top digit down (four waves, shuffles), not by one thread walking it. As soon as the
 // digit that crosses holds a single item, that item is the cut and one more walk fetches its
 // key (scores are mostly distinct, so this happens after three or four of the eight digits).
 template <int THREADS, class Visit>
-__device__ __forceinline__ unsigned long long radix_cut(CutState& st, long long rem, int n_items, Visit visit) {
+__device__ __forceinline__ unsigned long long radix_cut(CutState& st, long long rem, int n_items, Visit visit,
+                                                        int open_bits = 64, unsigned long long prefix0 = 0ull) {
   constexpr int U = 4;
   static_assert(THREADS >= 256 && THREADS % 64 == 0, "the histogram scan uses the first four waves");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (threadIdx.x == 0) {
     st.remaining = rem > 0 ? rem : 0;
-    st.prefix = 0ull;
+    st.prefix = prefix0;
   }
-  for (int pass = 0; pass < 8; ++pass) {
-    const int shift = 56 - 8 * pass;
+  for (int pass = 0; open_bits > 0; ++pass) {
+    const int width = open_bits < 8 ? open_bits : 8, above = open_bits;
+    const int shift = open_bits - width;
+    open_bits = shift;
     for (int i = threadIdx.x; i < 256; i += THREADS) {
       st.hist[i] = 0ull;
       st.count[i] = 0u;
@@ -88,12 +94,12 @@ __device__ __forceinline__ unsigned long long radix_cut(CutState& st, long long 
       for (int u = 0; u < U; ++u) {
         const int it = base + u * THREADS + (int)threadIdx.x;
         on[u] = it < n_items && visit(it, key[u], weight[u]);
-        on[u] = on[u] && (pass == 0 || (key[u] >> (shift + 8)) == prefix);
+        on[u] = on[u] && (above == 64 || (key[u] >> above) == prefix);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (!on[u]) continue;
-        const int digit = (int)((key[u] >> shift) & 255u);
+        const int digit = (int)((key[u] >> shift) & ((1u << width) - 1u));
         atomicAdd(&st.hist[digit], weight[u]);
         atomicAdd(&st.count[digit], 1u);
       }
@@ -116,15 +122,15 @@ __device__ __forceinline__ unsigned long long radix_cut(CutState& st, long long 
       for (int w = 0; w < wave; ++w) incl += st.wave_total[w];
       if (incl > left && incl - h <= left) {  // the first digit that does not fit: one thread at most
         st.remaining = left - (incl - h);
-        st.prefix = (prefix << 8) | (unsigned long long)(255 - threadIdx.x);
+        st.prefix = (prefix << width) | (unsigned long long)(255 - threadIdx.x);
         st.crossed[pass & 1] = 1;
         st.single = st.count[255 - threadIdx.x] == 1u;
       }
     }
     __syncthreads();
     if (!st.crossed[pass & 1]) return 0ull;  // everything fits (can only happen on the first pass)
-    if (st.single && pass < 7) {
-      const unsigned long long found = st.prefix;  // the leading 8 (pass + 1) bits of the cut
+    if (st.single && shift > 0) {
+      const unsigned long long found = st.prefix;  // the leading bits of the cut
       __syncthreads();
       for (int base = 0; base < n_items; base += THREADS) {
         const int it = base + (int)threadIdx.x;
@@ -161,7 +167,7 @@ select_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_of
     const int64_t qa = qo[seg + 1] - qo[seg];
     rem = (budget * qa) / (Nq > 0 ? Nq : 1) - qa * tk;
   } else {
-    rem = budget - (tq * Nk + (Nq - tq) * tk);
+    rem = budget - (tq * Nk + (Nq - tq) * tk);  // the text row and the text column come first
   }
   const unsigned long long cut = radix_cut<kSelThreads>(st, rem, n_items, [&](int it, uint64_t& key,
                                                                               unsigned long long& weight) {
@@ -238,11 +244,50 @@ top_p_budget_kernel(const float* __restrict__ sbar, const float* __restrict__ mr
   if (threadIdx.x == 0) row_budget[(int64_t)bh * Cq + a] = qa * (int64_t)sh_keys;
 }
 
+// Mask words and routed blocks of row a of a head (a whole wave): returns the count and adds the
+// lane's share of the cost. 64 consecutive key clusters per step (coalesced score loads), two mask
+// words per ballot.
+__device__ __forceinline__ int mask_row(const float* sc, const int32_t* qo, const int32_t* ko, int Cq, int Ck, int a,
+                                        uint64_t ks, uint32_t* words, long long& cost) {
+  const int Cc = Ck + 1, W = (Cc + 31) / 32, lane = threadIdx.x & 63;
+  const int64_t qa = qo[a + 1] - qo[a];
+  int cnt = 0;
+  for (int b0 = 0; b0 < W * 32; b0 += 64) {
+    const int b = b0 + lane;
+    bool on = false;
+    if (qa > 0 && b < Cc) {
+      const int64_t kb = ko[b + 1] - ko[b];
+      if (kb > 0) {
+        on = (a == Cq) || (b == Ck);
+        if (!on) on = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b)) > ks;
+        if (on) cost += qa * kb;
+      }
+    }
+    const unsigned long long bits = __ballot(on);
+    cnt += __popcll(bits);
+    if (lane == 0) {
+      words[b0 >> 5] = (uint32_t)bits;
+      if ((b0 >> 5) + 1 < W) words[(b0 >> 5) + 1] = (uint32_t)(bits >> 32);
+    }
+  }
+  return cnt;
+}
+
+// The set bits of a row, ascending, to ci[pos ...] (a whole wave, a lane per bit).
+__device__ __forceinline__ void list_row(const uint32_t* words, int W, int32_t pos, int32_t* ci) {
+  const int lane = threadIdx.x & 63;
+  for (int w0 = 0; w0 < W; w0 += 2) {
+    unsigned long long bits = words[w0];
+    if (w0 + 1 < W) bits |= (unsigned long long)words[w0 + 1] << 32;
+    if ((bits >> lane) & 1ull) ci[pos + __popcll(bits & ((1ull << lane) - 1ull))] = w0 * 32 + lane;
+    pos += __popcll(bits);
+  }
+}
+
 constexpr int kBuildThreads = 1024;
 
-// grid (BH). Builds the bit mask, the CSR lists and the routed cost from K*. A wave takes a
-// row of blocks at a time, 64 consecutive key clusters per step (coalesced score loads), and
-// forms two mask words with one ballot.
+// grid (BH). Builds the bit mask, the CSR lists and the routed cost of a head from K* in one launch
+// (heads of fewer than kWideItems blocks), a wave per row of blocks.
 __global__ void __launch_bounds__(kBuildThreads)
 build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
              const int32_t* __restrict__ k_offsets, int Cq, int Ck, int per_row,
@@ -261,27 +306,8 @@ build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_off
   __syncthreads();
   long long my_cost = 0;
   for (int a = wave; a < R; a += NWAVES) {
-    const int64_t qa = qo[a + 1] - qo[a];
     const uint64_t ks = (a < Cq) ? kstar[(int64_t)bh * (per_row ? Cq : 1) + (per_row ? a : 0)] : 0ull;
-    int cnt = 0;
-    for (int b0 = 0; b0 < W * 32; b0 += 64) {
-      const int b = b0 + lane;
-      bool on = false;
-      if (qa > 0 && b < Cc) {
-        const int64_t kb = ko[b + 1] - ko[b];
-        if (kb > 0) {
-          on = (a == Cq) || (b == Ck);
-          if (!on) on = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b)) > ks;
-          if (on) my_cost += qa * kb;
-        }
-      }
-      const unsigned long long bits = __ballot(on);
-      cnt += __popcll(bits);
-      if (lane == 0) {
-        mb[a * W + (b0 >> 5)] = (uint32_t)bits;
-        if ((b0 >> 5) + 1 < W) mb[a * W + (b0 >> 5) + 1] = (uint32_t)(bits >> 32);
-      }
-    }
+    const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, ks, mb + (int64_t)a * W, my_cost);
     if (lane == 0) rowcnt[a] = cnt;
   }
 #pragma unroll
@@ -302,17 +328,218 @@ build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_off
     routed_cost[bh] = (int64_t)cost_sum;
   }
   __syncthreads();
-  // routed key clusters of every row, ascending: a wave per row, a lane per set bit
+  // routed key clusters of every row, ascending
   int32_t* ci = col_idx + (int64_t)bh * R * Cc;
-  for (int a = wave; a < R; a += NWAVES) {
-    int32_t pos = rowcnt[a];
-    for (int w0 = 0; w0 < W; w0 += 2) {
-      unsigned long long bits = mb[a * W + w0];
-      if (w0 + 1 < W) bits |= (unsigned long long)mb[a * W + w0 + 1] << 32;
-      if ((bits >> lane) & 1ull) ci[pos + __popcll(bits & ((1ull << lane) - 1ull))] = w0 * 32 + lane;
-      pos += __popcll(bits);
-    }
+  for (int a = wave; a < R; a += NWAVES) list_row(mb + (int64_t)a * W, W, rowcnt[a], ci);
+}
+
+// ---- one budget over many blocks ---------------------------------------------------------
+// What bounds the cut of a head is reading its scores and, with one workgroup per head, the one
+// CU that does it: 300 x 1000 blocks of 40 heads took select_kernel 1.69 ms (four to five walks
+// over 1.2 MB, LDS atomics on the dozen exponents that an 8-bit digit tells apart) and
+// build_kernel 0.35 ms on 40 of 256 CUs. From kWideItems blocks a head on the work is spread:
+// two streaming passes over all CUs, after which a single workgroup sees only the blocks of one
+// 12-bit digit (an eighth of an octave of scores, a few thousand blocks). Measured at 300 x 1000
+// x 40 heads: cut, mask and lists 2.04 -> 0.25 ms (the whole call 3.75 -> 2.06). Below that size one workgroup walks a head's scores in a few
+// microseconds and the extra launches (three more) would cost more than they spread.
+constexpr int kWideItems = 16384;
+constexpr int kHistBits = 12, kHistBins = 1 << kHistBits;
+constexpr int kHistThreads = 512;
+constexpr int kHistItems = 16 * kHistThreads;  // blocks per workgroup of the streaming passes
+
+struct HeadCut {
+  unsigned long long hist[kHistBins];  // summed cost by leading digit
+  long long remaining;                 // budget left for the digit that crosses
+  int digit;                           // that digit, -1: everything fits
+  unsigned int n_cand;                 // blocks collected of it
+};
+
+// Clears what the passes below add to (kernels, not memory sets: the call may be captured).
+__global__ void __launch_bounds__(256)
+route_clear_kernel(HeadCut* __restrict__ cuts, int64_t* __restrict__ routed_cost) {
+  HeadCut& hc = cuts[blockIdx.y];
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < kHistBins) hc.hist[i] = 0ull;
+  if (i == 0) {
+    hc.n_cand = 0u;
+    routed_cost[blockIdx.y] = 0;
   }
+}
+
+// Cost of block i of a head (0: one side is empty).
+__device__ __forceinline__ unsigned long long block_cost(const int32_t* qo, const int32_t* ko, int i, int Ck) {
+  const int a = (int)((unsigned)i / (unsigned)Ck), b = i - a * Ck;
+  const int64_t qa = qo[a + 1] - qo[a], kb = ko[b + 1] - ko[b];
+  return qa > 0 && kb > 0 ? (unsigned long long)(qa * kb) : 0ull;
+}
+
+// grid (ceil(Cq Ck / kHistItems), BH)
+__global__ void __launch_bounds__(kHistThreads)
+route_hist_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
+                  const int32_t* __restrict__ k_offsets, int Cq, int Ck, HeadCut* __restrict__ cuts) {
+  __shared__ unsigned long long h[kHistBins];
+  const int bh = blockIdx.y, n_items = Cq * Ck;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const float* sc = scores + (int64_t)bh * Cq * Ck;
+  for (int i = threadIdx.x; i < kHistBins; i += kHistThreads) h[i] = 0ull;
+  __syncthreads();
+  const int lo = blockIdx.x * kHistItems + threadIdx.x;
+  float v[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) v[u] = lo + u * kHistThreads < n_items ? sc[lo + u * kHistThreads] : 0.f;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int i = lo + u * kHistThreads;
+    if (i >= n_items) break;
+    const unsigned long long cost = block_cost(qo, ko, i, Ck);
+    if (cost) atomicAdd(&h[(int)(block_key(v[u], (uint32_t)i) >> (64 - kHistBits))], cost);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kHistBins; i += kHistThreads)
+    if (h[i]) atomicAdd(&cuts[bh].hist[i], h[i]);
+}
+
+// Finds the digit that crosses the budget (every workgroup for itself: 32 KB of L2) and collects
+// the indices of its blocks, in any order: keys are unique, so the order does not matter.
+__global__ void __launch_bounds__(kHistThreads)
+route_collect_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
+                     const int32_t* __restrict__ k_offsets, int Cq, int Ck, int64_t budget, HeadCut* __restrict__ cuts,
+                     uint32_t* __restrict__ cand) {
+  constexpr int PER = kHistBins / kHistThreads;
+  __shared__ long long wave_total[kHistThreads / 64];
+  __shared__ int digit_s;
+  const int bh = blockIdx.y, n_items = Cq * Ck, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const float* sc = scores + (int64_t)bh * Cq * Ck;
+  HeadCut& hc = cuts[bh];
+  const int64_t Nq = qo[Cq + 1], Nk = ko[Ck + 1];
+  const int64_t tq = qo[Cq + 1] - qo[Cq], tk = ko[Ck + 1] - ko[Ck];
+  const long long rem = budget - (tq * Nk + (Nq - tq) * tk), left = rem > 0 ? rem : 0;
+  const int top = kHistBins - 1 - PER * (int)threadIdx.x;  // this thread's digits: top, top - 1, ...
+  long long h[PER], sum = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    h[u] = (long long)hc.hist[top - u];
+    sum += h[u];
+  }
+  long long incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) wave_total[wave] = incl;
+  if (threadIdx.x == 0) digit_s = -1;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) incl += wave_total[w];
+  if (incl > left && incl - sum <= left) {  // one thread at most
+    long long run = incl - sum;
+    int u = 0;
+    while (run + h[u] <= left) run += h[u++];
+    digit_s = top - u;
+    if (blockIdx.x == 0) hc.remaining = left - run;
+  }
+  __syncthreads();
+  const int digit = digit_s;
+  if (blockIdx.x == 0 && threadIdx.x == 0) hc.digit = digit;
+  if (digit < 0) return;
+  const int lo = blockIdx.x * kHistItems + threadIdx.x;
+  float v[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) v[u] = lo + u * kHistThreads < n_items ? sc[lo + u * kHistThreads] : 0.f;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int i = lo + u * kHistThreads;
+    const bool on = i < n_items && (int)(block_key(v[u], (uint32_t)i) >> (64 - kHistBits)) == digit &&
+                    block_cost(qo, ko, i, Ck) != 0ull;
+    const unsigned long long votes = __ballot(on);
+    if (!votes) continue;
+    const int leader = __ffsll((long long)votes) - 1;
+    unsigned int at = 0;
+    if (lane == leader) at = atomicAdd(&hc.n_cand, (unsigned int)__popcll(votes));
+    at = __shfl(at, leader) + (unsigned int)__popcll(votes & ((1ull << lane) - 1ull));
+    if (on) cand[(int64_t)bh * n_items + at] = (uint32_t)i;
+  }
+}
+
+// grid (BH): the cut among the collected blocks
+__global__ void __launch_bounds__(kSelThreads)
+route_cut_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
+                 const int32_t* __restrict__ k_offsets, int Cq, int Ck, const HeadCut* __restrict__ cuts,
+                 const uint32_t* __restrict__ cand, uint64_t* __restrict__ kstar) {
+  __shared__ CutState st;
+  const int bh = blockIdx.x, n_items = Cq * Ck;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const float* sc = scores + (int64_t)bh * n_items;
+  const uint32_t* list = cand + (int64_t)bh * n_items;
+  const HeadCut& hc = cuts[bh];
+  unsigned long long cut = 0ull;
+  if (hc.digit >= 0)
+    cut = radix_cut<kSelThreads>(st, hc.remaining, (int)hc.n_cand, [&](int it, uint64_t& key, unsigned long long& weight) {
+      const uint32_t i = list[it];
+      key = block_key(sc[i], i);
+      weight = block_cost(qo, ko, (int)i, Ck);
+      return true;
+    }, 64 - kHistBits, (unsigned long long)hc.digit);
+  if (threadIdx.x == 0) kstar[bh] = cut;
+}
+
+// grid (ceil((Cq + 1) / 4), BH): mask words, routed blocks and routed cost, a wave per row of blocks
+__global__ void __launch_bounds__(256)
+route_mask_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
+                  const int32_t* __restrict__ k_offsets, int Cq, int Ck, int per_row,
+                  const uint64_t* __restrict__ kstar, uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_count,
+                  int64_t* __restrict__ routed_cost) {
+  const int bh = blockIdx.y, lane = threadIdx.x & 63, a = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int R = Cq + 1, W = (Ck + 1 + 31) / 32;
+  if (a >= R) return;
+  long long cost = 0;
+  const int cnt = mask_row(scores + (int64_t)bh * Cq * Ck, q_offsets + (int64_t)bh * (Cq + 2),
+                           k_offsets + (int64_t)bh * (Ck + 2), Cq, Ck, a,
+                           a < Cq ? kstar[(int64_t)bh * (per_row ? Cq : 1) + (per_row ? a : 0)] : 0ull,
+                           mask_bits + ((int64_t)bh * R + a) * W, cost);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
+  if (lane == 0) {
+    row_count[(int64_t)bh * R + a] = cnt;
+    if (cost) atomicAdd(reinterpret_cast<unsigned long long*>(routed_cost + bh), (unsigned long long)cost);
+  }
+}
+
+// grid (ceil((Cq + 1) / kListRows), BH): row_ptr and col_idx of kListRows rows; the routed blocks of
+// the rows before them are summed by the workgroup itself
+constexpr int kListRows = 16;
+__global__ void __launch_bounds__(256)
+route_lists_kernel(int Cq, int Ck, const uint32_t* __restrict__ mask_bits, const int32_t* __restrict__ row_count,
+                   int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx) {
+  __shared__ int32_t part[4], start[kListRows + 1];
+  const int bh = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
+  const int a0 = blockIdx.x * kListRows, n = min(kListRows, R - a0);
+  const int32_t* rc = row_count + (int64_t)bh * R;
+  int32_t before = 0;
+  for (int a = threadIdx.x; a < a0; a += 256) before += rc[a];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+  if (lane == 0) part[wave] = before;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t run = part[0] + part[1] + part[2] + part[3];
+    for (int u = 0; u < n; ++u) {
+      start[u] = run;
+      run += rc[a0 + u];
+    }
+    start[n] = run;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < n || ((int)threadIdx.x == n && a0 + n == R))
+    row_ptr[(int64_t)bh * (R + 1) + a0 + threadIdx.x] = start[threadIdx.x];
+  int32_t* ci = col_idx + (int64_t)bh * R * Cc;
+  for (int u = wave; u < n; u += 4)
+    list_row(mask_bits + ((int64_t)bh * R + a0 + u) * W, W, start[u], ci);
 }
 
 }  // namespace
@@ -325,7 +552,9 @@ extern "C" size_t svgear_probe_route_workspace(int B, int H, int64_t Nk, int d, 
   const size_t BH = (size_t)B * H;
   return align_up(BH * Cq * Ck * 4, 256) + align_up(BH * Cq * 4, 256) + align_up(BH * (Cq + 1) * 8, 256) +
          // bf16 probe: qbar in three bf16 pieces (operand order), per-key value statistics
-         align_up(BH * align_up(Cq, 32) * d * 3 * 2, 256) + 2 * align_up(BH * probe_stat_stride(Nk) * 4, 256);
+         align_up(BH * align_up(Cq, 32) * d * 3 * 2, 256) + 2 * align_up(BH * probe_stat_stride(Nk) * 4, 256) +
+         // many blocks: cost histograms, routed blocks per row (the candidates reuse the centroid logits' place)
+         align_up(BH * sizeof(HeadCut), 256) + align_up(BH * (Cq + 1) * 4, 256);
 }
 
 namespace {
@@ -362,6 +591,8 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
   bf16_t* q3 = w.take<bf16_t>((size_t)BH * align_up(Cq, 32) * (d > 0 ? d : 1) * 3);
   float* nd = w.take<float>((size_t)BH * probe_stat_stride(Nk));
   float* dd = w.take<float>((size_t)BH * probe_stat_stride(Nk));
+  HeadCut* cuts = w.take<HeadCut>(BH);
+  int32_t* row_count = w.take<int32_t>((size_t)BH * (Cq + 1));
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!given) {
@@ -382,11 +613,36 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
         sbar, mrow, q_offsets, k_offsets, Cq, Ck, top_p, row_budget);
     SVGEAR_LAUNCH_CHECK();
   }
-  select_kernel<<<dim3(per_row ? Cq : 1, BH), kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost,
-                                                                  per_row, adaptive ? row_budget : nullptr, kstar);
+  const int64_t n_items = (int64_t)Cq * Ck;
+  const bool wide = n_items >= kWideItems;
+  if (wide) {
+    route_clear_kernel<<<dim3(kHistBins / 256, BH), 256, 0, s>>>(cuts, routed_cost);
+    SVGEAR_LAUNCH_CHECK();
+  }
+  if (wide && !per_row) {
+    const dim3 grid((unsigned)ceil_div(n_items, kHistItems), BH);
+    uint32_t* cand = reinterpret_cast<uint32_t*>(sbar);  // the probe is done with the centroid logits
+    route_hist_kernel<<<grid, kHistThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, cuts);
+    SVGEAR_LAUNCH_CHECK();
+    route_collect_kernel<<<grid, kHistThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost, cuts, cand);
+    SVGEAR_LAUNCH_CHECK();
+    route_cut_kernel<<<BH, kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, cuts, cand, kstar);
+  } else {  // few blocks, or a budget for every row of them: a workgroup walks all that share a budget
+    select_kernel<<<dim3(per_row ? Cq : 1, BH), kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost,
+                                                                    per_row, adaptive ? row_budget : nullptr, kstar);
+  }
   SVGEAR_LAUNCH_CHECK();
-  build_kernel<<<BH, kBuildThreads, (Cq + 2) * sizeof(int32_t), s>>>(scores, q_offsets, k_offsets, Cq, Ck, per_row, kstar,
-                                                          mask_bits, row_ptr, col_idx, routed_cost);
+  if (wide) {
+    route_mask_kernel<<<dim3((unsigned)ceil_div(Cq + 1, 4), BH), 256, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck,
+                                                                             per_row, kstar, mask_bits, row_count,
+                                                                             routed_cost);
+    SVGEAR_LAUNCH_CHECK();
+    route_lists_kernel<<<dim3((unsigned)ceil_div(Cq + 1, kListRows), BH), 256, 0, s>>>(Cq, Ck, mask_bits, row_count,
+                                                                                      row_ptr, col_idx);
+  } else {
+    build_kernel<<<BH, kBuildThreads, (Cq + 2) * sizeof(int32_t), s>>>(scores, q_offsets, k_offsets, Cq, Ck, per_row,
+                                                                      kstar, mask_bits, row_ptr, col_idx, routed_cost);
+  }
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
 }
