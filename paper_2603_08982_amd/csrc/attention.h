@@ -7,6 +7,7 @@ namespace svgear {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int BN = 64;  // keys per tile
+constexpr int kZeros = 128;  // floats in the fp32 kernel's row of zeros
 
 struct AttnArgs {
   const void* qp;
@@ -44,6 +45,11 @@ struct AttnArgs {
   const int32_t* tok_perm;
   Strides q_st, out_st;
   int H;
+  // fp32 kernel: a row of zeros, and where the keys of a tile are split the partial rows with their
+  // (maximum, sum)
+  float* zeros;
+  float* part_o;
+  float2* part_ml;
 };
 
 // Element offset of query row `row` of head bh.
@@ -79,6 +85,12 @@ int plan_d128(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s);
 size_t attn_bf16_lds_bytes(int d, int Ck);
 // Launches the bf16 MFMA kernel over `total` (multiple of 8) workgroups.
 int launch_attn_bf16(const AttnArgs& a, int d, unsigned total, hipStream_t s);
+
+// fp32 kernel: query rows per workgroup tile, scratch beside the tile list (it starts with the row of
+// zeros that plan_kernel writes) and launch.
+int attn_f32_bm();
+size_t f32_partial_bytes(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d);
+int launch_attn_f32(AttnArgs& a, int d, unsigned total, void* ws, size_t ws_bytes, hipStream_t s);
 
 // out = merge of (o1, lse1) and (o2, lse2), partial softmax results over disjoint key sets.
 int launch_merge(const bf16_t* o1, const float* lse1, const bf16_t* o2, const float* lse2, int64_t rows, int d,

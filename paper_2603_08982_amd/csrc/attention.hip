@@ -16,35 +16,76 @@
 // single query (lane%32) and row max / row sum need one cross-lane exchange (with lane^32)
 // instead of a butterfly; exp2'd scores are then already in B-operand layout for
 // O^T += V^T P^T. V tiles are transposed on their way into LDS.
-// fp32 kernel: one query row per lane, plain fp32 FMAs (the fp32 reference-quality path).
+// fp32 kernel: the same decomposition on the fp32 matrix cores (attention_f32.hip).
 #include "attention.h"
 
 namespace svgear {
 namespace {
 
 // ------------------------------------------------------------------------------ plan
-// Tile list of every head: tile -> (query cluster, first row). One workgroup per head.
-__global__ void __launch_bounds__(256)
-plan_kernel(const int32_t* __restrict__ q_offsets, int Cq, int BM, int max_tiles, int32_t* __restrict__ tile_a,
-            int32_t* __restrict__ tile_row0, int32_t* __restrict__ n_tiles) {
-  extern __shared__ int32_t first[];  // Cq+2
-  const int bh = blockIdx.x, R = Cq + 1;
+// Tile list of every head: tile -> (query cluster, first row). One workgroup per head. With at most
+// kPlanSort clusters the tiles of the clusters that route the most keys come first: lists differ
+// by two orders of magnitude, and a long one that starts last has the chip to itself (measured on
+// the fp32 kernel at 8 heads x 5,957 rows: 0.58 -> 0.51 ms).
+constexpr int kPlanThreads = 1024, kPlanSort = 1024;
+__global__ void __launch_bounds__(kPlanThreads)
+plan_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
+            const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int Cq, int Ck, int BM,
+            int max_tiles, int32_t* __restrict__ tile_a, int32_t* __restrict__ tile_row0, int32_t* __restrict__ n_tiles,
+            float* __restrict__ zeros) {
+  extern __shared__ int32_t first[];  // Cq+2: tiles of the clusters, then their first tile, in list order
+  __shared__ int32_t len[kPlanSort], order[kPlanSort];
+  const int bh = blockIdx.x, R = Cq + 1, Cc = Ck + 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
-  for (int a = threadIdx.x; a < R; a += 256) first[a] = (qo[a + 1] - qo[a] + BM - 1) / BM;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int a = 0; a < R; ++a) {
-      const int c = first[a];
-      first[a] = run;
-      run += c;
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
+  const bool sorted = R <= kPlanSort;
+  if (zeros && bh == 0 && threadIdx.x < kZeros) zeros[threadIdx.x] = 0.f;
+  if (sorted) {
+    for (int a = wave; a < R; a += kPlanThreads / 64) {  // a wave per cluster, its lanes over the routed key clusters
+      const int32_t* ci = col_idx + (int64_t)bh * R * Cc + rp[a];
+      const int ne = rp[a + 1] - rp[a];
+      int n = 0;
+      for (int e = lane; e < ne; e += 64) n += max(ko[ci[e] + 1] - ko[ci[e]], 0);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+      if (lane == 0) len[a] = n;
     }
-    first[R] = run;
-    n_tiles[bh] = run < max_tiles ? run : max_tiles;
+    __syncthreads();
+    for (int a = threadIdx.x; a < R; a += kPlanThreads) {
+      int rank = 0;
+      for (int b = 0; b < R; ++b) rank += len[b] > len[a] || (len[b] == len[a] && b < a);
+      order[rank] = a;
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < R; i += kPlanThreads) {
+    const int a = sorted ? order[i] : i;
+    first[i] = (qo[a + 1] - qo[a] + BM - 1) / BM;
   }
   __syncthreads();
-  for (int a = threadIdx.x; a < R; a += 256) {
-    const int lo = first[a], hi = first[a + 1];
+  if (wave == 0) {
+    int carry = 0;
+    for (int i0 = 0; i0 < R; i0 += 64) {
+      const int i = i0 + lane, c = i < R ? first[i] : 0;
+      int incl = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+      }
+      if (i < R) first[i] = carry + incl - c;
+      carry += __shfl(incl, 63);
+    }
+    if (lane == 0) {
+      first[R] = carry;
+      n_tiles[bh] = carry < max_tiles ? carry : max_tiles;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < R; i += kPlanThreads) {
+    const int a = sorted ? order[i] : i;
+    const int lo = first[i], hi = first[i + 1];
     for (int t = lo; t < hi && t < max_tiles; ++t) {
       tile_a[(int64_t)bh * max_tiles + t] = a;
       tile_row0[(int64_t)bh * max_tiles + t] = qo[a] + (t - lo) * BM;
@@ -61,160 +102,19 @@ __global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __re
   else dst1[i] = f32_to_bf16(src1[i]);
 }
 
-// ------------------------------------------------------------------------------ fp32
-template <int D>
-__global__ void __launch_bounds__(64)
-attn_f32_kernel(AttnArgs p) {
-  constexpr int TK = 16;
-  __shared__ float4 ks[TK * D / 4];
-  __shared__ float4 vs[TK * D / 4];
-  const int bh = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x;
-  if (tile >= p.n_tiles[bh]) return;
-  const int Cq = p.Cq, Ck = p.Ck, R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
-  const int a = p.tile_a[(int64_t)bh * p.max_tiles + tile];
-  const int row0 = p.tile_row0[(int64_t)bh * p.max_tiles + tile];
-  const int32_t* qo = p.q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = p.k_offsets + (int64_t)bh * (Ck + 2);
-  const int row_end = qo[a + 1];
-  const int row = row0 + tid;
-  const bool valid = row < row_end;
-  const float* kh = static_cast<const float*>(p.kp) + (int64_t)bh * p.Nk * D;
-  const float* vh = static_cast<const float*>(p.vp) + (int64_t)bh * p.Nk * D;
-  const float c = p.scale * kLog2e;
-  float q[D], acc[D];
-  {
-    const float4* qr = reinterpret_cast<const float4*>(static_cast<const float*>(p.qp) +
-                                                       q_row_offset(p, bh, valid ? row : row_end - 1, D));
-#pragma unroll
-    for (int t = 0; t < D / 4; ++t) {
-      const float4 v = qr[t];
-      q[4 * t] = v.x; q[4 * t + 1] = v.y; q[4 * t + 2] = v.z; q[4 * t + 3] = v.w;
-      acc[4 * t] = acc[4 * t + 1] = acc[4 * t + 2] = acc[4 * t + 3] = 0.f;
-    }
-  }
-  float m = -INFINITY, l = 0.f;
-  const int32_t* rp = p.row_ptr + (int64_t)bh * (R + 1);
-  const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + rp[a];
-  const int ne = rp[a + 1] - rp[a];
-  for (int e = 0; e < ne; ++e) {
-    const int b = ci[e];
-    const int kend = ko[b + 1];
-    for (int j0 = ko[b]; j0 < kend; j0 += TK) {
-      const int nk = min(TK, kend - j0);
-      __syncthreads();
-      const float4* ksrc = reinterpret_cast<const float4*>(kh + (int64_t)j0 * D);
-      const float4* vsrc = reinterpret_cast<const float4*>(vh + (int64_t)j0 * D);
-      for (int i = tid; i < nk * D / 4; i += 64) {
-        ks[i] = ksrc[i];
-        vs[i] = vsrc[i];
-      }
-      __syncthreads();
-      float s[TK];
-      float mx = m;
-#pragma unroll
-      for (int kk = 0; kk < TK; ++kk) {
-        s[kk] = -INFINITY;
-        if (kk < nk) {
-          float dot = 0.f;
-#pragma unroll
-          for (int t = 0; t < D / 4; ++t) {
-            const float4 v = ks[kk * (D / 4) + t];
-            dot = __builtin_fmaf(q[4 * t], v.x, dot);
-            dot = __builtin_fmaf(q[4 * t + 1], v.y, dot);
-            dot = __builtin_fmaf(q[4 * t + 2], v.z, dot);
-            dot = __builtin_fmaf(q[4 * t + 3], v.w, dot);
-          }
-          s[kk] = dot * c;
-          mx = fmaxf(mx, s[kk]);
-        }
-      }
-      if (mx > m) {
-        const float alpha = exp2f(m - mx);
-        l *= alpha;
-#pragma unroll
-        for (int t = 0; t < D; ++t) acc[t] *= alpha;
-        m = mx;
-      }
-#pragma unroll
-      for (int kk = 0; kk < TK; ++kk) {
-        if (kk < nk) {
-          const float pr = exp2f(s[kk] - m);
-          l += pr;
-#pragma unroll
-          for (int t = 0; t < D / 4; ++t) {
-            const float4 v = vs[kk * (D / 4) + t];
-            acc[4 * t] = __builtin_fmaf(pr, v.x, acc[4 * t]);
-            acc[4 * t + 1] = __builtin_fmaf(pr, v.y, acc[4 * t + 1]);
-            acc[4 * t + 2] = __builtin_fmaf(pr, v.z, acc[4 * t + 2]);
-            acc[4 * t + 3] = __builtin_fmaf(pr, v.w, acc[4 * t + 3]);
-          }
-        }
-      }
-    }
-  }
-  // compensation: every non-routed, non-empty key cluster as one pseudo-key
-  if (a < Cq) {
-    const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
-    for (int b = 0; b < Ck; ++b) {
-      const int sz = ko[b + 1] - ko[b];
-      if (sz <= 0 || mask_bit(mrow, b)) continue;
-      const float4* kb = reinterpret_cast<const float4*>(p.kbar + ((int64_t)bh * Ck + b) * D);
-      const float4* vb = reinterpret_cast<const float4*>(p.vbar + ((int64_t)bh * Ck + b) * D);
-      float dot = 0.f;
-#pragma unroll
-      for (int t = 0; t < D / 4; ++t) {
-        const float4 v = kb[t];
-        dot = __builtin_fmaf(q[4 * t], v.x, dot);
-        dot = __builtin_fmaf(q[4 * t + 1], v.y, dot);
-        dot = __builtin_fmaf(q[4 * t + 2], v.z, dot);
-        dot = __builtin_fmaf(q[4 * t + 3], v.w, dot);
-      }
-      const float s = __builtin_fmaf(dot, c, log2f((float)sz));
-      if (s > m) {
-        const float alpha = exp2f(m - s);
-        l *= alpha;
-#pragma unroll
-        for (int t = 0; t < D; ++t) acc[t] *= alpha;
-        m = s;
-      }
-      const float pr = exp2f(s - m);
-      l += pr;
-#pragma unroll
-      for (int t = 0; t < D / 4; ++t) {
-        const float4 v = vb[t];
-        acc[4 * t] = __builtin_fmaf(pr, v.x, acc[4 * t]);
-        acc[4 * t + 1] = __builtin_fmaf(pr, v.y, acc[4 * t + 1]);
-        acc[4 * t + 2] = __builtin_fmaf(pr, v.z, acc[4 * t + 2]);
-        acc[4 * t + 3] = __builtin_fmaf(pr, v.w, acc[4 * t + 3]);
-      }
-    }
-  }
-  if (valid) {
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
-    int64_t lse_idx;
-    float4* o = reinterpret_cast<float4*>(static_cast<float*>(p.op) + out_row_offset(p, bh, row, D, lse_idx));
-#pragma unroll
-    for (int t = 0; t < D / 4; ++t)
-      o[t] = make_float4(acc[4 * t] * inv, acc[4 * t + 1] * inv, acc[4 * t + 2] * inv, acc[4 * t + 3] * inv);
-    if (p.lse) p.lse[lse_idx] = (m + log2f(l)) * kLn2;
-  }
-}
-
-
 }  // namespace
 }  // namespace svgear
 
 using namespace svgear;
 
-static int attn_bm(svgear_dtype dt, int d) { return dt == SVGEAR_F32 ? 64 : attn_bf16_bm(d); }
+static int attn_bm(svgear_dtype dt, int d) { return dt == SVGEAR_F32 ? attn_f32_bm() : attn_bf16_bm(d); }
 
 extern "C" size_t svgear_sparse_attn_comp_workspace(int B, int H, int64_t Nq, int64_t Nk, int d, int Cq, int Ck) {
-  (void)Nk;
   if (B <= 0 || H <= 0 || Nq <= 0 || Cq <= 0 || Ck <= 0 || d <= 0) return 0;
   const size_t BH = (size_t)B * H;
-  const size_t max_tiles = (size_t)ceil_div(Nq, 64) + Cq + 1;  // bound for either tile height
+  const size_t max_tiles = (size_t)ceil_div(Nq, 32) + Cq + 1;  // bound for every tile height
   return 2 * align_up(BH * max_tiles * 4, 256) + align_up(BH * 4, 256) + 2 * align_up(BH * Ck * d * 2, 256) +
-         plan_d128_workspace((int)BH, Cq, Nq);
+         plan_d128_workspace((int)BH, Cq, Nq) + f32_partial_bytes((int64_t)BH, Nq, Nk, Cq, d);
 }
 
 static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype dt, const float* kbar,
@@ -253,37 +153,33 @@ static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype
   Workspace w(ws, ws_bytes);
   const int BM = attn_bm(dt, d);
   const int max_tiles = (int)(ceil_div(Nq, BM) + Cq + 1);
-  const size_t cap = (size_t)ceil_div(Nq, 64) + Cq + 1;
+  const size_t cap = (size_t)ceil_div(Nq, 32) + Cq + 1;
   int32_t* tile_a = w.take<int32_t>((size_t)BH * cap);
   int32_t* tile_row0 = w.take<int32_t>((size_t)BH * cap);
   int32_t* n_tiles = w.take<int32_t>(BH);
   bf16_t* kbar16 = w.take<bf16_t>((size_t)BH * Ck * d);
   bf16_t* vbar16 = w.take<bf16_t>((size_t)BH * Ck * d);
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
+  char* rest = static_cast<char*>(ws) + w.used;  // work lists (d = 128 bf16), or zeros and partial rows (fp32)
+  const size_t rest_bytes = ws_bytes - w.used;
   if (!(dt == SVGEAR_BF16 && d == 128)) {  // the d = 128 bf16 kernel has work lists of its own (plan_d128)
-    plan_kernel<<<BH, 256, (Cq + 2) * sizeof(int32_t), s>>>(q_offsets, Cq, BM, max_tiles, tile_a, tile_row0, n_tiles);
+    plan_kernel<<<BH, kPlanThreads, (Cq + 2) * sizeof(int32_t), s>>>(
+        q_offsets, k_offsets, row_ptr, col_idx, Cq, Ck, BM, max_tiles, tile_a, tile_row0, n_tiles,
+        dt == SVGEAR_F32 ? reinterpret_cast<float*>(rest) : nullptr);
     SVGEAR_LAUNCH_CHECK();
   }
   AttnArgs a{qp, kp, vp, kbar, vbar, kbar16, vbar16, q_offsets, k_offsets, mask_bits, row_ptr, col_idx,
              tile_a, tile_row0, n_tiles, nullptr, nullptr, nullptr, nullptr, nullptr,
-             Nq, Nk, BH, Cq, Ck, max_tiles, scale, op, lse, part, tok_perm, q_st, out_st, H};
-  if (dt == SVGEAR_F32) {
-    dim3 grid(max_tiles, BH);
-    if (d == 64)
-      attn_f32_kernel<64><<<grid, 64, 0, s>>>(a);
-    else
-      attn_f32_kernel<128><<<grid, 64, 0, s>>>(a);
-    SVGEAR_LAUNCH_CHECK();
-    return SVGEAR_OK;
-  }
+             Nq, Nk, BH, Cq, Ck, max_tiles, scale, op, lse, part, tok_perm, q_st, out_st, H, nullptr, nullptr, nullptr};
+  const unsigned total = (unsigned)align_up((size_t)BH * max_tiles, 8);
+  if (dt == SVGEAR_F32) return launch_attn_f32(a, d, total, rest, rest_bytes, s);
   const int64_t n = (int64_t)BH * Ck * d;
   to_bf16_kernel<<<dim3((unsigned)ceil_div(n, 256), 2), 256, 0, s>>>(kbar, vbar, n, kbar16, vbar16);
   SVGEAR_LAUNCH_CHECK();
   if (d == 128) {
-    const int rc = plan_d128(a, static_cast<char*>(ws) + w.used, ws_bytes - w.used, s);
+    const int rc = plan_d128(a, rest, rest_bytes, s);
     if (rc != SVGEAR_OK) return rc;
   }
-  const unsigned total = (unsigned)align_up((size_t)BH * max_tiles, 8);
   return launch_attn_bf16(a, d, total, s);
 }
 

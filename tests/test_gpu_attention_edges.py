@@ -1,0 +1,99 @@
+"""GPU attention kernels where their tiles and lists can go wrong: query clusters of 1 to a few
+hundred rows around the tile heights (32-row blocks, tiles of 128 and 384 rows), key clusters
+around the 32- and 64-key tiles, empty ones, text rows, no / some / all blocks routed, few query
+tiles with many keys (the keys of a tile split over workgroups) and the reverse, against the
+definition in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_08982_amd as sv
+from helpers import dev, mask_to_bits, csr_from_mask
+
+pytestmark = pytest.mark.gpu
+
+Q_EDGES = [1, 31, 0, 32, 33, 64, 127, 128, 129, 0, 383, 385]
+K_EDGES = [0, 1, 31, 32, 33, 63, 64, 65, 0, 127, 200, 5, 17, 96, 255, 0]
+# rel-L2 of the output and largest log-sum-exp error. fp32: d products and N weights per sum, each
+# rounded to 2^-24, errors of either sign: a few 1e-7 (measured 7e-7); bf16: rounded probabilities, values
+# and outputs, 2^-9 each
+TOL = {torch.float32: (3e-6, 2e-5), torch.bfloat16: (1e-2, 2e-2)}
+
+
+def _sizes(name, rng):
+    if name == "edges":
+        return Q_EDGES, K_EDGES, 13
+    if name == "few_rows":  # a handful of tiles over thousands of keys
+        return [40, 3], list(rng.integers(1, 90, 120)), 0
+    if name == "many_rows":
+        return list(rng.integers(1, 70, 150)), [7, 90], 1
+    return [130, 64], list(rng.integers(0, 3, 900)), 40  # hundreds of tiny clusters
+
+
+def _definition(Q, K, V, kbar, vbar, qs, ks, mask, scale):
+    rows_of = np.repeat(np.arange(len(qs)), qs)
+    keys_of = np.repeat(np.arange(len(ks)), ks)
+    on = torch.from_numpy(mask)
+    s = (Q @ K.t()) * scale
+    s.masked_fill_(~on[rows_of][:, keys_of], -np.inf)
+    n = torch.tensor(ks[:-1], dtype=torch.float64)
+    c = (Q @ kbar.t()) * scale + torch.log(n)[None]
+    c.masked_fill_(on[rows_of][:, : len(ks) - 1] | torch.from_numpy(rows_of == len(qs) - 1)[:, None], -np.inf)
+    lse = torch.logsumexp(torch.cat([s, c], 1), 1, keepdim=True)
+    return torch.exp(s - lse) @ V + torch.exp(c - lse) @ vbar, lse[:, 0]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters"])
+@pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
+def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
+    rng = np.random.default_rng(3)
+    qs, ks, tail = _sizes(name, rng)
+    qs, ks = np.array(list(qs) + [tail]), np.array(list(ks) + [tail])
+    Cq, Ck, Nq, Nk = len(qs) - 1, len(ks) - 1, int(qs.sum()), int(ks.sum())
+    H, scale = 2, float(d) ** -0.5
+    g = torch.Generator().manual_seed(11)
+    Q, K, V = (torch.randn(1, H, n, d, generator=g).to(dtype) for n in (Nq, Nk, Nk))
+    kbar, vbar = (torch.randn(1, H, Ck, d, generator=g).to(torch.bfloat16).float() for _ in range(2))
+    masks, bits, ptrs, cols = [], [], [], []
+    for h in range(H):
+        m = rng.random((Cq + 1, Ck + 1)) < density
+        m[Cq], m[:, Ck] = True, True
+        m &= np.outer(qs > 0, ks > 0)
+        masks.append(m)
+        bits.append(torch.from_numpy(mask_to_bits(m, Cq, Ck).view(np.int32)))
+        ptr, col = csr_from_mask(m)
+        ptrs.append(torch.from_numpy(ptr))
+        cols.append(torch.from_numpy(col))
+    # keys of a cluster that no query cluster of a head routes are never looked at, whatever they hold
+    unseen = [b for b in range(Ck) if ks[b] and not any(m[:Cq, b].any() for m in masks) and tail == 0]
+    off = np.concatenate([[0], np.cumsum(ks)])
+    Kx, Vx = K.clone(), V.clone()
+    if dtype == torch.float32:
+        for b in unseen:
+            Kx[:, :, off[b]:off[b + 1]] = float("nan")
+            Vx[:, :, off[b]:off[b + 1]] = float("inf")
+    offs = [torch.from_numpy(np.concatenate([[0], np.cumsum(x)]).astype(np.int32)).expand(1, H, -1).contiguous().to(dev())
+            for x in (qs, ks)]
+    lists = [torch.stack(x)[None].contiguous().to(dev()) for x in (bits, ptrs, cols)]
+    tables = [t.to(dev()) for t in (Kx, Vx, kbar, vbar)]
+    O, lse = sv.sparse_attn_comp(Q.to(dev()), *tables, *offs, *lists, scale, want_lse=True)
+    # the same through a permutation of the queries, which only moves rows
+    perm = torch.stack([torch.randperm(Nq, generator=g) for _ in range(H)])[None]
+    tokens = torch.empty_like(Q)
+    for h in range(H):
+        tokens[0, h, perm[0, h]] = Q[0, h]
+    O2, lse2 = sv.sparse_attn_comp(tokens.to(dev()), *tables, *offs, *lists, scale, want_lse=True,
+                                   q_perm=perm.int().contiguous().to(dev()))
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref, ref_lse = _definition(Q[0, h].double(), K[0, h].double(), V[0, h].double(), kbar[0, h].double(),
+                                   vbar[0, h].double(), qs, ks, masks[h], scale)
+        got, got_lse = O[0, h].cpu(), lse[0, h].cpu()
+        none = torch.isinf(ref_lse)  # text rows of a head without text keys see nothing
+        assert torch.equal(torch.isinf(got_lse), none) and not got[none].any()
+        err = (got.double() - ref)[~none].norm() / ref[~none].norm()
+        assert err <= TOL[dtype][0], f"head {h}: rel-L2 {err:.3e}"
+        assert (got_lse.double() - ref_lse)[~none].abs().max() <= TOL[dtype][1]
+        assert torch.equal(O2[0, h].cpu()[perm[0, h]], got) and torch.equal(lse2[0, h].cpu()[perm[0, h]], got_lse)
