@@ -7,7 +7,6 @@ namespace svgear {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int BN = 64;  // keys per tile
-constexpr int kZeros = 128;  // floats in the fp32 kernel's row of zeros
 
 struct AttnArgs {
   const void* qp;
@@ -22,10 +21,10 @@ struct AttnArgs {
   const uint32_t* mask_bits;
   const int32_t* row_ptr;
   const int32_t* col_idx;
-  const int32_t* tile_a;
+  const int32_t* tile_a;  // tile lists of the fp32 kernel
   const int32_t* tile_row0;
   const int32_t* n_tiles;
-  // work lists of the d = 128 bf16 kernel (see plan_d128): tiles sorted longest first and
+  // work lists of the bf16 kernel (see plan_bf16): tiles sorted longest first and
   // dealt to 8 lists, one per XCD; sched_x = [8] first slot, [8] tile count, [8] next counter
   const int32_t* sched_bh;
   const int32_t* sched_a;
@@ -72,25 +71,21 @@ __device__ __forceinline__ int64_t out_row_offset(const AttnArgs& p, int bh, int
 __device__ __forceinline__ bool mask_bit(const uint32_t* mrow, int b) { return (mrow[b >> 5] >> (b & 31)) & 1u; }
 
 
-// Waves per workgroup of the generic bf16 kernel (32 query rows per wave).
-constexpr int kBf16Waves = 4;
-// Query rows per workgroup tile of the bf16 kernel used for head dimension d.
-int attn_bf16_bm(int d);
+// Query rows per workgroup tile of the bf16 kernel.
+int attn_bf16_bm();
 
-// Workspace of the d = 128 work lists (bytes) and their construction on stream s.
-size_t plan_d128_workspace(int BH, int Cq, int64_t Nq);
-int plan_d128(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s);
+// Workspace of its work lists (bytes) and their construction on stream s.
+size_t plan_bf16_workspace(int BH, int Cq, int64_t Nq);
+int plan_bf16(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s);
 
-// LDS bytes the bf16 kernel needs for head dimension d and Ck key clusters.
-size_t attn_bf16_lds_bytes(int d, int Ck);
+// Whether it takes Ck key clusters at head dimension d.
+bool attn_bf16_supported(int d, int Ck);
 // Launches the bf16 MFMA kernel over `total` (multiple of 8) workgroups.
 int launch_attn_bf16(const AttnArgs& a, int d, unsigned total, hipStream_t s);
 
-// fp32 kernel: query rows per workgroup tile, scratch beside the tile list (it starts with the row of
-// zeros that plan_kernel writes) and launch.
-int attn_f32_bm();
-size_t f32_partial_bytes(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d);
-int launch_attn_f32(AttnArgs& a, int d, unsigned total, void* ws, size_t ws_bytes, hipStream_t s);
+// fp32 kernel: scratch and launch (with its tile lists).
+size_t f32_workspace(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d);
+int launch_attn_f32(AttnArgs& a, int d, void* ws, size_t ws_bytes, hipStream_t s);
 
 // out = merge of (o1, lse1) and (o2, lse2), partial softmax results over disjoint key sets.
 int launch_merge(const bf16_t* o1, const float* lse1, const bf16_t* o2, const float* lse2, int64_t rows, int d,

@@ -22,77 +22,6 @@
 namespace svgear {
 namespace {
 
-// ------------------------------------------------------------------------------ plan
-// Tile list of every head: tile -> (query cluster, first row). One workgroup per head. With at most
-// kPlanSort clusters the tiles of the clusters that route the most keys come first: lists differ
-// by two orders of magnitude, and a long one that starts last has the chip to itself (measured on
-// the fp32 kernel at 8 heads x 5,957 rows: 0.58 -> 0.51 ms).
-constexpr int kPlanThreads = 1024, kPlanSort = 1024;
-__global__ void __launch_bounds__(kPlanThreads)
-plan_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
-            const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int Cq, int Ck, int BM,
-            int max_tiles, int32_t* __restrict__ tile_a, int32_t* __restrict__ tile_row0, int32_t* __restrict__ n_tiles,
-            float* __restrict__ zeros) {
-  extern __shared__ int32_t first[];  // Cq+2: tiles of the clusters, then their first tile, in list order
-  __shared__ int32_t len[kPlanSort], order[kPlanSort];
-  const int bh = blockIdx.x, R = Cq + 1, Cc = Ck + 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
-  const int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
-  const bool sorted = R <= kPlanSort;
-  if (zeros && bh == 0 && threadIdx.x < kZeros) zeros[threadIdx.x] = 0.f;
-  if (sorted) {
-    for (int a = wave; a < R; a += kPlanThreads / 64) {  // a wave per cluster, its lanes over the routed key clusters
-      const int32_t* ci = col_idx + (int64_t)bh * R * Cc + rp[a];
-      const int ne = rp[a + 1] - rp[a];
-      int n = 0;
-      for (int e = lane; e < ne; e += 64) n += max(ko[ci[e] + 1] - ko[ci[e]], 0);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
-      if (lane == 0) len[a] = n;
-    }
-    __syncthreads();
-    for (int a = threadIdx.x; a < R; a += kPlanThreads) {
-      int rank = 0;
-      for (int b = 0; b < R; ++b) rank += len[b] > len[a] || (len[b] == len[a] && b < a);
-      order[rank] = a;
-    }
-    __syncthreads();
-  }
-  for (int i = threadIdx.x; i < R; i += kPlanThreads) {
-    const int a = sorted ? order[i] : i;
-    first[i] = (qo[a + 1] - qo[a] + BM - 1) / BM;
-  }
-  __syncthreads();
-  if (wave == 0) {
-    int carry = 0;
-    for (int i0 = 0; i0 < R; i0 += 64) {
-      const int i = i0 + lane, c = i < R ? first[i] : 0;
-      int incl = c;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-      }
-      if (i < R) first[i] = carry + incl - c;
-      carry += __shfl(incl, 63);
-    }
-    if (lane == 0) {
-      first[R] = carry;
-      n_tiles[bh] = carry < max_tiles ? carry : max_tiles;
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < R; i += kPlanThreads) {
-    const int a = sorted ? order[i] : i;
-    const int lo = first[i], hi = first[i + 1];
-    for (int t = lo; t < hi && t < max_tiles; ++t) {
-      tile_a[(int64_t)bh * max_tiles + t] = a;
-      tile_row0[(int64_t)bh * max_tiles + t] = qo[a] + (t - lo) * BM;
-    }
-  }
-}
-
 // Both centroid tables to bf16 in one launch (blockIdx.y picks the table).
 __global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __restrict__ src1, int64_t n,
                                bf16_t* __restrict__ dst0, bf16_t* __restrict__ dst1) {
@@ -107,14 +36,12 @@ __global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __re
 
 using namespace svgear;
 
-static int attn_bm(svgear_dtype dt, int d) { return dt == SVGEAR_F32 ? attn_f32_bm() : attn_bf16_bm(d); }
-
 extern "C" size_t svgear_sparse_attn_comp_workspace(int B, int H, int64_t Nq, int64_t Nk, int d, int Cq, int Ck) {
   if (B <= 0 || H <= 0 || Nq <= 0 || Cq <= 0 || Ck <= 0 || d <= 0) return 0;
   const size_t BH = (size_t)B * H;
-  const size_t max_tiles = (size_t)ceil_div(Nq, 32) + Cq + 1;  // bound for every tile height
-  return 2 * align_up(BH * max_tiles * 4, 256) + align_up(BH * 4, 256) + 2 * align_up(BH * Ck * d * 2, 256) +
-         plan_d128_workspace((int)BH, Cq, Nq) + f32_partial_bytes((int64_t)BH, Nq, Nk, Cq, d);
+  const size_t bf16 = 2 * align_up(BH * Ck * d * 2, 256) + plan_bf16_workspace((int)BH, Cq, Nq);
+  const size_t f32 = f32_workspace((int64_t)BH, Nq, Nk, Cq, d);
+  return bf16 > f32 ? bf16 : f32;
 }
 
 static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype dt, const float* kbar,
@@ -146,41 +73,26 @@ static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype
   const int BH = B * H;
   if ((int64_t)BH * ((int64_t)ceil_div(Nq, 64) + Cq + 1) > INT32_MAX / 2) return SVGEAR_ERR_UNSUPPORTED;
   if (part != 0 && !(dt == SVGEAR_BF16 && d == 128)) return SVGEAR_ERR_UNSUPPORTED;
-  if (dt == SVGEAR_BF16 && attn_bf16_lds_bytes(d, Ck) > 160 * 1024) return SVGEAR_ERR_UNSUPPORTED;
+  if (dt == SVGEAR_BF16 && !attn_bf16_supported(d, Ck)) return SVGEAR_ERR_UNSUPPORTED;
   // the d = 128 bf16 kernel addresses K/V rows of a head by 32-bit byte offsets (256 bytes a row)
   if (dt == SVGEAR_BF16 && d == 128 && Nk > (int64_t)(UINT32_MAX / 256)) return SVGEAR_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  AttnArgs a{qp, kp, vp, kbar, vbar, nullptr, nullptr, q_offsets, k_offsets, mask_bits, row_ptr, col_idx,
+             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+             Nq, Nk, BH, Cq, Ck, 0, scale, op, lse, part, tok_perm, q_st, out_st, H, nullptr, nullptr, nullptr};
+  if (dt == SVGEAR_F32) return launch_attn_f32(a, d, ws, ws_bytes, s);
   Workspace w(ws, ws_bytes);
-  const int BM = attn_bm(dt, d);
-  const int max_tiles = (int)(ceil_div(Nq, BM) + Cq + 1);
-  const size_t cap = (size_t)ceil_div(Nq, 32) + Cq + 1;
-  int32_t* tile_a = w.take<int32_t>((size_t)BH * cap);
-  int32_t* tile_row0 = w.take<int32_t>((size_t)BH * cap);
-  int32_t* n_tiles = w.take<int32_t>(BH);
   bf16_t* kbar16 = w.take<bf16_t>((size_t)BH * Ck * d);
   bf16_t* vbar16 = w.take<bf16_t>((size_t)BH * Ck * d);
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
-  char* rest = static_cast<char*>(ws) + w.used;  // work lists (d = 128 bf16), or zeros and partial rows (fp32)
-  const size_t rest_bytes = ws_bytes - w.used;
-  if (!(dt == SVGEAR_BF16 && d == 128)) {  // the d = 128 bf16 kernel has work lists of its own (plan_d128)
-    plan_kernel<<<BH, kPlanThreads, (Cq + 2) * sizeof(int32_t), s>>>(
-        q_offsets, k_offsets, row_ptr, col_idx, Cq, Ck, BM, max_tiles, tile_a, tile_row0, n_tiles,
-        dt == SVGEAR_F32 ? reinterpret_cast<float*>(rest) : nullptr);
-    SVGEAR_LAUNCH_CHECK();
-  }
-  AttnArgs a{qp, kp, vp, kbar, vbar, kbar16, vbar16, q_offsets, k_offsets, mask_bits, row_ptr, col_idx,
-             tile_a, tile_row0, n_tiles, nullptr, nullptr, nullptr, nullptr, nullptr,
-             Nq, Nk, BH, Cq, Ck, max_tiles, scale, op, lse, part, tok_perm, q_st, out_st, H, nullptr, nullptr, nullptr};
-  const unsigned total = (unsigned)align_up((size_t)BH * max_tiles, 8);
-  if (dt == SVGEAR_F32) return launch_attn_f32(a, d, total, rest, rest_bytes, s);
+  a.kbar16 = kbar16;
+  a.vbar16 = vbar16;
   const int64_t n = (int64_t)BH * Ck * d;
   to_bf16_kernel<<<dim3((unsigned)ceil_div(n, 256), 2), 256, 0, s>>>(kbar, vbar, n, kbar16, vbar16);
   SVGEAR_LAUNCH_CHECK();
-  if (d == 128) {
-    const int rc = plan_d128(a, rest, rest_bytes, s);
-    if (rc != SVGEAR_OK) return rc;
-  }
-  return launch_attn_bf16(a, d, total, s);
+  const int rc = plan_bf16(a, static_cast<char*>(ws) + w.used, ws_bytes - w.used, s);
+  if (rc != SVGEAR_OK) return rc;
+  return launch_attn_bf16(a, d, (unsigned)((size_t)BH * (ceil_div(Nq, attn_bf16_bm()) + Cq + 1)), s);
 }
 
 extern "C" int svgear_sparse_attn_comp(const void* qp, const void* kp, const void* vp, svgear_dtype dt,

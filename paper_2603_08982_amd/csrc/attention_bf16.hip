@@ -26,344 +26,24 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return c.u;
 }
 
-template <int D>
-struct Bf16Tile {
-  static constexpr int KROW = D + 8;         // bf16 per K row in LDS (16-byte pad: conflict-free b128 reads)
-  static constexpr int VROW = BN + 8;        // bf16 per V^T row in LDS
-  static constexpr int K_ELEMS = BN * KROW;  // per buffer
-  static constexpr int V_ELEMS = D * VROW;
-};
-
-static inline size_t lds_bytes_generic(int D, int Ck) {
-  const size_t kv = 2 * ((size_t)BN * (D + 8) + (size_t)D * (BN + 8)) * 2;
-  const size_t lw = (size_t)align_up(Ck, 64) * 4;
-  const size_t seg = (size_t)(2 * (Ck + 1) + 1) * 4;
-  return kv + 2 * BN * 4 + lw + align_up(seg, 16);
-}
-
-// NW waves of 32 query rows each.
-template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
-attn_bf16_kernel(AttnArgs p) {
-  constexpr int NT = 64 * NW;
-  constexpr int BM = 32 * NW;
-  constexpr int KS = D / 16;           // k-steps of the QK^T product
-  constexpr int DB = D / 32;           // 32-row blocks of O^T
-  constexpr int CPR = D / 8;           // 16-byte chunks per K/V row
-  constexpr int KCH = BN * CPR / NT;   // K chunks per thread
-  constexpr int VUNITS = 16 * CPR;     // (4-key group) x (8-dim group) units per V tile
-  constexpr int VCH = (VUNITS + NT - 1) / NT;
-  using TL = Bf16Tile<D>;
-  static_assert(BN * CPR % NT == 0, "tile/threads mismatch");
-  (void)BM;
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem);                       // [2][BN][KROW]
-  bf16_t* Vs = Ks + 2 * TL::K_ELEMS;                                  // [2][D][VROW]
-  int32_t* rowmap = reinterpret_cast<int32_t*>(Vs + 2 * TL::V_ELEMS);  // [2][BN]
-  float* lw = reinterpret_cast<float*>(rowmap + 2 * BN);              // [align64(Ck)]
-  int32_t* vstart = reinterpret_cast<int32_t*>(lw + ((p.Ck + 63) & ~63));  // [ne+1]
-  int32_t* pstart = vstart + (p.Ck + 2);                                    // [ne]
-
-  // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs; give each XCD one
-  // contiguous range of logical tiles so tiles that share routed K/V share an L2.
-  const int total = gridDim.x;
-  const int wg = blockIdx.x;
-  const int logical = (wg & 7) * (total >> 3) + (wg >> 3);
-  const int bh = logical / p.max_tiles, tile = logical % p.max_tiles;
-  if (bh >= p.BH || tile >= p.n_tiles[bh]) return;
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-  const int Cq = p.Cq, Ck = p.Ck, R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
-  const int a = p.tile_a[(int64_t)bh * p.max_tiles + tile];
-  const int row0 = p.tile_row0[(int64_t)bh * p.max_tiles + tile];
-  const int32_t* qo = p.q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = p.k_offsets + (int64_t)bh * (Ck + 2);
-  const int row_end = qo[a + 1];
-  const int32_t* rp = p.row_ptr + (int64_t)bh * (R + 1);
-  const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + rp[a];
-  const int ne = rp[a + 1] - rp[a];
-  const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
-
-  // ---- prologue: virtual key sequence of the routed clusters, compensation biases
-  if (wave == 0) {
-    int carry = 0;
-    for (int e0 = 0; e0 < ne; e0 += 64) {
-      const int e = e0 + lane;
-      int sz = 0;
-      if (e < ne) {
-        const int b = ci[e];
-        const int ps = ko[b];
-        sz = ko[b + 1] - ps;
-        sz = sz > 0 ? sz : 0;
-        pstart[e] = ps;
-      }
-      int incl = sz;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-      }
-      if (e < ne) vstart[e] = carry + incl - sz;
-      carry += __shfl(incl, 63);
-    }
-    if (lane == 0) vstart[ne] = carry;
-  }
-  for (int b = tid; b < ((Ck + 63) & ~63); b += NT) {
-    float v = -INFINITY;
-    if (b < Ck && a < Cq) {
-      const int sz = ko[b + 1] - ko[b];
-      if (sz > 0 && !mask_bit(mrow, b)) v = log2f((float)sz);
-    }
-    lw[b] = v;
-  }
-  __syncthreads();
-  const int n_r = vstart[ne];
-  const int nt_r = (n_r + BN - 1) / BN;
-  const int nt_c = (a < Cq) ? (Ck + BN - 1) / BN : 0;
-  const int T = nt_r + nt_c;
-
-  const bf16_t* kh = static_cast<const bf16_t*>(p.kp) + (int64_t)bh * p.Nk * D;
-  const bf16_t* vh = static_cast<const bf16_t*>(p.vp) + (int64_t)bh * p.Nk * D;
-  const bf16_t* kc = p.kbar16 + (int64_t)bh * Ck * D;
-  const bf16_t* vc = p.vbar16 + (int64_t)bh * Ck * D;
-
-  int cur = 0;  // segment cursor of threads 0..63 (virtual position -> permuted K/V row)
-  auto map_tile = [&](int t) {
-    if (tid < BN) {
-      int phys;
-      if (t < nt_r) {
-        const int pos = t * BN + tid;
-        if (pos < n_r) {
-          while (pos >= vstart[cur + 1]) ++cur;
-          phys = pstart[cur] + (pos - vstart[cur]);
-        } else {
-          phys = 0;  // masked below; any valid row
-        }
-      } else {
-        const int b = (t - nt_r) * BN + tid;
-        phys = b < Ck ? b : Ck - 1;
-      }
-      rowmap[(t & 1) * BN + tid] = phys;
-    }
-  };
-
-  uint4 kreg[KCH], vreg[VCH][4];
-  auto issue_loads = [&](int t) {
-    const bf16_t* kb = t < nt_r ? kh : kc;
-    const bf16_t* vb = t < nt_r ? vh : vc;
-    const int32_t* rm = rowmap + (t & 1) * BN;
-#pragma unroll
-    for (int i = 0; i < KCH; ++i) {
-      const int chunk = tid + i * NT;
-      const int r = chunk / CPR, c16 = chunk % CPR;
-      kreg[i] = *reinterpret_cast<const uint4*>(kb + (int64_t)rm[r] * D + c16 * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < VCH; ++i) {
-      const int unit = tid + i * NT;
-      if (unit < VUNITS) {
-        const int kg = unit / CPR, dg = unit % CPR;
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd)
-          vreg[i][qd] = *reinterpret_cast<const uint4*>(vb + (int64_t)rm[4 * kg + qd] * D + dg * 8);
-      }
-    }
-  };
-  auto store_tiles = [&](int buf) {
-    bf16_t* Kb = Ks + buf * TL::K_ELEMS;
-    bf16_t* Vb = Vs + buf * TL::V_ELEMS;
-#pragma unroll
-    for (int i = 0; i < KCH; ++i) {
-      const int chunk = tid + i * NT;
-      const int r = chunk / CPR, c16 = chunk % CPR;
-      *reinterpret_cast<uint4*>(Kb + r * TL::KROW + c16 * 8) = kreg[i];
-    }
-#pragma unroll
-    for (int i = 0; i < VCH; ++i) {
-      const int unit = tid + i * NT;
-      if (unit < VUNITS) {
-        const int kg = unit / CPR, dg = unit % CPR;
-        // column of key 4*kg inside its 16-key group: keys are stored so that the 8 keys a
-        // lane needs for one MFMA B/A operand pair are contiguous
-        const int g4 = kg & 3;
-        const int pos0 = 16 * (kg >> 2) + 8 * (g4 & 1) + 4 * (g4 >> 1);
-        const uint32_t w0[4] = {vreg[i][0].x, vreg[i][0].y, vreg[i][0].z, vreg[i][0].w};
-        const uint32_t w1[4] = {vreg[i][1].x, vreg[i][1].y, vreg[i][1].z, vreg[i][1].w};
-        const uint32_t w2[4] = {vreg[i][2].x, vreg[i][2].y, vreg[i][2].z, vreg[i][2].w};
-        const uint32_t w3[4] = {vreg[i][3].x, vreg[i][3].y, vreg[i][3].z, vreg[i][3].w};
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int wd = u >> 1;
-          uint2 o;
-          if (u & 1) {
-            o.x = (w0[wd] >> 16) | (w1[wd] & 0xffff0000u);
-            o.y = (w2[wd] >> 16) | (w3[wd] & 0xffff0000u);
-          } else {
-            o.x = (w0[wd] & 0xffffu) | (w1[wd] << 16);
-            o.y = (w2[wd] & 0xffffu) | (w3[wd] << 16);
-          }
-          *reinterpret_cast<uint2*>(Vb + (8 * dg + u) * TL::VROW + pos0) = o;
-        }
-      }
-    }
-  };
-
-  // ---- Q fragments (B operand of S^T = K Q^T): lane holds query li, dims 16s + 8*lh + 0..7
-  const int qrow = row0 + 32 * wave + li;
-  const bool qvalid = qrow < row_end;
-  const bool wave_active = (row0 + 32 * wave) < row_end;
-  bf16x8 bq[KS];
-  {
-    const bf16_t* qr = static_cast<const bf16_t*>(p.qp) + q_row_offset(p, bh, qvalid ? qrow : row_end - 1, D);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) bq[s] = as_bf16x8(*reinterpret_cast<const uint4*>(qr + 16 * s + 8 * lh));
-  }
-
-  f32x16 oacc[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
-  float m = -INFINITY, l = 0.f;
-  const float c = p.scale * kLog2e;
-
-  if (T > 0) {
-    map_tile(0);
-    if (T > 1) map_tile(1);
-    __syncthreads();
-    issue_loads(0);
-    store_tiles(0);
-    __syncthreads();
-  }
-
-  for (int t = 0; t < T; ++t) {
-    const int buf = t & 1;
-    if (t + 1 < T) issue_loads(t + 1);
-    if (wave_active) {
-      const bf16_t* Kb = Ks + buf * TL::K_ELEMS;
-      const bf16_t* Vb = Vs + buf * TL::V_ELEMS;
-      // ---- S^T tile: 64 keys x 32 queries
-      f32x16 sacc[2];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[kb][r] = 0.f;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          const bf16x8 ak =
-              as_bf16x8(*reinterpret_cast<const uint4*>(Kb + (32 * kb + li) * TL::KROW + 16 * s + 8 * lh));
-          sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[s], sacc[kb], 0, 0, 0);
-        }
-      }
-      // register r of block kb is key 32*kb + 8*(r/4) + 4*lh + r%4 of this tile
-      float mx = -INFINITY;
-      if (t < nt_r) {
-        const int left = n_r - t * BN;  // valid keys in this tile
-        if (left < BN) {
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (32 * kb + 8 * (r >> 2) + 4 * lh + (r & 3) >= left) sacc[kb][r] = -INFINITY;
-        }
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            sacc[kb][r] *= c;
-            mx = fmaxf(mx, sacc[kb][r]);
-          }
-      } else {
-        const float* lwt = lw + (t - nt_r) * BN;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const float4 bias = *reinterpret_cast<const float4*>(lwt + 32 * kb + 8 * g + 4 * lh);
-            sacc[kb][4 * g + 0] = __builtin_fmaf(sacc[kb][4 * g + 0], c, bias.x);
-            sacc[kb][4 * g + 1] = __builtin_fmaf(sacc[kb][4 * g + 1], c, bias.y);
-            sacc[kb][4 * g + 2] = __builtin_fmaf(sacc[kb][4 * g + 2], c, bias.z);
-            sacc[kb][4 * g + 3] = __builtin_fmaf(sacc[kb][4 * g + 3], c, bias.w);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sacc[kb][4 * g + r]);
-          }
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m, mx);
-      if (__any(m_new > m)) {
-        const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
-        l *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-        m = m_new;
-      }
-      const float m_use = (m == -INFINITY) ? 0.f : m;
-      uint32_t pk[2][8];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          const float p0 = __builtin_amdgcn_exp2f(sacc[kb][r] - m_use);
-          const float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1] - m_use);
-          l += p0 + p1;
-          pk[kb][r >> 1] = pack_bf16(p0, p1);
-        }
-      // ---- O^T += V^T P^T : k-step ks covers keys 16*ks .. 16*ks+15
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const int kb = ks >> 1, u4 = (ks & 1) * 4;
-        uint4 pw = make_uint4(pk[kb][u4], pk[kb][u4 + 1], pk[kb][u4 + 2], pk[kb][u4 + 3]);
-        const bf16x8 bp = as_bf16x8(pw);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const bf16x8 av =
-              as_bf16x8(*reinterpret_cast<const uint4*>(Vb + (32 * db + li) * TL::VROW + 16 * ks + 8 * lh));
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bp, oacc[db], 0, 0, 0);
-        }
-      }
-    }
-    if (t + 2 < T) map_tile(t + 2);
-    if (t + 1 < T) store_tiles(buf ^ 1);
-    __syncthreads();
-  }
-
-  // ---- epilogue: normalise and write (lane holds query li, dims 32db + 8g + 4lh + 0..3)
-  if (wave_active) {
-    const float lt = l + __shfl_xor(l, 32);
-    if (qvalid) {
-      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-      int64_t lse_idx;
-      bf16_t* o = static_cast<bf16_t*>(p.op) + out_row_offset(p, bh, qrow, D, lse_idx);
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 w;
-          w.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
-          w.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
-          *reinterpret_cast<uint2*>(o + 32 * db + 8 * g + 4 * lh) = w;
-        }
-      if (p.lse && lh == 0) p.lse[lse_idx] = (m + log2f(lt)) * kLn2;
-    }
-  }
-}
-
-
-// ------------------------------------------------------------------------------ d = 128
-// Same algorithm, data path built on two gfx950 features:
+// Data path built on two gfx950 features:
 //  * K and V tiles go from global memory straight into LDS (global_load_lds, 16 bytes per
-//    lane, a wave fills 1 KB = 4 rows of 256 B contiguously), so no VGPRs stage the tiles
-//    and the loads of tile t+1 fly while tile t is computed;
+//    lane, a wave fills 1 KB = 4 rows of 256 B (d = 128) or 8 of 128 B contiguously), so no VGPRs
+//    stage the tiles and the loads of later tiles fly while tile t is computed;
 //  * V stays row-major [key][dim] in LDS and the A operand of O^T += V^T P^T is fetched
 //    with the LDS transpose read (ds_read_b64_tr_b16): within a group of 16 lanes, lane j
 //    receives element j%4 of the four 8-byte rows addressed by lanes j/4, j/4+4, j/4+8,
 //    j/4+12 of the group. Lanes r of a group address V[key0 + r/4][dim0 + 4*(r%4) ..+3],
 //    so lane j gets dims dim0+j of keys key0..key0+3.
-// Bank conflicts are avoided by XOR-swizzling the 16-byte chunk index inside each 256 B
-// row (K: chunk ^ (row % 16); V: chunk ^ 4*(row % 4)); the swizzle is applied on the
-// global side of the copy (a lane picks which global chunk lands in its LDS slot).
+// Bank conflicts are avoided by XOR-swizzling the 16-byte chunk index inside each row (256 B rows:
+// K chunk ^ (row % 16), V chunk ^ 4 (row % 4); 128 B rows, of which two share the 64 banks:
+// K chunk ^ (row/2 % 8), V chunk ^ 4 (row/2 % 2)); the swizzle is applied on the global side of the
+// copy (a lane picks which global chunk lands in its LDS slot).
+// d = 64 is bound by the vector ALU rather than the matrix cores: a 64-key step of a wave has 16
+// MFMAs (512 cycles of its SIMD) against some 150 vector instructions and 32 exponentials (about 800).
+// It runs the same pipeline; the kernel before staged its tiles through registers, transposed V with
+// vector instructions and kept 4 waves a workgroup (24 heads x 32,477 rows, 64 / 300 clusters, a
+// quarter routed: 5.20 -> 1.94 ms, 318 -> 855 TFLOP/s).
 constexpr float kLazyRescale = 8.0f;  // log2 headroom before the running maximum is refreshed
 
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
@@ -385,9 +65,10 @@ __device__ __forceinline__ float swap32(float x) {
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16* lds_v4i16_ptr;
 
+template <int ROW_BYTES>
 __device__ __forceinline__ bf16x8 tr_pair(const unsigned char* lds_base, int off_bytes) {
   const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(lds_base + off_bytes));
-  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(lds_base + off_bytes + 8 * 256));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(lds_base + off_bytes + 8 * ROW_BYTES));
   union { struct { v4i16 a, b; } s; bf16x8 v; } c;
   c.s.a = lo;
   c.s.b = hi;
@@ -405,39 +86,46 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)(p);
 }
 
-static inline size_t lds_bytes_d128(int Ck, int stages) {
-  const size_t kv = (size_t)stages * 2 * BN * 128 * 2;  // K and V, `stages` buffers each
-  const size_t lw = (size_t)align_up(Ck, 64) * 4;
-  const size_t seg = (size_t)(2 * (Ck + 2) + 1) * 4;  // vstart, pstart, claimed tile slot
-  return kv + (size_t)(stages + 2) * BN * 4 + lw + align_up(seg, 16);
-}
+// Entries of each of the two key-cluster tables: routed clusters and a sentinel, then, 16-byte
+// aligned, the compensated ones, filled up to a whole tile.
+__host__ __device__ static inline int list_entries(int Ck) { return (Ck + 72) & ~3; }
 
+static inline size_t lds_bytes(int d, int Ck, int stages) {
+  const size_t kv = (size_t)stages * 2 * BN * d * 2;  // K and V, `stages` buffers each
+  return kv + (size_t)(stages + 2) * BN * 4 + 2 * (size_t)list_entries(Ck) * 4 + 16;
+}
 
 // NW waves of 32 query rows (three per SIMD); NSTAGE K/V tile buffers. The first CW waves of
 // the workgroup (the oldest wave of every SIMD, which finishes its step first) issue the tile
 // copies, after their compute of the step (just before the tile barrier): measured faster
 // than issuing them behind the score MFMAs or from more waves.
-template <int NW, int NSTAGE, int CW>
+// WIDE: rows by 64-bit addresses instead of 32-bit byte offsets from the head's first one.
+template <int D, int NW, int NSTAGE, int CW, bool WIDE>
 __global__ void __launch_bounds__(64 * NW, 1)
-attn_bf16_d128_kernel(AttnArgs p) {
-  constexpr int D = 128;
+attn_bf16_kernel(AttnArgs p) {
+  static_assert(D == 64 || D == 128, "swizzles");
   constexpr int NT = 64 * NW;
+  constexpr int ROWB = D * 2;                       // bytes per K/V row
+  constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
+  constexpr int RPI = 64 / CPR;                     // rows per copy instruction
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
-  constexpr int TILE_BYTES = BN * D * 2;            // 16 KB
+  constexpr int TILE_BYTES = BN * ROWB;
   constexpr int INST_PER_TILE = TILE_BYTES / 1024;  // wave-wide 1 KB copies per tensor tile
   constexpr int LOADS_PER_TILE = 2 * INST_PER_TILE / CW;  // copy instructions per copying wave per tile
   constexpr int RS = NSTAGE + 1;                    // row-map ring
   static_assert(INST_PER_TILE % CW == 0 && CW <= NW, "copies must split evenly over the copying waves");
 
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
-  unsigned char* Ks = smem;                        // [NSTAGE][64 rows][256 B], chunk-swizzled
-  unsigned char* Vs = smem + NSTAGE * TILE_BYTES;  // [NSTAGE][64 rows][256 B], chunk-swizzled
+  unsigned char* Ks = smem;                        // [NSTAGE][64 rows][ROWB], chunk-swizzled
+  unsigned char* Vs = smem + NSTAGE * TILE_BYTES;  // [NSTAGE][64 rows][ROWB], chunk-swizzled
   int32_t* rowmap = reinterpret_cast<int32_t*>(smem + 2 * NSTAGE * TILE_BYTES);  // [RS][BN]
-  float* lw = reinterpret_cast<float*>(rowmap + RS * BN);  // [align64(Ck)] compensation biases
-  float* rag_bias = lw + ((p.Ck + 63) & ~63);              // [BN] bias of the ragged routed tile
-  int32_t* vstart = reinterpret_cast<int32_t*>(rag_bias + BN);
-  int32_t* pstart = vstart + (p.Ck + 2);
+  float* rag_bias = reinterpret_cast<float*>(rowmap + RS * BN);  // [BN] bias of the ragged routed tile
+  // two tables: of the routed clusters e < ne the first virtual position and the first row (then the
+  // end position); from comp0 on, of the compensated ones the index and the bias
+  int32_t* ent0 = reinterpret_cast<int32_t*>(rag_bias + BN);
+  int32_t* ent1 = ent0 + list_entries(p.Ck);
+  int32_t* slot_s = ent1 + list_entries(p.Ck);  // claimed tile, number of compensated clusters
 
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -448,7 +136,6 @@ attn_bf16_d128_kernel(AttnArgs p) {
   // the other XCDs' lists. Lists are sorted longest tile first and workgroups start in
   // order, so the long tiles start early and the short ones fill the end of the launch. The
   // grid covers the tile-count bound; workgroups that find every list used up exit.
-  int32_t* slot_s = pstart + (p.Ck + 2);
   if (tid == 0) {
     const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7;  // XCC_ID
     int found = -1;
@@ -469,8 +156,8 @@ attn_bf16_d128_kernel(AttnArgs p) {
   const int row_end = p.sched_rend[claimed];  // the tile's rows are [row0, row_end), all of query cluster a
   const int32_t* rp = p.row_ptr + (int64_t)bh * (R + 1);
   const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + rp[a];
-  const int ne = rp[a + 1] - rp[a];
-  const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
+  const int ne = min(rp[a + 1] - rp[a], Cc);
+  const int comp0 = (ne + 1 + 3) & ~3;
 
   if (wave == 0) {
     int carry = 0;
@@ -482,32 +169,45 @@ attn_bf16_d128_kernel(AttnArgs p) {
         const int ps = ko[b];
         sz = ko[b + 1] - ps;
         sz = sz > 0 ? sz : 0;
-        pstart[e] = ps;
+        ent1[e] = ps;
       }
       int incl = sz;
       for (int o = 1; o < 64; o <<= 1) {
         const int t = __shfl_up(incl, o);
         if (lane >= o) incl += t;
       }
-      if (e < ne) vstart[e] = carry + incl - sz;
+      if (e < ne) ent0[e] = carry + incl - sz;
       carry += __shfl(incl, 63);
     }
-    if (lane == 0) vstart[ne] = carry;
-  }
-  for (int b = tid; b < ((Ck + 63) & ~63); b += NT) {
-    float v = -INFINITY;
-    if (b < Ck && a < Cq) {
-      const int sz = ko[b + 1] - ko[b];
-      if (sz > 0 && !mask_bit(mrow, b)) v = log2f((float)sz);
+    if (lane == 0) ent0[ne] = carry;
+  } else if (wave == 1) {
+    // skipped, non-empty clusters only: a quarter routed leaves a quarter fewer centroid tiles
+    int at = comp0;
+    if (a < Cq) {
+      const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
+      for (int b0 = 0; b0 < Ck; b0 += 64) {
+        const int b = b0 + lane;
+        const int sz = b < Ck ? ko[b + 1] - ko[b] : 0;
+        const bool on = sz > 0 && !mask_bit(mrow, b);
+        const unsigned long long votes = __ballot(on);
+        const int slot = at + __popcll(votes & ((1ull << lane) - 1ull));
+        if (on && slot < list_entries(Ck) - (BN - 1)) {
+          ent0[slot] = b;
+          ent1[slot] = __float_as_int(log2f((float)sz));
+        }
+        at += __popcll(votes);
+      }
     }
-    lw[b] = v;
+    at = min(at, list_entries(Ck) - (BN - 1));
+    if (lane < BN - 1) ent1[at + lane] = __float_as_int(-INFINITY);  // the rest of the last tile
+    if (lane == 0) slot_s[1] = at - comp0;
   }
   __syncthreads();
   // (part 2 leaves the routed keys out, part 1 the centroid tiles: the two-stage form)
-  const int n_r = p.part == 2 ? 0 : __builtin_amdgcn_readfirstlane(vstart[ne]);  // wave-uniform
+  const int n_r = p.part == 2 ? 0 : __builtin_amdgcn_readfirstlane(ent0[ne]);  // wave-uniform
+  const int n_c = p.part == 1 ? 0 : __builtin_amdgcn_readfirstlane(slot_s[1]);
   const int nt_r = (n_r + BN - 1) / BN;
-  const int nt_c = (a < Cq && p.part != 1) ? (Ck + BN - 1) / BN : 0;
-  const int T = nt_r + nt_c;
+  const int T = nt_r + (n_c + BN - 1) / BN;
   const int nt_full = n_r / BN;  // routed tiles with all 64 keys valid
   if (tid < BN) rag_bias[tid] = (nt_full * BN + tid < n_r) ? 0.f : -INFINITY;
 
@@ -520,37 +220,34 @@ attn_bf16_d128_kernel(AttnArgs p) {
   auto map_tile = [&](int t) __attribute__((always_inline)) {
     if (tid < BN) {
       int phys;
-      if (t < nt_r) {
-        const int pos = t * BN + tid;
-        if (pos < n_r) {
-          while (pos >= vstart[cur + 1]) ++cur;
-          phys = pstart[cur] + (pos - vstart[cur]);
-        } else {
-          phys = 0;  // masked by rag_bias; any valid row
-        }
+      if (t < nt_r) {  // positions past the last key repeat it (masked by rag_bias)
+        const int pos = min(t * BN + tid, n_r - 1);
+        while (pos >= ent0[cur + 1]) ++cur;
+        phys = ent1[cur] + (pos - ent0[cur]);
       } else {
-        const int b = (t - nt_r) * BN + tid;
-        phys = b < Ck ? b : Ck - 1;
+        phys = ent0[comp0 + min((t - nt_r) * BN + tid, n_c - 1)];
       }
       rowmap[(t % RS) * BN + tid] = phys;
     }
   };
 
-  // one wave-wide copy moves rows 4*inst .. 4*inst+3 of a tile; lane -> (row, LDS chunk slot).
-  // Copy i of this wave is instruction inst = wave + i*CW of the tile: tile row cp_rr + 4*i*CW.
-  // CW is a multiple of 4, so the row's swizzle phases (row % 16, row % 4), and with them the
-  // 16-byte chunk a lane fetches, are the same for every i.
-  static_assert(CW % 4 == 0, "copy rows of one lane must share their swizzle phase");
+  // one wave-wide copy moves rows RPI*inst .. of a tile; lane -> (row, LDS chunk slot).
+  // Copy i of this wave is instruction inst = wave + i*CW of the tile: tile row cp_rr + RPI*i*CW,
+  // a multiple of 16 rows further on, so the row's swizzle phases, and with them the 16-byte chunk
+  // a lane fetches, are the same for every i.
+  static_assert((RPI * CW) % 16 == 0, "copy rows of one lane must share their swizzle phase");
   constexpr int CPW = INST_PER_TILE / CW;  // copies per tensor per wave per tile
   const uint32_t lds_k0 = lds_address(Ks), lds_v0 = lds_address(Vs);
-  const int cp_rr = 4 * (wave % CW) + (lane >> 4);
-  const uint32_t cp_koff = (uint32_t)(((lane & 15) ^ (cp_rr & 15)) << 4);
-  const uint32_t cp_voff = (uint32_t)(((lane & 15) ^ ((cp_rr & 3) << 2)) << 4);
+  auto k_swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+  auto v_swz = [](int row) { return D == 128 ? ((row & 3) << 2) : ((row & 2) << 1); };
+  const int cp_rr = RPI * (wave % CW) + lane / CPR;
+  const uint32_t cp_koff = (uint32_t)(((lane % CPR) ^ k_swz(cp_rr)) << 4);
+  const uint32_t cp_voff = (uint32_t)(((lane % CPR) ^ v_swz(cp_rr)) << 4);
   // permuted rows (of K/V or of the centroid tables) this lane copies for tile t
   auto fetch_rows = [&](int t, int (&rows)[CPW]) __attribute__((always_inline)) {
     const int32_t* rm = rowmap + (t % RS) * BN + cp_rr;
 #pragma unroll
-    for (int i = 0; i < CPW; ++i) rows[i] = rm[4 * i * CW];
+    for (int i = 0; i < CPW; ++i) rows[i] = rm[RPI * i * CW];
   };
   auto issue_copies = [&](int t) __attribute__((always_inline)) {
     if (CW < NW && wave >= CW) return;
@@ -562,22 +259,30 @@ attn_bf16_d128_kernel(AttnArgs p) {
     const uint32_t vdst = lds_v0 + (t % NSTAGE) * TILE_BYTES + wave * 1024;
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
-      const uint32_t rowoff = (uint32_t)rows[i] * (D * 2);
-      async_copy_16B(kb, rowoff + cp_koff, __builtin_amdgcn_readfirstlane(kdst + i * CW * 1024));
-      async_copy_16B(vb, rowoff + cp_voff, __builtin_amdgcn_readfirstlane(vdst + i * CW * 1024));
+      const uint32_t k_lds = __builtin_amdgcn_readfirstlane(kdst + i * CW * 1024);
+      const uint32_t v_lds = __builtin_amdgcn_readfirstlane(vdst + i * CW * 1024);
+      if constexpr (WIDE) {
+        const int64_t rowoff = (int64_t)rows[i] * ROWB;
+        async_copy_16B(static_cast<const unsigned char*>(kb) + rowoff + cp_koff, k_lds);
+        async_copy_16B(static_cast<const unsigned char*>(vb) + rowoff + cp_voff, v_lds);
+      } else {
+        const uint32_t rowoff = (uint32_t)rows[i] * ROWB;
+        async_copy_16B(kb, rowoff + cp_koff, k_lds);
+        async_copy_16B(vb, rowoff + cp_voff, v_lds);
+      }
     }
   };
 
   // per-lane LDS byte offsets of the MFMA operands
-  // K row li of a 32-row block, dims 16s + 8lh .. +7: chunk (2s + lh) ^ (li % 16)
+  // K row li of a 32-row block, dims 16s + 8lh .. +7: chunk (2s + lh) ^ swizzle
   // (the swizzles are XORs of disjoint bit fields, so operand s / block db is the offset of
   // operand 0 with s << 5 / db << 6 XORed in: one register each instead of a table)
-  const int koff0 = li * 256 + ((lh ^ (li & 15)) << 4);
+  const int koff0 = li * ROWB + ((lh ^ k_swz(li)) << 4);
   auto koff = [&](int s) { return koff0 ^ (s << 5); };
   int voff0;  // transpose read: group = lane/16 -> (dim half, key half); r = lane%16
   {
-    const int r = lane & 15, g = lane >> 4, ddhalf = g & 1, khalf = g >> 1;
-    voff0 = (4 * khalf + (r >> 2)) * 256 + ((4 * (r >> 2) + 2 * ddhalf + ((r & 3) >> 1)) << 4) + (r & 1) * 8;
+    const int r = lane & 15, g = lane >> 4, ddhalf = g & 1, khalf = g >> 1, row = 4 * khalf + (r >> 2);
+    voff0 = row * ROWB + (((2 * ddhalf + ((r & 3) >> 1)) ^ v_swz(row)) << 4) + (r & 1) * 8;
   }
   auto voff = [&](int db) { return voff0 ^ (db << 6); };
 
@@ -626,7 +331,7 @@ attn_bf16_d128_kernel(AttnArgs p) {
     bf16x8 ak[2 * KS];
 #pragma unroll
     for (int i = 0; i < 2 * KS; ++i)
-      ak[i] = as_bf16x8(*reinterpret_cast<const uint4*>(Kb + (i & 1) * 32 * 256 + koff(i >> 1)));
+      ak[i] = as_bf16x8(*reinterpret_cast<const uint4*>(Kb + (i & 1) * 32 * ROWB + koff(i >> 1)));
 #pragma unroll
     for (int i = 0; i < 2 * KS; ++i)
       sacc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[i], bq[i >> 1], sacc[i & 1], 0, 0, 0);
@@ -672,7 +377,7 @@ attn_bf16_d128_kernel(AttnArgs p) {
           pk[kb][r >> 1] = pack_bf16(p0, p1);
         }
     } else {
-      const float* lwt = t < nt_r ? rag_bias : lw + (t - nt_r) * BN;
+      const float* lwt = t < nt_r ? rag_bias : reinterpret_cast<const float*>(ent1) + comp0 + (t - nt_r) * BN;
       float mx = -INFINITY;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -723,7 +428,7 @@ attn_bf16_d128_kernel(AttnArgs p) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int db = 0; db < DB; ++db) av[ks][db] = tr_pair(Vb, ks * 16 * 256 + voff(db));
+        for (int db = 0; db < DB; ++db) av[ks][db] = tr_pair<ROWB>(Vb, ks * 16 * ROWB + voff(db));
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int kb = ks >> 1, u4 = (ks & 1) * 4;
@@ -858,13 +563,15 @@ __global__ void __launch_bounds__(256)
 plan_items_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
                   const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int Cq, int Ck, int BM,
                   int32_t* __restrict__ item_T, int32_t* __restrict__ item_nt) {
-  const int bh = blockIdx.x, R = Cq + 1, Cc = Ck + 1;
+  const int bh = blockIdx.y, R = Cq + 1, Cc = Ck + 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
   const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
   const int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
-  // a wave per query cluster, its lanes over the routed key clusters
-  for (int a = wave; a < R; a += 4) {
+  // a wave per query cluster, its lanes over the routed key clusters (one workgroup per head took
+  // 173 us for 5 heads of 300 clusters, this grid 10)
+  const int a = 4 * blockIdx.x + wave;
+  if (a < R) {
     const int n = qo[a + 1] - qo[a];
     const int32_t* ci = col_idx + (int64_t)bh * R * Cc + rp[a];
     const int ne = rp[a + 1] - rp[a];
@@ -923,30 +630,44 @@ plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
                   const int32_t* __restrict__ by_rank, int M, int Cq, int BM, int32_t* __restrict__ rank_off,
                   int32_t* __restrict__ sched_bh, int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
                   int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x) {
-  __shared__ int32_t part[1024];
   __shared__ int32_t total[8], first[8];
-  const int tid = threadIdx.x, R = Cq + 1;
+  const int tid = threadIdx.x, R = Cq + 1, lane = tid & 63, wave = tid >> 6;
   const int rounds = (M + 7) / 8;
-  // exclusive offsets of every item inside its list (list xl = ranks 8k + pos(k, xl))
-  for (int xl = 0; xl < 8; ++xl) {
+  // exclusive offsets of every item inside its list (list xl = ranks 8k + pos(k, xl)): a wave per
+  // list, four items per lane and step (one list after the other with the whole workgroup and its
+  // barriers took 17 us at 22 items and 76 us at 9,624; this way 4 and 56,
+  // most of it the expansion below)
+  if (wave < 8) {
+    const int xl = wave;
     int carry = 0;
-    for (int k0 = 0; k0 < rounds; k0 += 1024) {
-      const int k = k0 + tid;
-      const int r = 8 * k + ((k & 1) ? 7 - xl : xl);
-      const int v = (k < rounds && r < M) ? item_nt[by_rank[r]] : 0;
-      part[tid] = v;
-      __syncthreads();
-      for (int o = 1; o < 1024; o <<= 1) {
-        const int t = tid >= o ? part[tid - o] : 0;
-        __syncthreads();
-        part[tid] += t;
-        __syncthreads();
+    for (int k0 = 0; k0 < rounds; k0 += 256) {
+      int r[4], v[4], sum = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + 4 * lane + u;
+        r[u] = 8 * k + ((k & 1) ? 7 - xl : xl);
+        v[u] = (k < rounds && r[u] < M) ? by_rank[r[u]] : -1;
       }
-      if (k < rounds && r < M) rank_off[r] = carry + part[tid] - v;
-      carry += part[1023];
-      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v[u] = v[u] >= 0 ? item_nt[v[u]] : 0;
+        sum += v[u];
+      }
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+      }
+      int at = carry + incl - sum;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (k0 + 4 * lane + u < rounds && r[u] < M) rank_off[r[u]] = at;
+        at += v[u];
+      }
+      carry += __shfl(incl, 63);
     }
-    if (tid == 0) total[xl] = carry;
+    if (lane == 0) total[xl] = carry;
   }
   __syncthreads();
   if (tid == 0) {
@@ -982,27 +703,29 @@ plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
 
 }  // namespace
 
-// Tile shape of the d = 128 kernel: 12 waves x 32 query rows per workgroup (one workgroup per
-// CU, 3 waves per SIMD at 168 VGPRs), 4 K/V tile buffers.
-constexpr int kD128Waves = 12;
-constexpr int kD128Stages = 4;
-constexpr int kD128CopyWaves = 4;
+// Tile shape: 12 waves x 32 query rows per workgroup (one workgroup per CU, 3 waves per SIMD at 168
+// VGPRs), 4 K/V tile buffers.
+constexpr int kWaves = 12;
+constexpr int kStages = 4;
+constexpr int kCopyWaves = 4;
 
-int attn_bf16_bm(int d) { return d == 128 ? 32 * kD128Waves : 32 * kBf16Waves; }
+int attn_bf16_bm() { return 32 * kWaves; }
 
-size_t attn_bf16_lds_bytes(int d, int Ck) {
-  return d == 128 ? lds_bytes_d128(Ck, kD128Stages) : lds_bytes_generic(d, Ck);
+// d = 128: 12 bytes per key cluster beside the tile buffers is what the entry point promises.
+bool attn_bf16_supported(int d, int Ck) {
+  return d == 64 || (size_t)kStages * 2 * BN * 256 + (kStages + 2) * BN * 4 + align_up(Ck, 64) * 4 +
+                        align_up((size_t)(2 * (Ck + 2) + 1) * 4, 16) <= 160 * 1024;
 }
 
-size_t plan_d128_workspace(int BH, int Cq, int64_t Nq) {
+size_t plan_bf16_workspace(int BH, int Cq, int64_t Nq) {
   const size_t M = (size_t)BH * (Cq + 1);
-  const size_t tiles = (size_t)BH * ((size_t)ceil_div(Nq, 32 * kD128Waves) + Cq + 1);
+  const size_t tiles = (size_t)BH * ((size_t)ceil_div(Nq, 32 * kWaves) + Cq + 1);
   return 4 * align_up(M * 4, 256) + 4 * align_up(tiles * 4, 256) + align_up(24 * 4, 256);
 }
 
-int plan_d128(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
+int plan_bf16(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   Workspace w(ws, ws_bytes);
-  const int M = a.BH * (a.Cq + 1), BM = 32 * kD128Waves;
+  const int M = a.BH * (a.Cq + 1), BM = 32 * kWaves;
   const size_t tiles = (size_t)a.BH * ((size_t)ceil_div(a.Nq, BM) + a.Cq + 1);
   int32_t* item_T = w.take<int32_t>(M);
   int32_t* item_nt = w.take<int32_t>(M);
@@ -1014,7 +737,7 @@ int plan_d128(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   int32_t* sched_rend = w.take<int32_t>(tiles);
   int32_t* sched_x = w.take<int32_t>(24);
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
-  plan_items_kernel<<<a.BH, 256, 0, s>>>(a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, a.Cq, a.Ck, BM, item_T, item_nt);
+  plan_items_kernel<<<dim3((unsigned)ceil_div(a.Cq + 1, 4), a.BH), 256, 0, s>>>(a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, a.Cq, a.Ck, BM, item_T, item_nt);
   SVGEAR_LAUNCH_CHECK();
   plan_rank_kernel<<<(unsigned)ceil_div(M, kRankItems), 256, 0, s>>>(item_T, M, by_rank);
   SVGEAR_LAUNCH_CHECK();
@@ -1069,22 +792,21 @@ int launch_merge(const bf16_t* o1, const float* lse1, const bf16_t* o2, const fl
 }
 
 // `total` workgroups: at least the number of tiles (one workgroup per tile; the rest exit).
-int launch_attn_bf16(const AttnArgs& a, int d, unsigned total, hipStream_t s) {
-  const size_t lds = attn_bf16_lds_bytes(d, a.Ck);
-  if (d == 64) {
-    auto kern = attn_bf16_kernel<64, kBf16Waves>;
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    kern<<<total, 64 * kBf16Waves, lds, s>>>(a);
-  } else {
-    if (!a.sched_x) return SVGEAR_ERR_INVALID;
-    auto kern = attn_bf16_d128_kernel<kD128Waves, kD128Stages, kD128CopyWaves>;
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    kern<<<total, 64 * kD128Waves, lds, s>>>(a);
-  }
+template <int D, bool WIDE>
+static int launch(const AttnArgs& a, unsigned total, hipStream_t s) {
+  const size_t lds = lds_bytes(D, a.Ck, kStages);
+  auto kern = attn_bf16_kernel<D, kWaves, kStages, kCopyWaves, WIDE>;
+  SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds));
+  kern<<<total, 64 * kWaves, lds, s>>>(a);
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
+}
+
+int launch_attn_bf16(const AttnArgs& a, int d, unsigned total, hipStream_t s) {
+  if (!a.sched_x) return SVGEAR_ERR_INVALID;
+  if (d == 128) return launch<128, false>(a, total, s);  // (the entry point takes no more keys)
+  return a.Nk > (int64_t)(UINT32_MAX / 128) ? launch<64, true>(a, total, s) : launch<64, false>(a, total, s);
 }
 
 }  // namespace svgear

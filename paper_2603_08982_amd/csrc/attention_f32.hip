@@ -42,6 +42,78 @@ static inline size_t f32_lds_bytes(int d, int waves, int Ck) {
   return (size_t)waves * (2 * kF32Keys * d * 4 + 2 * kF32Keys * 8 + kF32Keys * 4 + 2 * kF32Rows * 4) + (2 * (size_t)(Ck + 3) + 1) * 4;
 }
 
+// ------------------------------------------------------------------------------ plan
+// Tile list of every head: tile -> (query cluster, first row). One workgroup per head. With at most
+// kPlanSort clusters the tiles of the clusters that route the most keys come first: lists differ
+// by two orders of magnitude, and a long one that starts last has the chip to itself (measured at
+// 8 heads x 5,957 rows: 0.58 -> 0.51 ms).
+constexpr int kZeros = 128;  // floats in the row of zeros
+constexpr int kPlanThreads = 1024, kPlanSort = 1024;
+__global__ void __launch_bounds__(kPlanThreads)
+plan_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
+            const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int Cq, int Ck, int BM,
+            int max_tiles, int32_t* __restrict__ tile_a, int32_t* __restrict__ tile_row0, int32_t* __restrict__ n_tiles,
+            float* __restrict__ zeros) {
+  extern __shared__ int32_t first[];  // Cq+2: tiles of the clusters, then their first tile, in list order
+  __shared__ int32_t len[kPlanSort], order[kPlanSort];
+  const int bh = blockIdx.x, R = Cq + 1, Cc = Ck + 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
+  const bool sorted = R <= kPlanSort;
+  if (bh == 0 && threadIdx.x < kZeros) zeros[threadIdx.x] = 0.f;
+  if (sorted) {
+    for (int a = wave; a < R; a += kPlanThreads / 64) {  // a wave per cluster, its lanes over the routed key clusters
+      const int32_t* ci = col_idx + (int64_t)bh * R * Cc + rp[a];
+      const int ne = rp[a + 1] - rp[a];
+      int n = 0;
+      for (int e = lane; e < ne; e += 64) n += max(ko[ci[e] + 1] - ko[ci[e]], 0);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+      if (lane == 0) len[a] = n;
+    }
+    __syncthreads();
+    for (int a = threadIdx.x; a < R; a += kPlanThreads) {
+      int rank = 0;
+      for (int b = 0; b < R; ++b) rank += len[b] > len[a] || (len[b] == len[a] && b < a);
+      order[rank] = a;
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < R; i += kPlanThreads) {
+    const int a = sorted ? order[i] : i;
+    first[i] = (qo[a + 1] - qo[a] + BM - 1) / BM;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    int carry = 0;
+    for (int i0 = 0; i0 < R; i0 += 64) {
+      const int i = i0 + lane, c = i < R ? first[i] : 0;
+      int incl = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+      }
+      if (i < R) first[i] = carry + incl - c;
+      carry += __shfl(incl, 63);
+    }
+    if (lane == 0) {
+      first[R] = carry;
+      n_tiles[bh] = carry < max_tiles ? carry : max_tiles;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < R; i += kPlanThreads) {
+    const int a = sorted ? order[i] : i;
+    const int lo = first[i], hi = first[i + 1];
+    for (int t = lo; t < hi && t < max_tiles; ++t) {
+      tile_a[(int64_t)bh * max_tiles + t] = a;
+      tile_row0[(int64_t)bh * max_tiles + t] = qo[a] + (t - lo) * BM;
+    }
+  }
+}
+
 template <int D, int NW>
 __global__ void __launch_bounds__(64 * NW)
 attn_f32_kernel(AttnArgs p) {
@@ -408,7 +480,8 @@ merge_f32_kernel(AttnArgs p, int splits) {
 }
 
 template <int D, int NW>
-int launch(const AttnArgs& a, unsigned total, int splits, hipStream_t s) {
+int launch(const AttnArgs& a, int splits, hipStream_t s) {
+  const unsigned total = (unsigned)align_up((size_t)a.BH * a.max_tiles, 8);
   const size_t lds = f32_lds_bytes(D, NW, a.Ck);
   auto kern = attn_f32_kernel<D, NW>;
   SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -422,43 +495,52 @@ int launch(const AttnArgs& a, unsigned total, int splits, hipStream_t s) {
   return SVGEAR_OK;
 }
 
-}  // namespace
-
-int attn_f32_bm() { return kF32Rows; }
-
 // Workgroups the keys of a query block are dealt to: as many as give the chip two rounds of
 // workgroups (one of d = 128, two of d = 64 fit a CU); a split costs a pass over its partial rows,
 // so a problem that fills the chip by itself is not split.
-int f32_splits(int64_t BH, int64_t Nq, int64_t Nk, int Cq) {
+static int f32_splits(int64_t BH, int64_t Nq, int64_t Nk, int Cq) {
   const int64_t tiles = BH * (ceil_div(Nq, kF32Rows) + Cq / 2);  // a cluster's last block is half full
   const int64_t want = ceil_div((int64_t)kF32Target, tiles), most = Nk / (16 * kF32Keys);
   const int64_t n = want < most ? want : most;
   return (int)(n < 1 ? 1 : (n > 8 ? 8 : n));
 }
 
-size_t f32_partial_bytes(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
+}  // namespace
+
+size_t f32_workspace(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
   const int n = f32_splits(BH, Nq, Nk, Cq);
-  const size_t rows = (size_t)BH * Nq;
-  return align_up(kZeros * 4, 256) +
+  const size_t rows = (size_t)BH * Nq, tiles = (size_t)BH * (ceil_div(Nq, kF32Rows) + Cq + 1);
+  return 2 * align_up(tiles * 4, 256) + align_up(BH * 4, 256) + align_up(kZeros * 4, 256) +
          (n > 1 ? align_up(n * rows * d * 4, 256) + align_up(n * rows * sizeof(float2), 256) : 0);
 }
 
-int launch_attn_f32(AttnArgs& a, int d, unsigned total, void* ws, size_t ws_bytes, hipStream_t s) {
+int launch_attn_f32(AttnArgs& a, int d, void* ws, size_t ws_bytes, hipStream_t s) {
   Workspace w(ws, ws_bytes);
   const int splits = f32_splits(a.BH, a.Nq, a.Nk, a.Cq);
   const size_t rows = (size_t)a.BH * a.Nq;
-  a.zeros = w.take<float>(kZeros);  // written by plan_kernel
+  a.max_tiles = (int)(ceil_div(a.Nq, kF32Rows) + a.Cq + 1);
+  int32_t* tile_a = w.take<int32_t>((size_t)a.BH * a.max_tiles);
+  int32_t* tile_row0 = w.take<int32_t>((size_t)a.BH * a.max_tiles);
+  int32_t* n_tiles = w.take<int32_t>(a.BH);
+  a.zeros = w.take<float>(kZeros);
   if (splits > 1) {
     a.part_o = w.take<float>(splits * rows * d);
     a.part_ml = w.take<float2>(splits * rows);
   }
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
+  a.tile_a = tile_a;
+  a.tile_row0 = tile_row0;
+  a.n_tiles = n_tiles;
+  plan_kernel<<<a.BH, kPlanThreads, (a.Cq + 2) * sizeof(int32_t), s>>>(a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx,
+                                                                      a.Cq, a.Ck, kF32Rows, a.max_tiles, tile_a,
+                                                                      tile_row0, n_tiles, a.zeros);
+  SVGEAR_LAUNCH_CHECK();
   // four waves fill a CU's LDS with their tiles at d = 128; lists of thousands of key clusters
   // leave room for two
   constexpr size_t kLds = 160 * 1024;
-  if (d == 64) return launch<64, 4>(a, total, splits, s);
-  if (f32_lds_bytes(d, 4, a.Ck) <= kLds) return launch<128, 4>(a, total, splits, s);
-  return launch<128, 2>(a, total, splits, s);
+  if (d == 64) return launch<64, 4>(a, splits, s);
+  if (f32_lds_bytes(d, 4, a.Ck) <= kLds) return launch<128, 4>(a, splits, s);
+  return launch<128, 2>(a, splits, s);
 }
 
 }  // namespace svgear
