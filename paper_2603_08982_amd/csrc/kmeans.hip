@@ -169,8 +169,7 @@ __device__ __forceinline__ void load_row_operands(const bf16_t* xr, int h, float
 // (min, argmin) in ascending centroid order; the two lanes of a row merge once at the end.
 // Centroid chunks (64 centroids, in operand order) stream through two LDS stages with
 // asynchronous global-to-LDS copies shared by the 8 waves (256 rows) of the workgroup.
-// (Every row of fp32 inputs goes through this kernel; of bf16 inputs only the rows the filter
-// below cannot decide, through assign_few_kernel.)
+// (fp32 inputs only; bf16 inputs go through the filter below.)
 template <typename T, int D>
 __global__ void __launch_bounds__(64 * kAssignWaves)
 assign_mfma_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const float* __restrict__ cperm,
@@ -267,94 +266,6 @@ assign_mfma_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const
   if (lh == 0 && pos < nv) labels[(int64_t)bh * nv + row] = arg;
 }
 
-// The same assignment for a short list of rows (the filter's ambiguous ones): with few rows
-// the kernel above leaves most of the chip idle while each of its waves walks every centroid, so
-// here the centroids of a 32-row tile are dealt to the 4 waves of the workgroup (32-blocks
-// round-robin), every wave fetches its operand fragments straight from the table (1 KB
-// contiguous per fetch; no LDS stage, no barrier inside the walk), and the four partial
-// (min, argmin) meet in LDS at the end. Every score is the same chain of matrix-core
-// instructions as above, and ties still go to the lowest index.
-template <typename T, int D>
-__global__ void __launch_bounds__(256)
-assign_few_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const float* __restrict__ cperm,
-                  const float* __restrict__ cn, int Cpad, int32_t* __restrict__ labels,
-                  const int32_t* __restrict__ row_list, const int32_t* __restrict__ row_count,
-                  int32_t* __restrict__ dirty) {
-  constexpr int QG = D / 8;  // 16-byte operand groups per 32-block
-  __shared__ float s_best[4][32];
-  __shared__ int s_arg[4][32];
-  const int bh = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t n_rows = row_count[bh];
-  const float* cp = cperm + (int64_t)bh * Cpad * D;
-  const float* cnb = cn + (int64_t)bh * Cpad;
-  for (int64_t tile = blockIdx.x; tile * 32 < n_rows; tile += gridDim.x) {
-    const int64_t pos = tile * 32 + li;
-    const int64_t row = row_list[(int64_t)bh * nv + (pos < n_rows ? pos : n_rows - 1)];
-    float xb[D / 2];
-    load_row_operands<D>(x + head_base(st, bh, H) + row * st.n, lh, xb);
-    float best = INFINITY;
-    int arg = 0;
-    for (int blk = wave; blk < Cpad / 32; blk += 4) {
-      const float* cb = cp + (int64_t)blk * 32 * D + lane * 4;
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-      for (int q0 = 0; q0 < QG; q0 += 8) {  // 8 fetches in flight, then their 32 MFMAs in k order
-        float4 a[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) a[q] = *reinterpret_cast<const float4*>(cb + (q0 + q) * 256);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].x, xb[4 * (q0 + q) + 0], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].y, xb[4 * (q0 + q) + 1], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].z, xb[4 * (q0 + q) + 2], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].w, xb[4 * (q0 + q) + 3], acc, 0, 0, 0);
-        }
-      }
-      // register r is centroid 32 blk + 8(r/4) + 4 lh + r%4, row li
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 n4 = *reinterpret_cast<const float4*>(cnb + 32 * blk + 8 * g + 4 * lh);
-        const float nn[4] = {n4.x, n4.y, n4.z, n4.w};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float score = __builtin_fmaf(-2.0f, acc[4 * g + r], nn[r]);
-          const int idx = 32 * blk + 8 * g + 4 * lh + r;
-          if (score < best) { best = score; arg = idx; }
-        }
-      }
-    }
-    const float ob = __shfl_xor(best, 32);
-    const int oa = __shfl_xor(arg, 32);
-    if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
-    if (lh == 0) {
-      s_best[wave][li] = best;
-      s_arg[wave][li] = arg;
-    }
-    __syncthreads();
-    if (wave == 0 && lh == 0 && pos < n_rows) {
-#pragma unroll
-      for (int w = 1; w < 4; ++w) {
-        const float wb = s_best[w][li];
-        const int wa = s_arg[w][li];
-        if (wb < best || (wb == best && wa < arg)) { best = wb; arg = wa; }
-      }
-      if (dirty) {  // a row that moves marks the cluster it leaves and the one it joins
-        const int cur = labels[(int64_t)bh * nv + row];
-        if (cur != arg) {
-          dirty[(int64_t)bh * Cpad + cur] = 1;
-          dirty[(int64_t)bh * Cpad + arg] = 1;
-        }
-      }
-      labels[(int64_t)bh * nv + row] = arg;
-    }
-    __syncthreads();  // the LDS slots are written again by the next tile
-  }
-}
-
 // ---- bf16 filter -----------------------------------------------------------------------
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
@@ -402,7 +313,7 @@ template <int D>
 __device__ __forceinline__ void settle_row(float best, float second, int arg, bool valid, int64_t row, float X,
                                            float Cm, float far_lb, const int32_t* __restrict__ positions, int cur,
                                            int bh, int64_t nv, int Cpad, int32_t* __restrict__ labels,
-                                           int32_t* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
+                                           int2* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
                                            float2* __restrict__ bnd, int32_t* __restrict__ dirty) {
   constexpr float kappa = 1.52587890625e-05f + (2 * D + 1) * 1.1920928955078125e-07f + D * 5.9604644775390625e-08f;
   const int lane = threadIdx.x & 63, lh = lane >> 5;
@@ -430,7 +341,9 @@ __device__ __forceinline__ void settle_row(float best, float second, int arg, bo
       int slot = 0;
       if (lane == leader) slot = atomicAdd(&amb_count[bh], __popcll(am));
       slot = __shfl(slot, leader) + __popcll(am & ((1ull << lane) - 1ull));
-      amb_rows[(int64_t)bh * nv + slot] = (int32_t)row;
+      // no centroid whose filter score exceeds this can be the fixed-order argmin (rounded up)
+      const float limit = __builtin_fmaf(2.0002f, B, lo) + 2.384185791015625e-07f * fabsf(lo);
+      amb_rows[(int64_t)bh * nv + slot] = make_int2((int)row, __float_as_int(limit));
     }
     if (bnd) {
       const float F = B + fixed_order_error<D>(X, Cm);
@@ -459,7 +372,7 @@ template <int D, bool RESIDENT>
 __global__ void __launch_bounds__(64 * kFilterWaves) __attribute__((amdgpu_waves_per_eu(2)))
 assign_filter_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, const bf16_t* __restrict__ chl,
                      const float* __restrict__ cn, float* __restrict__ xnorm, int C, int Cpad,
-                     int32_t* __restrict__ labels, int32_t* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
+                     int32_t* __restrict__ labels, int2* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
                      const int32_t* __restrict__ row_list, const int32_t* __restrict__ row_count,
                      float2* __restrict__ bnd, int32_t* __restrict__ dirty) {
   constexpr int KSN = D / 16;
@@ -640,6 +553,197 @@ assign_filter_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv
                   Cpad, labels, amb_rows, amb_count, bnd, dirty);
   grp += gridDim.x;
   } while (RESIDENT && grp * kFilterRows < n_rows);
+}
+
+// The rows the filter could not decide, exactly. A row's fixed-order argmin has a filter score of at
+// most lo + 2B (lo the row's lowest), whoever evaluates it, so the kernel computes the bf16 scores
+// of 64 queued rows again, collects the few centroids per row that stay below that limit, and
+// evaluates the fixed-order score for those pairs alone, a pair per lane: the matrix work of a row
+// falls eightfold against fp32 products with every centroid, and what bounds the kernel is fetching
+// the centroid fragments (4 d bytes each), which 64 rows share. The lowest (score, index) of a row
+// wins through an LDS minimum, so the order of the pairs does not matter. Measured (us a launch,
+// against fp32 products with every centroid): 40 heads of 75,600 keys, 1,000 centroids, 500 to 2,400
+// rows queued per head, 143 -> 73; 24 heads of 118,800 rows, warm, 400 and 1,000 centroids, 574 -> 103.
+// Three waves per SIMD and no fragments fetched ahead: two waves with the next block's fragments in
+// flight took 75, one wave 65 on the first shape but 478 on the second.
+// More than kFewPairs candidates (NaN rows, hosts of repeated centroids): those rows do take every
+// centroid, on fp32 MFMAs. The centroid blocks are dealt to the four waves throughout.
+constexpr int kFewRows = 64;     // rows per workgroup
+constexpr int kFewPairs = 1024;  // candidate pairs kept per workgroup
+
+// Keys that order (score, index) pairs like "lower score, then lower index", zeros of both signs equal.
+__device__ __forceinline__ unsigned long long score_key(float score, int idx) {
+  if (score == 0.f) score = 0.f;
+  uint32_t u = __float_as_uint(score);
+  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((unsigned long long)u << 32) | (uint32_t)idx;
+}
+
+template <int D>
+__global__ void __launch_bounds__(256, 3)
+assign_few_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, const bf16_t* __restrict__ chl,
+                  const float* __restrict__ cent, const float* __restrict__ cperm, const float* __restrict__ cn, int C,
+                  int Cpad, int32_t* __restrict__ labels, const int2* __restrict__ amb_rows,
+                  const int32_t* __restrict__ amb_count, int32_t* __restrict__ dirty, int BH, int per_head) {
+  constexpr int KSN = D / 16;
+  constexpr int QG = D / 8;  // 16-byte fp32 operand groups per 32-block
+  __shared__ int s_row[kFewRows];
+  __shared__ unsigned long long s_best[kFewRows];
+  __shared__ uint32_t s_pair[kFewPairs];  // row << 16 | centroid
+  __shared__ int s_n;
+  // Workgroups go round-robin over the 8 XCDs; each XCD takes a contiguous range of (head, tile), so
+  // that its L2 holds the fragments of a few heads (512 KB each at 1,000 centroids of 128) and not of
+  // all (97 -> 94 us)
+  const int logical = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int bh = logical / per_head;
+  if (bh >= BH) return;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t n_rows = amb_count[bh];
+  const float* cnb = cn + (int64_t)bh * Cpad;
+  const bf16_t* xh = x + head_base(st, bh, H);
+  for (int64_t tile = logical % per_head; tile * kFewRows < n_rows; tile += per_head) {
+    const int n_here = (int)(n_rows - tile * kFewRows < kFewRows ? n_rows - tile * kFewRows : kFewRows);
+    if (tid == 0) s_n = 0;
+    if (tid < kFewRows) s_best[tid] = ~0ull;
+    bf16x8 bx[2][KSN];
+    float limit[2];
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+      const int at = 32 * rs + li;
+      const int2 q = amb_rows[(int64_t)bh * nv + tile * kFewRows + min(at, n_here - 1)];
+      limit[rs] = __int_as_float(q.y);
+      if (wave == 0 && lh == 0) s_row[at] = q.x;
+      const bf16_t* xr = xh + (int64_t)q.x * st.n;
+#pragma unroll
+      for (int s = 0; s < KSN; ++s) bx[rs][s] = as_bf16x8(*reinterpret_cast<const uint4*>(xr + 16 * s + 8 * lh));
+    }
+    __syncthreads();
+    const bool on[2] = {li < n_here, 32 + li < n_here};
+    const bf16_t* tab = chl + (int64_t)bh * 2 * Cpad * D + lane * 8;
+    for (int blk = wave; blk < Cpad / 32; blk += 4) {
+      const bf16_t* src = tab + (int64_t)blk * 2 * KSN * 512;
+      bf16x8 av[2 * KSN];
+#pragma unroll
+      for (int i = 0; i < 2 * KSN; ++i) av[i] = as_bf16x8(*reinterpret_cast<const uint4*>(src + i * 512));
+      float nn[16];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = *reinterpret_cast<const float4*>(cnb + 32 * blk + 8 * g + 4 * lh);
+        nn[4 * g] = v.x; nn[4 * g + 1] = v.y; nn[4 * g + 2] = v.z; nn[4 * g + 3] = v.w;
+      }
+      f32x16 acc[2];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 2 * KSN; ++i) {
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bx[0][i % KSN], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bx[1][i % KSN], acc[1], 0, 0, 0);
+      }
+      // register r is centroid 32 blk + 8(r/4) + 4 lh + r%4; a NaN on either side makes a candidate.
+      // Candidates are rare (two or three of a row's centroids): first a bit per register, then
+      // one list slot per set bit.
+      uint32_t found = 0;
+#pragma unroll
+      for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          found |= !(__builtin_fmaf(-2.0f, acc[rs][r], nn[r]) > limit[rs]) ? 1u << (16 * rs + r) : 0u;
+      found &= (on[0] ? 0xffffu : 0u) | (on[1] ? 0xffff0000u : 0u);
+      while (found) {
+        const int bit = __ffs(found) - 1, rs = bit >> 4, r = bit & 15;
+        found &= found - 1;
+        const int c = 32 * blk + 8 * (r >> 2) + 4 * lh + (r & 3);
+        if (c < C) {
+          const int slot = atomicAdd(&s_n, 1);
+          if (slot < kFewPairs) s_pair[slot] = ((uint32_t)(32 * rs + li) << 16) | (uint32_t)c;
+        }
+      }
+    }
+    __syncthreads();
+    const int n = s_n;
+    if (n <= kFewPairs) {
+      for (int i = tid; i < n; i += 256) {
+        const int at = s_pair[i] >> 16, c = s_pair[i] & 0xffff;
+        const bf16_t* xr = xh + (int64_t)s_row[at] * st.n;
+        const float* cr = cent + ((int64_t)bh * C + c) * D;
+        float dot = 0.f;
+        for (int t0 = 0; t0 < D; t0 += 32) {  // 32 dims in flight, then the chain in order
+          uint4 xv[4];
+          float4 cv[8];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) xv[u] = *reinterpret_cast<const uint4*>(xr + t0 + 8 * u);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) cv[u] = *reinterpret_cast<const float4*>(cr + t0 + 4 * u);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const uint32_t w[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+            const float cc[8] = {cv[2 * u].x, cv[2 * u].y, cv[2 * u].z, cv[2 * u].w,
+                                 cv[2 * u + 1].x, cv[2 * u + 1].y, cv[2 * u + 1].z, cv[2 * u + 1].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              dot = __builtin_fmaf(cc[2 * e], __uint_as_float(w[e] << 16), dot);
+              dot = __builtin_fmaf(cc[2 * e + 1], __uint_as_float(w[e] & 0xffff0000u), dot);
+            }
+          }
+        }
+        const float score = __builtin_fmaf(-2.0f, dot, cnb[c]);
+        if (score < INFINITY) atomicMin(&s_best[at], score_key(score, c));
+      }
+    } else {
+      for (int rs = 0; rs < 2; ++rs) {
+        float xb[D / 2];
+        load_row_operands<D>(xh + (int64_t)s_row[32 * rs + li] * st.n, lh, xb);
+        float best = INFINITY;
+        int arg = 0;
+        for (int blk = wave; blk < Cpad / 32; blk += 4) {
+          const float* cb = cperm + (int64_t)bh * Cpad * D + (int64_t)blk * 32 * D + lane * 4;
+          f32x16 acc;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+          for (int q0 = 0; q0 < QG; q0 += 8) {  // 8 fetches in flight, then their 32 MFMAs in k order
+            float4 f[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) f[q] = *reinterpret_cast<const float4*>(cb + (q0 + q) * 256);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].x, xb[4 * (q0 + q) + 0], acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].y, xb[4 * (q0 + q) + 1], acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].z, xb[4 * (q0 + q) + 2], acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f[q].w, xb[4 * (q0 + q) + 3], acc, 0, 0, 0);
+            }
+          }
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const float4 n4 = *reinterpret_cast<const float4*>(cnb + 32 * blk + 8 * g + 4 * lh);
+            const float nn[4] = {n4.x, n4.y, n4.z, n4.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float score = __builtin_fmaf(-2.0f, acc[4 * g + r], nn[r]);
+              if (score < best) { best = score; arg = 32 * blk + 8 * g + 4 * lh + r; }
+            }
+          }
+        }
+        if (best < INFINITY) atomicMin(&s_best[32 * rs + li], score_key(best, arg));
+      }
+    }
+    __syncthreads();
+    if (tid < n_here) {
+      const unsigned long long key = s_best[tid];
+      const int arg = key == ~0ull ? 0 : (int)(uint32_t)key;  // (a row without a finite score: centroid 0)
+      const int64_t at = (int64_t)bh * nv + s_row[tid];
+      if (dirty) {  // a row that moves marks the cluster it leaves and the one it joins
+        const int cur = labels[at];
+        if (cur != arg) {
+          dirty[(int64_t)bh * Cpad + cur] = 1;
+          dirty[(int64_t)bh * Cpad + arg] = 1;
+        }
+      }
+      labels[at] = arg;
+    }
+    __syncthreads();  // the LDS tables are written again by the next tile
+  }
 }
 
 constexpr int kBoundRows = 8;  // rows per thread of bounds_update_kernel
@@ -921,7 +1025,7 @@ template <int D>
 __global__ void __launch_bounds__(64)
 assign_list_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, const bf16_t* __restrict__ crow,
                    const float* __restrict__ cn, int C, int Cpad, int32_t* __restrict__ labels,
-                   int32_t* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
+                   int2* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
                    const int32_t* __restrict__ prow, const int4* __restrict__ tiles, int tile_cap,
                    const int32_t* __restrict__ rmax, const int32_t* __restrict__ nlist,
                    const int32_t* __restrict__ nlen, const float* __restrict__ dout,
@@ -1234,7 +1338,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   constexpr bool kFilter = sizeof(T) == 2;  // bf16 input: filter on bf16 MFMAs, then exact on the ambiguous rows
   bf16_t* chl = kFilter ? ws.take<bf16_t>((size_t)BH * 2 * Cpad * D) : nullptr;
   bf16_t* crow = kFilter ? ws.take<bf16_t>((size_t)BH * 2 * Cpad * D) : nullptr;
-  int32_t* amb_rows = kFilter ? ws.take<int32_t>((size_t)BH * nv) : nullptr;
+  int2* amb_rows = kFilter ? ws.take<int2>((size_t)BH * nv) : nullptr;
   int32_t* amb_count = kFilter ? ws.take<int32_t>((size_t)BH) : nullptr;
   const int P = means_parts(nv, C);
   float* partial = P > 1 ? ws.take<float>((size_t)BH * C * P * D) : nullptr;
@@ -1325,8 +1429,12 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
                                                     act_rows, head_state, bnd, dirty);
         SVGEAR_LAUNCH_CHECK();
       }
-      assign_few_kernel<T, D><<<dim3((unsigned)ceil_div(nv, 32 * 8), BH), 256, 0, s>>>(
-          x, st, H, nv, cperm, cn, Cpad, labels, amb_rows, amb_count, it > 0 ? dirty : nullptr);
+      // workgroups per head: enough for 1,024 in all (two rounds of the chip) or, where every row is
+      // queued, for 64 tiles each; those beyond the queue's length leave at once
+      const int64_t few_tiles = ceil_div(nv, kFewRows), few_spread = ceil_div(1024, BH), few_least = ceil_div(few_tiles, 64);
+      const int few = (int)(few_tiles < few_spread ? few_tiles : (few_spread > few_least ? few_spread : few_least));
+      assign_few_kernel<D><<<(unsigned)align_up((size_t)few * BH, 8), 256, 0, s>>>(
+          xb, st, H, nv, chl, cent, cperm, cn, C, Cpad, labels, amb_rows, amb_count, it > 0 ? dirty : nullptr, BH, few);
     } else {
       assign<<<ga, 64 * kAssignWaves, lds, s>>>(x, st, H, nv, cperm, cn, Cpad, labels);
     }
@@ -1361,7 +1469,7 @@ extern "C" size_t svgear_kmeans_workspace(int B, int H, int64_t N, int d, int C)
   return align_up(BH * sort_chunks(N) * (C + 1) * 4, 256) + align_up(BH * N * 4, 256) +
          align_up(BH * (C + 2) * 4, 256) + align_up(BH * Cpad * 4, 256) + align_up(BH * Cpad * d * 4, 256) +
          // bf16 filter: hi/lo operand tables (two layouts), ambiguous-row list and counter
-         2 * align_up(BH * 2 * Cpad * d * 2, 256) + align_up(BH * N * 4, 256) + align_up(BH * 4, 256) +
+         2 * align_up(BH * 2 * Cpad * d * 2, 256) + align_up(BH * N * 8, 256) + align_up(BH * 4, 256) +
          // partial sums of the split centroid update
          (means_parts(N, C) > 1 ? align_up(BH * C * means_parts(N, C) * d * 4, 256) : 0) +
          // row skipping: per row two bounds, the norm, the sorted position, the flagged-row table and
