@@ -1,0 +1,34 @@
+"""GPU counting sort at the sizes where its one-workgroup form changes: tokens around multiples of the
+64-token step and of the 1,024-token round, at its largest and just above, few and many labels, text
+rows. Whole numbers, equal to a stable argsort."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_08982_amd as sv
+from helpers import dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [2, 63, 64, 65, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("C", [1, 2, 63, 1000, 1023, 1024, 2048, 2049])
+def test_sort_is_the_stable_argsort(N, C):
+    if C > N - 1:
+        pytest.skip("more clusters than tokens")
+    rng = np.random.default_rng(N + C)
+    H = 3
+    for n_tail in (0, 1 if N < 66 else 37):
+        nv = N - n_tail
+        if C > nv:
+            continue
+        lab = np.stack([rng.integers(0, C, nv), np.full(nv, C - 1), np.sort(rng.integers(0, max(1, C // 3), nv))[::-1]])
+        x = torch.randn(1, H, N, 64, device=dev())
+        perm, off, (xp,) = sv.permute(torch.from_numpy(lab.astype(np.int32))[None].to(dev()), C, [x], n_tail=n_tail)
+        torch.cuda.synchronize()
+        for h in range(H):
+            full = np.concatenate([lab[h], np.full(n_tail, C)])
+            ref = np.argsort(full, kind="stable")
+            assert np.array_equal(to_np(perm[0, h]), ref)
+            assert np.array_equal(to_np(off[0, h]), np.concatenate([[0], np.cumsum(np.bincount(full, minlength=C + 1))]))
+            assert torch.equal(xp[0, h], x[0, h][torch.from_numpy(ref).to(dev())])
