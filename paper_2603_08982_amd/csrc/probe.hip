@@ -3,9 +3,9 @@
 // stabiliser m_a = max_b Sbar_ab; streaming over the keys of a cluster without writing
 // logits to memory), "Error-Aware Routing" (error-to-size ratio).
 //
-// One workgroup per (head, key cluster b); lane a of the workgroup owns query centroid a,
-// holds qbar_a in registers and streams the cluster's keys once. The squared difference of
-// Eq. (7) is expanded around the cluster mean instead of around zero:
+// Logits come from the matrix cores, in tiles of keys x query centroids that leave a lane with 16
+// keys of one centroid, so a block's error accumulates in the lane. The squared difference of Eq. (7)
+// is expanded around the cluster mean instead of around zero:
 //   W vbar - w v_j = (W - w) vbar - w delta_j,   delta_j = v_j - vbar
 //   || . ||^2 = (W-w)^2 |vbar|^2 - 2 (W-w) w (vbar.delta_j) + w^2 |delta_j|^2
 // so each key contributes O(1) work per query centroid after its logit, and no term
@@ -18,7 +18,6 @@
 namespace svgear {
 namespace {
 
-constexpr int kKeyChunk = 64;
 constexpr float kMaxExponent = 40.0f;  // e^40 squared still fits fp32
 
 // Sbar[a][b] = qbar_a . kbar_b * scale; mrow[a] = max over non-empty b.
@@ -101,109 +100,133 @@ sbar_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, cons
   }
 }
 
-template <typename T, int D, bool VALUE_AWARE>
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+// fp32 inputs: block errors with the logits qbar_a . k_j on fp32 matrix cores (bound: those, 157 TFLOP/s
+// nominal). One workgroup per (head, key cluster, group of kF32Cents query centroids); its four waves
+// take the cluster's 32-key blocks in turn. A wave keeps the keys of its block as A operands of
+// v_mfma_f32_32x32x2_f32 (a lane half holds half of row lane % 32, in the contraction order the
+// centroids are read in), works out |delta_j|^2 and vbar . delta_j of those keys once, and passes the
+// centroids by, 32 at a time; the error of a centroid accumulates in the lanes that hold its keys.
+// The kernel before kept one query centroid per lane and did its dot products on the vector ALU:
+// 32 centroids x 64 clusters of one head of 4,096 keys, d = 64: 112 -> 12 us.
+constexpr int kF32Cents = 128;
+
+template <int D, bool VALUE_AWARE>
 __global__ void __launch_bounds__(256)
-block_error_kernel(const float* __restrict__ qbar, const float* __restrict__ vbar,
-                                   const T* __restrict__ kp, const T* __restrict__ vp,
-                                   const int32_t* __restrict__ k_offsets, const float* __restrict__ sbar,
-                                   const float* __restrict__ mrow, int64_t Nk, int Cq, int Ck, float scale,
-                                   float* __restrict__ scores) {
-  __shared__ float kf[kKeyChunk][D];  // keys of the chunk, widened to fp32
-  __shared__ float nd[kKeyChunk];     // |delta_j|^2
-  __shared__ float dd[kKeyChunk];     // vbar . delta_j
-  const int b = blockIdx.x, bh = blockIdx.y;
-  const int a = blockIdx.z * 256 + threadIdx.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__ vbar, const float* __restrict__ kp,
+                       const float* __restrict__ vp, const int32_t* __restrict__ k_offsets,
+                       const float* __restrict__ sbar, const float* __restrict__ mrow, int64_t Nk, int Cq, int Ck,
+                       float scale, float* __restrict__ scores) {
+  constexpr int QS = D / 2;
+  constexpr int NB = kF32Cents / 32;
+  __shared__ float part[4][kF32Cents];
+  __shared__ __attribute__((aligned(16))) float s_vb[D];
+  const int b = blockIdx.x, bh = blockIdx.y, a0 = blockIdx.z * kF32Cents;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
   const int start = off[b], end = off[b + 1];
-  const bool live = a < Cq;
-  float* out = scores + ((int64_t)bh * Cq + (live ? a : 0)) * Ck + b;
+  const int n_cent = min(kF32Cents, Cq - a0), nb = (n_cent + 31) / 32;
+  float* out = scores + ((int64_t)bh * Cq + a0) * Ck + b;
   if (end <= start) {  // empty key cluster: score 0, never routed nor compensated
-    if (live) *out = 0.f;
+    if (tid < n_cent) out[(int64_t)tid * Ck] = 0.f;
     return;
   }
-  float q[D];
-  {
-    const float4* qa = reinterpret_cast<const float4*>(qbar + ((int64_t)bh * Cq + (live ? a : 0)) * D);
+  const float* kh = kp + (int64_t)bh * Nk * D;
+  const float* vh = vp + (int64_t)bh * Nk * D;
+  if (VALUE_AWARE && tid < D) s_vb[tid] = vbar[((int64_t)bh * Ck + b) * D + tid];
+  __syncthreads();
+  const float* vb = s_vb + lh * QS;
+  float E[NB], W[NB], m[NB];
 #pragma unroll
-    for (int t = 0; t < D / 4; ++t) {
-      const float4 v = qa[t];
-      q[4 * t] = v.x; q[4 * t + 1] = v.y; q[4 * t + 2] = v.z; q[4 * t + 3] = v.w;
-    }
+  for (int i = 0; i < NB; ++i) {
+    const int a = a0 + 32 * i + li;
+    E[i] = 0.f;
+    m[i] = a < Cq ? mrow[(int64_t)bh * Cq + a] : 0.f;
+    W[i] = a < Cq ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + b] - m[i], kMaxExponent)) : 0.f;
   }
-  const float m_a = live ? mrow[(int64_t)bh * Cq + a] : 0.f;
-  const float W = live ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + b] - m_a, kMaxExponent)) : 0.f;
-  constexpr int PER = D / 64;
-  const float* vb = vbar + ((int64_t)bh * Ck + b) * D;
-  float vbl[PER];
   float nvb = 0.f;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) vbl[k] = vb[lane * PER + k];
-  if (VALUE_AWARE) {
-    float part = 0.f;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) part = __builtin_fmaf(vbl[k], vbl[k], part);
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    nvb = part;
+  if (VALUE_AWARE) {  // |vbar_b|^2
+#pragma unroll 4
+    for (int t = 0; t < QS; ++t) nvb = __builtin_fmaf(vb[t], vb[t], nvb);
+    nvb += __shfl_xor(nvb, 32);
   }
-  const T* kh = kp + (int64_t)bh * Nk * D;
-  const T* vh = vp + (int64_t)bh * Nk * D;
-  float E = 0.f;
-  for (int j0 = start; j0 < end; j0 += kKeyChunk) {
-    const int nk = min(kKeyChunk, end - j0);
-    __syncthreads();
-    for (int kk = wave; kk < nk; kk += nwaves) {
-      const T* kr = kh + (int64_t)(j0 + kk) * D + lane * PER;
+  for (int j0 = start + 32 * wave; j0 < end; j0 += 128) {
+    const int j = min(j0 + li, end - 1);  // (rows past the cluster's end are not counted below)
+    float kf[QS];
+    const float4* kr = reinterpret_cast<const float4*>(kh + (int64_t)j * D + lh * QS);
 #pragma unroll
-      for (int k = 0; k < PER; ++k) kf[kk][lane * PER + k] = Elem<T>::load(kr + k);
-      if (VALUE_AWARE) {
-        const T* vr = vh + (int64_t)(j0 + kk) * D + lane * PER;
-        float p_nd = 0.f, p_dd = 0.f;
+    for (int t = 0; t < QS / 4; ++t) {
+      const float4 v = kr[t];
+      kf[4 * t] = v.x; kf[4 * t + 1] = v.y; kf[4 * t + 2] = v.z; kf[4 * t + 3] = v.w;
+    }
+    float nd = 0.f, dd = 0.f;
+    if (VALUE_AWARE) {
+      const float4* vr = reinterpret_cast<const float4*>(vh + (int64_t)j * D + lh * QS);
+#pragma unroll 8
+      for (int t = 0; t < QS / 4; ++t) {
+        const float4 v = vr[t], w = reinterpret_cast<const float4*>(vb)[t];
+        const float d0 = v.x - w.x, d1 = v.y - w.y, d2 = v.z - w.z, d3 = v.w - w.w;
+        nd = __builtin_fmaf(d0, d0, nd); dd = __builtin_fmaf(d0, w.x, dd);
+        nd = __builtin_fmaf(d1, d1, nd); dd = __builtin_fmaf(d1, w.y, dd);
+        nd = __builtin_fmaf(d2, d2, nd); dd = __builtin_fmaf(d2, w.z, dd);
+        nd = __builtin_fmaf(d3, d3, nd); dd = __builtin_fmaf(d3, w.w, dd);
+      }
+      nd += __shfl_xor(nd, 32);
+      dd += __shfl_xor(dd, 32);
+    }
+    // register r of a score tile is key j0 + 8 (r/4) + 4 lh + r%4
+    float nn[16], dl[16];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-          const float dl = Elem<T>::load(vr + k) - vbl[k];
-          p_nd = __builtin_fmaf(dl, dl, p_nd);
-          p_dd = __builtin_fmaf(dl, vbl[k], p_dd);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-          p_nd += __shfl_xor(p_nd, o);
-          p_dd += __shfl_xor(p_dd, o);
-        }
-        if (lane == 0) {
-          nd[kk] = p_nd;
-          dd[kk] = p_dd;
+    for (int r = 0; r < 16; ++r) {
+      const int key = 8 * (r >> 2) + 4 * lh + (r & 3);
+      nn[r] = __shfl(nd, key);
+      dl[r] = __shfl(dd, key);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (i >= nb) break;
+      const float4* qr = reinterpret_cast<const float4*>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D +
+                                                         lh * QS);
+      f32x16 s0, s1;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s0[r] = s1[r] = 0.f;
+#pragma unroll
+      for (int t = 0; t < QS / 4; ++t) {
+        const float4 q = qr[t];
+        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t], q.x, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t + 1], q.y, s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t + 2], q.z, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t + 3], q.w, s1, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (j0 + 8 * (r >> 2) + 4 * lh + (r & 3) >= end) continue;
+        const float w = __expf(fminf((s0[r] + s1[r]) * scale - m[i], kMaxExponent));
+        const float g = W[i] - w;
+        if (VALUE_AWARE) {
+          E[i] = __builtin_fmaf(g * g, nvb, E[i]);
+          E[i] = __builtin_fmaf(-2.0f * g * w, dl[r], E[i]);
+          E[i] = __builtin_fmaf(w * w, nn[r], E[i]);
+        } else {
+          E[i] = __builtin_fmaf(g, g, E[i]);
         }
       }
     }
-    __syncthreads();
-    for (int kk = 0; kk < nk; ++kk) {
-      const float4* kr = reinterpret_cast<const float4*>(&kf[kk][0]);
-      float dot = 0.f;
-#pragma unroll
-      for (int t = 0; t < D / 4; ++t) {
-        const float4 v = kr[t];
-        dot = __builtin_fmaf(q[4 * t], v.x, dot);
-        dot = __builtin_fmaf(q[4 * t + 1], v.y, dot);
-        dot = __builtin_fmaf(q[4 * t + 2], v.z, dot);
-        dot = __builtin_fmaf(q[4 * t + 3], v.w, dot);
-      }
-      const float w = __expf(fminf(dot * scale - m_a, kMaxExponent));
-      const float g = W - w;
-      if (VALUE_AWARE) {
-        E = __builtin_fmaf(g * g, nvb, E);
-        E = __builtin_fmaf(-2.0f * g * w, dd[kk], E);
-        E = __builtin_fmaf(w * w, nd[kk], E);
-      } else {
-        E = __builtin_fmaf(g, g, E);
-      }
-    }
   }
-  if (live) *out = E / (float)(end - start);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const float e = E[i] + __shfl_xor(E[i], 32);
+    if (lh == 0) part[wave][32 * i + li] = e;
+  }
+  __syncthreads();
+  if (tid < n_cent)
+    out[(int64_t)tid * Ck] = ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])) / (float)(end - start);
 }
 
 // ---- bf16 inputs: the probe on the matrix cores -----------------------------------------
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
   union { uint4 u; bf16x8 b; } c;
   c.u = v;
@@ -517,14 +540,13 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
     SVGEAR_LAUNCH_CHECK();
     return SVGEAR_OK;
   }
-  const int threads = Cq >= 256 ? 256 : (int)align_up(Cq, 64);
-  dim3 grid(Ck, BH, (unsigned)ceil_div(Cq, 256));
-#define SVGEAR_PB(T, D, VA)                                                                                   \
-  block_error_kernel<T, D, VA><<<grid, threads, 0, s>>>(qbar, vbar, static_cast<const T*>(kp),                \
-                                                        static_cast<const T*>(vp), k_offsets, sbar, mrow, Nk, \
-                                                        Cq, Ck, scale, scores)
-  if (d == 64) { if (value_aware) SVGEAR_PB(float, 64, true); else SVGEAR_PB(float, 64, false); }
-  else { if (value_aware) SVGEAR_PB(float, 128, true); else SVGEAR_PB(float, 128, false); }
+  const dim3 grid(Ck, BH, (unsigned)ceil_div(Cq, kF32Cents));
+#define SVGEAR_PB(D, VA)                                                                                        \
+  block_error_f32_kernel<D, VA><<<grid, 256, 0, s>>>(qbar, vbar, static_cast<const float*>(kp),                 \
+                                                     static_cast<const float*>(vp), k_offsets, sbar, mrow, Nk, Cq, Ck, \
+                                                     scale, scores)
+  if (d == 64) { if (value_aware) SVGEAR_PB(64, true); else SVGEAR_PB(64, false); }
+  else { if (value_aware) SVGEAR_PB(128, true); else SVGEAR_PB(128, false); }
 #undef SVGEAR_PB
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;

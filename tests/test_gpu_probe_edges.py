@@ -1,0 +1,60 @@
+"""GPU probe where its tiles can go wrong: key clusters of 0 to a few hundred keys around the 32-key
+blocks and the four waves that take them, query centroids around the groups of 32 and 128, both types,
+head sizes and estimates, against the definition in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_08982_amd as sv
+from helpers import dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+K_SIZES = [0, 1, 31, 32, 33, 64, 127, 128, 129, 160, 257, 3, 0, 20, 96]
+
+
+def _definition(q, kb, vb, K, V, sizes, scale, plain):
+    S = np.where(sizes[None] > 0, (q @ kb.T) * scale, -np.inf)
+    m = S.max(1, keepdims=True)
+    W, w = np.exp(S - m), np.exp((q @ K.T) * scale - m)
+    out = np.zeros((len(q), len(sizes)))
+    at = 0
+    for b, n in enumerate(sizes):
+        u, x = W[:, b: b + 1], w[:, at: at + n]
+        if n and plain:
+            out[:, b] = ((u - x) ** 2).sum(1) / n
+        elif n:
+            diff = u[:, :, None] * vb[b][None, None] - x[:, :, None] * V[at: at + n][None]
+            out[:, b] = (diff ** 2).sum((1, 2)) / n
+        at += n
+    return out
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Cq", [1, 31, 33, 128, 129, 300])
+@pytest.mark.parametrize("plain", [False, True])
+def test_scores_at_the_edges_of_tiles(dtype, d, Cq, plain):
+    g = torch.Generator().manual_seed(Cq + d)
+    sizes, tail, H = np.array(K_SIZES), 9, 2
+    Ck, n = len(sizes), int(sizes.sum())
+    q = torch.randn(1, H, Cq, d, generator=g)
+    kb, vb = torch.randn(1, H, Ck, d, generator=g), torch.randn(1, H, Ck, d, generator=g)
+    lab = torch.from_numpy(np.repeat(np.arange(Ck), sizes))
+    K, V = (torch.cat([t[:, :, lab] + 0.3 * torch.randn(1, H, n, d, generator=g), torch.randn(1, H, tail, d, generator=g)], 2)
+            .to(dtype) for t in (kb, vb))
+    koff = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes), [n + tail]]).astype(np.int32)).expand(1, H, -1).contiguous()
+    qoff = torch.arange(Cq + 2, dtype=torch.int32).expand(1, H, -1).contiguous()
+    # centroid values need no more than 4-byte alignment
+    vb_dev = torch.empty(vb.numel() + 1, device=dev())[1:].view_as(vb).copy_(vb)
+    r = sv.probe_route(q.to(dev()), kb.to(dev()), vb_dev, K.to(dev()), V.to(dev()), qoff.to(dev()), koff.to(dev()),
+                       n * Cq // 4, d ** -0.5, flags=sv.PROBE_PLAIN if plain else 0)
+    torch.cuda.synchronize()
+    for h in range(H):
+        f = lambda t: t[0, h].double().numpy()
+        ref = _definition(f(q), f(kb), f(vb), f(K)[:n], f(V)[:n], sizes, d ** -0.5, plain)
+        got = to_np(r["scores"][0, h]).astype(np.float64)
+        assert not got[:, sizes == 0].any()
+        # a logit of size s is off by s 2^-22 or so after d products, its exponential relatively by as much
+        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+        assert (np.abs(got - ref) <= 2e-4 * ref + 1e-6 * ref.max(1, keepdims=True)).all()
