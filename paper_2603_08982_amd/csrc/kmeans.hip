@@ -51,7 +51,7 @@ constexpr int kListFromIteration = SVGEAR_LIST_FROM;
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-// Prepares the centroids of one iteration for the matrix cores:
+// Prepares the caller's centroids for the matrix cores (later iterations: publish_centroid):
 //  * cn[c] = |c|^2 as ONE fp32 fma chain over t = 0..d-1 (+inf for the padding centroids that
 //    round C up to a multiple of 64, so they never win the argmin);
 //  * cperm: the centroid table re-laid in MFMA operand order. For v_mfma_f32_32x32x2_f32 the
@@ -63,7 +63,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 //    the operand order of v_mfma_f32_32x32x16_bf16 (A[i = lane%32][k = 16s + 8(lane/32) + e]):
 //    [blk][piece][s][lane][e], 16 bytes per lane; crow (with chl): the same two pieces row by row,
 //    [c][piece][d], for the kernel that fetches single centroids;
-//  * amb_count, head_state, rmax (optional): the per-iteration counters and maxima are reset.
+//  * amb_count, head_state, rmax, dirty (optional): the per-iteration counters, maxima and flags are reset.
 __global__ void __launch_bounds__(256)
 prep_centroids_kernel(const float* __restrict__ cent, int C, int Cpad, int d, float* __restrict__ cperm,
                       float* __restrict__ cn, bf16_t* __restrict__ chl, bf16_t* __restrict__ crow,
@@ -1178,6 +1178,78 @@ assign_list_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, 
   }
 }
 
+// What the update hands to the next iteration's assignment: the operand tables of every centroid it
+// changes (prep_centroids_kernel lays them out once per call, at the start) and cleared counters.
+// Null tables: nothing follows.
+struct NextIteration {
+  float* cperm;
+  float* cn;
+  bf16_t* chl;
+  bf16_t* crow;
+  int32_t* amb_count;
+  int32_t* head_state;
+  int32_t* rmax;
+};
+
+// Entries of centroid c (its D values in `row`, 16-byte aligned LDS) in the tables described at
+// prep_centroids_kernel; called by D threads, t = 0 .. D-1. One of them walks the |c|^2 chain. (Laying
+// all tables out again took a launch per iteration, 50 us at 40 x 1,000 centroids, 3 us in a small layer;
+// most centroids stay as they are in the later iterations. 40 x 75,600 keys, 10 iterations: 10.35 ->
+// 10.09 ms.)
+template <int D>
+__device__ __forceinline__ void publish_centroid(const NextIteration& nx, const float* row, int t, int bh, int c,
+                                                 int Cpad) {
+  constexpr int KSN = D / 16;
+  const int64_t n = (int64_t)Cpad * D;
+  const int blk = c >> 5, i = c & 31;
+  if (t < D / 4) {
+    const int q = t >> 1, h = t & 1;
+    const float4 v0 = *reinterpret_cast<const float4*>(row + 8 * q), v1 = *reinterpret_cast<const float4*>(row + 8 * q + 4);
+    *reinterpret_cast<float4*>(nx.cperm + (int64_t)bh * n + (((int64_t)blk * (D / 8) + q) * 64 + i + 32 * h) * 4) =
+        h ? make_float4(v0.y, v0.w, v1.y, v1.w) : make_float4(v0.x, v0.z, v1.x, v1.z);
+  } else if (t < D / 4 + D / 8) {
+    if (nx.chl) {
+      const int u = t - D / 4, k0 = 8 * u;
+      uint32_t hw[4], lw[4];
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const float a = row[k0 + e], b = row[k0 + e + 1];
+        const bf16_t h0 = f32_to_bf16(a), h1 = f32_to_bf16(b);
+        const bf16_t l0 = f32_to_bf16(a - bf16_to_f32(h0)), l1 = f32_to_bf16(b - bf16_to_f32(h1));
+        hw[e >> 1] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        lw[e >> 1] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+      }
+      bf16_t* op = nx.chl + (int64_t)bh * 2 * n + (((int64_t)blk * 2) * KSN + (u >> 1)) * 512 + (i + 32 * (u & 1)) * 8;
+      *reinterpret_cast<uint4*>(op) = uint4{hw[0], hw[1], hw[2], hw[3]};
+      *reinterpret_cast<uint4*>(op + (int64_t)KSN * 512) = uint4{lw[0], lw[1], lw[2], lw[3]};
+      bf16_t* rw = nx.crow + (int64_t)bh * 2 * n + (int64_t)c * 2 * D + k0;
+      *reinterpret_cast<uint4*>(rw) = uint4{hw[0], hw[1], hw[2], hw[3]};
+      *reinterpret_cast<uint4*>(rw + D) = uint4{lw[0], lw[1], lw[2], lw[3]};
+    }
+  } else if (t == D - 1) {
+    float acc = 0.f;  // one chain over the dims in order
+#pragma unroll 8
+    for (int k = 0; k < D / 4; ++k) {
+      const float4 v = *reinterpret_cast<const float4*>(row + 4 * k);
+      acc = __builtin_fmaf(v.x, v.x, acc);
+      acc = __builtin_fmaf(v.y, v.y, acc);
+      acc = __builtin_fmaf(v.z, v.z, acc);
+      acc = __builtin_fmaf(v.w, v.w, acc);
+    }
+    nx.cn[(int64_t)bh * Cpad + c] = acc;
+  }
+}
+
+// The next iteration's counters: those of cluster c, and with the first cluster those of the head.
+__device__ __forceinline__ void clear_counters(const NextIteration& nx, int bh, int c, int Cpad) {
+  if (!nx.cperm || !nx.amb_count) return;
+  nx.rmax[(int64_t)bh * Cpad + c] = 0;
+  if (c == 0) {
+    nx.amb_count[bh] = 0;
+    for (int k = 0; k < kHeadState; ++k) nx.head_state[bh * kHeadState + k] = 0;
+  }
+}
+
 // Mean of the members of one cluster. A row is covered by LPR lanes of 16 bytes each; the
 // 256 threads form 256/LPR member slots. Slot s sums members s, s+SLOTS, ... in order;
 // slots are then added in slot order. With gridDim.z = P > 1 the members are cut into P
@@ -1188,13 +1260,14 @@ template <typename T, int D>
 __global__ void __launch_bounds__(256)
 means_kernel(const T* __restrict__ x, Strides st, int H, const int32_t* __restrict__ perm, int64_t N,
              const int32_t* __restrict__ offsets, int C, float* __restrict__ cent,
-             int32_t* __restrict__ counts, float* __restrict__ partial, const int32_t* __restrict__ dirty,
-             int Cpad, float* __restrict__ drift) {
+             int32_t* __restrict__ counts, float* __restrict__ partial, int32_t* __restrict__ dirty,
+             int Cpad, float* __restrict__ drift, NextIteration next) {
   constexpr int VEC = 16 / sizeof(T);  // elements per lane
   constexpr int LPR = D / VEC;         // lanes per row
   constexpr int SLOTS = 256 / LPR;
-  __shared__ float red[SLOTS][D];
+  __shared__ __attribute__((aligned(16))) float red[SLOTS][D];
   const int c = blockIdx.x, bh = blockIdx.y;
+  if (gridDim.z == 1 && threadIdx.x == 0) clear_counters(next, bh, c, Cpad);
   // a cluster whose membership did not change keeps its centroid and count (same sum)
   if (dirty && !dirty[(int64_t)bh * Cpad + c]) {
     if (drift && gridDim.z == 1 && threadIdx.x == 0) drift[(int64_t)bh * Cpad + c] = 0.f;  // it did not move
@@ -1252,11 +1325,17 @@ means_kernel(const T* __restrict__ x, Strides st, int H, const int32_t* __restri
         dv2 = dv * dv;
       }
       cent[ci] = v;
+      red[0][threadIdx.x] = v;  // (this thread's own column)
     } else {
       partial[(((int64_t)bh * C + c) * P + part) * D + threadIdx.x] = s;
     }
   }
   if (P == 1 && threadIdx.x == 0 && counts) counts[(int64_t)bh * C + c] = cnt;
+  if (P == 1 && threadIdx.x == 0 && dirty) dirty[(int64_t)bh * Cpad + c] = 0;  // (everyone has read it)
+  if (P == 1 && next.cperm && cnt > 0) {
+    __syncthreads();
+    if (threadIdx.x < D) publish_centroid<D>(next, red[0], threadIdx.x, bh, c, Cpad);
+  }
   if (P == 1 && drift) {
     // how far the centroid moved, rounded up (an fp32 sum of D non-negative terms is within
     // D 2^-23 of the exact one): the row bounds of the next iteration need it
@@ -1278,19 +1357,23 @@ means_kernel(const T* __restrict__ x, Strides st, int H, const int32_t* __restri
 // cluster without members keeps its centroid. With drift != nullptr it also records how far
 // every centroid moved (rounded up; 0 for the clusters that were not touched). D is 64 or 128,
 // so the D threads of a centroid are whole waves of one workgroup.
+template <int D>
 __global__ void __launch_bounds__(256)
-means_finish_kernel(const float* __restrict__ partial, const int32_t* __restrict__ offsets, int C, int P, int D,
-                    float* __restrict__ cent, int32_t* __restrict__ counts, const int32_t* __restrict__ dirty,
-                    int Cpad, float* __restrict__ drift) {
+means_finish_kernel(const float* __restrict__ partial, const int32_t* __restrict__ offsets, int C, int P,
+                    float* __restrict__ cent, int32_t* __restrict__ counts, int32_t* __restrict__ dirty,
+                    int Cpad, float* __restrict__ drift, NextIteration next) {
   __shared__ float dpart[4];
+  __shared__ __attribute__((aligned(16))) float row[256];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (bh, c, dim)
   const int bh = blockIdx.y;
   const bool in = i < (int64_t)C * D;
   const int c = in ? (int)(i / D) : 0, dim = in ? (int)(i % D) : 1;
+  const bool on = in && !(dirty && !dirty[(int64_t)bh * Cpad + c]);
   float dv2 = 0.f;
-  if (in && !(dirty && !dirty[(int64_t)bh * Cpad + c])) {
+  int cnt = 0;
+  if (on) {
     const int32_t* off = offsets + (int64_t)bh * (C + 2);
-    const int cnt = off[c + 1] - off[c];
+    cnt = off[c + 1] - off[c];
     if (cnt > 0) {
       const float* pp = partial + (((int64_t)bh * C + c) * P) * D + dim;
       float s = pp[0];
@@ -1302,21 +1385,27 @@ means_finish_kernel(const float* __restrict__ partial, const int32_t* __restrict
         dv2 = dv * dv;
       }
       cent[ci] = v;
+      row[threadIdx.x] = v;
     }
     if (dim == 0 && counts) counts[(int64_t)bh * C + c] = cnt;
   }
+  const int wave = threadIdx.x >> 6;
   if (drift) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) dv2 += __shfl_xor(dv2, o);
-    const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) dpart[wave] = dv2;
-    __syncthreads();
-    if (in && dim == 0) {
+  }
+  __syncthreads();
+  if (in && dim == 0) {
+    if (drift) {
       float t = dpart[wave];
       for (int w = 1; w < D / 64; ++w) t += dpart[wave + w];
       drift[(int64_t)bh * Cpad + c] = sqrtf(t) * 1.0001f;
     }
+    if (dirty) dirty[(int64_t)bh * Cpad + c] = 0;
+    clear_counters(next, bh, c, Cpad);
   }
+  if (next.cperm && on && cnt > 0) publish_centroid<D>(next, row + threadIdx.x / D * D, dim, bh, c, Cpad);
 }
 
 // Parts per cluster of the centroid update: about 128 members per part on average, at most 8.
@@ -1376,21 +1465,24 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   // only_changed: clusters that neither gained nor lost a member in this iteration keep their
   // centroid (flags set by the assignment kernels; null = every cluster)
   // moves: where the update records how far every centroid moved (null = not needed)
-  auto update = [&](const T* src, float* dst, int32_t* cnt_out, const int32_t* only_changed, float* moves) -> int {
+  // next: the tables the update refreshes for the iteration that follows (null = none follows)
+  auto update = [&](const T* src, float* dst, int32_t* cnt_out, int32_t* only_changed, float* moves,
+                    const NextIteration& next) -> int {
     means_kernel<T, D><<<dim3(C, BH, P), 256, 0, s>>>(src, st, H, perm, nv, offsets, C, dst, cnt_out, partial,
-                                                      only_changed, Cpad, moves);
+                                                      only_changed, Cpad, moves, next);
     SVGEAR_LAUNCH_CHECK();
     if (P > 1) {
-      means_finish_kernel<<<dim3((unsigned)ceil_div((int64_t)C * D, 256), BH), 256, 0, s>>>(
-          partial, offsets, C, P, D, dst, cnt_out, only_changed, Cpad, moves);
+      means_finish_kernel<D><<<dim3((unsigned)ceil_div((int64_t)C * D, 256), BH), 256, 0, s>>>(
+          partial, offsets, C, P, dst, cnt_out, only_changed, Cpad, moves, next);
       SVGEAR_LAUNCH_CHECK();
     }
     return SVGEAR_OK;
   };
+  const NextIteration tables{cperm, cn, chl, crow, amb_count, head_state, rmax};
+  const NextIteration nothing{};
+  prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, chl, crow, amb_count, head_state, rmax, dirty);
+  SVGEAR_LAUNCH_CHECK();
   for (int it = 0; it < iters; ++it) {
-    prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, chl, crow, amb_count, head_state, rmax,
-                                             dirty);
-    SVGEAR_LAUNCH_CHECK();
     if constexpr (kFilter) {
       // (with at most two chunks of centroids a workgroup of the filter takes several groups of rows)
       const bool resident = Cpad <= 2 * kCentChunk;
@@ -1442,11 +1534,11 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     int rc = sort_labels(labels, BH, nv, 0, C, perm, offsets, chunk_hist, s, use_lists ? tiles : nullptr, tile_cap,
                          kListChunk, use_lists ? rank : nullptr);
     if (rc != SVGEAR_OK) return rc;
-    rc = update(x, cent, counts, (kFilter && it > 0) ? dirty : nullptr, drift);
+    rc = update(x, cent, counts, (kFilter && it > 0) ? dirty : nullptr, drift, it + 1 < iters ? tables : nothing);
     if (rc != SVGEAR_OK) return rc;
   }
   if (x2) {
-    const int rc = update(x2, cent2, nullptr, nullptr, nullptr);
+    const int rc = update(x2, cent2, nullptr, nullptr, nullptr, nothing);
     if (rc != SVGEAR_OK) return rc;
   }
   return SVGEAR_OK;
