@@ -74,9 +74,9 @@ __device__ __forceinline__ bool mask_bit(const uint32_t* mrow, int b) { return (
 // Query rows per workgroup tile of the bf16 kernel.
 int attn_bf16_bm();
 
-// Workspace of its work lists (bytes) and their construction on stream s.
+// Workspace of its work lists (bytes); their construction, and the centroid tables in bf16, on stream s.
 size_t plan_bf16_workspace(int BH, int Cq, int64_t Nq);
-int plan_bf16(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s);
+int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size_t ws_bytes, hipStream_t s);
 
 // Whether it takes Ck key clusters at head dimension d.
 bool attn_bf16_supported(int d, int Ck);

@@ -19,21 +19,6 @@
 // fp32 kernel: the same decomposition on the fp32 matrix cores (attention_f32.hip).
 #include "attention.h"
 
-namespace svgear {
-namespace {
-
-// Both centroid tables to bf16 in one launch (blockIdx.y picks the table).
-__global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __restrict__ src1, int64_t n,
-                               bf16_t* __restrict__ dst0, bf16_t* __restrict__ dst1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (blockIdx.y == 0) dst0[i] = f32_to_bf16(src0[i]);
-  else dst1[i] = f32_to_bf16(src1[i]);
-}
-
-}  // namespace
-}  // namespace svgear
-
 using namespace svgear;
 
 extern "C" size_t svgear_sparse_attn_comp_workspace(int B, int H, int64_t Nq, int64_t Nk, int d, int Cq, int Ck) {
@@ -87,10 +72,7 @@ static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
   a.kbar16 = kbar16;
   a.vbar16 = vbar16;
-  const int64_t n = (int64_t)BH * Ck * d;
-  to_bf16_kernel<<<dim3((unsigned)ceil_div(n, 256), 2), 256, 0, s>>>(kbar, vbar, n, kbar16, vbar16);
-  SVGEAR_LAUNCH_CHECK();
-  const int rc = plan_bf16(a, static_cast<char*>(ws) + w.used, ws_bytes - w.used, s);
+  const int rc = plan_bf16(a, d, kbar16, vbar16, static_cast<char*>(ws) + w.used, ws_bytes - w.used, s);
   if (rc != SVGEAR_OK) return rc;
   return launch_attn_bf16(a, d, (unsigned)((size_t)BH * (ceil_div(Nq, attn_bf16_bm()) + Cq + 1)), s);
 }

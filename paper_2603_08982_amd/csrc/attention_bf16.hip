@@ -554,41 +554,54 @@ attn_bf16_kernel(AttnArgs p) {
   }
 }
 
+// Both centroid tables to bf16 in one launch (blockIdx.y picks the table).
+__global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __restrict__ src1, int64_t n,
+                               bf16_t* __restrict__ dst0, bf16_t* __restrict__ dst1) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (blockIdx.y == 0) dst0[i] = f32_to_bf16(src0[i]);
+  else dst1[i] = f32_to_bf16(src1[i]);
+}
+
 // ------------------------------------------------------------------------ work lists
 // Item = (head, query cluster); its tiles all run T = #routed key tiles + #centroid tiles
 // pipeline steps. Items are ranked by T, longest first (ties by index), and dealt to the 8
 // lists in boustrophedon order, which keeps the lists' totals close; inside a list the
 // longest come first, so a list's tail consists of its shortest tiles.
+// Steps and tiles of item (bh, a), by a whole wave, its lanes over the routed key clusters.
+__device__ __forceinline__ void plan_item(const int32_t* q_offsets, const int32_t* k_offsets, const int32_t* row_ptr,
+                                          const int32_t* col_idx, int bh, int a, int Cq, int Ck, int BM, int32_t& T,
+                                          int32_t& nt) {
+  const int R = Cq + 1, Cc = Ck + 1, lane = threadIdx.x & 63;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
+  const int n = qo[a + 1] - qo[a];
+  const int32_t* ci = col_idx + (int64_t)bh * R * Cc + rp[a];
+  const int ne = rp[a + 1] - rp[a];
+  int64_t nr = 0;
+  for (int e = lane; e < ne; e += 64) {
+    const int b = ci[e];
+    const int sz = ko[b + 1] - ko[b];
+    nr += sz > 0 ? sz : 0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) nr += __shfl_xor(nr, o);
+  if (lane == 0) {
+    const int tiles = n > 0 ? (n + BM - 1) / BM : 0;
+    nt = tiles;
+    T = tiles > 0 ? (int)((nr + BN - 1) / BN) + (a < Cq ? (Ck + BN - 1) / BN : 0) : 0;
+  }
+}
+
+// A wave per item over the whole grid (one workgroup per head took 173 us for 5 heads of 300 clusters,
+// this grid 10).
 __global__ void __launch_bounds__(256)
 plan_items_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
                   const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int Cq, int Ck, int BM,
                   int32_t* __restrict__ item_T, int32_t* __restrict__ item_nt) {
-  const int bh = blockIdx.y, R = Cq + 1, Cc = Ck + 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
-  const int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
-  // a wave per query cluster, its lanes over the routed key clusters (one workgroup per head took
-  // 173 us for 5 heads of 300 clusters, this grid 10)
-  const int a = 4 * blockIdx.x + wave;
-  if (a < R) {
-    const int n = qo[a + 1] - qo[a];
-    const int32_t* ci = col_idx + (int64_t)bh * R * Cc + rp[a];
-    const int ne = rp[a + 1] - rp[a];
-    int64_t nr = 0;
-    for (int e = lane; e < ne; e += 64) {
-      const int b = ci[e];
-      const int sz = ko[b + 1] - ko[b];
-      nr += sz > 0 ? sz : 0;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nr += __shfl_xor(nr, o);
-    if (lane == 0) {
-      const int nt = n > 0 ? (n + BM - 1) / BM : 0;
-      item_nt[bh * R + a] = nt;
-      item_T[bh * R + a] = nt > 0 ? (int)((nr + BN - 1) / BN) + (a < Cq ? (Ck + BN - 1) / BN : 0) : 0;
-    }
-  }
+  const int bh = blockIdx.y, R = Cq + 1, a = 4 * blockIdx.x + (threadIdx.x >> 6);
+  if (a < R) plan_item(q_offsets, k_offsets, row_ptr, col_idx, bh, a, Cq, Ck, BM, item_T[bh * R + a], item_nt[bh * R + a]);
 }
 
 // Rank of every item by (T descending, index ascending), by counting: a workgroup ranks 64 items,
@@ -625,11 +638,11 @@ plan_rank_kernel(const int32_t* __restrict__ item_T, int M, int32_t* __restrict_
 // rank r -> (list, position): round r/8 deals one item to every list, odd rounds in reverse
 __device__ __forceinline__ int list_of_rank(int r) { return ((r >> 3) & 1) ? 7 - (r & 7) : (r & 7); }
 
-__global__ void __launch_bounds__(1024)
-plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ item_nt,
-                  const int32_t* __restrict__ by_rank, int M, int Cq, int BM, int32_t* __restrict__ rank_off,
-                  int32_t* __restrict__ sched_bh, int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
-                  int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x) {
+// The lists from the ranked items (one workgroup of 1024).
+__device__ __forceinline__ void write_lists(const int32_t* q_offsets, const int32_t* item_nt, const int32_t* by_rank,
+                                            int M, int Cq, int BM, int32_t* rank_off, int32_t* sched_bh,
+                                            int32_t* sched_a, int32_t* sched_row0, int32_t* sched_rend,
+                                            int32_t* sched_x) {
   __shared__ int32_t total[8], first[8];
   const int tid = threadIdx.x, R = Cq + 1, lane = tid & 63, wave = tid >> 6;
   const int rounds = (M + 7) / 8;
@@ -701,6 +714,47 @@ plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
   }
 }
 
+__global__ void __launch_bounds__(1024)
+plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ item_nt,
+                  const int32_t* __restrict__ by_rank, int M, int Cq, int BM, int32_t* __restrict__ rank_off,
+                  int32_t* __restrict__ sched_bh, int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
+                  int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x) {
+  write_lists(q_offsets, item_nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
+}
+
+// The whole plan of a call with up to kPlanItems items in one workgroup (block 0: a small layer is
+// bound by launches, and the three kernels took 9 us of it; 256 items take 16 waves longer than that),
+// and beside it the centroid tables in
+// bf16 (the other blocks).
+constexpr int kPlanItems = 64;
+__global__ void __launch_bounds__(1024)
+plan_small_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
+                  const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int M, int Cq, int Ck, int BM,
+                  int32_t* __restrict__ sched_bh, int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
+                  int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x, const float* __restrict__ kbar,
+                  const float* __restrict__ vbar, int64_t n, bf16_t* __restrict__ kbar16, bf16_t* __restrict__ vbar16) {
+  if (blockIdx.x > 0) {
+    const int64_t i = (int64_t)(blockIdx.x - 1) * 1024 + threadIdx.x;
+    if (i < n) {
+      kbar16[i] = f32_to_bf16(kbar[i]);
+      vbar16[i] = f32_to_bf16(vbar[i]);
+    }
+    return;
+  }
+  __shared__ int32_t item_T[kPlanItems], item_nt[kPlanItems], by_rank[kPlanItems], rank_off[kPlanItems];
+  const int wave = threadIdx.x >> 6, R = Cq + 1;
+  for (int i = wave; i < M; i += 16)
+    plan_item(q_offsets, k_offsets, row_ptr, col_idx, i / R, i % R, Cq, Ck, BM, item_T[i], item_nt[i]);
+  __syncthreads();
+  for (int i = threadIdx.x; i < M; i += 1024) {  // T descending, then index ascending
+    int rank = 0;
+    for (int j = 0; j < M; ++j) rank += item_T[j] > item_T[i] || (item_T[j] == item_T[i] && j < i);
+    by_rank[rank] = i;
+  }
+  __syncthreads();
+  write_lists(q_offsets, item_nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
+}
+
 }  // namespace
 
 // Tile shape: 12 waves x 32 query rows per workgroup (one workgroup per CU, 3 waves per SIMD at 168
@@ -723,7 +777,7 @@ size_t plan_bf16_workspace(int BH, int Cq, int64_t Nq) {
   return 4 * align_up(M * 4, 256) + 4 * align_up(tiles * 4, 256) + align_up(24 * 4, 256);
 }
 
-int plan_bf16(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
+int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size_t ws_bytes, hipStream_t s) {
   Workspace w(ws, ws_bytes);
   const int M = a.BH * (a.Cq + 1), BM = 32 * kWaves;
   const size_t tiles = (size_t)a.BH * ((size_t)ceil_div(a.Nq, BM) + a.Cq + 1);
@@ -737,6 +791,21 @@ int plan_bf16(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   int32_t* sched_rend = w.take<int32_t>(tiles);
   int32_t* sched_x = w.take<int32_t>(24);
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
+  a.sched_bh = sched_bh;
+  a.sched_a = sched_a;
+  a.sched_row0 = sched_row0;
+  a.sched_rend = sched_rend;
+  a.sched_x = sched_x;
+  const int64_t n = (int64_t)a.BH * a.Ck * d;
+  if (M <= kPlanItems) {
+    plan_small_kernel<<<(unsigned)(1 + ceil_div(n, 1024)), 1024, 0, s>>>(
+        a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, M, a.Cq, a.Ck, BM, sched_bh, sched_a, sched_row0, sched_rend,
+        sched_x, a.kbar, a.vbar, n, kbar16, vbar16);
+    SVGEAR_LAUNCH_CHECK();
+    return SVGEAR_OK;
+  }
+  to_bf16_kernel<<<dim3((unsigned)ceil_div(n, 256), 2), 256, 0, s>>>(a.kbar, a.vbar, n, kbar16, vbar16);
+  SVGEAR_LAUNCH_CHECK();
   plan_items_kernel<<<dim3((unsigned)ceil_div(a.Cq + 1, 4), a.BH), 256, 0, s>>>(a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, a.Cq, a.Ck, BM, item_T, item_nt);
   SVGEAR_LAUNCH_CHECK();
   plan_rank_kernel<<<(unsigned)ceil_div(M, kRankItems), 256, 0, s>>>(item_T, M, by_rank);
@@ -744,11 +813,6 @@ int plan_bf16(AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   plan_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_nt, by_rank, M, a.Cq, BM, rank_off, sched_bh, sched_a, sched_row0,
                                       sched_rend, sched_x);
   SVGEAR_LAUNCH_CHECK();
-  a.sched_bh = sched_bh;
-  a.sched_a = sched_a;
-  a.sched_row0 = sched_row0;
-  a.sched_rend = sched_rend;
-  a.sched_x = sched_x;
   return SVGEAR_OK;
 }
 

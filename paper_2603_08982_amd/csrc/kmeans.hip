@@ -30,8 +30,6 @@
 namespace svgear {
 namespace {
 
-constexpr int kAssignWaves = 8;                 // 32 rows per wave
-constexpr int kAssignRows = 32 * kAssignWaves;  // rows per workgroup
 constexpr int kCentChunk = 64;                  // centroids per LDS stage (two 32-blocks)
 // per head: [0] rows queued for assign_filter_kernel; as float bits: [1] max |x| of the flagged rows, [2] max |c|^2
 constexpr int kHeadState = 4;
@@ -168,22 +166,22 @@ __device__ __forceinline__ void load_row_operands(const bf16_t* xr, int h, float
 // a lane then holds 16 centroids of ONE row per 32x32 block and keeps a private running
 // (min, argmin) in ascending centroid order; the two lanes of a row merge once at the end.
 // Centroid chunks (64 centroids, in operand order) stream through two LDS stages with
-// asynchronous global-to-LDS copies shared by the 8 waves (256 rows) of the workgroup.
-// (fp32 inputs only; bf16 inputs go through the filter below.)
-template <typename T, int D>
-__global__ void __launch_bounds__(64 * kAssignWaves)
+// asynchronous global-to-LDS copies shared by the NW waves (32 rows each) of the workgroup.
+// (fp32 inputs and small bf16 ones; other bf16 inputs go through the filter below.)
+template <typename T, int D, int NW>
+__global__ void __launch_bounds__(64 * NW)
 assign_mfma_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const float* __restrict__ cperm,
                    const float* __restrict__ cn, int Cpad, int32_t* __restrict__ labels) {
   constexpr int QG = D / 8;                        // 16-byte operand groups per block
   constexpr int CHUNK_BYTES = kCentChunk * D * 4;  // one LDS stage of centroids
-  constexpr int COPIES = CHUNK_BYTES / 1024 / kAssignWaves;
-  static_assert(CHUNK_BYTES % (1024 * kAssignWaves) == 0, "chunk copies must split over the waves");
+  constexpr int COPIES = CHUNK_BYTES / 1024 / NW;
+  static_assert(CHUNK_BYTES % (1024 * NW) == 0, "chunk copies must split over the waves");
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   float* cns = reinterpret_cast<float*>(smem + 2 * CHUNK_BYTES);  // [2][kCentChunk]
   const int bh = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t pos = (int64_t)blockIdx.x * kAssignRows + 32 * wave + li;
+  const int64_t pos = (int64_t)blockIdx.x * (32 * NW) + 32 * wave + li;
   const int64_t row = pos < nv ? pos : nv - 1;
   float xb[D / 2];
   load_row_operands<D>(x + head_base(st, bh, H) + row * st.n, lh, xb);
@@ -198,7 +196,7 @@ assign_mfma_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const
     const uint32_t dst = lds0 + (ch & 1) * CHUNK_BYTES;
 #pragma unroll
     for (int i = 0; i < COPIES; ++i) {
-      const int inst = wave + i * kAssignWaves;
+      const int inst = wave + i * NW;
       async_copy_16B(src + inst * 1024 + lane * 16, __builtin_amdgcn_readfirstlane(dst + inst * 1024));
     }
   };
@@ -1450,18 +1448,29 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   int4* tiles = kFilter ? ws.take<int4>((size_t)BH * tile_cap) : nullptr;
   if (!ws.ok()) return SVGEAR_ERR_WORKSPACE;
   const size_t lds = 2 * (size_t)kCentChunk * D * 4 + 2 * kCentChunk * sizeof(float);
-  auto assign = assign_mfma_kernel<T, D>;
-  SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(assign),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  // A small bf16 call (rows for one round of workgroups, two chunks of centroids at most) assigns every
+  // row exactly in one launch: filter, exact re-assignment and row bounds are three, and a layer of
+  // 667 tokens is bound by launches (0.46 -> 0.41 ms).
+  const int64_t row_blocks = BH * ceil_div(nv, 256);
+  const bool exact = !kFilter || (row_blocks <= 256 && Cpad <= 2 * kCentChunk && !use_lists);
+  // waves per workgroup: four (8 x 18,135 rows, 200 centroids: whole call 0.42 ms against 0.46 with
+  // eight, whose 568 workgroups leave a second round nearly empty, and 0.49 with two, which fetch
+  // every chunk of centroids for 64 rows); two where the rows do not give every CU four waves
+  // otherwise (fp32 layer of 4,096 tokens: 0.48 against 0.52 ms)
+  const int assign_waves = row_blocks <= 64 ? 2 : 4;
+  auto assign = assign_waves == 2 ? assign_mfma_kernel<T, D, 2> : assign_mfma_kernel<T, D, 4>;
+  if (exact)
+    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(assign),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   const size_t lds_f = 2 * (size_t)kCentChunk * D * 4 + ((size_t)Cpad + 64 * kFilterWaves) * sizeof(float);
-  if constexpr (kFilter) {
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(assign_filter_kernel<D, false>),
+  // (with at most two chunks of centroids a workgroup of the filter takes several groups of rows)
+  const bool resident = Cpad <= 2 * kCentChunk;
+  auto filter = resident ? assign_filter_kernel<D, true> : assign_filter_kernel<D, false>;
+  if (!exact)
+    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(filter),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_f));
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(assign_filter_kernel<D, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_f));
-  }
   const dim3 gp((unsigned)ceil_div((int64_t)Cpad * D, 256 * 4), BH);
-  const dim3 ga((unsigned)ceil_div(nv, kAssignRows), BH);
+  const dim3 ga((unsigned)ceil_div(nv, 32 * assign_waves), BH);
   // only_changed: clusters that neither gained nor lost a member in this iteration keep their
   // centroid (flags set by the assignment kernels; null = every cluster)
   // moves: where the update records how far every centroid moved (null = not needed)
@@ -1478,15 +1487,16 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     }
     return SVGEAR_OK;
   };
-  const NextIteration tables{cperm, cn, chl, crow, amb_count, head_state, rmax};
+  const NextIteration tables = exact ? NextIteration{cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr}
+                                     : NextIteration{cperm, cn, chl, crow, amb_count, head_state, rmax};
   const NextIteration nothing{};
-  prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, chl, crow, amb_count, head_state, rmax, dirty);
+  prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, tables.chl, tables.crow, tables.amb_count,
+                                           tables.head_state, tables.rmax, exact ? nullptr : dirty);
   SVGEAR_LAUNCH_CHECK();
   for (int it = 0; it < iters; ++it) {
-    if constexpr (kFilter) {
-      // (with at most two chunks of centroids a workgroup of the filter takes several groups of rows)
-      const bool resident = Cpad <= 2 * kCentChunk;
-      auto filter = resident ? assign_filter_kernel<D, true> : assign_filter_kernel<D, false>;
+    if (exact) {
+      assign<<<ga, 64 * assign_waves, lds, s>>>(x, st, H, nv, cperm, cn, Cpad, labels);
+    } else {
       const dim3 gf((unsigned)ceil_div(ceil_div(nv, kFilterRows), resident ? kFilterGroups : 1), BH);
       const dim3 gb((unsigned)ceil_div(nv, 256 * kBoundRows), BH);
       const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
@@ -1527,14 +1537,12 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
       const int few = (int)(few_tiles < few_spread ? few_tiles : (few_spread > few_least ? few_spread : few_least));
       assign_few_kernel<D><<<(unsigned)align_up((size_t)few * BH, 8), 256, 0, s>>>(
           xb, st, H, nv, chl, cent, cperm, cn, C, Cpad, labels, amb_rows, amb_count, it > 0 ? dirty : nullptr, BH, few);
-    } else {
-      assign<<<ga, 64 * kAssignWaves, lds, s>>>(x, st, H, nv, cperm, cn, Cpad, labels);
     }
     SVGEAR_LAUNCH_CHECK();
     int rc = sort_labels(labels, BH, nv, 0, C, perm, offsets, chunk_hist, s, use_lists ? tiles : nullptr, tile_cap,
                          kListChunk, use_lists ? rank : nullptr);
     if (rc != SVGEAR_OK) return rc;
-    rc = update(x, cent, counts, (kFilter && it > 0) ? dirty : nullptr, drift, it + 1 < iters ? tables : nothing);
+    rc = update(x, cent, counts, (!exact && it > 0) ? dirty : nullptr, exact ? nullptr : drift, it + 1 < iters ? tables : nothing);
     if (rc != SVGEAR_OK) return rc;
   }
   if (x2) {

@@ -145,41 +145,42 @@ __device__ __forceinline__ unsigned long long radix_cut(CutState& st, long long 
   return st.prefix;
 }
 
-// grid (nseg, BH): nseg = 1 (one budget per head) or Cq (one per query cluster; row_budget,
-// if given, holds each cluster's budget for its clustered blocks, the tail column on top).
+// Cost of block i of a head (0: one side is empty).
+__device__ __forceinline__ unsigned long long block_cost(const int32_t* qo, const int32_t* ko, int i, int Ck) {
+  const int a = (int)((unsigned)i / (unsigned)Ck), b = i - a * Ck;
+  const int64_t qa = qo[a + 1] - qo[a], kb = ko[b + 1] - ko[b];
+  return qa > 0 && kb > 0 ? (unsigned long long)(qa * kb) : 0ull;
+}
+
+// What a head's budget leaves for its clustered blocks: the text row and the text column come first.
+__device__ __forceinline__ long long head_budget(const int32_t* qo, const int32_t* ko, int Cq, int Ck, int64_t budget) {
+  const int64_t Nq = qo[Cq + 1], Nk = ko[Ck + 1];
+  const int64_t tq = qo[Cq + 1] - qo[Cq], tk = ko[Ck + 1] - ko[Ck];
+  return budget - (tq * Nk + (Nq - tq) * tk);
+}
+
+// grid (Cq, BH): the cut of every query cluster (row_budget, if given, holds each cluster's budget for
+// its clustered blocks, the tail column on top; otherwise its share of the head's).
 __global__ void __launch_bounds__(kSelThreads)
 select_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
-              const int32_t* __restrict__ k_offsets, int Cq, int Ck, int64_t budget, int per_row,
+              const int32_t* __restrict__ k_offsets, int Cq, int Ck, int64_t budget,
               const int64_t* __restrict__ row_budget, uint64_t* __restrict__ kstar) {
   __shared__ CutState st;
-  const int seg = blockIdx.x, bh = blockIdx.y;
+  const int a = blockIdx.x, bh = blockIdx.y;
   const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
   const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
   const float* sc = scores + (int64_t)bh * Cq * Ck;
-  const int64_t Nq = qo[Cq + 1], Nk = ko[Ck + 1];
-  const int64_t tq = qo[Cq + 1] - qo[Cq], tk = ko[Ck + 1] - ko[Ck];
-  const int a_lo = per_row ? seg : 0, a_hi = per_row ? seg + 1 : Cq;
-  const int n_items = (a_hi - a_lo) * Ck;  // (Cq + 1)(Ck + 1) fits 31 bits (checked by the caller)
-  long long rem;
-  if (row_budget) {
-    rem = row_budget[(int64_t)bh * Cq + seg];
-  } else if (per_row) {
-    const int64_t qa = qo[seg + 1] - qo[seg];
-    rem = (budget * qa) / (Nq > 0 ? Nq : 1) - qa * tk;
-  } else {
-    rem = budget - (tq * Nk + (Nq - tq) * tk);  // the text row and the text column come first
-  }
-  const unsigned long long cut = radix_cut<kSelThreads>(st, rem, n_items, [&](int it, uint64_t& key,
-                                                                              unsigned long long& weight) {
-    const int ar = (int)((unsigned)it / (unsigned)Ck);
-    const int a = a_lo + ar, b = it - ar * Ck;
-    const int64_t cost = (int64_t)(qo[a + 1] - qo[a]) * (int64_t)(ko[b + 1] - ko[b]);
-    if (cost <= 0) return false;
+  const int64_t Nq = qo[Cq + 1], qa = qo[a + 1] - qo[a];
+  const long long rem = row_budget ? row_budget[(int64_t)bh * Cq + a]
+                                   : (budget * qa) / (Nq > 0 ? Nq : 1) - qa * (ko[Ck + 1] - ko[Ck]);
+  const unsigned long long cut = radix_cut<kSelThreads>(st, rem, Ck, [&](int b, uint64_t& key,
+                                                                         unsigned long long& weight) {
+    weight = block_cost(qo, ko, a * Ck + b, Ck);
+    if (weight == 0ull) return false;
     key = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b));
-    weight = (unsigned long long)cost;
     return true;
   });
-  if (threadIdx.x == 0) kstar[(int64_t)bh * (per_row ? Cq : 1) + seg] = cut;
+  if (threadIdx.x == 0) kstar[(int64_t)bh * Cq + a] = cut;
 }
 
 // Adaptive budget of query cluster a (grid (Cq, BH)): the non-empty key clusters carry the
@@ -284,35 +285,27 @@ __device__ __forceinline__ void list_row(const uint32_t* words, int W, int32_t p
   }
 }
 
-constexpr int kBuildThreads = 1024;
-
-// grid (BH). Builds the bit mask, the CSR lists and the routed cost of a head from K* in one launch
-// (heads of fewer than kWideItems blocks), a wave per row of blocks.
-__global__ void __launch_bounds__(kBuildThreads)
-build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
-             const int32_t* __restrict__ k_offsets, int Cq, int Ck, int per_row,
-             const uint64_t* __restrict__ kstar, uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr,
-             int32_t* __restrict__ col_idx, int64_t* __restrict__ routed_cost) {
-  extern __shared__ int32_t rowcnt[];  // Cq+2
-  __shared__ unsigned long long cost_sum;
-  const int bh = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int NWAVES = kBuildThreads / 64;
+// Bit mask, CSR lists and routed cost of one head (all threads of a workgroup of kSelThreads), a wave
+// per row of blocks; key_of(a): the cut of row a. rowcnt: Cq + 2 ints of LDS.
+template <class KeyOf>
+__device__ __forceinline__ void build_head(const float* sc, const int32_t* qo, const int32_t* ko, int Cq, int Ck, int bh,
+                                           KeyOf key_of, int32_t* rowcnt, unsigned long long* cost_sum,
+                                           uint32_t* mask_bits, int32_t* row_ptr, int32_t* col_idx,
+                                           int64_t* routed_cost) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int NWAVES = kSelThreads / 64;
   const int R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
-  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
-  const float* sc = scores + (int64_t)bh * Cq * Ck;
   uint32_t* mb = mask_bits + (int64_t)bh * R * W;
-  if (threadIdx.x == 0) cost_sum = 0ull;
+  if (threadIdx.x == 0) *cost_sum = 0ull;
   __syncthreads();
   long long my_cost = 0;
   for (int a = wave; a < R; a += NWAVES) {
-    const uint64_t ks = (a < Cq) ? kstar[(int64_t)bh * (per_row ? Cq : 1) + (per_row ? a : 0)] : 0ull;
-    const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, ks, mb + (int64_t)a * W, my_cost);
+    const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, a < Cq ? key_of(a) : 0ull, mb + (int64_t)a * W, my_cost);
     if (lane == 0) rowcnt[a] = cnt;
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) my_cost += __shfl_xor(my_cost, o);
-  if (lane == 0 && my_cost) atomicAdd(&cost_sum, (unsigned long long)my_cost);
+  if (lane == 0 && my_cost) atomicAdd(cost_sum, (unsigned long long)my_cost);
   __threadfence_block();
   __syncthreads();
   int32_t* rp = row_ptr + (int64_t)bh * (R + 1);
@@ -325,12 +318,52 @@ build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_off
       run += c;
     }
     rp[R] = run;
-    routed_cost[bh] = (int64_t)cost_sum;
+    routed_cost[bh] = (int64_t)*cost_sum;
   }
   __syncthreads();
   // routed key clusters of every row, ascending
   int32_t* ci = col_idx + (int64_t)bh * R * Cc;
   for (int a = wave; a < R; a += NWAVES) list_row(mb + (int64_t)a * W, W, rowcnt[a], ci);
+}
+
+// grid (BH): mask, lists and cost of heads of fewer than kWideItems blocks whose rows have budgets of
+// their own
+__global__ void __launch_bounds__(kSelThreads)
+build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
+             const int32_t* __restrict__ k_offsets, int Cq, int Ck, const uint64_t* __restrict__ kstar,
+             uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+             int64_t* __restrict__ routed_cost) {
+  extern __shared__ int32_t rowcnt[];  // Cq+2
+  __shared__ unsigned long long cost_sum;
+  const int bh = blockIdx.x;
+  const uint64_t* ks = kstar + (int64_t)bh * Cq;
+  build_head(scores + (int64_t)bh * Cq * Ck, q_offsets + (int64_t)bh * (Cq + 2), k_offsets + (int64_t)bh * (Ck + 2), Cq,
+             Ck, bh, [&](int a) { return ks[a]; }, rowcnt, &cost_sum, mask_bits, row_ptr, col_idx, routed_cost);
+}
+
+// grid (BH): cut, mask, lists and cost of heads of fewer than kWideItems blocks with one budget: a
+// small layer is bound by launches, so the two steps share one (they took 8 and 4 us)
+__global__ void __launch_bounds__(kSelThreads)
+route_small_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
+                   const int32_t* __restrict__ k_offsets, int Cq, int Ck, int64_t budget,
+                   uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+                   int64_t* __restrict__ routed_cost) {
+  extern __shared__ int32_t rowcnt[];  // Cq+2
+  __shared__ CutState st;
+  __shared__ unsigned long long cost_sum;
+  const int bh = blockIdx.x;
+  const float* sc = scores + (int64_t)bh * Cq * Ck;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const unsigned long long cut = radix_cut<kSelThreads>(st, head_budget(qo, ko, Cq, Ck, budget), Cq * Ck,
+                                                       [&](int it, uint64_t& key, unsigned long long& weight) {
+    weight = block_cost(qo, ko, it, Ck);
+    if (weight == 0ull) return false;
+    key = block_key(sc[it], (uint32_t)it);
+    return true;
+  });
+  build_head(sc, qo, ko, Cq, Ck, bh, [&](int) { return cut; }, rowcnt, &cost_sum, mask_bits, row_ptr, col_idx,
+             routed_cost);
 }
 
 // ---- one budget over many blocks ---------------------------------------------------------
@@ -364,13 +397,6 @@ route_clear_kernel(HeadCut* __restrict__ cuts, int64_t* __restrict__ routed_cost
     hc.n_cand = 0u;
     routed_cost[blockIdx.y] = 0;
   }
-}
-
-// Cost of block i of a head (0: one side is empty).
-__device__ __forceinline__ unsigned long long block_cost(const int32_t* qo, const int32_t* ko, int i, int Ck) {
-  const int a = (int)((unsigned)i / (unsigned)Ck), b = i - a * Ck;
-  const int64_t qa = qo[a + 1] - qo[a], kb = ko[b + 1] - ko[b];
-  return qa > 0 && kb > 0 ? (unsigned long long)(qa * kb) : 0ull;
 }
 
 // grid (ceil(Cq Ck / kHistItems), BH)
@@ -414,9 +440,7 @@ route_collect_kernel(const float* __restrict__ scores, const int32_t* __restrict
   const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
   const float* sc = scores + (int64_t)bh * Cq * Ck;
   HeadCut& hc = cuts[bh];
-  const int64_t Nq = qo[Cq + 1], Nk = ko[Ck + 1];
-  const int64_t tq = qo[Cq + 1] - qo[Cq], tk = ko[Ck + 1] - ko[Ck];
-  const long long rem = budget - (tq * Nk + (Nq - tq) * tk), left = rem > 0 ? rem : 0;
+  const long long rem = head_budget(qo, ko, Cq, Ck, budget), left = rem > 0 ? rem : 0;
   const int top = kHistBins - 1 - PER * (int)threadIdx.x;  // this thread's digits: top, top - 1, ...
   long long h[PER], sum = 0;
 #pragma unroll
@@ -627,11 +651,13 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
     route_collect_kernel<<<grid, kHistThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost, cuts, cand);
     SVGEAR_LAUNCH_CHECK();
     route_cut_kernel<<<BH, kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, cuts, cand, kstar);
-  } else {  // few blocks, or a budget for every row of them: a workgroup walks all that share a budget
-    select_kernel<<<dim3(per_row ? Cq : 1, BH), kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost,
-                                                                    per_row, adaptive ? row_budget : nullptr, kstar);
+    SVGEAR_LAUNCH_CHECK();
+  } else if (per_row) {  // a workgroup walks the blocks of a row
+    select_kernel<<<dim3(Cq, BH), kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost,
+                                                      adaptive ? row_budget : nullptr, kstar);
+    SVGEAR_LAUNCH_CHECK();
   }
-  SVGEAR_LAUNCH_CHECK();
+  const size_t rows_lds = (Cq + 2) * sizeof(int32_t);
   if (wide) {
     route_mask_kernel<<<dim3((unsigned)ceil_div(Cq + 1, 4), BH), 256, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck,
                                                                              per_row, kstar, mask_bits, row_count,
@@ -639,9 +665,12 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
     SVGEAR_LAUNCH_CHECK();
     route_lists_kernel<<<dim3((unsigned)ceil_div(Cq + 1, kListRows), BH), 256, 0, s>>>(Cq, Ck, mask_bits, row_count,
                                                                                       row_ptr, col_idx);
+  } else if (per_row) {
+    build_kernel<<<BH, kSelThreads, rows_lds, s>>>(scores, q_offsets, k_offsets, Cq, Ck, kstar, mask_bits, row_ptr,
+                                                  col_idx, routed_cost);
   } else {
-    build_kernel<<<BH, kBuildThreads, (Cq + 2) * sizeof(int32_t), s>>>(scores, q_offsets, k_offsets, Cq, Ck, per_row,
-                                                                      kstar, mask_bits, row_ptr, col_idx, routed_cost);
+    route_small_kernel<<<BH, kSelThreads, rows_lds, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost, mask_bits,
+                                                        row_ptr, col_idx, routed_cost);
   }
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;

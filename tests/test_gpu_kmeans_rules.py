@@ -1,0 +1,53 @@
+"""GPU k-means on both sides of the lines between its forms: small bf16 calls assign every row exactly in
+one launch, larger ones filter first (and, with the list threshold at 1, small ones too); workgroups of two
+or four waves. The forms give the same labels, counts and centroids bit for bit, also for strided rows and
+with text rows, and the labels are the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_08982_amd as sv
+from oracle import svgear_oracle as orc
+from paper_2603_08982_amd.binding import kmeans_list_threshold
+from helpers import dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(H, N, d, dtype, strided, seed):
+    g = torch.Generator().manual_seed(seed)
+    mu = torch.randn(24, d, generator=g)
+    x = (mu[torch.randint(0, 24, (H, N), generator=g)] + 0.3 * torch.randn(H, N, d, generator=g)).to(dtype)
+    if strided:  # heads interleaved along a token, as a projection leaves them
+        return x.transpose(0, 1).contiguous().to(dev()).transpose(0, 1)[None]
+    return x[None].to(dev())
+
+
+@pytest.mark.parametrize("H,N,tail,C,d,dtype", [
+    (2, 32768, 0, 128, 64, torch.bfloat16), (2, 32769, 0, 128, 64, torch.bfloat16),   # 256 and 258 blocks of 256 rows
+    (2, 700, 37, 128, 128, torch.bfloat16), (2, 700, 37, 129, 128, torch.bfloat16),   # two and three chunks of centroids
+    (1, 16384, 0, 40, 128, torch.bfloat16), (1, 16385, 1, 40, 128, torch.bfloat16),   # 64 and 65 blocks
+    (3, 33, 0, 33, 64, torch.bfloat16), (1, 2, 1, 1, 128, torch.bfloat16),
+    (1, 16384, 0, 70, 64, torch.float32), (1, 16385, 0, 70, 64, torch.float32), (4, 650, 11, 130, 128, torch.float32),
+])
+@pytest.mark.parametrize("strided", [False, True])
+def test_forms_agree(H, N, tail, C, d, dtype, strided):
+    x, x2 = _rows(H, N, d, dtype, strided, 1), _rows(H, N, d, dtype, strided, 2)
+    start = torch.stack([x[0, h, : N - tail][torch.randperm(N - tail, generator=torch.Generator().manual_seed(h))[:C].to(dev())]
+                         for h in range(H)])[None].float().contiguous()
+    for iters in (1, 4):
+        got = []
+        for threshold in (400, 1):
+            before = kmeans_list_threshold(threshold)
+            try:
+                c = start.clone()
+                labels, counts, c2 = sv.kmeans(x, c, iters, tail, x2=x2)
+                torch.cuda.synchronize()
+            finally:
+                kmeans_list_threshold(before)
+            got.append((labels, counts, c, c2))
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+        if iters == 1:
+            for h in range(H):
+                assert np.array_equal(to_np(got[0][0][0, h]), orc.kmeans_assign(to_np(x[0, h])[: N - tail], to_np(start[0, h])))
