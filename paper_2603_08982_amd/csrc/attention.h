@@ -24,7 +24,7 @@ struct AttnArgs {
   const int32_t* tile_a;  // tile lists of the fp32 kernel
   const int32_t* tile_row0;
   const int32_t* n_tiles;
-  // work lists of the bf16 kernel (see plan_bf16): tiles sorted longest first and
+  // work lists of the bf16 kernels (see plan_bf16): tiles sorted longest first and
   // dealt to 8 lists, one per XCD; sched_x = [8] first slot, [8] tile count, [8] next counter
   const int32_t* sched_bh;
   const int32_t* sched_a;
@@ -44,11 +44,11 @@ struct AttnArgs {
   const int32_t* tok_perm;
   Strides q_st, out_st;
   int H;
-  // fp32 kernel: a row of zeros, and where the keys of a tile are split the partial rows with their
-  // (maximum, sum)
-  float* zeros;
+  // where the keys of a tile are split: the partial rows with their (maximum, sum)
   float* part_o;
   float2* part_ml;
+  int splits, tile_rows;  // bf16 kernels
+  float* zeros;           // fp32 kernel: a row of zeros
 };
 
 // Element offset of query row `row` of head bh.
@@ -71,17 +71,15 @@ __device__ __forceinline__ int64_t out_row_offset(const AttnArgs& p, int bh, int
 __device__ __forceinline__ bool mask_bit(const uint32_t* mrow, int b) { return (mrow[b >> 5] >> (b & 31)) & 1u; }
 
 
-// Query rows per workgroup tile of the bf16 kernel.
-int attn_bf16_bm();
-
-// Workspace of its work lists (bytes); their construction, and the centroid tables in bf16, on stream s.
-size_t plan_bf16_workspace(int BH, int Cq, int64_t Nq);
+// Workspace of the bf16 kernels' work lists and partial rows (bytes); the lists' construction, and the
+// centroid tables in bf16, on stream s.
+size_t plan_bf16_workspace(int64_t BH, int Cq, int64_t Nq, int64_t Nk, int d);
 int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size_t ws_bytes, hipStream_t s);
 
 // Whether it takes Ck key clusters at head dimension d.
 bool attn_bf16_supported(int d, int Ck);
-// Launches the bf16 MFMA kernel over `total` (multiple of 8) workgroups.
-int launch_attn_bf16(const AttnArgs& a, int d, unsigned total, hipStream_t s);
+// Launches the bf16 kernel that plan_bf16 has planned for.
+int launch_attn_bf16(const AttnArgs& a, int d, hipStream_t s);
 
 // fp32 kernel: scratch and launch (with its tile lists).
 size_t f32_workspace(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d);

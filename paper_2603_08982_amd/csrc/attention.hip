@@ -24,7 +24,7 @@ using namespace svgear;
 extern "C" size_t svgear_sparse_attn_comp_workspace(int B, int H, int64_t Nq, int64_t Nk, int d, int Cq, int Ck) {
   if (B <= 0 || H <= 0 || Nq <= 0 || Cq <= 0 || Ck <= 0 || d <= 0) return 0;
   const size_t BH = (size_t)B * H;
-  const size_t bf16 = 2 * align_up(BH * Ck * d * 2, 256) + plan_bf16_workspace((int)BH, Cq, Nq);
+  const size_t bf16 = 2 * align_up(BH * Ck * d * 2, 256) + plan_bf16_workspace((int64_t)BH, Cq, Nq, Nk, d);
   const size_t f32 = f32_workspace((int64_t)BH, Nq, Nk, Cq, d);
   return bf16 > f32 ? bf16 : f32;
 }
@@ -64,7 +64,7 @@ static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype
   hipStream_t s = static_cast<hipStream_t>(stream);
   AttnArgs a{qp, kp, vp, kbar, vbar, nullptr, nullptr, q_offsets, k_offsets, mask_bits, row_ptr, col_idx,
              nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-             Nq, Nk, BH, Cq, Ck, 0, scale, op, lse, part, tok_perm, q_st, out_st, H, nullptr, nullptr, nullptr};
+             Nq, Nk, BH, Cq, Ck, 0, scale, op, lse, part, tok_perm, q_st, out_st, H, nullptr, nullptr, 1, 0, nullptr};
   if (dt == SVGEAR_F32) return launch_attn_f32(a, d, ws, ws_bytes, s);
   Workspace w(ws, ws_bytes);
   bf16_t* kbar16 = w.take<bf16_t>((size_t)BH * Ck * d);
@@ -74,7 +74,7 @@ static int attn_run(const void* qp, const void* kp, const void* vp, svgear_dtype
   a.vbar16 = vbar16;
   const int rc = plan_bf16(a, d, kbar16, vbar16, static_cast<char*>(ws) + w.used, ws_bytes - w.used, s);
   if (rc != SVGEAR_OK) return rc;
-  return launch_attn_bf16(a, d, (unsigned)((size_t)BH * (ceil_div(Nq, attn_bf16_bm()) + Cq + 1)), s);
+  return launch_attn_bf16(a, d, s);
 }
 
 extern "C" int svgear_sparse_attn_comp(const void* qp, const void* kp, const void* vp, svgear_dtype dt,

@@ -92,7 +92,7 @@ __host__ __device__ static inline int list_entries(int Ck) { return (Ck + 72) & 
 
 static inline size_t lds_bytes(int d, int Ck, int stages) {
   const size_t kv = (size_t)stages * 2 * BN * d * 2;  // K and V, `stages` buffers each
-  return kv + (size_t)(stages + 2) * BN * 4 + 2 * (size_t)list_entries(Ck) * 4 + 16;
+  return kv + (size_t)(stages + 3) * BN * 4 + 2 * (size_t)list_entries(Ck) * 4 + 16;
 }
 
 // NW waves of 32 query rows (three per SIMD); NSTAGE K/V tile buffers. The first CW waves of
@@ -554,6 +554,433 @@ attn_bf16_kernel(AttnArgs p) {
   }
 }
 
+// ---- 128-row tiles, two workgroups per CU
+// The 12-wave kernel keeps a CU to itself: a tile pays its start (a chain of a dozen fetches, some 20 us
+// with the first copies) and its end alone, a cluster of a few dozen rows leaves most of its waves
+// idle, and a head or two of a few thousand rows have fewer tiles of 384 rows than the chip has CUs.
+// Here a workgroup is four waves (one per SIMD) over 128 rows with two K and two V buffers (64 KB at
+// d = 128), so that two of them share a CU and one's start overlaps the other's steps; a wave overlaps
+// its own phases (the exponentials of tile t between the MFMAs of S(t + 1), the maximum of tile t + 1
+// between those of PV(t)), and where even these tiles are few the keys of a tile are dealt to several
+// workgroups (partial rows in fp32, merged in a fixed order). The choice between the two kernels is
+// made in bf16_form.
+constexpr int kQuadWaves = 4;
+
+template <int D, bool WIDE>
+__global__ void __launch_bounds__(64 * kQuadWaves, 2)
+attn_bf16_quad_kernel(AttnArgs p) {
+  constexpr int NW = kQuadWaves, NSTAGE = 2, CW = kQuadWaves;
+  static_assert(D == 64 || D == 128, "swizzles");
+  constexpr int NT = 64 * NW;
+  constexpr int ROWB = D * 2;                       // bytes per K/V row
+  constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
+  constexpr int RPI = 64 / CPR;                     // rows per copy instruction
+  constexpr int KS = D / 16;
+  constexpr int DB = D / 32;
+  constexpr int TILE_BYTES = BN * ROWB;
+  constexpr int INST_PER_TILE = TILE_BYTES / 1024;  // wave-wide 1 KB copies per tensor tile
+  constexpr int RS = 4;                             // row-map ring
+  static_assert(INST_PER_TILE % CW == 0 && CW <= NW, "copies must split evenly over the copying waves");
+
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+  unsigned char* Ks = smem;                        // [NSTAGE][64 rows][ROWB], chunk-swizzled
+  unsigned char* Vs = smem + NSTAGE * TILE_BYTES;  // [NSTAGE][64 rows][ROWB], chunk-swizzled
+  int32_t* rowmap = reinterpret_cast<int32_t*>(smem + 2 * NSTAGE * TILE_BYTES);  // [RS][BN]
+  float* rag_bias = reinterpret_cast<float*>(rowmap + RS * BN);  // [BN] bias of the ragged routed tile
+  // two tables: of the routed clusters e < ne the first virtual position and the first row (then the
+  // end position); from comp0 on, of the compensated ones the index and the bias
+  int32_t* ent0 = reinterpret_cast<int32_t*>(rag_bias + BN);
+  int32_t* ent1 = ent0 + list_entries(p.Ck);
+  int32_t* slot_s = ent1 + list_entries(p.Ck);  // claimed tile, number of compensated clusters
+
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // (claimed as in the kernel above; `splits` slots per tile)
+  const int splits = p.splits;
+  if (tid == 0) {
+    const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7;  // XCC_ID
+    int found = -1, part = 0;
+    for (int xk = 0; xk < 8 && found < 0; ++xk) {
+      const int xl = (my_xcd + xk) & 7, slots = p.sched_x[8 + xl] * splits;
+      if (p.sched_x[16 + xl] >= slots) continue;  // used up (the counter only grows)
+      const int slot = atomicAdd(p.sched_x + 16 + xl, 1);
+      if (slot < slots) {
+        found = p.sched_x[xl] + slot / splits;
+        part = slot % splits;
+      }
+    }
+    slot_s[0] = found;
+    slot_s[2] = part;
+  }
+  __syncthreads();
+  const int claimed = __builtin_amdgcn_readfirstlane(slot_s[0]);
+  if (claimed < 0) return;
+  const int split = __builtin_amdgcn_readfirstlane(slot_s[2]);
+  const int bh = p.sched_bh[claimed], a = p.sched_a[claimed], row0 = p.sched_row0[claimed];
+  const int Cq = p.Cq, Ck = p.Ck, R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
+  const int32_t* ko = p.k_offsets + (int64_t)bh * (Ck + 2);
+  const int row_end = p.sched_rend[claimed];  // the tile's rows are [row0, row_end), all of query cluster a
+  const int32_t* rp = p.row_ptr + (int64_t)bh * (R + 1);
+  const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + rp[a];
+  const int ne = min(rp[a + 1] - rp[a], Cc);
+  const int comp0 = (ne + 1 + 3) & ~3;
+
+  if (wave == 0) {
+    int carry = 0;
+    for (int e0 = 0; e0 < ne; e0 += 64) {
+      const int e = e0 + lane;
+      int sz = 0;
+      if (e < ne) {
+        const int b = ci[e];
+        const int ps = ko[b];
+        sz = ko[b + 1] - ps;
+        sz = sz > 0 ? sz : 0;
+        ent1[e] = ps;
+      }
+      int incl = sz;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+      }
+      if (e < ne) ent0[e] = carry + incl - sz;
+      carry += __shfl(incl, 63);
+    }
+    if (lane == 0) ent0[ne] = carry;
+  } else if (wave == 1) {
+    // skipped, non-empty clusters only: a quarter routed leaves a quarter fewer centroid tiles
+    int at = comp0;
+    if (a < Cq) {
+      const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
+      for (int b0 = 0; b0 < Ck; b0 += 64) {
+        const int b = b0 + lane;
+        const int sz = b < Ck ? ko[b + 1] - ko[b] : 0;
+        const bool on = sz > 0 && !mask_bit(mrow, b);
+        const unsigned long long votes = __ballot(on);
+        const int slot = at + __popcll(votes & ((1ull << lane) - 1ull));
+        if (on && slot < list_entries(Ck) - (BN - 1)) {
+          ent0[slot] = b;
+          ent1[slot] = __float_as_int(log2f((float)sz));
+        }
+        at += __popcll(votes);
+      }
+    }
+    at = min(at, list_entries(Ck) - (BN - 1));
+    if (lane < BN - 1) ent1[at + lane] = __float_as_int(-INFINITY);  // the rest of the last tile
+    if (lane == 0) slot_s[1] = at - comp0;
+  }
+  __syncthreads();
+  // (part 2 leaves the routed keys out, part 1 the centroid tiles: the two-stage form)
+  const int n_r = p.part == 2 ? 0 : __builtin_amdgcn_readfirstlane(ent0[ne]);  // wave-uniform
+  const int n_c = p.part == 1 ? 0 : __builtin_amdgcn_readfirstlane(slot_s[1]);
+  const int nt_r = (n_r + BN - 1) / BN;
+  const int T_all = nt_r + (n_c + BN - 1) / BN;
+  // this workgroup's tiles: [t_lo, T)
+  const int t_lo = (int)((int64_t)T_all * split / splits), T = (int)((int64_t)T_all * (split + 1) / splits);
+  const int nt_full = n_r / BN;  // routed tiles with all 64 keys valid
+  if (tid < BN) rag_bias[tid] = (nt_full * BN + tid < n_r) ? 0.f : -INFINITY;
+
+  const bf16_t* kh = static_cast<const bf16_t*>(p.kp) + (int64_t)bh * p.Nk * D;
+  const bf16_t* vh = static_cast<const bf16_t*>(p.vp) + (int64_t)bh * p.Nk * D;
+  const bf16_t* kc = p.kbar16 + (int64_t)bh * Ck * D;
+  const bf16_t* vc = p.vbar16 + (int64_t)bh * Ck * D;
+
+  // segment cursor of threads 0..63 (virtual key position -> permuted row): the last cluster that starts
+  // at or before the thread's first position
+  int cur = 0;
+  for (int hi = ne, pos = min(t_lo * BN + (tid & 63), n_r - 1); hi - cur > 1;) {
+    const int mid = (cur + hi) >> 1;
+    if (ent0[mid] <= pos) cur = mid;
+    else hi = mid;
+  }
+  auto map_tile = [&](int t) __attribute__((always_inline)) {
+    if (tid < BN) {
+      int phys;
+      if (t < nt_r) {  // positions past the last key repeat it (masked by rag_bias)
+        const int pos = min(t * BN + tid, n_r - 1);
+        while (pos >= ent0[cur + 1]) ++cur;
+        phys = ent1[cur] + (pos - ent0[cur]);
+      } else {
+        phys = ent0[comp0 + min((t - nt_r) * BN + tid, n_c - 1)];
+      }
+      rowmap[(t % RS) * BN + tid] = phys;
+    }
+  };
+
+  // one wave-wide copy moves rows RPI*inst .. of a tile; lane -> (row, LDS chunk slot).
+  // Copy i of this wave is instruction inst = wave + i*CW of the tile: tile row cp_rr + RPI*i*CW,
+  // a multiple of 16 rows further on, so the row's swizzle phases, and with them the 16-byte chunk
+  // a lane fetches, are the same for every i.
+  static_assert((RPI * CW) % 16 == 0, "copy rows of one lane must share their swizzle phase");
+  constexpr int CPW = INST_PER_TILE / CW;  // copies per tensor per wave per tile
+  const uint32_t lds_k0 = lds_address(Ks), lds_v0 = lds_address(Vs);
+  auto k_swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+  auto v_swz = [](int row) { return D == 128 ? ((row & 3) << 2) : ((row & 2) << 1); };
+  const int cp_rr = RPI * (wave % CW) + lane / CPR;
+  const uint32_t cp_koff = (uint32_t)(((lane % CPR) ^ k_swz(cp_rr)) << 4);
+  const uint32_t cp_voff = (uint32_t)(((lane % CPR) ^ v_swz(cp_rr)) << 4);
+  // permuted rows (of K/V or of the centroid tables) this lane copies for tile t
+  auto fetch_rows = [&](int t, int (&rows)[CPW]) __attribute__((always_inline)) {
+    const int32_t* rm = rowmap + (t % RS) * BN + cp_rr;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) rows[i] = rm[RPI * i * CW];
+  };
+  auto issue = [&](int t, bool is_k) __attribute__((always_inline)) {
+    int rows[CPW];
+    fetch_rows(t, rows);
+    const void* base = uniform_ptr(is_k ? (t < nt_r ? kh : kc) : (t < nt_r ? vh : vc));
+    const uint32_t dst = (is_k ? lds_k0 : lds_v0) + (t % NSTAGE) * TILE_BYTES + wave * 1024;
+    const uint32_t off = is_k ? cp_koff : cp_voff;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+      const uint32_t l = __builtin_amdgcn_readfirstlane(dst + i * CW * 1024);
+      if constexpr (WIDE) async_copy_16B(static_cast<const unsigned char*>(base) + (int64_t)rows[i] * ROWB + off, l);
+      else async_copy_16B(base, (uint32_t)rows[i] * ROWB + off, l);
+    }
+  };
+
+  // per-lane LDS byte offsets of the MFMA operands
+  // K row li of a 32-row block, dims 16s + 8lh .. +7: chunk (2s + lh) ^ swizzle
+  // (the swizzles are XORs of disjoint bit fields, so operand s / block db is the offset of
+  // operand 0 with s << 5 / db << 6 XORed in: one register each instead of a table)
+  const int koff0 = li * ROWB + ((lh ^ k_swz(li)) << 4);
+  auto koff = [&](int s) { return koff0 ^ (s << 5); };
+  int voff0;  // transpose read: group = lane/16 -> (dim half, key half); r = lane%16
+  {
+    const int r = lane & 15, g = lane >> 4, ddhalf = g & 1, khalf = g >> 1, row = 4 * khalf + (r >> 2);
+    voff0 = row * ROWB + (((2 * ddhalf + ((r & 3) >> 1)) ^ v_swz(row)) << 4) + (r & 1) * 8;
+  }
+  auto voff = [&](int db) { return voff0 ^ (db << 6); };
+
+  // (the blocks of a partly filled tile rotate over the SIMDs with the tile)
+  const int my_row0 = row0 + 32 * ((wave + claimed) & (NW - 1));
+  const bool wave_active = my_row0 < row_end;
+  bf16x8 bq[KS];
+  {
+    const int qrow = my_row0 + li;
+    const bf16_t* qr = static_cast<const bf16_t*>(p.qp) + q_row_offset(p, bh, qrow < row_end ? qrow : row_end - 1, D);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) bq[s] = as_bf16x8(*reinterpret_cast<const uint4*>(qr + 16 * s + 8 * lh));
+  }
+  // Q must be in registers before the asynchronous tile copies start: the compiler does not
+  // see those copies and would otherwise wait for "its" loads inside the main loop
+  SVGEAR_WAIT_VMCNT(0);
+
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  const float c = p.scale * kLog2e;
+
+  auto rescale = [&](float m_new) __attribute__((always_inline)) {
+    const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
+    l *= alpha;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+    m = m_new;
+  };
+
+  f32x16 sA[2], sB[2];
+  uint32_t pk[2][8];
+  float cc = c;  // factor still to be applied to the scores whose maximum is known
+  constexpr int AHEAD = 4;
+  // S^T = K Q^T of tile t into sn (registers as above); with EXPS, between its MFMAs, the
+  // probabilities of the tile whose scores are sc (running maximum m) into pk
+  auto scores = [&](int t, f32x16 (&sn)[2], const f32x16 (&sc)[2], auto exps_tag) __attribute__((always_inline)) {
+    constexpr bool EXPS = decltype(exps_tag)::value;
+    const unsigned char* Kb = Ks + (t % NSTAGE) * TILE_BYTES;
+    bf16x8 kf[2 * KS];
+    auto rd = [&](int i) { kf[i] = as_bf16x8(*reinterpret_cast<const uint4*>(Kb + (i & 1) * 32 * ROWB + koff(i >> 1))); };
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sn[kb][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) rd(i);
+    const float neg_m = m == -INFINITY ? 0.f : -m;
+    float ls[4] = {0.f, 0.f, 0.f, 0.f};
+    constexpr int E = 16 / (2 * KS);  // pairs of scores per MFMA
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + AHEAD < 2 * KS) rd(i + AHEAD);
+      sn[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], bq[i >> 1], sn[i & 1], 0, 0, 0);
+      if constexpr (EXPS) {
+#pragma unroll
+        for (int e = i * E; e < (i + 1) * E; ++e) {
+          const int kb = e >> 3, r = 2 * (e & 7);
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], cc, neg_m));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r + 1], cc, neg_m));
+          pk[kb][r >> 1] = pack_bf16(p0, p1);
+          ls[e & 3] = dot2_ones(pk[kb][r >> 1], ls[e & 3]);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EXPS) l += (ls[0] + ls[1]) + (ls[2] + ls[3]);
+  };
+  auto max_pair = [&](const f32x16 (&sn)[2], float& mx, int e) __attribute__((always_inline)) {
+    const int kb = e >> 3, r = 2 * (e & 7);
+    mx = fmaxf(fmaxf(mx, sn[kb][r]), sn[kb][r + 1]);
+  };
+  // the running maximum covers tile t's scores sn afterwards; a ragged or centroid tile gets its biases
+  auto settle = [&](int t, f32x16 (&sn)[2], float mx) __attribute__((always_inline)) {
+    cc = c;
+    if (t >= nt_full) {
+      const float* lwt = t < nt_r ? rag_bias : reinterpret_cast<const float*>(ent1) + comp0 + (t - nt_r) * BN;
+      mx = -INFINITY;
+      cc = 1.f;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 bias = *reinterpret_cast<const float4*>(lwt + 32 * kb + 8 * g + 4 * lh);
+          sn[kb][4 * g + 0] = __builtin_fmaf(sn[kb][4 * g + 0], c, bias.x);
+          sn[kb][4 * g + 1] = __builtin_fmaf(sn[kb][4 * g + 1], c, bias.y);
+          sn[kb][4 * g + 2] = __builtin_fmaf(sn[kb][4 * g + 2], c, bias.z);
+          sn[kb][4 * g + 3] = __builtin_fmaf(sn[kb][4 * g + 3], c, bias.w);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sn[kb][4 * g + r]);
+        }
+    }
+    mx = fmaxf(mx, swap32(mx));
+    const float ms = mx * cc;
+    if (__any(ms > m + kLazyRescale)) rescale(fmaxf(m, ms));
+  };
+  // O^T += V^T P^T of tile t, and between its MFMAs the maximum of the scores sn of tile t + 1
+  auto values = [&](int t, f32x16 (&sn)[2]) __attribute__((always_inline)) {
+    const unsigned char* Vb = Vs + (t % NSTAGE) * TILE_BYTES;
+    constexpr int N = 4 * DB;
+    bf16x8 vf[N];
+    auto rd = [&](int i) { vf[i] = tr_pair<ROWB>(Vb, (i / DB) * 16 * ROWB + voff(i % DB)); };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) rd(i);
+    float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + AHEAD < N) rd(i + AHEAD);
+      const int ks = i / DB, kb = ks >> 1, u4 = (ks & 1) * 4;
+      const bf16x8 bp = as_bf16x8(make_uint4(pk[kb][u4], pk[kb][u4 + 1], pk[kb][u4 + 2], pk[kb][u4 + 3]));
+      oacc[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], bp, oacc[i % DB], 0, 0, 0);
+      if (i >= N / 4) {
+#pragma unroll
+        for (int e = (i - N / 4) * 16 / (3 * N / 4); e < (i + 1 - N / 4) * 16 / (3 * N / 4); ++e)
+          max_pair(sn, mx[e & 3], e);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 1 < T) settle(t + 1, sn, fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
+  };
+
+  // Step t reads K(t + 1) and V(t) and copies K(t + 2) and V(t + 1), over K(t) and V(t - 1), which step
+  // t - 1 was the last to read.
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (t_lo + u < T) map_tile(t_lo + u);
+  __syncthreads();
+  if (t_lo < T) {
+    issue(t_lo, true);
+    issue(t_lo, false);
+    if (t_lo + 1 < T) issue(t_lo + 1, true);
+  }
+  SVGEAR_WAIT_VMCNT(0);
+  __syncthreads();
+  if (wave_active && t_lo < T) {
+    scores(t_lo, sA, sB, std::false_type{});
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) max_pair(sA, mx, e);
+    settle(t_lo, sA, mx);
+  }
+  __syncthreads();  // everyone is done with the first K tile before it is copied over
+  auto step = [&](int t, f32x16 (&now)[2], f32x16 (&next)[2]) __attribute__((always_inline)) {
+    if (t + 2 < T) issue(t + 2, true);
+    if (t + 1 < T) issue(t + 1, false);
+    if (wave_active) {
+      scores(t + 1 < T ? t + 1 : t, next, now, std::true_type{});  // (the last step's scores are not used)
+      values(t, next);
+    }
+    if (t + 3 < T) map_tile(t + 3);
+    SVGEAR_WAIT_VMCNT(0);
+    __syncthreads();
+  };
+  for (int t = t_lo; t < T; t += 2) {
+    step(t, sA, sB);
+    if (t + 1 < T) step(t + 1, sB, sA);
+  }
+
+  // ---- epilogue: lane holds query li, dims 32db + 8g + 4lh + 0..3
+  if (wave_active) {
+    const float lt = l + swap32(l);
+    const int qrow = my_row0 + li;
+    if (qrow < row_end && splits > 1) {
+      const int64_t rows = (int64_t)p.BH * p.Nq, at = split * rows + (int64_t)bh * p.Nq + qrow;
+      if (lh == 0) p.part_ml[at] = make_float2(m, lt);
+      float* o = p.part_o + at * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<float4*>(o + 32 * db + 8 * g + 4 * lh) =
+              make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
+    } else if (qrow < row_end) {
+      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+      int64_t lse_idx;
+      bf16_t* o = static_cast<bf16_t*>(p.op) + out_row_offset(p, bh, qrow, D, lse_idx);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          uint2 w;
+          w.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
+          w.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
+          *reinterpret_cast<uint2*>(o + 32 * db + 8 * g + 4 * lh) = w;
+        }
+      if (p.lse && lh == 0) p.lse[lse_idx] = (m + log2f(lt)) * kLn2;
+    }
+  }
+}
+
+// Adds the splits of every row, in split order: one thread per 8 dims.
+template <int D>
+__global__ void __launch_bounds__(256)
+merge_splits_kernel(AttnArgs p) {
+  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t rows = (int64_t)p.BH * p.Nq, row = u / (D / 8);
+  if (row >= rows) return;
+  const int dim = 8 * (int)(u % (D / 8));
+  float M = -INFINITY;
+  for (int s = 0; s < p.splits; ++s) M = fmaxf(M, p.part_ml[s * rows + row].x);
+  float l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < p.splits; ++s) {
+    const float2 ml = p.part_ml[s * rows + row];
+    if (ml.x == -INFINITY && ml.y == 0.f) continue;  // no key there
+    const float w = __builtin_amdgcn_exp2f(ml.x - M);
+    const float* o = p.part_o + (s * rows + row) * D + dim;
+    const float4 v0 = *reinterpret_cast<const float4*>(o), v1 = *reinterpret_cast<const float4*>(o + 4);
+    const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+    l = __builtin_fmaf(w, ml.y, l);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(w, v[i], acc[i]);
+  }
+  const float inv = l > 0.f ? 1.0f / l : 0.f;
+  int64_t lse_idx;
+  const int bh = (int)(row / p.Nq);
+  bf16_t* o = static_cast<bf16_t*>(p.op) + out_row_offset(p, bh, row - (int64_t)bh * p.Nq, D, lse_idx) + dim;
+  uint4 w;
+  w.x = pack_bf16(acc[0] * inv, acc[1] * inv);
+  w.y = pack_bf16(acc[2] * inv, acc[3] * inv);
+  w.z = pack_bf16(acc[4] * inv, acc[5] * inv);
+  w.w = pack_bf16(acc[6] * inv, acc[7] * inv);
+  *reinterpret_cast<uint4*>(o) = w;
+  if (p.lse && dim == 0) p.lse[lse_idx] = (M + log2f(l)) * kLn2;
+}
+
 // Both centroid tables to bf16 in one launch (blockIdx.y picks the table).
 __global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __restrict__ src1, int64_t n,
                                bf16_t* __restrict__ dst0, bf16_t* __restrict__ dst1) {
@@ -763,7 +1190,30 @@ constexpr int kWaves = 12;
 constexpr int kStages = 4;
 constexpr int kCopyWaves = 4;
 
-int attn_bf16_bm() { return 32 * kWaves; }
+// Tile height and splits of a call, from its sizes alone.
+struct Bf16Form {
+  int rows;    // per tile: 384 (12-wave kernel) or 128 (four waves, two workgroups per CU)
+  int splits;  // workgroups that share the keys of a 128-row tile
+};
+// Measured at d = 128 unless stated, 384-row against 128-row tiles, us a call (a quarter routed):
+//  * few tiles, keys split: 1 head x 11,970 rows, 8 / 942 clusters 199 -> 99; 1 x 4,096, 32 / 64 63 -> 44
+//    (with fewer than some 1,000 keys a split the merge costs what it saves: 1 x 1,200, d = 64 31 -> 33);
+//  * clusters of 32 to 160 rows, which fill at most five of twelve waves: 12 x 16,200, 81 rows 1047 -> 829;
+//    24 x 10,800, 108 rows 838 -> 725; d = 64, 8 x 32,400, 162 rows 1008 -> 967; smaller clusters are all
+//    start and end either way (40 x 594, 12 rows 140 -> 144), larger ones want the larger tile (5 x
+//    75,600, 252 rows 4018 -> 4507; d = 64, 24 x 32,477, 507 rows 2025 -> 2294);
+//  * at most four 128-row tiles a CU, d = 128: 1 x 75,600, 756 rows 1675 -> 1611; 4 x 18,900 497 -> 491
+//    (d = 64: 12 x 7,000 128 -> 133).
+static Bf16Form bf16_form(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
+  const int64_t quads = BH * (ceil_div(Nq, 32 * kQuadWaves) + Cq / 2);  // a cluster's last tile is half full
+  const int64_t want = ceil_div(512, quads), most = Nk / 1024;
+  const int64_t n = want < most ? want : most;
+  const bool small_clusters = Nq >= (int64_t)32 * Cq && Nq <= (int64_t)160 * Cq;
+  if (n >= 2) return {32 * kQuadWaves, (int)(n < 8 ? n : 8)};
+  if ((small_clusters && quads > 64) || (d == 128 && quads <= 1024 && quads > 64 && Nq >= (int64_t)32 * Cq))
+    return {32 * kQuadWaves, 1};
+  return {32 * kWaves, 1};
+}
 
 // d = 128: 12 bytes per key cluster beside the tile buffers is what the entry point promises.
 bool attn_bf16_supported(int d, int Ck) {
@@ -771,15 +1221,18 @@ bool attn_bf16_supported(int d, int Ck) {
                         align_up((size_t)(2 * (Ck + 2) + 1) * 4, 16) <= 160 * 1024;
 }
 
-size_t plan_bf16_workspace(int BH, int Cq, int64_t Nq) {
-  const size_t M = (size_t)BH * (Cq + 1);
-  const size_t tiles = (size_t)BH * ((size_t)ceil_div(Nq, 32 * kWaves) + Cq + 1);
-  return 4 * align_up(M * 4, 256) + 4 * align_up(tiles * 4, 256) + align_up(24 * 4, 256);
+size_t plan_bf16_workspace(int64_t BH, int Cq, int64_t Nq, int64_t Nk, int d) {
+  const Bf16Form f = bf16_form(BH, Nq, Nk, Cq, d);
+  const size_t M = (size_t)BH * (Cq + 1), rows = (size_t)BH * Nq;
+  const size_t tiles = (size_t)BH * ((size_t)ceil_div(Nq, f.rows) + Cq + 1);
+  return 4 * align_up(M * 4, 256) + 4 * align_up(tiles * 4, 256) + align_up(24 * 4, 256) +
+         (f.splits > 1 ? align_up(f.splits * rows * d * 4, 256) + align_up(f.splits * rows * sizeof(float2), 256) : 0);
 }
 
 int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size_t ws_bytes, hipStream_t s) {
   Workspace w(ws, ws_bytes);
-  const int M = a.BH * (a.Cq + 1), BM = 32 * kWaves;
+  const Bf16Form f = bf16_form(a.BH, a.Nq, a.Nk, a.Cq, d);
+  const int M = a.BH * (a.Cq + 1), BM = f.rows;
   const size_t tiles = (size_t)a.BH * ((size_t)ceil_div(a.Nq, BM) + a.Cq + 1);
   int32_t* item_T = w.take<int32_t>(M);
   int32_t* item_nt = w.take<int32_t>(M);
@@ -790,6 +1243,12 @@ int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size
   int32_t* sched_row0 = w.take<int32_t>(tiles);
   int32_t* sched_rend = w.take<int32_t>(tiles);
   int32_t* sched_x = w.take<int32_t>(24);
+  a.tile_rows = f.rows;
+  a.splits = f.splits;
+  if (f.splits > 1) {
+    a.part_o = w.take<float>((size_t)f.splits * a.BH * a.Nq * d);
+    a.part_ml = w.take<float2>((size_t)f.splits * a.BH * a.Nq);
+  }
   if (!w.ok()) return SVGEAR_ERR_WORKSPACE;
   a.sched_bh = sched_bh;
   a.sched_a = sched_a;
@@ -855,22 +1314,28 @@ int launch_merge(const bf16_t* o1, const float* lse1, const bf16_t* o2, const fl
   return SVGEAR_OK;
 }
 
-// `total` workgroups: at least the number of tiles (one workgroup per tile; the rest exit).
+// Grids cover the bound on the number of tiles (one workgroup per tile and split; the rest exit).
 template <int D, bool WIDE>
-static int launch(const AttnArgs& a, unsigned total, hipStream_t s) {
-  const size_t lds = lds_bytes(D, a.Ck, kStages);
-  auto kern = attn_bf16_kernel<D, kWaves, kStages, kCopyWaves, WIDE>;
+static int launch(const AttnArgs& a, hipStream_t s) {
+  const unsigned total = (unsigned)((size_t)a.BH * (ceil_div(a.Nq, a.tile_rows) + a.Cq + 1) * a.splits);
+  const bool quad = a.tile_rows == 32 * kQuadWaves;
+  const size_t lds = lds_bytes(D, a.Ck, quad ? 2 : kStages);
+  auto kern = quad ? attn_bf16_quad_kernel<D, WIDE> : attn_bf16_kernel<D, kWaves, kStages, kCopyWaves, WIDE>;
   SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds));
-  kern<<<total, 64 * kWaves, lds, s>>>(a);
+  kern<<<total, quad ? 64 * kQuadWaves : 64 * kWaves, lds, s>>>(a);
   SVGEAR_LAUNCH_CHECK();
+  if (a.splits > 1) {
+    merge_splits_kernel<D><<<(unsigned)ceil_div((int64_t)a.BH * a.Nq * (D / 8), 256), 256, 0, s>>>(a);
+    SVGEAR_LAUNCH_CHECK();
+  }
   return SVGEAR_OK;
 }
 
-int launch_attn_bf16(const AttnArgs& a, int d, unsigned total, hipStream_t s) {
+int launch_attn_bf16(const AttnArgs& a, int d, hipStream_t s) {
   if (!a.sched_x) return SVGEAR_ERR_INVALID;
-  if (d == 128) return launch<128, false>(a, total, s);  // (the entry point takes no more keys)
-  return a.Nk > (int64_t)(UINT32_MAX / 128) ? launch<64, true>(a, total, s) : launch<64, false>(a, total, s);
+  if (d == 128) return launch<128, false>(a, s);  // (the entry point takes no more keys)
+  return a.Nk > (int64_t)(UINT32_MAX / 128) ? launch<64, true>(a, s) : launch<64, false>(a, s);
 }
 
 }  // namespace svgear

@@ -27,6 +27,10 @@ def _sizes(name, rng):
         return [40, 3], list(rng.integers(1, 90, 120)), 0
     if name == "many_rows":
         return list(rng.integers(1, 70, 150)), [7, 90], 1
+    if name == "split_keys":  # a few tiles over keys enough for every number of splits
+        return [200, 1, 129], list(rng.integers(1, 250, 80)), 5
+    if name == "full_tiles":  # enough tiles of clusters that want the largest tile
+        return list(rng.integers(385, 800, 40)), [30, 64, 500], 3
     return [130, 64], list(rng.integers(0, 3, 900)), 40  # hundreds of tiny clusters
 
 
@@ -45,7 +49,7 @@ def _definition(Q, K, V, kbar, vbar, qs, ks, mask, scale):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters"])
+@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters", "split_keys", "full_tiles"])
 @pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
 def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
     rng = np.random.default_rng(3)
