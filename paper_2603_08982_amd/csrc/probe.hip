@@ -18,6 +18,8 @@
 namespace svgear {
 namespace {
 
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
 constexpr float kMaxExponent = 40.0f;  // e^40 squared still fits fp32
 
 // Sbar[a][b] = qbar_a . kbar_b * scale; mrow[a] = max over non-empty b.
@@ -100,7 +102,95 @@ sbar_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, cons
   }
 }
 
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+// The same for many centroids: one workgroup per 32 query centroids, whose waves take the 32-blocks of
+// key centroids in turn. The dot products run on fp32 MFMAs, k-step s contracting dims 2s (lanes 0-31) and
+// 2s + 1: every product is the fma chain over the dims in order, bit for bit that of the kernel above,
+// which fetches every key centroid Cq / 4 times. 40 heads, 300 x 1,000 centroids of 128: 240 -> 113 us;
+// with too few workgroups for the chip the longer chain of each loses (5 heads, 200 x 500: 20 -> 33), so
+// run_sbar asks for one a CU.
+constexpr int kSbarWaves = 8;
+
+// dims h, 2 + h, 4 + h ... of a row: the operands of steps 0 .. D/2 - 1 for lane half h
+template <int D>
+__device__ __forceinline__ void row_operands(const float* row, int h, float (&x)[D / 2]) {
+#pragma unroll
+  for (int t = 0; t < D / 4; ++t) {
+    const float4 v = *reinterpret_cast<const float4*>(row + 4 * t);
+    x[2 * t] = h ? v.y : v.x;
+    x[2 * t + 1] = h ? v.w : v.z;
+  }
+}
+
+template <int D>
+__global__ void __launch_bounds__(64 * kSbarWaves)
+sbar_mfma_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, const int32_t* __restrict__ k_offsets,
+            int Cq, int Ck, float scale, float* __restrict__ sbar, float* __restrict__ mrow,
+            bf16_t* __restrict__ q3) {
+  __shared__ float red[kSbarWaves][32];
+  const int ab = blockIdx.x, bh = blockIdx.y, a0 = 32 * ab;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (q3) {
+    constexpr int KSN = D / 16;
+    const int nab = (Cq + 31) >> 5;
+    for (int i = tid; i < 32 * D; i += 64 * kSbarWaves) {
+      const int a = a0 + i / D, k = i % D;
+      const float v = a < Cq ? qbar[((int64_t)bh * Cq + a) * D + k] : 0.f;
+      const bf16_t hi = f32_to_bf16(v);
+      const float r1 = v - bf16_to_f32(hi);
+      const bf16_t mid = f32_to_bf16(r1);
+      const bf16_t lo = f32_to_bf16(r1 - bf16_to_f32(mid));
+      const int ln = (a & 31) + 32 * ((k & 15) >> 3);
+      bf16_t* dst = q3 + ((((int64_t)bh * nab + ab) * 3) * KSN + (k >> 4)) * 512 + ln * 8 + (k & 7);
+      dst[0] = hi;
+      dst[(int64_t)KSN * 512] = mid;
+      dst[(int64_t)2 * KSN * 512] = lo;
+    }
+  }
+  const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
+  const int a = a0 + li;
+  float q[D / 2];
+  row_operands<D>(qbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * D, lh, q);
+  float* out = sbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * Ck;
+  float mx = -INFINITY;
+  for (int b0 = 32 * wave; b0 < Ck; b0 += 32 * kSbarWaves) {
+    float kf[D / 2];
+    row_operands<D>(kbar + ((int64_t)bh * Ck + min(b0 + li, Ck - 1)) * D, lh, kf);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 2; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s], q[s], acc, 0, 0, 0);
+    // register r is key centroid b0 + 8 (r/4) + 4 lh + r%4, query centroid a
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int b = b0 + 8 * g + 4 * lh;
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        v[r] = acc[4 * g + r] * scale;
+        if (b + r < Ck && off[b + r + 1] > off[b + r]) mx = fmaxf(mx, v[r]);
+      }
+      if (a >= Cq) continue;
+      if (b + 4 <= Ck && (Ck & 3) == 0) {
+        *reinterpret_cast<float4*>(out + b) = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (b + r < Ck) out[b + r] = v[r];
+      }
+    }
+  }
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  if (lh == 0) red[wave][li] = mx;
+  __syncthreads();
+  if (tid < 32 && a0 + tid < Cq) {
+    float m = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < kSbarWaves; ++w) m = fmaxf(m, red[w][tid]);
+    mrow[(int64_t)bh * Cq + a0 + tid] = m;
+  }
+}
 
 // fp32 inputs: block errors with the logits qbar_a . k_j on fp32 matrix cores (bound: those, 157 TFLOP/s
 // nominal). One workgroup per (head, key cluster, group of kF32Cents query centroids); its four waves
@@ -299,12 +389,18 @@ value_stats_kernel(const float* __restrict__ vbar, const bf16_t* __restrict__ vp
 // key once and has few workgroups per CU: without that depth too few bytes are in flight),
 // together with its per-key value statistics; the 16-byte chunks of a row are XOR-swizzled
 // with the row index so that the operand reads of 32 rows do not collide. One barrier per
-// block.
+// block. A block of a wave is 24 MFMAs (d = 128, 768 cycles of its SIMD) and about as long on the vector
+// ALU for the errors of its 512 pairs, and a SIMD holds two waves: the errors of block k - 1 are written
+// between the MFMAs of block k, and a
+// cluster's last block, a third of them at 75 keys a cluster, selects instead of branching per register
+// (40 heads, 300 x 1,000 centroids: 1.58 -> 1.53 ms; 5 heads, 200 x 500: 129 -> 118 us). What is left is the
+// vector ALU, some 160 to 250 instructions a block, at the two waves that 96 registers of centroid
+// fragments leave room for (three waves spill: 1.85 ms).
 constexpr int kProbeClusters = 4;  // key clusters per workgroup
 constexpr int kProbeStages = 4;    // LDS ring buffers
 
 template <int D, bool VALUE_AWARE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
 block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__ vbar, const bf16_t* __restrict__ kp,
                         const int32_t* __restrict__ k_offsets, const float* __restrict__ sbar,
                         const float* __restrict__ mrow, const float* __restrict__ nd, const float* __restrict__ dd,
@@ -318,7 +414,8 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   constexpr int PF = kProbeStages - 1;   // blocks in flight ahead of the one computed
   static_assert(32 % (RPI * 4) == 0 && (CPR == 16 || CPR == 8), "tile split / swizzle assume d = 64 or 128");
   __shared__ __attribute__((aligned(1024))) unsigned char ktile[kProbeStages][TILE_B];
-  __shared__ __attribute__((aligned(256))) float stat[kProbeStages][64];  // [|delta|^2 x 32, vbar.delta x 32]
+  // [|delta|^2 x 32, vbar.delta x 32]; read one block later than the keys, so one buffer more
+  __shared__ __attribute__((aligned(256))) float stat[kProbeStages + 1][64];
   // scores of the workgroup's key clusters, per wave [query centroid][key cluster]: a row leaves
   // as ONE 16-byte store at the end instead of kProbeClusters 4-byte stores a score row apart
   __shared__ __attribute__((aligned(16))) float sc[4][32][kProbeClusters];
@@ -385,7 +482,8 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   };
   // row r of a block keeps its 16-byte chunk c at position c ^ swz(r)
   auto swz = [](int r) { return CPR == 16 ? (r & 15) : ((r >> 1) & 7); };
-  auto issue = [&](const Cursor& c, int buf) {  // rows past the cluster's end repeat its last key
+  auto issue = [&](const Cursor& c, int k) {  // block k of the sequence; rows past the cluster's end repeat its last key
+    const int buf = k % kProbeStages;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int inst = wave * NCH + i;
@@ -397,7 +495,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
     }
     if (VALUE_AWARE) {  // every wave copies the 64 statistics (same values to the same words)
       const int j = min(c.j0 + li, c.end - 1);
-      async_copy_4B((lh ? ddh : ndh) + j, __builtin_amdgcn_readfirstlane(lds_s + buf * 256));
+      async_copy_4B((lh ? ddh : ndh) + j, __builtin_amdgcn_readfirstlane(lds_s + (k % (kProbeStages + 1)) * 256));
     }
   };
 
@@ -407,32 +505,99 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
     flush();
     return;
   }
-  Cursor cc = fc;             // block being computed
+  Cursor pc = fc;             // block whose errors are being added up
   int issued = 0;
   for (; issued < PF && fc.b < b_end; ++issued) {
     issue(fc, issued);
     advance(fc);
   }
   float E = 0.f, W = 0.f, nvb = 0.f;
-  for (int k = 0; cc.b < b_end; ++k) {
-    // block k has landed once at most the copies of the later blocks are outstanding
-    const int ahead = issued - k - 1;
-    if (ahead >= 2) SVGEAR_WAIT_VMCNT(2 * LPB);
-    else if (ahead == 1) SVGEAR_WAIT_VMCNT(LPB);
-    else SVGEAR_WAIT_VMCNT(0);
-    __syncthreads();  // everyone's part of block k is in LDS; everyone is done with block k - 1
-    if (fc.b < b_end) {
-      issue(fc, issued % kProbeStages);
-      advance(fc);
-      ++issued;
+  f32x16 acc_even, acc_odd;  // logits of the even and odd blocks
+  // logits of block k (MF) and errors of block k - 1 (RANK: 0 none, 1 a full block, 2 a cluster's last one,
+  // whose unused rows do not count)
+  auto block = [&](int k, f32x16& acc_new, const f32x16& acc, auto mf_tag, auto rank_tag) __attribute__((always_inline)) {
+    constexpr bool MF = decltype(mf_tag)::value;
+    constexpr int RANK = decltype(rank_tag)::value;
+    constexpr int RPS = 16 / KSN;  // registers ranked per k-step
+    const unsigned char* kr = &ktile[k % kProbeStages][li * (D * 2)];
+    const float* st = stat[(k + kProbeStages) % (kProbeStages + 1)];  // block k - 1
+    const int key = swz(li);
+    bf16x8 ak[KSN];
+    auto rd = [&](int s) { ak[s] = as_bf16x8(*reinterpret_cast<const uint4*>(kr + (((2 * s + lh) ^ key) << 4))); };
+    float nn[16], dl[16];
+    if constexpr (MF) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc_new[r] = 0.f;
+      rd(0);
+      rd(1);
     }
-    const int buf = k % kProbeStages;
-    if (cc.j0 == cc.start) {  // first block of key cluster cc.b
+    if constexpr (RANK != 0 && VALUE_AWARE) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 n4 = *reinterpret_cast<const float4*>(st + 8 * g + 4 * lh);
+        const float4 d4 = *reinterpret_cast<const float4*>(st + 32 + 8 * g + 4 * lh);
+        nn[4 * g] = n4.x; nn[4 * g + 1] = n4.y; nn[4 * g + 2] = n4.z; nn[4 * g + 3] = n4.w;
+        dl[4 * g] = d4.x; dl[4 * g + 1] = d4.y; dl[4 * g + 2] = d4.z; dl[4 * g + 3] = d4.w;
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < KSN; ++s) {
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (MF) {
+        if (s + 2 < KSN) rd(s + 2);
+#pragma unroll
+        for (int pc3 = 0; pc3 < 3; ++pc3)
+          acc_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[s], bq[pc3][s], acc_new, 0, 0, 0);
+      }
+      if constexpr (RANK != 0) {
+        // register r is key j0 + 8(r/4) + 4lh + r%4, query centroid a. Per key, with u = W - w:
+        //   |W vbar - w v_j|^2 = u (u |vbar|^2 - 2 w vbar.delta_j) + w^2 |delta_j|^2
+#pragma unroll
+        for (int r = s * RPS; r < (s + 1) * RPS; ++r) {
+          const float w = __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(acc[r], scale2, neg_m2), cap2));
+          // (an unused row, which repeats the cluster's last key, adds 0: selects, no branch per register)
+          const bool used = RANK == 1 || pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end;
+          const float u = used ? W - w : 0.f;
+          if (VALUE_AWARE) {
+            const float d = used ? dl[r] : 0.f, n = used ? nn[r] : 0.f;
+            E = __builtin_fmaf(u, __builtin_fmaf(w, d, u * nvb), E);
+            E = __builtin_fmaf(w * w, n, E);
+          } else {
+            E = __builtin_fmaf(u, u, E);
+          }
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using No = std::integral_constant<int, 0>;
+  using Full = std::integral_constant<int, 1>;
+  using Last = std::integral_constant<int, 2>;
+  auto iteration = [&](int k, f32x16& acc_new, f32x16& acc) __attribute__((always_inline)) {
+    const bool mf = k < issued;  // block k exists
+    if (mf) {
+      // it has landed once at most the copies of the later blocks are outstanding
+      const int ahead = issued - k - 1;
+      if (ahead >= 2) SVGEAR_WAIT_VMCNT(2 * LPB);
+      else if (ahead == 1) SVGEAR_WAIT_VMCNT(LPB);
+      else SVGEAR_WAIT_VMCNT(0);
+      __syncthreads();  // everyone's part of block k is in LDS; everyone is done with iteration k - 1
+      if (fc.b < b_end) {
+        issue(fc, issued);
+        advance(fc);
+        ++issued;
+      }
+    }
+    if (k == 0) {
+      if (wave_on) block(k, acc_new, acc, std::true_type{}, No{});
+      return true;
+    }
+    if (pc.j0 == pc.start) {  // first block of key cluster pc.b
       E = 0.f;
-      W = live ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + cc.b] - m_a, kMaxExponent)) : 0.f;
+      W = live ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + pc.b] - m_a, kMaxExponent)) : 0.f;
       nvb = 0.f;
       if (VALUE_AWARE) {  // |vbar_b|^2: D/64 dims per lane, then across the wave
-        const float* vb = vbar + ((int64_t)bh * Ck + cc.b) * D;
+        const float* vb = vbar + ((int64_t)bh * Ck + pc.b) * D;
 #pragma unroll
         for (int t = 0; t < D / 64; ++t) nvb = __builtin_fmaf(vb[lane + 64 * t], vb[lane + 64 * t], nvb);
 #pragma unroll
@@ -440,70 +605,40 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       }
     }
     if (wave_on) {
-      // A operand: key row li of the block, dims 16s + 8lh .. = chunk 2s + lh
-      const unsigned char* kr = &ktile[buf][li * (D * 2)];
-      const int key = swz(li);
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-      for (int s = 0; s < KSN; ++s) {
-        const bf16x8 ak = as_bf16x8(*reinterpret_cast<const uint4*>(kr + (((2 * s + lh) ^ key) << 4)));
-#pragma unroll
-        for (int pc = 0; pc < 3; ++pc) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[pc][s], acc, 0, 0, 0);
-      }
-      // register r is key j0 + 8(r/4) + 4lh + r%4, query centroid a. Per key, with u = W - w:
-      //   |W vbar - w v_j|^2 = u (u |vbar|^2 - 2 w vbar.delta_j) + w^2 |delta_j|^2
-      auto rank = [&](auto tail_tag) __attribute__((always_inline)) {
-        constexpr bool TAIL = decltype(tail_tag)::value;  // only a cluster's last block has unused rows
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int jb = cc.j0 + 8 * g + 4 * lh;
-          float nn[4] = {0.f, 0.f, 0.f, 0.f}, dl[4] = {0.f, 0.f, 0.f, 0.f};
-          if (VALUE_AWARE) {
-            const float4 n4 = *reinterpret_cast<const float4*>(&stat[buf][8 * g + 4 * lh]);
-            const float4 d4 = *reinterpret_cast<const float4*>(&stat[buf][32 + 8 * g + 4 * lh]);
-            nn[0] = n4.x; nn[1] = n4.y; nn[2] = n4.z; nn[3] = n4.w;
-            dl[0] = d4.x; dl[1] = d4.y; dl[2] = d4.z; dl[3] = d4.w;
-          }
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (!TAIL || jb + r < cc.end) {
-              const float w = __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(acc[4 * g + r], scale2, neg_m2), cap2));
-              const float u = W - w;
-              if (VALUE_AWARE) {
-                E = __builtin_fmaf(u, __builtin_fmaf(w, dl[r], u * nvb), E);
-                E = __builtin_fmaf(w * w, nn[r], E);
-              } else {
-                E = __builtin_fmaf(u, u, E);
-              }
-            }
-          }
-        }
-      };
-      if (cc.j0 + 32 <= cc.end) rank(std::false_type{});
-      else rank(std::true_type{});
-      if (cc.j0 + 32 >= cc.end) {  // last block of the cluster
+      const bool full = pc.j0 + 32 <= pc.end;
+      if (mf && full) block(k, acc_new, acc, std::true_type{}, Full{});
+      else if (mf) block(k, acc_new, acc, std::true_type{}, Last{});
+      else if (full) block(k, acc_new, acc, std::false_type{}, Full{});
+      else block(k, acc_new, acc, std::false_type{}, Last{});
+      if (pc.j0 + 32 >= pc.end) {  // last block of the cluster
         const float Et = E + __shfl_xor(E, 32);
-        if (lh == 0) sc[wave][li][cc.b - b_lo] = Et / (float)(cc.end - cc.start);
+        if (lh == 0) sc[wave][li][pc.b - b_lo] = Et / (float)(pc.end - pc.start);
       }
     }
-    advance(cc);
+    advance(pc);
+    return mf;
+  };
+  for (int k = 0;; k += 2) {  // (two at a time: the accumulators swap their parts without a move)
+    if (!iteration(k, acc_even, acc_odd)) break;
+    if (!iteration(k + 1, acc_odd, acc_even)) break;
   }
   flush();
 }
 
 }  // namespace
 
-// Centroid logits and their row maxima alone (no block errors).
+// Centroid logits and their row maxima alone (no block errors); q3: see sbar_kernel.
 int run_sbar(const float* qbar, const float* kbar, const int32_t* k_offsets, int BH, int d, int Cq, int Ck,
-             float scale, float* sbar, float* mrow, hipStream_t s) {
-  if (d == 64)
-    sbar_kernel<64><<<dim3((unsigned)ceil_div(Cq, kSbarRows), BH), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale,
-                                                                              sbar, mrow, nullptr);
-  else
-    sbar_kernel<128><<<dim3((unsigned)ceil_div(Cq, kSbarRows), BH), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale,
-                                                                               sbar, mrow, nullptr);
+             float scale, float* sbar, float* mrow, bf16_t* q3, hipStream_t s) {
+  const int64_t blocks = ceil_div(Cq, 32);
+  if (blocks * BH >= 256) {
+    auto kern = d == 64 ? sbar_mfma_kernel<64> : sbar_mfma_kernel<128>;
+    kern<<<dim3((unsigned)blocks, BH), 64 * kSbarWaves, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3);
+  } else {
+    const int64_t rows = q3 ? align_up(Cq, 32) : Cq;
+    auto kern = d == 64 ? sbar_kernel<64> : sbar_kernel<128>;
+    kern<<<dim3((unsigned)ceil_div(rows, kSbarRows), BH), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3);
+  }
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
 }
@@ -513,14 +648,8 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
               bool value_aware, float* scores, float* sbar, float* mrow, bf16_t* q3, float* nd, float* dd,
               hipStream_t s) {
   const bool mfma = dt == SVGEAR_BF16;
-  const int rows = mfma ? (int)align_up(Cq, 32) : Cq;
-  if (d == 64)
-    sbar_kernel<64><<<dim3((unsigned)ceil_div(rows, kSbarRows), BH), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale,
-                                                                                sbar, mrow, mfma ? q3 : nullptr);
-  else
-    sbar_kernel<128><<<dim3((unsigned)ceil_div(rows, kSbarRows), BH), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale,
-                                                                                 sbar, mrow, mfma ? q3 : nullptr);
-  SVGEAR_LAUNCH_CHECK();
+  const int rc = run_sbar(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, mfma ? q3 : nullptr, s);
+  if (rc != SVGEAR_OK) return rc;
   if (mfma) {
     const int64_t stat_stride = probe_stat_stride(Nk);
     const bf16_t* k16 = static_cast<const bf16_t*>(kp);

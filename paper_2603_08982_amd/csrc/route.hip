@@ -23,7 +23,7 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
               hipStream_t s);
 
 int run_sbar(const float* qbar, const float* kbar, const int32_t* k_offsets, int BH, int d, int Cq, int Ck,
-             float scale, float* sbar, float* mrow, hipStream_t s);
+             float scale, float* sbar, float* mrow, bf16_t* q3, hipStream_t s);
 
 namespace {
 
@@ -624,7 +624,7 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
                        !(flags & SVGEAR_PROBE_PLAIN), scores, sbar, mrow, q3, nd, dd, s);
     if (rc != SVGEAR_OK) return rc;
   } else if (adaptive) {
-    int rc = run_sbar(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, s);
+    int rc = run_sbar(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, nullptr, s);
     if (rc != SVGEAR_OK) return rc;
   }
   const int per_row = (adaptive || (flags & SVGEAR_ROUTE_PER_ROW)) ? 1 : 0;

@@ -58,3 +58,25 @@ def test_scores_at_the_edges_of_tiles(dtype, d, Cq, plain):
         # a logit of size s is off by s 2^-22 or so after d products, its exponential relatively by as much
         assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
         assert (np.abs(got - ref) <= 2e-4 * ref + 1e-6 * ref.max(1, keepdims=True)).all()
+
+
+def test_many_heads_give_the_scores_of_one_head():
+    """Enough workgroups of 32 query centroids switch the centroid logits to the matrix cores: bit for bit
+    the vector-ALU chain of a head by itself."""
+    H, Cq, Ck, d, n = 9, 1000, 51, 128, 500
+    g = torch.Generator().manual_seed(5)
+    sizes = np.full(Ck, n // Ck)
+    sizes[7], sizes[50] = 0, n - n // Ck * (Ck - 2)
+    koff = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes), [n]]).astype(np.int32)).expand(1, H, -1).contiguous().to(dev())
+    qoff = torch.arange(Cq + 2, dtype=torch.int32).expand(1, H, -1).contiguous().to(dev())
+    for dtype in (torch.float32, torch.bfloat16):
+        q, kb, vb = (torch.randn(1, H, c, d, generator=g).to(dev()) for c in (Cq, Ck, Ck))
+        K, V = (torch.randn(1, H, n, d, generator=g).to(dtype).to(dev()) for _ in range(2))
+        for p in (None, 0.6):
+            r = sv.probe_route(q, kb, vb, K, V, qoff, koff, n * Cq // 4, d ** -0.5, top_p=p)
+            for h in (0, 4, 8):
+                one = sv.probe_route(*(t[:, h: h + 1].contiguous() for t in (q, kb, vb, K, V, qoff, koff)), n * Cq // 4,
+                                     d ** -0.5, top_p=p)
+                torch.cuda.synchronize()
+                for key in ("scores", "mask_bits", "row_ptr", "routed_cost") + (("row_budget",) if p else ()):
+                    assert torch.equal(r[key][:, h: h + 1], one[key]), key
