@@ -2,6 +2,7 @@
 // Paper: Eq. (1), Eq. (6), Algorithm 2 (see attention.hip for the decomposition).
 #include "attention.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace svgear {
@@ -981,15 +982,6 @@ merge_splits_kernel(AttnArgs p) {
   if (p.lse && dim == 0) p.lse[lse_idx] = (M + log2f(l)) * kLn2;
 }
 
-// Both centroid tables to bf16 in one launch (blockIdx.y picks the table).
-__global__ void to_bf16_kernel(const float* __restrict__ src0, const float* __restrict__ src1, int64_t n,
-                               bf16_t* __restrict__ dst0, bf16_t* __restrict__ dst1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (blockIdx.y == 0) dst0[i] = f32_to_bf16(src0[i]);
-  else dst1[i] = f32_to_bf16(src1[i]);
-}
-
 // ------------------------------------------------------------------------ work lists
 // Item = (head, query cluster); its tiles all run T = #routed key tiles + #centroid tiles
 // pipeline steps. Items are ranked by T, longest first (ties by index), and dealt to the 8
@@ -1021,14 +1013,26 @@ __device__ __forceinline__ void plan_item(const int32_t* q_offsets, const int32_
   }
 }
 
+// The centroid tables in bf16: a block of a planning kernel per blockDim.x elements of each.
+__device__ __forceinline__ void centroids_to_bf16(unsigned block, const float* kbar, const float* vbar, int64_t n,
+                                                  bf16_t* kbar16, bf16_t* vbar16) {
+  const int64_t i = (int64_t)block * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  kbar16[i] = f32_to_bf16(kbar[i]);
+  vbar16[i] = f32_to_bf16(vbar[i]);
+}
+
 // A wave per item over the whole grid (one workgroup per head took 173 us for 5 heads of 300 clusters,
-// this grid 10).
+// this grid 10); the blocks after the item_blocks first ones convert the centroids, a launch less.
 __global__ void __launch_bounds__(256)
 plan_items_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
-                  const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int Cq, int Ck, int BM,
-                  int32_t* __restrict__ item_T, int32_t* __restrict__ item_nt) {
-  const int bh = blockIdx.y, R = Cq + 1, a = 4 * blockIdx.x + (threadIdx.x >> 6);
-  if (a < R) plan_item(q_offsets, k_offsets, row_ptr, col_idx, bh, a, Cq, Ck, BM, item_T[bh * R + a], item_nt[bh * R + a]);
+                  const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int M, int Cq, int Ck, int BM,
+                  int32_t* __restrict__ item_T, int32_t* __restrict__ item_nt, const float* __restrict__ kbar,
+                  const float* __restrict__ vbar, int64_t n, bf16_t* __restrict__ kbar16, bf16_t* __restrict__ vbar16) {
+  const unsigned item_blocks = (unsigned)(M + 3) / 4;
+  if (blockIdx.x >= item_blocks) return centroids_to_bf16(blockIdx.x - item_blocks, kbar, vbar, n, kbar16, vbar16);
+  const int i = 4 * blockIdx.x + (threadIdx.x >> 6), R = Cq + 1;
+  if (i < M) plan_item(q_offsets, k_offsets, row_ptr, col_idx, i / R, i % R, Cq, Ck, BM, item_T[i], item_nt[i]);
 }
 
 // Rank of every item by (T descending, index ascending), by counting: a workgroup ranks 64 items,
@@ -1149,10 +1153,41 @@ plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
   write_lists(q_offsets, item_nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
 }
 
+// Ranks and lists of up to kRankListItems items in one workgroup: the counting is M^2 / 1024 LDS reads a
+// thread, less than the launch it saves (132 items: 76.5 -> 74.2 us a call; 336 items cost 1.7 us more).
+constexpr int kRankListItems = 256;
+__global__ void __launch_bounds__(1024)
+plan_rank_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ item_T,
+                       const int32_t* __restrict__ item_nt, int M, int Cq, int BM, int32_t* __restrict__ sched_bh,
+                       int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
+                       int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x) {
+  __shared__ int32_t T[kRankListItems], nt[kRankListItems], rank[kRankListItems], by_rank[kRankListItems],
+      rank_off[kRankListItems];
+  const int tid = threadIdx.x;
+  if (tid < M) {
+    T[tid] = item_T[tid];
+    nt[tid] = item_nt[tid];
+    rank[tid] = 0;
+  }
+  __syncthreads();
+  const int width = (M + 63) & ~63, parts = 1024 / width;  // waves of one part rank the items over a stretch of them
+  const int part = tid / width, i = tid % width;
+  if (part < parts && i < M) {
+    const int mine = T[i], lo = (int)((int64_t)M * part / parts), hi = (int)((int64_t)M * (part + 1) / parts);
+    int before = 0;
+#pragma unroll 8
+    for (int j = lo; j < hi; ++j) before += T[j] > mine || (T[j] == mine && j < i);
+    atomicAdd(&rank[i], before);
+  }
+  __syncthreads();
+  if (tid < M) by_rank[rank[tid]] = tid;
+  __syncthreads();
+  write_lists(q_offsets, nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
+}
+
 // The whole plan of a call with up to kPlanItems items in one workgroup (block 0: a small layer is
 // bound by launches, and the three kernels took 9 us of it; 256 items take 16 waves longer than that),
-// and beside it the centroid tables in
-// bf16 (the other blocks).
+// and beside it the centroid tables in bf16 (the other blocks).
 constexpr int kPlanItems = 64;
 __global__ void __launch_bounds__(1024)
 plan_small_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets,
@@ -1160,14 +1195,7 @@ plan_small_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
                   int32_t* __restrict__ sched_bh, int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
                   int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x, const float* __restrict__ kbar,
                   const float* __restrict__ vbar, int64_t n, bf16_t* __restrict__ kbar16, bf16_t* __restrict__ vbar16) {
-  if (blockIdx.x > 0) {
-    const int64_t i = (int64_t)(blockIdx.x - 1) * 1024 + threadIdx.x;
-    if (i < n) {
-      kbar16[i] = f32_to_bf16(kbar[i]);
-      vbar16[i] = f32_to_bf16(vbar[i]);
-    }
-    return;
-  }
+  if (blockIdx.x > 0) return centroids_to_bf16(blockIdx.x - 1, kbar, vbar, n, kbar16, vbar16);
   __shared__ int32_t item_T[kPlanItems], item_nt[kPlanItems], by_rank[kPlanItems], rank_off[kPlanItems];
   const int wave = threadIdx.x >> 6, R = Cq + 1;
   for (int i = wave; i < M; i += 16)
@@ -1196,8 +1224,18 @@ struct Bf16Form {
   int splits;  // workgroups that share the keys of a 128-row tile
 };
 // Measured at d = 128 unless stated, 384-row against 128-row tiles, us a call (a quarter routed):
-//  * few tiles, keys split: 1 head x 11,970 rows, 8 / 942 clusters 199 -> 99; 1 x 4,096, 32 / 64 63 -> 44
-//    (with fewer than some 1,000 keys a split the merge costs what it saves: 1 x 1,200, d = 64 31 -> 33);
+//  * keys split, for the longest tiles: a cluster may have anything from a dozen keys to all of them routed,
+//    and a launch ends no sooner than its longest tile. As many splits as the largest of three rules:
+//    - fill: workgroups for the 512 that are resident at once, 1,024 keys each or more (fewer, and the
+//      merge costs what it saves). 1 head x 11,970 rows, 8 / 942 clusters 199 -> 80; 1 x 4,096, 32 / 64
+//      63 -> 36. Rounded to the nearest, since a few workgroups beyond 512 wait for a whole tile: 12 x
+//      2,376, 384 tiles in two splits 80, in one 56; 4 x 5,400, 236 tiles in three 76, in two 58;
+//    - fine: two rounds of workgroups at 4,096 keys or more a split: 1 x 37,800, 396 tiles in one split 912,
+//      in two 491, in three 353; 4 x 10,000, 356 tiles in one 172, in two 120;
+//    - spread: up to 1,536 tiles, four rounds at 8,192 keys or more: 1 x 75,600, 641 tiles in one split 1588,
+//      in two 955, in four 860; 1 x 118,800, 1,079 tiles 2817 -> 2085; d = 64, 2 x 75,600, 1,482 tiles
+//      1506 -> 1229. Not where the keys are few for so many tiles (8 x 20,000, 1,456 tiles 597 -> 613) nor
+//      with more tiles, which even out by themselves (3 x 75,600, 1,923 tiles 2240 -> 2279);
 //  * clusters of 32 to 160 rows, which fill at most five of twelve waves: 12 x 16,200, 81 rows 1047 -> 829;
 //    24 x 10,800, 108 rows 838 -> 725; d = 64, 8 x 32,400, 162 rows 1008 -> 967; smaller clusters are all
 //    start and end either way (40 x 594, 12 rows 140 -> 144), larger ones want the larger tile (5 x
@@ -1206,8 +1244,11 @@ struct Bf16Form {
 //    (d = 64: 12 x 7,000 128 -> 133).
 static Bf16Form bf16_form(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
   const int64_t quads = BH * (ceil_div(Nq, 32 * kQuadWaves) + Cq / 2);  // a cluster's last tile is half full
-  const int64_t want = ceil_div(512, quads), most = Nk / 1024;
-  const int64_t n = want < most ? want : most;
+  const int64_t fill = std::min((512 + quads / 2) / quads, Nk / 1024);
+  const int64_t fine = std::min({ceil_div(1024, quads), Nk / 4096, (int64_t)4});
+  const int64_t spread =
+      quads <= 1536 && Nk >= 16 * quads ? std::min({ceil_div(2048, quads), Nk / 8192, (int64_t)4}) : 1;
+  const int64_t n = std::max({fill, fine, spread});
   const bool small_clusters = Nq >= (int64_t)32 * Cq && Nq <= (int64_t)160 * Cq;
   if (n >= 2) return {32 * kQuadWaves, (int)(n < 8 ? n : 8)};
   if ((small_clusters && quads > 64) || (d == 128 && quads <= 1024 && quads > 64 && Nq >= (int64_t)32 * Cq))
@@ -1263,10 +1304,15 @@ int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size
     SVGEAR_LAUNCH_CHECK();
     return SVGEAR_OK;
   }
-  to_bf16_kernel<<<dim3((unsigned)ceil_div(n, 256), 2), 256, 0, s>>>(a.kbar, a.vbar, n, kbar16, vbar16);
+  plan_items_kernel<<<(unsigned)(ceil_div(M, 4) + ceil_div(n, 256)), 256, 0, s>>>(
+      a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, M, a.Cq, a.Ck, BM, item_T, item_nt, a.kbar, a.vbar, n, kbar16, vbar16);
   SVGEAR_LAUNCH_CHECK();
-  plan_items_kernel<<<dim3((unsigned)ceil_div(a.Cq + 1, 4), a.BH), 256, 0, s>>>(a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, a.Cq, a.Ck, BM, item_T, item_nt);
-  SVGEAR_LAUNCH_CHECK();
+  if (M <= kRankListItems) {
+    plan_rank_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_T, item_nt, M, a.Cq, BM, sched_bh, sched_a, sched_row0,
+                                              sched_rend, sched_x);
+    SVGEAR_LAUNCH_CHECK();
+    return SVGEAR_OK;
+  }
   plan_rank_kernel<<<(unsigned)ceil_div(M, kRankItems), 256, 0, s>>>(item_T, M, by_rank);
   SVGEAR_LAUNCH_CHECK();
   plan_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_nt, by_rank, M, a.Cq, BM, rank_off, sched_bh, sched_a, sched_row0,

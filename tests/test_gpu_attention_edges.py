@@ -31,6 +31,12 @@ def _sizes(name, rng):
         return [200, 1, 129], list(rng.integers(1, 250, 80)), 5
     if name == "full_tiles":  # enough tiles of clusters that want the largest tile
         return list(rng.integers(385, 800, 40)), [30, 64, 500], 3
+    if name == "ranked":  # 256 items over both heads
+        return list(rng.integers(1, 200, 127)), [64, 0, 300], 2
+    if name == "fine_splits":  # a few hundred tiles over 8,192 keys and more
+        return list(rng.integers(1, 3, 400)), list(rng.integers(1, 400, 42)) + [1000], 9
+    if name == "spread_splits":  # more than a thousand over 16,384 and more
+        return list(rng.integers(0, 3, 1100)), list(rng.integers(1, 600, 86)) + [300], 0
     return [130, 64], list(rng.integers(0, 3, 900)), 40  # hundreds of tiny clusters
 
 
@@ -49,7 +55,8 @@ def _definition(Q, K, V, kbar, vbar, qs, ks, mask, scale):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters", "split_keys", "full_tiles"])
+@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters", "split_keys", "full_tiles", "ranked", "fine_splits",
+                                  "spread_splits"])
 @pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
 def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
     rng = np.random.default_rng(3)
