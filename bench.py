@@ -349,7 +349,7 @@ def run_sweep(sv, args, wl, Q, K, V, cq0, ck0):
 
 
 def run_attention_steps(sv):
-    """Kernel-level timing of attn_bf16_d128_kernel on synthetic layouts (bf16, d = 128, 16 heads): every query
+    """Kernel-level timing of attn_bf16_kernel on synthetic layouts (bf16, d = 128, 16 heads): every query
     cluster has 32 k rows (k active waves per tile), every key cluster the same size, each query cluster routes
     `routed` random key clusters. (1) k = 12, exactly 12 tiles per CU, the routed count varied: a least-squares fit
     of time per tile against the steps per tile T gives the fixed time per tile and the time per step. (2) a quarter
@@ -397,7 +397,7 @@ def run_attention_steps(sv):
     y = np.array([r["us_per_tile"] for r in fit_rows])
     (a, b), *_ = np.linalg.lstsq(A, y, rcond=None)
     wave_rows = [run_case(k, 2304 // k, 128) for k in (12, 9, 8, 6, 4, 3, 2, 1)]
-    print(json.dumps({"mode": "attention-steps", "kernel": "attn_bf16_d128_kernel", "heads": H, "key_clusters": Ck,
+    print(json.dumps({"mode": "attention-steps", "kernel": "attn_bf16_kernel", "heads": H, "key_clusters": Ck,
                       "fit_us_per_tile": a, "fit_ns_per_step": b * 1e3, "fit_cases": fit_rows, "wave_cases": wave_rows}))
 
 
@@ -557,8 +557,7 @@ def main():
         "probe_max_exponent_above_row_stabiliser": {"value": excess, "cap": 40.0, "cap_reached": bool(excess > 40.0)},
         "attention_stage": {"ms": attn_ms, "dense_equiv_tflops": dense_flops / (attn_ms * 1e-3) / 1e12},
         "roofline": {"bound": "mfma" if wl.dtype == "bf16" else "alu",
-                     "kernel": ("attn_bf16_d128_kernel" if wl.d == 128 else "attn_bf16_kernel") if wl.dtype == "bf16"
-                     else "attn_f32_kernel",
+                     "kernel": "attn_bf16_kernel" if wl.dtype == "bf16" else "attn_f32_kernel",
                      "achieved": achieved, "peak": peak_tflops, "unit": "TFLOP/s",
                      "frac": achieved / peak_tflops,
                      "traffic": measured_attention_traffic(wl.name, wl.rho, wl.H),

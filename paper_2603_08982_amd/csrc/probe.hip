@@ -391,11 +391,10 @@ value_stats_kernel(const float* __restrict__ vbar, const bf16_t* __restrict__ vp
 // with the row index so that the operand reads of 32 rows do not collide. One barrier per
 // block. A block of a wave is 24 MFMAs (d = 128, 768 cycles of its SIMD) and about as long on the vector
 // ALU for the errors of its 512 pairs, and a SIMD holds two waves: the errors of block k - 1 are written
-// between the MFMAs of block k, and a
-// cluster's last block, a third of them at 75 keys a cluster, selects instead of branching per register
-// (40 heads, 300 x 1,000 centroids: 1.58 -> 1.53 ms; 5 heads, 200 x 500: 129 -> 118 us). What is left is the
-// vector ALU, some 160 to 250 instructions a block, at the two waves that 96 registers of centroid
-// fragments leave room for (three waves spill: 1.85 ms).
+// between the MFMAs of block k, and a cluster's last block, a third of them at 75 keys a cluster, selects
+// instead of branching per register (40 heads, 300 x 1,000 centroids: 1.58 -> 1.53 ms; 5 heads,
+// 200 x 500: 129 -> 118 us). What is left is the vector ALU, some 160 to 250 instructions a block, at
+// the two waves that 96 registers of centroid fragments leave room for (three waves spill: 1.85 ms).
 constexpr int kProbeClusters = 4;  // key clusters per workgroup
 constexpr int kProbeStages = 4;    // LDS ring buffers
 
