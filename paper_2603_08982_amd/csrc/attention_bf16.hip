@@ -44,8 +44,15 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // MFMAs (512 cycles of its SIMD) against some 150 vector instructions and 32 exponentials (about 800).
 // It runs the same pipeline; the kernel before staged its tiles through registers, transposed V with
 // vector instructions and kept 4 waves a workgroup (24 heads x 32,477 rows, 64 / 300 clusters, a
-// quarter routed: 5.20 -> 1.94 ms, 318 -> 855 TFLOP/s).
+// quarter routed: 5.21 -> 2.00 ms, 318 -> 828 TFLOP/s).
 constexpr float kLazyRescale = 8.0f;  // log2 headroom before the running maximum is refreshed
+
+// The row sums (softmax denominators, log-sum-exp): at d = 128 over the bf16-rounded probabilities that the
+// PV product uses, at d = 64 over the probabilities as computed in fp32: the log-sum-exp is within 2e-5 of
+// 64 bits (the sum of rounded ones is up to 4e-3 off at a few keys) for 32 additions a step instead of 16
+// packed ones (24 heads x 32,477 rows: 1.98 -> 2.00 ms).
+template <int D>
+constexpr bool kSumRounded = D == 128;
 
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 // acc + lo(p) + hi(p) for a packed bf16 pair (v_dot2c_f32_bf16 against (1, 1))
@@ -353,6 +360,7 @@ attn_bf16_kernel(AttnArgs p) {
   uint32_t pk[2][8];
   auto softmax = [&](int t, auto biased_tag) __attribute__((always_inline)) {
     constexpr bool BIASED = decltype(biased_tag)::value;
+    float ls[4] = {0.f, 0.f, 0.f, 0.f};  // row sums, four independent parts (see kSumRounded)
     if constexpr (!BIASED) {
       // four independent max chains (a single chain of 16 dependent ops stalls the wave)
       float mxa = fmaxf(sacc[0][0], sacc[1][0]), mxb = fmaxf(sacc[0][1], sacc[1][1]);
@@ -375,6 +383,7 @@ attn_bf16_kernel(AttnArgs p) {
         for (int r = 0; r < 16; r += 2) {
           const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][r], c, neg_m));
           const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][r + 1], c, neg_m));
+          if constexpr (!kSumRounded<D>) ls[(r >> 1) & 3] += p0 + p1;
           pk[kb][r >> 1] = pack_bf16(p0, p1);
         }
     } else {
@@ -401,24 +410,17 @@ attn_bf16_kernel(AttnArgs p) {
         for (int r = 0; r < 16; r += 2) {
           const float p0 = __builtin_amdgcn_exp2f(sacc[kb][r] - m_use);
           const float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1] - m_use);
+          if constexpr (!kSumRounded<D>) ls[(r >> 1) & 3] += p0 + p1;
           pk[kb][r >> 1] = pack_bf16(p0, p1);
         }
     }
-    // row sums from the bf16-rounded probabilities (the values the PV product uses), in
-    // four independent partial sums
-    {
-      float l0 = 0.f, l1 = 0.f, l2 = 0.f, l3 = 0.f;
+    if constexpr (kSumRounded<D>) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int u = 0; u < 8; u += 4) {
-          l0 = dot2_ones(pk[kb][u], l0);
-          l1 = dot2_ones(pk[kb][u + 1], l1);
-          l2 = dot2_ones(pk[kb][u + 2], l2);
-          l3 = dot2_ones(pk[kb][u + 3], l3);
-        }
-      l += (l0 + l1) + (l2 + l3);
+        for (int u = 0; u < 8; ++u) ls[u & 3] = dot2_ones(pk[kb][u], ls[u & 3]);
     }
+    l += (ls[0] + ls[1]) + (ls[2] + ls[3]);
   };
   // ---- O^T += V^T P^T of tile t: k-step ks covers keys 16ks .. 16ks+15; the transpose reads
   // of k-step ks+1 are issued before the MFMAs of k-step ks
@@ -817,7 +819,8 @@ attn_bf16_quad_kernel(AttnArgs p) {
           const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], cc, neg_m));
           const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r + 1], cc, neg_m));
           pk[kb][r >> 1] = pack_bf16(p0, p1);
-          ls[e & 3] = dot2_ones(pk[kb][r >> 1], ls[e & 3]);
+          if constexpr (kSumRounded<D>) ls[e & 3] = dot2_ones(pk[kb][r >> 1], ls[e & 3]);
+          else ls[e & 3] += p0 + p1;
         }
       }
     }

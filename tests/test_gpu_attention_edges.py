@@ -14,10 +14,15 @@ pytestmark = pytest.mark.gpu
 
 Q_EDGES = [1, 31, 0, 32, 33, 64, 127, 128, 129, 0, 383, 385]
 K_EDGES = [0, 1, 31, 32, 33, 63, 64, 65, 0, 127, 200, 5, 17, 96, 255, 0]
-# rel-L2 of the output and largest log-sum-exp error. fp32: d products and N weights per sum, each
-# rounded to 2^-24, errors of either sign: a few 1e-7 (measured 7e-7); bf16: rounded probabilities, values
-# and outputs, 2^-9 each
-TOL = {torch.float32: (3e-6, 2e-5), torch.bfloat16: (1e-2, 2e-2)}
+# rel-L2 of the output. fp32: d products and N weights per sum, each rounded to 2^-24, errors of either
+# sign: a few 1e-7 (measured 7e-7); bf16: rounded probabilities, values and outputs, 2^-9 each
+TOL = {torch.float32: 3e-6, torch.bfloat16: 1e-2}
+
+
+def _lse_tol(dtype, d):
+    """Largest log-sum-exp error. bf16 products are exact in fp32, so a logit below 8 is off by a few 2^-21 in
+    either type and the fp32 sum of the weights by less; bf16 heads of 128 sum rounded weights, 2^-9 each."""
+    return 2e-2 if dtype == torch.bfloat16 and d == 128 else 2e-5
 
 
 def _sizes(name, rng):
@@ -105,6 +110,7 @@ def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
         none = torch.isinf(ref_lse)  # text rows of a head without text keys see nothing
         assert torch.equal(torch.isinf(got_lse), none) and not got[none].any()
         err = (got.double() - ref)[~none].norm() / ref[~none].norm()
-        assert err <= TOL[dtype][0], f"head {h}: rel-L2 {err:.3e}"
-        assert (got_lse.double() - ref_lse)[~none].abs().max() <= TOL[dtype][1]
+        assert err <= TOL[dtype], f"head {h}: rel-L2 {err:.3e}"
+        lse_err = (got_lse.double() - ref_lse)[~none].abs().max()
+        assert lse_err <= _lse_tol(dtype, d), f"head {h}: log-sum-exp {lse_err:.3e}"
         assert torch.equal(O2[0, h].cpu()[perm[0, h]], got) and torch.equal(lse2[0, h].cpu()[perm[0, h]], got_lse)
