@@ -376,7 +376,7 @@ attn_bf16_kernel(AttnArgs p) {
       mx = fmaxf(mx, swap32(mx));
       const float ms = mx * c;
       if (__any(ms > m + kLazyRescale)) rescale(fmaxf(m, ms));
-      const float neg_m = -m;
+      const float neg_m = m == -INFINITY ? 0.f : -m;  // (every score so far -inf: weights of 0, not NaN)
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll

@@ -114,3 +114,32 @@ def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
         lse_err = (got_lse.double() - ref_lse)[~none].abs().max()
         assert lse_err <= _lse_tol(dtype, d), f"head {h}: log-sum-exp {lse_err:.3e}"
         assert torch.equal(O2[0, h].cpu()[perm[0, h]], got) and torch.equal(lse2[0, h].cpu()[perm[0, h]], got_lse)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows", [[40, 5], [70] * 40])  # tiles of 384 rows and of 128
+def test_whole_tiles_of_keys_without_weight_come_first(dtype, d, rows):
+    """Keys whose logits are all -inf weigh nothing, also where a row meets them before any other."""
+    qs, ks = np.array(rows + [3]), np.array([200, 61, 90, 7, 0])
+    Cq, Ck, Nq, Nk, H = len(qs) - 1, len(ks) - 1, int(qs.sum()), int(ks.sum()), 2
+    g = torch.Generator().manual_seed(7)
+    Q, K, V = (torch.randn(1, H, n, d, generator=g) for n in (Nq, Nk, Nk))
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    K[:, :, :250, 0] = -float("inf")
+    Q, K, V = (x.to(dtype) for x in (Q, K, V))
+    kbar, vbar = (torch.randn(1, H, Ck, d, generator=g).to(torch.bfloat16).float() for _ in range(2))
+    mask = np.outer(qs > 0, ks > 0)
+    mask[:Cq, 2] = False
+    row_ptr, col_idx = csr_from_mask(mask)
+    lists = [torch.from_numpy(x)[None, None].expand(1, H, *x.shape).contiguous().to(dev())
+             for x in (mask_to_bits(mask, Cq, Ck).view(np.int32), row_ptr, col_idx)]
+    offs = [torch.from_numpy(np.concatenate([[0], np.cumsum(x)]).astype(np.int32)).expand(1, H, -1).contiguous().to(dev())
+            for x in (qs, ks)]
+    O, lse = sv.sparse_attn_comp(*(x.to(dev()) for x in (Q, K, V, kbar, vbar)), *offs, *lists, d ** -0.5, want_lse=True)
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref, ref_lse = _definition(*(x[0, h].double() for x in (Q, K, V, kbar, vbar)), qs, ks, mask, d ** -0.5)
+        got, got_lse = O[0, h].cpu().double(), lse[0, h].cpu().double()
+        assert (got - ref).norm() <= TOL[dtype] * ref.norm()
+        assert (got_lse - ref_lse).abs().max() <= _lse_tol(dtype, d)
