@@ -554,16 +554,17 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
 #pragma unroll
         for (int r = s * RPS; r < (s + 1) * RPS; ++r) {
           const float w = __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(acc[r], scale2, neg_m2), cap2));
-          // (an unused row, which repeats the cluster's last key, adds 0: selects, no branch per register)
-          const bool used = RANK == 1 || pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end;
-          const float u = used ? W - w : 0.f;
+          const float u = W - w;
+          float e;
           if (VALUE_AWARE) {
-            const float d = used ? dl[r] : 0.f, n = used ? nn[r] : 0.f;
-            E = __builtin_fmaf(u, __builtin_fmaf(w, d, u * nvb), E);
-            E = __builtin_fmaf(w * w, n, E);
+            e = __builtin_fmaf(u, __builtin_fmaf(w, dl[r], u * nvb), E);
+            e = __builtin_fmaf(w * w, nn[r], e);
           } else {
-            E = __builtin_fmaf(u, u, E);
+            e = __builtin_fmaf(u, u, E);
           }
+          // (an unused row, which repeats the cluster's last key, does not count: a select of the sum, no
+          // branch per register, and no product of 0 with a value that has overflowed)
+          E = RANK == 1 || pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end ? e : E;
         }
       }
     }

@@ -80,3 +80,22 @@ def test_many_heads_give_the_scores_of_one_head():
                 torch.cuda.synchronize()
                 for key in ("scores", "mask_bits", "row_ptr", "routed_cost") + (("row_budget",) if p else ()):
                     assert torch.equal(r[key][:, h: h + 1], one[key]), key
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_errors_beyond_fp32_are_infinite(dtype, d):
+    """Values whose squared norm leaves fp32: the scores are +inf for every number of keys in a cluster's
+    last 32-key block, never NaN."""
+    sizes, Cq, H = np.array([1, 20, 32, 33, 63, 64, 95, 0, 130]), 40, 1
+    Ck, n = len(sizes), int(sizes.sum())
+    g = torch.Generator().manual_seed(d)
+    q, kb = torch.randn(1, H, Cq, d, generator=g), torch.randn(1, H, Ck, d, generator=g)
+    lab = torch.from_numpy(np.repeat(np.arange(Ck), sizes))
+    vb = torch.full((1, H, Ck, d), 2.0 ** 65)
+    K, V = (kb[:, :, lab] + 0.3 * torch.randn(1, H, n, d, generator=g)).to(dtype), vb[:, :, lab].to(dtype)
+    off = lambda s: torch.from_numpy(np.concatenate([[0], np.cumsum(s), [np.sum(s)]]).astype(np.int32))[None, None].to(dev())
+    r = sv.probe_route(*(t.to(dev()).contiguous() for t in (q, kb, vb, K, V)), off(np.full(Cq, 3)), off(sizes), n, d ** -0.5)
+    torch.cuda.synchronize()
+    got = to_np(r["scores"][0, 0])
+    assert np.isposinf(got[:, sizes > 0]).all() and not got[:, sizes == 0].any()
