@@ -347,21 +347,44 @@ extern "C" size_t svgear_permute_workspace(int B, int H, int64_t N, int C) {
 namespace svgear {
 namespace {
 
-// dst[k][bh][p][:] = src[k][b,h,perm[p],:] for every tensor k
+// dst[k][bh][p][:] = src[k][b,h,perm[p],:] for every tensor k, as if one were moved after the other
 int gather_tensors(const int32_t* perm, int BH, int H, int64_t N, int n_tensors, const void* const* src,
                    const int64_t (*sstride)[3], void* const* dst, svgear_dtype dt, int d, hipStream_t s) {
   const int row_units = (int)(d * esize(dt) / 16);
   const int upe = (int)(16 / esize(dt));  // elements per 16-byte unit
-  if (n_tensors == 0) return SVGEAR_OK;
   GatherArgs g{};
   for (int k = 0; k < n_tensors; ++k) {
     g.src[k] = static_cast<const uint4*>(src[k]);
     g.dst[k] = static_cast<uint4*>(dst[k]);
     g.st[k] = Strides{sstride[k][0] / upe, sstride[k][1] / upe, sstride[k][2] / upe};
   }
-  gather_rows_kernel<<<dim3((unsigned)ceil_div(N * row_units, kThreads), BH, n_tensors), kThreads, 0, s>>>(
-      g, H, perm, N, row_units);
-  SVGEAR_LAUNCH_CHECK();
+  // One launch moves them all (two tensors of 600 rows a head 33 -> 25 us with the sort), unless the
+  // destination of one meets the rows of another: a caller may send V's rows to where K's were.
+  struct Span { uintptr_t lo, hi; };
+  Span from[4], to[4];
+  for (int k = 0; k < n_tensors; ++k) {
+    from[k].lo = reinterpret_cast<uintptr_t>(src[k]);
+    from[k].hi = from[k].lo + 16 * (uintptr_t)((BH / H - 1) * g.st[k].b + (H - 1) * g.st[k].h + (N - 1) * g.st[k].n + row_units);
+    to[k].lo = reinterpret_cast<uintptr_t>(dst[k]);
+    to[k].hi = to[k].lo + 16 * (uintptr_t)BH * N * row_units;
+  }
+  auto meet = [](const Span& x, const Span& y) { return x.lo < y.hi && y.lo < x.hi; };
+  bool apart = true;
+  for (int j = 0; j < n_tensors; ++j)
+    for (int k = 0; k < n_tensors; ++k)
+      if (j != k && (meet(to[j], from[k]) || meet(to[j], to[k]))) apart = false;
+  const int step = apart ? n_tensors : 1;
+  for (int k = 0; k < n_tensors; k += step) {
+    GatherArgs part{};
+    for (int i = 0; i < step; ++i) {
+      part.src[i] = g.src[k + i];
+      part.dst[i] = g.dst[k + i];
+      part.st[i] = g.st[k + i];
+    }
+    gather_rows_kernel<<<dim3((unsigned)ceil_div(N * row_units, kThreads), BH, step), kThreads, 0, s>>>(part, H, perm, N,
+                                                                                                        row_units);
+    SVGEAR_LAUNCH_CHECK();
+  }
   return SVGEAR_OK;
 }
 

@@ -32,3 +32,26 @@ def test_sort_is_the_stable_argsort(N, C):
             assert np.array_equal(to_np(perm[0, h]), ref)
             assert np.array_equal(to_np(off[0, h]), np.concatenate([[0], np.cumsum(np.bincount(full, minlength=C + 1))]))
             assert torch.equal(xp[0, h], x[0, h][torch.from_numpy(ref).to(dev())])
+
+
+@pytest.mark.parametrize("N", [3000, 30000])
+def test_tensors_move_as_if_one_after_the_other(N):
+    """A destination may be where another tensor's rows lie: a chain of three moves through one spare buffer,
+    and a source that an earlier move has written."""
+    C, d = 50, 128
+    lab = torch.randint(0, C, (1, 1, N), generator=torch.Generator().manual_seed(N), dtype=torch.int32).to(dev())
+    order = torch.argsort(lab[0, 0].long(), stable=True)
+    fresh = lambda: [torch.randn(1, 1, N, d, device=dev()).to(torch.bfloat16) for _ in range(3)]
+    out = lambda tensors: (torch.empty(1, 1, N, dtype=torch.int32, device=dev()),
+                           torch.empty(1, 1, C + 2, dtype=torch.int32, device=dev()), tensors)
+    a, b, c = fresh()
+    spare, want = torch.empty_like(a), [x[:, :, order].clone() for x in (a, b, c)]
+    sv.permute(lab, C, [a, b, c], out=out([spare, a, b]))
+    torch.cuda.synchronize()
+    for got, ref in zip((spare, a, b), want):
+        assert torch.equal(got, ref)
+    a, b, c = fresh()
+    want = [a[:, :, order].clone(), a[:, :, order][:, :, order].clone()]
+    sv.permute(lab, C, [a, b], out=out([b, c]))
+    torch.cuda.synchronize()
+    assert torch.equal(b, want[0]) and torch.equal(c, want[1])
