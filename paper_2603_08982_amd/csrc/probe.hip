@@ -192,12 +192,30 @@ sbar_mfma_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
   }
 }
 
+// The same operands from half the fetches: the lane halves take alternate 16-byte pieces of the row and
+// exchange them (v_permlane32_swap: the high lanes of one register for the low lanes of another).
+template <int D>
+__device__ __forceinline__ void row_operands_swapped(const float* row, int h, float (&x)[D / 2]) {
+  auto swap = [](float a, float b, float& lo, float& hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    lo = __uint_as_float(r[0]);  // a of the low lanes, b of the low lanes
+    hi = __uint_as_float(r[1]);  // a of the high lanes, b of the high lanes
+  };
+#pragma unroll
+  for (int u = 0; u < D / 8; ++u) {
+    const float4 v = *reinterpret_cast<const float4*>(row + 8 * u + 4 * h);
+    swap(v.x, v.y, x[4 * u], x[4 * u + 2]);
+    swap(v.z, v.w, x[4 * u + 1], x[4 * u + 3]);
+  }
+}
+
 // fp32 inputs: block errors with the logits qbar_a . k_j on fp32 matrix cores (bound: those, 157 TFLOP/s
 // nominal). One workgroup per (head, key cluster, group of kF32Cents query centroids); its four waves
 // take the cluster's 32-key blocks in turn. A wave keeps the keys of its block as A operands of
-// v_mfma_f32_32x32x2_f32 (a lane half holds half of row lane % 32, in the contraction order the
-// centroids are read in), works out |delta_j|^2 and vbar . delta_j of those keys once, and passes the
+// v_mfma_f32_32x32x2_f32, works out |delta_j|^2 and vbar . delta_j of those keys once, and passes the
 // centroids by, 32 at a time; the error of a centroid accumulates in the lanes that hold its keys.
+// Every logit is the fma chain over the dims in order, as the centroid logits are: where all keys of a
+// cluster equal its centroid (a cluster of one key) W - w is 0 and so is the score, exactly.
 // The kernel before kept one query centroid per lane and did its dot products on the vector ALU:
 // 32 centroids x 64 clusters of one head of 4,096 keys, d = 64: 112 -> 12 us.
 constexpr int kF32Cents = 128;
@@ -245,12 +263,7 @@ block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__
   for (int j0 = start + 32 * wave; j0 < end; j0 += 128) {
     const int j = min(j0 + li, end - 1);  // (rows past the cluster's end are not counted below)
     float kf[QS];
-    const float4* kr = reinterpret_cast<const float4*>(kh + (int64_t)j * D + lh * QS);
-#pragma unroll
-    for (int t = 0; t < QS / 4; ++t) {
-      const float4 v = kr[t];
-      kf[4 * t] = v.x; kf[4 * t + 1] = v.y; kf[4 * t + 2] = v.z; kf[4 * t + 3] = v.w;
-    }
+    row_operands_swapped<D>(kh + (int64_t)j * D, lh, kf);
     float nd = 0.f, dd = 0.f;
     if (VALUE_AWARE) {
       const float4* vr = reinterpret_cast<const float4*>(vh + (int64_t)j * D + lh * QS);
@@ -277,23 +290,17 @@ block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       if (i >= nb) break;
-      const float4* qr = reinterpret_cast<const float4*>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D +
-                                                         lh * QS);
-      f32x16 s0, s1;
+      float q[QS];
+      row_operands_swapped<D>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D, lh, q);
+      f32x16 acc;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s0[r] = s1[r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-      for (int t = 0; t < QS / 4; ++t) {
-        const float4 q = qr[t];
-        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t], q.x, s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t + 1], q.y, s1, 0, 0, 0);
-        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t + 2], q.z, s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[4 * t + 3], q.w, s1, 0, 0, 0);
-      }
+      for (int s = 0; s < QS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s], q[s], acc, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if (j0 + 8 * (r >> 2) + 4 * lh + (r & 3) >= end) continue;
-        const float w = __expf(fminf((s0[r] + s1[r]) * scale - m[i], kMaxExponent));
+        const float w = __expf(fminf(acc[r] * scale - m[i], kMaxExponent));
         const float g = W[i] - w;
         if (VALUE_AWARE) {
           E[i] = __builtin_fmaf(g * g, nvb, E[i]);

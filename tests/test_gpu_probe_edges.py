@@ -99,3 +99,20 @@ def test_errors_beyond_fp32_are_infinite(dtype, d):
     torch.cuda.synchronize()
     got = to_np(r["scores"][0, 0])
     assert np.isposinf(got[:, sizes > 0]).all() and not got[:, sizes == 0].any()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Cq", [(1, 40), (9, 1000)])  # centroid logits on the vector ALU and on the matrix cores
+@pytest.mark.parametrize("plain", [False, True])
+def test_fp32_clusters_of_equal_keys_have_no_error(d, H, Cq, plain):
+    """The logit of a key that equals its cluster's centroid is the centroid's, bit for bit: the score is 0."""
+    sizes = np.array([1, 1, 4, 1, 2, 32, 1, 64])
+    Ck, n = len(sizes), int(sizes.sum())
+    g = torch.Generator().manual_seed(d)
+    q, kb, vb = (torch.randn(1, H, c, d, generator=g).to(dev()) for c in (Cq, Ck, Ck))
+    lab = torch.from_numpy(np.repeat(np.arange(Ck), sizes)).to(dev())
+    off = lambda s: torch.from_numpy(np.concatenate([[0], np.cumsum(s), [np.sum(s)]]).astype(np.int32)).expand(1, H, -1).contiguous().to(dev())
+    r = sv.probe_route(q, kb, vb, kb[:, :, lab].contiguous(), vb[:, :, lab].contiguous(), off(np.ones(Cq)), off(sizes), n,
+                       d ** -0.5, flags=sv.PROBE_PLAIN if plain else 0)
+    torch.cuda.synchronize()
+    assert not r["scores"].any()
