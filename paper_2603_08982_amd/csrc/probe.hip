@@ -211,7 +211,11 @@ __device__ __forceinline__ void row_operands_swapped(const float* row, int h, fl
 
 // fp32 inputs: block errors with the logits qbar_a . k_j on fp32 matrix cores (bound: those, 157 TFLOP/s
 // nominal). One workgroup per (head, key cluster, group of kF32Cents query centroids); its four waves
-// take the cluster's 32-key blocks in turn. A wave keeps the keys of its block as A operands of
+// take the cluster's 32-key blocks in turn (CW = 4). Clusters of about one block leave three of them idle:
+// up to 40 keys a cluster each wave takes a cluster of its own (CW = 1), provided that gives every CU a
+// workgroup. us a call with four waves a cluster, with one: 40 heads x 9,000 keys, 400 clusters 518, 338;
+// 8 x 6,000, 200 clusters 172, 171; 40 x 4,000, 60 clusters (67 keys) 150, 184; 1 x 4,096, 400 clusters, too
+// few for the chip, 72, 75. A wave keeps the keys of its block as A operands of
 // v_mfma_f32_32x32x2_f32, works out |delta_j|^2 and vbar . delta_j of those keys once, and passes the
 // centroids by, 32 at a time; the error of a centroid accumulates in the lanes that hold its keys.
 // Every logit is the fma chain over the dims in order, as the centroid logits are: where all keys of a
@@ -220,7 +224,7 @@ __device__ __forceinline__ void row_operands_swapped(const float* row, int h, fl
 // 32 centroids x 64 clusters of one head of 4,096 keys, d = 64: 112 -> 12 us.
 constexpr int kF32Cents = 128;
 
-template <int D, bool VALUE_AWARE>
+template <int D, bool VALUE_AWARE, int CW>
 __global__ void __launch_bounds__(256)
 block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__ vbar, const float* __restrict__ kp,
                        const float* __restrict__ vp, const int32_t* __restrict__ k_offsets,
@@ -228,31 +232,29 @@ block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__
                        float scale, float* __restrict__ scores) {
   constexpr int QS = D / 2;
   constexpr int NB = kF32Cents / 32;
+  constexpr int CLUSTERS = 4 / CW;  // of the workgroup
   __shared__ float part[4][kF32Cents];
-  __shared__ __attribute__((aligned(16))) float s_vb[D];
-  const int b = blockIdx.x, bh = blockIdx.y, a0 = blockIdx.z * kF32Cents;
+  __shared__ __attribute__((aligned(16))) float s_vb[CLUSTERS][D];
+  const int bh = blockIdx.y, a0 = blockIdx.z * kF32Cents;
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int in_wg = wave / CW, share = wave % CW, b = blockIdx.x * CLUSTERS + in_wg;
   const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
-  const int start = off[b], end = off[b + 1];
+  const int start = b < Ck ? off[b] : 0, end = b < Ck ? off[b + 1] : 0;
   const int n_cent = min(kF32Cents, Cq - a0), nb = (n_cent + 31) / 32;
   float* out = scores + ((int64_t)bh * Cq + a0) * Ck + b;
-  if (end <= start) {  // empty key cluster: score 0, never routed nor compensated
-    if (tid < n_cent) out[(int64_t)tid * Ck] = 0.f;
-    return;
-  }
   const float* kh = kp + (int64_t)bh * Nk * D;
   const float* vh = vp + (int64_t)bh * Nk * D;
-  if (VALUE_AWARE && tid < D) s_vb[tid] = vbar[((int64_t)bh * Ck + b) * D + tid];
+  if (VALUE_AWARE && b < Ck && share == 0)
+    for (int t = lane; t < D; t += 64) s_vb[in_wg][t] = vbar[((int64_t)bh * Ck + b) * D + t];
   __syncthreads();
-  const float* vb = s_vb + lh * QS;
+  const float* vb = s_vb[in_wg] + lh * QS;
   float E[NB], W[NB], m[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int a = a0 + 32 * i + li;
-    E[i] = 0.f;
     m[i] = a < Cq ? mrow[(int64_t)bh * Cq + a] : 0.f;
-    W[i] = a < Cq ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + b] - m[i], kMaxExponent)) : 0.f;
+    W[i] = a < Cq && end > start ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + b] - m[i], kMaxExponent)) : 0.f;
   }
   float nvb = 0.f;
   if (VALUE_AWARE) {  // |vbar_b|^2
@@ -260,66 +262,82 @@ block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__
     for (int t = 0; t < QS; ++t) nvb = __builtin_fmaf(vb[t], vb[t], nvb);
     nvb += __shfl_xor(nvb, 32);
   }
-  for (int j0 = start + 32 * wave; j0 < end; j0 += 128) {
-    const int j = min(j0 + li, end - 1);  // (rows past the cluster's end are not counted below)
-    float kf[QS];
-    row_operands_swapped<D>(kh + (int64_t)j * D, lh, kf);
-    float nd = 0.f, dd = 0.f;
-    if (VALUE_AWARE) {
-      const float4* vr = reinterpret_cast<const float4*>(vh + (int64_t)j * D + lh * QS);
+  // Blocks k, k + 4, ... of a cluster make the k-th of four partial sums whoever takes them, so that the
+  // scores do not depend on the form.
+  float both[2][NB] = {};
+  for (int quarter = share; quarter < 4 && start + 32 * quarter < end; quarter += CW) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) E[i] = 0.f;
+    for (int j0 = start + 32 * quarter; j0 < end; j0 += 128) {
+      const int j = min(j0 + li, end - 1);  // (rows past the cluster's end are not counted below)
+      float kf[QS];
+      row_operands_swapped<D>(kh + (int64_t)j * D, lh, kf);
+      float nd = 0.f, dd = 0.f;
+      if (VALUE_AWARE) {
+        const float4* vr = reinterpret_cast<const float4*>(vh + (int64_t)j * D + lh * QS);
 #pragma unroll 8
-      for (int t = 0; t < QS / 4; ++t) {
-        const float4 v = vr[t], w = reinterpret_cast<const float4*>(vb)[t];
-        const float d0 = v.x - w.x, d1 = v.y - w.y, d2 = v.z - w.z, d3 = v.w - w.w;
-        nd = __builtin_fmaf(d0, d0, nd); dd = __builtin_fmaf(d0, w.x, dd);
-        nd = __builtin_fmaf(d1, d1, nd); dd = __builtin_fmaf(d1, w.y, dd);
-        nd = __builtin_fmaf(d2, d2, nd); dd = __builtin_fmaf(d2, w.z, dd);
-        nd = __builtin_fmaf(d3, d3, nd); dd = __builtin_fmaf(d3, w.w, dd);
+        for (int t = 0; t < QS / 4; ++t) {
+          const float4 v = vr[t], w = reinterpret_cast<const float4*>(vb)[t];
+          const float d0 = v.x - w.x, d1 = v.y - w.y, d2 = v.z - w.z, d3 = v.w - w.w;
+          nd = __builtin_fmaf(d0, d0, nd); dd = __builtin_fmaf(d0, w.x, dd);
+          nd = __builtin_fmaf(d1, d1, nd); dd = __builtin_fmaf(d1, w.y, dd);
+          nd = __builtin_fmaf(d2, d2, nd); dd = __builtin_fmaf(d2, w.z, dd);
+          nd = __builtin_fmaf(d3, d3, nd); dd = __builtin_fmaf(d3, w.w, dd);
+        }
+        nd += __shfl_xor(nd, 32);
+        dd += __shfl_xor(dd, 32);
       }
-      nd += __shfl_xor(nd, 32);
-      dd += __shfl_xor(dd, 32);
-    }
-    // register r of a score tile is key j0 + 8 (r/4) + 4 lh + r%4
-    float nn[16], dl[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int key = 8 * (r >> 2) + 4 * lh + (r & 3);
-      nn[r] = __shfl(nd, key);
-      dl[r] = __shfl(dd, key);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (i >= nb) break;
-      float q[QS];
-      row_operands_swapped<D>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D, lh, q);
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-      for (int s = 0; s < QS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s], q[s], acc, 0, 0, 0);
+      // register r of a score tile is key j0 + 8 (r/4) + 4 lh + r%4
+      float nn[16], dl[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        if (j0 + 8 * (r >> 2) + 4 * lh + (r & 3) >= end) continue;
-        const float w = __expf(fminf(acc[r] * scale - m[i], kMaxExponent));
-        const float g = W[i] - w;
-        if (VALUE_AWARE) {
-          E[i] = __builtin_fmaf(g * g, nvb, E[i]);
-          E[i] = __builtin_fmaf(-2.0f * g * w, dl[r], E[i]);
-          E[i] = __builtin_fmaf(w * w, nn[r], E[i]);
-        } else {
-          E[i] = __builtin_fmaf(g, g, E[i]);
+        const int key = 8 * (r >> 2) + 4 * lh + (r & 3);
+        nn[r] = __shfl(nd, key);
+        dl[r] = __shfl(dd, key);
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (i >= nb) break;
+        float q[QS];
+        row_operands_swapped<D>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D, lh, q);
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int s = 0; s < QS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s], q[s], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          if (j0 + 8 * (r >> 2) + 4 * lh + (r & 3) >= end) continue;
+          const float w = __expf(fminf(acc[r] * scale - m[i], kMaxExponent));
+          const float g = W[i] - w;
+          if (VALUE_AWARE) {
+            E[i] = __builtin_fmaf(g * g, nvb, E[i]);
+            E[i] = __builtin_fmaf(-2.0f * g * w, dl[r], E[i]);
+            E[i] = __builtin_fmaf(w * w, nn[r], E[i]);
+          } else {
+            E[i] = __builtin_fmaf(g, g, E[i]);
+          }
         }
       }
     }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const float e = E[i] + __shfl_xor(E[i], 32);
+      both[0][i] += quarter < 2 ? e : 0.f;
+      both[1][i] += quarter < 2 ? 0.f : e;
+    }
   }
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const float e = E[i] + __shfl_xor(E[i], 32);
-    if (lh == 0) part[wave][32 * i + li] = e;
-  }
+  for (int i = 0; i < NB; ++i)
+    if (lh == 0) part[wave][32 * i + li] = both[0][i] + both[1][i];
   __syncthreads();
-  if (tid < n_cent)
-    out[(int64_t)tid * Ck] = ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])) / (float)(end - start);
+  if (b >= Ck) return;
+  const float n = end > start ? (float)(end - start) : INFINITY;  // empty: score 0, never routed nor compensated
+  for (int t = share * 64 + lane; t < n_cent; t += 64 * CW) {
+    float e = part[in_wg * CW][t];
+    if constexpr (CW == 4) e = (e + part[1][t]) + (part[2][t] + part[3][t]);
+    out[(int64_t)t * Ck] = e / n;
+  }
 }
 
 // ---- bf16 inputs: the probe on the matrix cores -----------------------------------------
@@ -676,14 +694,18 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
     SVGEAR_LAUNCH_CHECK();
     return SVGEAR_OK;
   }
-  const dim3 grid(Ck, BH, (unsigned)ceil_div(Cq, kF32Cents));
-#define SVGEAR_PB(D, VA)                                                                                        \
-  block_error_f32_kernel<D, VA><<<grid, 256, 0, s>>>(qbar, vbar, static_cast<const float*>(kp),                 \
-                                                     static_cast<const float*>(vp), k_offsets, sbar, mrow, Nk, Cq, Ck, \
-                                                     scale, scores)
-  if (d == 64) { if (value_aware) SVGEAR_PB(64, true); else SVGEAR_PB(64, false); }
-  else { if (value_aware) SVGEAR_PB(128, true); else SVGEAR_PB(128, false); }
-#undef SVGEAR_PB
+  const unsigned groups = (unsigned)ceil_div(Cq, kF32Cents);
+  const bool wave_each = Nk <= (int64_t)40 * Ck && (int64_t)BH * Ck * groups >= 1024;
+  const dim3 grid((unsigned)(wave_each ? ceil_div(Ck, 4) : Ck), BH, groups);
+  using Kernel = decltype(&block_error_f32_kernel<64, true, 4>);
+  static const Kernel kernels[2][2][2] = {
+      {{block_error_f32_kernel<64, false, 4>, block_error_f32_kernel<64, false, 1>},
+       {block_error_f32_kernel<64, true, 4>, block_error_f32_kernel<64, true, 1>}},
+      {{block_error_f32_kernel<128, false, 4>, block_error_f32_kernel<128, false, 1>},
+       {block_error_f32_kernel<128, true, 4>, block_error_f32_kernel<128, true, 1>}}};
+  kernels[d == 128][value_aware][wave_each]<<<grid, 256, 0, s>>>(qbar, vbar, static_cast<const float*>(kp),
+                                                                 static_cast<const float*>(vp), k_offsets, sbar, mrow,
+                                                                 Nk, Cq, Ck, scale, scores);
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
 }

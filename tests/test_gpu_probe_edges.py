@@ -116,3 +116,26 @@ def test_fp32_clusters_of_equal_keys_have_no_error(d, H, Cq, plain):
                        d ** -0.5, flags=sv.PROBE_PLAIN if plain else 0)
     torch.cuda.synchronize()
     assert not r["scores"].any()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Ck,Cq", [(255, 20), (257, 33), (259, 150)])  # a workgroup per cluster; four clusters in one
+@pytest.mark.parametrize("plain", [False, True])
+def test_fp32_scores_of_many_small_clusters(d, Ck, Cq, plain):
+    rng = np.random.default_rng(Ck)
+    H, sizes = 4, rng.integers(0, 70, Ck)
+    n = int(sizes.sum())
+    assert n <= 40 * Ck
+    g = torch.Generator().manual_seed(d)
+    q, kb, vb = (torch.randn(1, H, c, d, generator=g) for c in (Cq, Ck, Ck))
+    lab = torch.from_numpy(np.repeat(np.arange(Ck), sizes))
+    K, V = (t[:, :, lab] + 0.3 * torch.randn(1, H, n, d, generator=g) for t in (kb, vb))
+    off = lambda s: torch.from_numpy(np.concatenate([[0], np.cumsum(s), [np.sum(s)]]).astype(np.int32)).expand(1, H, -1).contiguous().to(dev())
+    r = sv.probe_route(*(t.to(dev()).contiguous() for t in (q, kb, vb, K, V)), off(np.ones(Cq)), off(sizes), n, d ** -0.5,
+                       flags=sv.PROBE_PLAIN if plain else 0)
+    torch.cuda.synchronize()
+    for h in (0, H - 1):
+        ref = _definition(*(t[0, h].double().numpy() for t in (q, kb, vb, K, V)), sizes, d ** -0.5, plain)
+        got = to_np(r["scores"][0, h]).astype(np.float64)
+        assert not got[:, sizes == 0].any()
+        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
