@@ -420,11 +420,14 @@ value_stats_kernel(const float* __restrict__ vbar, const bf16_t* __restrict__ vp
 // instead of branching per register (40 heads, 300 x 1,000 centroids: 1.58 -> 1.53 ms; 5 heads,
 // 200 x 500: 129 -> 118 us). What is left is the vector ALU, some 160 to 250 instructions a block, at
 // the two waves that 96 registers of centroid fragments leave room for (three waves spill: 1.85 ms).
+// d = 64 has half the MFMAs and fragments and is bound by the vector ALU and latencies: three waves a SIMD,
+// for which the statistics are read group by group (240 heads x 2,000 keys, 60 clusters, 30 centroids: the
+// whole call 127 us with two waves, 103 with three).
 constexpr int kProbeClusters = 4;  // key clusters per workgroup
 constexpr int kProbeStages = 4;    // LDS ring buffers
 
 template <int D, bool VALUE_AWARE>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, D == 64 ? 3 : 2)
 block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__ vbar, const bf16_t* __restrict__ kp,
                         const int32_t* __restrict__ k_offsets, const float* __restrict__ sbar,
                         const float* __restrict__ mrow, const float* __restrict__ nd, const float* __restrict__ dd,
@@ -555,15 +558,16 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       rd(0);
       rd(1);
     }
-    if constexpr (RANK != 0 && VALUE_AWARE) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
+    auto rd_stats = [&](int g) {  // of the keys that registers 4g .. 4g + 3 hold
+      if constexpr (RANK != 0 && VALUE_AWARE) {
         const float4 n4 = *reinterpret_cast<const float4*>(st + 8 * g + 4 * lh);
         const float4 d4 = *reinterpret_cast<const float4*>(st + 32 + 8 * g + 4 * lh);
         nn[4 * g] = n4.x; nn[4 * g + 1] = n4.y; nn[4 * g + 2] = n4.z; nn[4 * g + 3] = n4.w;
         dl[4 * g] = d4.x; dl[4 * g + 1] = d4.y; dl[4 * g + 2] = d4.z; dl[4 * g + 3] = d4.w;
       }
-    }
+    };
+#pragma unroll
+    for (int g = 0; g < (D == 64 ? 1 : 4); ++g) rd_stats(g);
 #pragma unroll
     for (int s = 0; s < KSN; ++s) {
       __builtin_amdgcn_sched_barrier(0);
@@ -573,6 +577,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
         for (int pc3 = 0; pc3 < 3; ++pc3)
           acc_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[s], bq[pc3][s], acc_new, 0, 0, 0);
       }
+      if (D == 64 && s + 1 < KSN) rd_stats(s + 1);
       if constexpr (RANK != 0) {
         // register r is key j0 + 8(r/4) + 4lh + r%4, query centroid a. Per key, with u = W - w:
         //   |W vbar - w v_j|^2 = u (u |vbar|^2 - 2 w vbar.delta_j) + w^2 |delta_j|^2
