@@ -25,7 +25,7 @@ struct AttnArgs {
   const int32_t* tile_row0;
   const int32_t* n_tiles;
   // work lists of the bf16 kernels (see plan_bf16): tiles sorted longest first and
-  // dealt to 8 lists, one per XCD; sched_x = [8] first slot, [8] tile count, [8] next counter
+  // dealt to 8 lists, one per XCD; sched_x = [8] first slot, [8] tile count, then the next counters (sched_counter)
   const int32_t* sched_bh;
   const int32_t* sched_a;
   const int32_t* sched_row0;

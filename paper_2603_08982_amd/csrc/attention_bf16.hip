@@ -98,6 +98,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // aligned, the compensated ones, filled up to a whole tile.
 __host__ __device__ static inline int list_entries(int Ck) { return (Ck + 72) & ~3; }
 
+// The list counters lie in cache lines of their own: every workgroup adds to one, and additions to one
+// line from all XCDs follow each other at some 57 ns.
+__host__ __device__ static constexpr int sched_counter(int list) { return 64 * (1 + list); }
+constexpr int kSchedInts = 64 * 9;
+
 static inline size_t lds_bytes(int d, int Ck, int stages) {
   const size_t kv = (size_t)stages * 2 * BN * d * 2;  // K and V, `stages` buffers each
   return kv + (size_t)(stages + 3) * BN * 4 + 2 * (size_t)list_entries(Ck) * 4 + 16;
@@ -149,8 +154,8 @@ attn_bf16_kernel(AttnArgs p) {
     int found = -1;
     for (int xk = 0; xk < 8 && found < 0; ++xk) {
       const int xl = (my_xcd + xk) & 7;
-      if (p.sched_x[16 + xl] >= p.sched_x[8 + xl]) continue;  // used up (the counter only grows)
-      const int slot = atomicAdd(p.sched_x + 16 + xl, 1);
+      if (p.sched_x[sched_counter(xl)] >= p.sched_x[8 + xl]) continue;  // used up (the counter only grows)
+      const int slot = atomicAdd(p.sched_x + sched_counter(xl), 1);
       if (slot < p.sched_x[8 + xl]) found = p.sched_x[xl] + slot;
     }
     *slot_s = found;
@@ -606,8 +611,8 @@ attn_bf16_quad_kernel(AttnArgs p) {
     int found = -1, part = 0;
     for (int xk = 0; xk < 8 && found < 0; ++xk) {
       const int xl = (my_xcd + xk) & 7, slots = p.sched_x[8 + xl] * splits;
-      if (p.sched_x[16 + xl] >= slots) continue;  // used up (the counter only grows)
-      const int slot = atomicAdd(p.sched_x + 16 + xl, 1);
+      if (p.sched_x[sched_counter(xl)] >= slots) continue;  // used up (the counter only grows)
+      const int slot = atomicAdd(p.sched_x + sched_counter(xl), 1);
       if (slot < slots) {
         found = p.sched_x[xl] + slot / splits;
         part = slot % splits;
@@ -1128,7 +1133,7 @@ __device__ __forceinline__ void write_lists(const int32_t* q_offsets, const int3
   if (tid < 8) {
     sched_x[tid] = first[tid];
     sched_x[8 + tid] = total[tid];
-    sched_x[16 + tid] = 0;
+    sched_x[sched_counter(tid)] = 0;
   }
   for (int r = tid; r < M; r += 1024) {
     const int i = by_rank[r], bh = i / R, a = i % R;
@@ -1269,7 +1274,7 @@ size_t plan_bf16_workspace(int64_t BH, int Cq, int64_t Nq, int64_t Nk, int d) {
   const Bf16Form f = bf16_form(BH, Nq, Nk, Cq, d);
   const size_t M = (size_t)BH * (Cq + 1), rows = (size_t)BH * Nq;
   const size_t tiles = (size_t)BH * ((size_t)ceil_div(Nq, f.rows) + Cq + 1);
-  return 4 * align_up(M * 4, 256) + 4 * align_up(tiles * 4, 256) + align_up(24 * 4, 256) +
+  return 4 * align_up(M * 4, 256) + 4 * align_up(tiles * 4, 256) + align_up(kSchedInts * 4, 256) +
          (f.splits > 1 ? align_up(f.splits * rows * d * 4, 256) + align_up(f.splits * rows * sizeof(float2), 256) : 0);
 }
 
@@ -1286,7 +1291,7 @@ int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size
   int32_t* sched_a = w.take<int32_t>(tiles);
   int32_t* sched_row0 = w.take<int32_t>(tiles);
   int32_t* sched_rend = w.take<int32_t>(tiles);
-  int32_t* sched_x = w.take<int32_t>(24);
+  int32_t* sched_x = w.take<int32_t>(kSchedInts);
   a.tile_rows = f.rows;
   a.splits = f.splits;
   if (f.splits > 1) {
