@@ -1244,12 +1244,13 @@ struct Bf16Form {
 //      in two 955, in four 860; 1 x 118,800, 1,079 tiles 2817 -> 2085; d = 64, 2 x 75,600, 1,482 tiles
 //      1506 -> 1229. Not where the keys are few for so many tiles (8 x 20,000, 1,456 tiles 597 -> 613) nor
 //      with more tiles, which even out by themselves (3 x 75,600, 1,923 tiles 2240 -> 2279);
-//  * clusters of 32 to 160 rows, which fill at most five of twelve waves: 12 x 16,200, 81 rows 1047 -> 829;
-//    24 x 10,800, 108 rows 838 -> 725; d = 64, 8 x 32,400, 162 rows 1008 -> 967; smaller clusters are all
-//    start and end either way (40 x 594, 12 rows 140 -> 144), larger ones want the larger tile (5 x
-//    75,600, 252 rows 4018 -> 4507; d = 64, 24 x 32,477, 507 rows 2025 -> 2294);
-//  * at most four 128-row tiles a CU, d = 128: 1 x 75,600, 756 rows 1675 -> 1611; 4 x 18,900 497 -> 491
-//    (d = 64: 12 x 7,000 128 -> 133).
+//  * clusters of at most 160 rows, which fill at most five of twelve waves: 12 x 16,200, 81 rows 1047 -> 829;
+//    24 x 10,800, 108 rows 838 -> 725; 24 x 4,000, 20 rows 492 -> 293; d = 64, 8 x 32,400, 162 rows 1008 ->
+//    967, 24 x 1,200, 6 rows 375 -> 229; larger ones want the larger tile (5 x 75,600, 252 rows 4018 -> 4507;
+//    d = 64, 24 x 32,477, 507 rows 2025 -> 2294);
+//  * at most four 128-row tiles a CU, d = 128: 1 x 75,600, 756 rows 1675 -> 1611; 4 x 18,900 497 -> 491; 3 x
+//    2,000, 1,000 rows 51 -> 42. d = 64 at most 64 of them: 1 x 2,000, 667 rows 31 -> 27, but 12 x 7,000
+//    128 -> 133.
 static Bf16Form bf16_form(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
   const int64_t quads = BH * (ceil_div(Nq, 32 * kQuadWaves) + Cq / 2);  // a cluster's last tile is half full
   const int64_t fill = std::min((512 + quads / 2) / quads, Nk / 1024);
@@ -1257,10 +1258,8 @@ static Bf16Form bf16_form(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
   const int64_t spread =
       quads <= 1536 && Nk >= 16 * quads ? std::min({ceil_div(2048, quads), Nk / 8192, (int64_t)4}) : 1;
   const int64_t n = std::max({fill, fine, spread});
-  const bool small_clusters = Nq >= (int64_t)32 * Cq && Nq <= (int64_t)160 * Cq;
   if (n >= 2) return {32 * kQuadWaves, (int)(n < 8 ? n : 8)};
-  if ((small_clusters && quads > 64) || (d == 128 && quads <= 1024 && quads > 64 && Nq >= (int64_t)32 * Cq))
-    return {32 * kQuadWaves, 1};
+  if (Nq <= (int64_t)160 * Cq || quads <= (d == 128 ? 1024 : 64)) return {32 * kQuadWaves, 1};
   return {32 * kWaves, 1};
 }
 

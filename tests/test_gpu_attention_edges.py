@@ -34,8 +34,10 @@ def _sizes(name, rng):
         return list(rng.integers(1, 70, 150)), [7, 90], 1
     if name == "split_keys":  # a few tiles over keys enough for every number of splits
         return [200, 1, 129], list(rng.integers(1, 250, 80)), 5
-    if name == "full_tiles":  # enough tiles of clusters that want the largest tile
+    if name == "full_tiles":  # clusters of several tiles; d = 64: tiles of 384 rows
         return list(rng.integers(385, 800, 40)), [30, 64, 500], 3
+    if name == "large_tiles":  # 16 heads: tiles of 384 rows at d = 128 too (more than 1,024 of 128), a few dozen a work list
+        return Q_EDGES + list(rng.integers(385, 800, 20)), K_EDGES, 13
     if name == "ranked":  # 256 items over both heads
         return list(rng.integers(1, 200, 127)), [64, 0, 300], 2
     if name == "fine_splits":  # a few hundred tiles over 8,192 keys and more
@@ -60,15 +62,15 @@ def _definition(Q, K, V, kbar, vbar, qs, ks, mask, scale):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters", "split_keys", "full_tiles", "ranked", "fine_splits",
-                                  "spread_splits"])
+@pytest.mark.parametrize("name", ["edges", "few_rows", "many_rows", "tiny_clusters", "split_keys", "full_tiles", "large_tiles",
+                                  "ranked", "fine_splits", "spread_splits"])
 @pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
 def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
     rng = np.random.default_rng(3)
     qs, ks, tail = _sizes(name, rng)
     qs, ks = np.array(list(qs) + [tail]), np.array(list(ks) + [tail])
     Cq, Ck, Nq, Nk = len(qs) - 1, len(ks) - 1, int(qs.sum()), int(ks.sum())
-    H, scale = 2, float(d) ** -0.5
+    H, scale = 16 if name == "large_tiles" else 2, float(d) ** -0.5
     g = torch.Generator().manual_seed(11)
     Q, K, V = (torch.randn(1, H, n, d, generator=g).to(dtype) for n in (Nq, Nk, Nk))
     kbar, vbar = (torch.randn(1, H, Ck, d, generator=g).to(torch.bfloat16).float() for _ in range(2))
@@ -102,27 +104,34 @@ def test_attention_at_the_edges_of_tiles_and_lists(dtype, d, name, density):
         tokens[0, h, perm[0, h]] = Q[0, h]
     O2, lse2 = sv.sparse_attn_comp(tokens.to(dev()), *tables, *offs, *lists, scale, want_lse=True,
                                    q_perm=perm.int().contiguous().to(dev()))
+    two = None
+    if dtype == torch.bfloat16 and d == 128:  # routed keys and centroids by themselves, merged
+        two = sv.sparse_attn_comp(Q.to(dev()), *tables, *offs, *lists, scale, want_lse=True, two_stage=True)
     torch.cuda.synchronize()
-    for h in range(H):
+    for h in sorted({0, H // 2, H - 1}):
         ref, ref_lse = _definition(Q[0, h].double(), K[0, h].double(), V[0, h].double(), kbar[0, h].double(),
                                    vbar[0, h].double(), qs, ks, masks[h], scale)
-        got, got_lse = O[0, h].cpu(), lse[0, h].cpu()
         none = torch.isinf(ref_lse)  # text rows of a head without text keys see nothing
-        assert torch.equal(torch.isinf(got_lse), none) and not got[none].any()
-        err = (got.double() - ref)[~none].norm() / ref[~none].norm()
-        assert err <= TOL[dtype], f"head {h}: rel-L2 {err:.3e}"
-        lse_err = (got_lse.double() - ref_lse)[~none].abs().max()
-        assert lse_err <= _lse_tol(dtype, d), f"head {h}: log-sum-exp {lse_err:.3e}"
+        for out in (O, lse), two:
+            if out is None:
+                continue
+            got, got_lse = out[0][0, h].cpu(), out[1][0, h].cpu()
+            assert torch.equal(torch.isinf(got_lse), none) and not got[none].any()
+            err = (got.double() - ref)[~none].norm() / ref[~none].norm()
+            assert err <= TOL[dtype], f"head {h}: rel-L2 {err:.3e}"
+            lse_err = (got_lse.double() - ref_lse)[~none].abs().max()
+            assert lse_err <= _lse_tol(dtype, d), f"head {h}: log-sum-exp {lse_err:.3e}"
+        got, got_lse = O[0, h].cpu(), lse[0, h].cpu()
         assert torch.equal(O2[0, h].cpu()[perm[0, h]], got) and torch.equal(lse2[0, h].cpu()[perm[0, h]], got_lse)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("rows", [[40, 5], [70] * 40])  # tiles of 384 rows and of 128
-def test_whole_tiles_of_keys_without_weight_come_first(dtype, d, rows):
+@pytest.mark.parametrize("H,rows", [(8, [400] * 40), (2, [70] * 40)])  # tiles of 384 rows and of 128
+def test_whole_tiles_of_keys_without_weight_come_first(dtype, d, H, rows):
     """Keys whose logits are all -inf weigh nothing, also where a row meets them before any other."""
     qs, ks = np.array(rows + [3]), np.array([200, 61, 90, 7, 0])
-    Cq, Ck, Nq, Nk, H = len(qs) - 1, len(ks) - 1, int(qs.sum()), int(ks.sum()), 2
+    Cq, Ck, Nq, Nk = len(qs) - 1, len(ks) - 1, int(qs.sum()), int(ks.sum())
     g = torch.Generator().manual_seed(7)
     Q, K, V = (torch.randn(1, H, n, d, generator=g) for n in (Nq, Nk, Nk))
     Q[..., 0] = Q[..., 0].abs() + 0.5
@@ -138,7 +147,7 @@ def test_whole_tiles_of_keys_without_weight_come_first(dtype, d, rows):
             for x in (qs, ks)]
     O, lse = sv.sparse_attn_comp(*(x.to(dev()) for x in (Q, K, V, kbar, vbar)), *offs, *lists, d ** -0.5, want_lse=True)
     torch.cuda.synchronize()
-    for h in range(H):
+    for h in (0, H - 1):
         ref, ref_lse = _definition(*(x[0, h].double() for x in (Q, K, V, kbar, vbar)), qs, ks, mask, d ** -0.5)
         got, got_lse = O[0, h].cpu().double(), lse[0, h].cpu().double()
         assert (got - ref).norm() <= TOL[dtype] * ref.norm()
