@@ -152,3 +152,31 @@ def test_whole_tiles_of_keys_without_weight_come_first(dtype, d, H, rows):
         got, got_lse = O[0, h].cpu().double(), lse[0, h].cpu().double()
         assert (got - ref).norm() <= TOL[dtype] * ref.norm()
         assert (got_lse - ref_lse).abs().max() <= _lse_tol(dtype, d)
+
+
+@pytest.mark.parametrize("H,rows", [(8, [400] * 40), (2, [70] * 40)])  # tiles of 384 rows and of 128
+def test_the_largest_weight_of_a_row_is_exact(H, rows):
+    """bf16 heads of 64: the weight of a row's largest logit, here of a key in the second tile, is 1 whatever came
+    before it. With equal values everywhere the output is that value to the bit: the other weights, some
+    2^-8 and less, are off by 2^-9 of themselves."""
+    qs, ks, d = np.array(rows + [0]), np.array([100, 41, 0]), 64
+    Cq, Ck, Nq, Nk = len(qs) - 1, len(ks) - 1, int(qs.sum()), int(ks.sum())
+    g = torch.Generator().manual_seed(2)
+    Q, K = torch.zeros(1, H, Nq, d), torch.zeros(1, H, Nk, d)
+    Q[..., 0] = 8.0 * (1.0 + 0.05 * torch.rand(1, H, Nq, generator=g))  # logits of 5.2 to 5.5 for key 90
+    K[..., 0], K[:, :, 0, 0], K[:, :, 90, 0] = -60.0, 0.0, 5.1875
+    V = torch.randn(1, H, 1, d, generator=g).expand(1, H, Nk, d)
+    Q, K, V = (x.to(torch.bfloat16) for x in (Q, K, V))
+    mask = np.outer(qs > 0, ks > 0)
+    row_ptr, col_idx = csr_from_mask(mask)
+    lists = [torch.from_numpy(x)[None, None].expand(1, H, *x.shape).contiguous().to(dev())
+             for x in (mask_to_bits(mask, Cq, Ck).view(np.int32), row_ptr, col_idx)]
+    offs = [torch.from_numpy(np.concatenate([[0], np.cumsum(x)]).astype(np.int32)).expand(1, H, -1).contiguous().to(dev())
+            for x in (qs, ks)]
+    means = torch.zeros(1, H, Ck, d, device=dev())
+    O, lse = sv.sparse_attn_comp(*(x.to(dev()).contiguous() for x in (Q, K, V)), means, means, *offs, *lists, d ** -0.5,
+                                 want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(O.cpu(), V[:, :, :1].expand_as(O))
+    logits = (Q.double()[..., :1] * K.double()[..., 0][:, :, None, :]) * d ** -0.5
+    assert (lse.cpu().double() - torch.logsumexp(logits, -1)).abs().max() <= 2e-5
