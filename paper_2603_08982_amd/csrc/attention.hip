@@ -15,7 +15,7 @@
 // computes the TRANSPOSED score tile S^T = K Q^T, so that every lane holds scores of a
 // single query (lane%32) and row max / row sum need one cross-lane exchange (with lane^32)
 // instead of a butterfly; exp2'd scores are then already in B-operand layout for
-// O^T += V^T P^T. V tiles are transposed on their way into LDS.
+// O^T += V^T P^T. V stays row-major in LDS and is fetched with the LDS transpose read.
 // fp32 kernel: the same decomposition on the fp32 matrix cores (attention_f32.hip).
 #include "attention.h"
 

@@ -103,7 +103,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 __host__ __device__ static inline int list_entries(int Ck) { return (Ck + 72) & ~3; }
 
 // The list counters lie in cache lines of their own: every workgroup adds to one, and additions to one
-// line from all XCDs follow each other at some 57 ns.
+// line from all XCDs follow each other at some 57 ns (24 heads x 1,200 rows, 4,800 tiles of d = 64: 305 -> 180 us).
 __host__ __device__ static constexpr int sched_counter(int list) { return 64 * (1 + list); }
 constexpr int kSchedInts = 64 * 9;
 
@@ -112,71 +112,40 @@ static inline size_t lds_bytes(int d, int Ck, int stages) {
   return kv + (size_t)(stages + 3) * BN * 4 + 2 * (size_t)list_entries(Ck) * 4 + 16;
 }
 
-// NW waves of 32 query rows (three per SIMD); NSTAGE K/V tile buffers. The first CW waves of
-// the workgroup (the oldest wave of every SIMD, which finishes its step first) issue the tile
-// copies, after their compute of the step (just before the tile barrier): measured faster
-// than issuing them behind the score MFMAs or from more waves.
-// WIDE: rows by 64-bit addresses instead of 32-bit byte offsets from the head's first one.
-template <int D, int NW, int NSTAGE, int CW, bool WIDE>
-__global__ void __launch_bounds__(64 * NW, 1)
-attn_bf16_kernel(AttnArgs p) {
-  static_assert(D == 64 || D == 128, "swizzles");
-  constexpr int NT = 64 * NW;
-  constexpr int ROWB = D * 2;                       // bytes per K/V row
-  constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
-  constexpr int RPI = 64 / CPR;                     // rows per copy instruction
-  constexpr int KS = D / 16;
-  constexpr int DB = D / 32;
-  constexpr int TILE_BYTES = BN * ROWB;
-  constexpr int INST_PER_TILE = TILE_BYTES / 1024;  // wave-wide 1 KB copies per tensor tile
-  constexpr int LOADS_PER_TILE = 2 * INST_PER_TILE / CW;  // copy instructions per copying wave per tile
-  constexpr int RS = NSTAGE + 1;                    // row-map ring
-  static_assert(INST_PER_TILE % CW == 0 && CW <= NW, "copies must split evenly over the copying waves");
+// ---- what the two kernels below share
 
-  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
-  unsigned char* Ks = smem;                        // [NSTAGE][64 rows][ROWB], chunk-swizzled
-  unsigned char* Vs = smem + NSTAGE * TILE_BYTES;  // [NSTAGE][64 rows][ROWB], chunk-swizzled
-  int32_t* rowmap = reinterpret_cast<int32_t*>(smem + 2 * NSTAGE * TILE_BYTES);  // [RS][BN]
-  float* rag_bias = reinterpret_cast<float*>(rowmap + RS * BN);  // [BN] bias of the ragged routed tile
-  // two tables: of the routed clusters e < ne the first virtual position and the first row (then the
-  // end position); from comp0 on, of the compensated ones the index and the bias
-  int32_t* ent0 = reinterpret_cast<int32_t*>(rag_bias + BN);
-  int32_t* ent1 = ent0 + list_entries(p.Ck);
-  int32_t* slot_s = ent1 + list_entries(p.Ck);  // claimed tile, number of compensated clusters
-
-  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // Every workgroup claims one tile: the next of the work list of the XCD it runs on (tiles
-  // of one query cluster are neighbours in a list, so the CUs of an XCD work on the same
-  // routed K/V at the same time and share it in their L2), or, once that list is used up, of
-  // the other XCDs' lists. Lists are sorted longest tile first and workgroups start in
-  // order, so the long tiles start early and the short ones fill the end of the launch. The
-  // grid covers the tile-count bound; workgroups that find every list used up exit.
-  if (tid == 0) {
-    const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7;  // XCC_ID
-    int found = -1;
-    for (int xk = 0; xk < 8 && found < 0; ++xk) {
-      const int xl = (my_xcd + xk) & 7;
-      if (p.sched_x[sched_counter(xl)] >= p.sched_x[8 + xl]) continue;  // used up (the counter only grows)
-      const int slot = atomicAdd(p.sched_x + sched_counter(xl), 1);
-      if (slot < p.sched_x[8 + xl]) found = p.sched_x[xl] + slot;
+// Every workgroup claims one tile: the next of the work list of the XCD it runs on (tiles
+// of one query cluster are neighbours in a list, so the CUs of an XCD work on the same
+// routed K/V at the same time and share it in their L2), or, once that list is used up, of
+// the other XCDs' lists. Lists are sorted longest tile first and workgroups start in
+// order, so the long tiles start early and the short ones fill the end of the launch. The
+// grid covers the tile-count bound; workgroups that find every list used up exit.
+// With keys split, a tile is `splits` slots of its list. One thread: slot_s[0] = tile or -1, slot_s[2] = split.
+__device__ __forceinline__ void claim_tile(const AttnArgs& p, int splits, int32_t* slot_s) {
+  const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7;  // XCC_ID
+  int found = -1, part = 0;
+  for (int xk = 0; xk < 8 && found < 0; ++xk) {
+    const int xl = (my_xcd + xk) & 7, slots = p.sched_x[8 + xl] * splits;
+    if (p.sched_x[sched_counter(xl)] >= slots) continue;  // used up (the counter only grows)
+    const int slot = atomicAdd(p.sched_x + sched_counter(xl), 1);
+    if (slot < slots) {
+      found = p.sched_x[xl] + slot / splits;
+      part = slot % splits;
     }
-    *slot_s = found;
   }
-  __syncthreads();
-  const int claimed = __builtin_amdgcn_readfirstlane(*slot_s);
-  if (claimed < 0) return;
-  const int bh = p.sched_bh[claimed], a = p.sched_a[claimed], row0 = p.sched_row0[claimed];
-  const int Cq = p.Cq, Ck = p.Ck, R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
-  const int32_t* ko = p.k_offsets + (int64_t)bh * (Ck + 2);
-  const int row_end = p.sched_rend[claimed];  // the tile's rows are [row0, row_end), all of query cluster a
-  const int32_t* rp = p.row_ptr + (int64_t)bh * (R + 1);
-  const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + rp[a];
-  const int ne = min(rp[a + 1] - rp[a], Cc);
-  const int comp0 = (ne + 1 + 3) & ~3;
+  slot_s[0] = found;
+  slot_s[2] = part;
+}
 
+// The key-cluster tables of a tile of query cluster a, by waves 0 and 1: of the routed clusters e < ne the
+// first virtual position and the first row, then the end position; from comp0 on, of the compensated ones the
+// index and the bias, filled up to a whole tile. slot_s[1] = number of the latter.
+__device__ __forceinline__ void cluster_tables(const AttnArgs& p, int bh, int a, int ne, int comp0, int wave, int lane,
+                                               int32_t* ent0, int32_t* ent1, int32_t* slot_s) {
+  const int Ck = p.Ck, R = p.Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
+  const int32_t* ko = p.k_offsets + (int64_t)bh * (Ck + 2);
   if (wave == 0) {
+    const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + p.row_ptr[(int64_t)bh * (R + 1) + a];
     int carry = 0;
     for (int e0 = 0; e0 < ne; e0 += 64) {
       const int e = e0 + lane;
@@ -200,7 +169,7 @@ attn_bf16_kernel(AttnArgs p) {
   } else if (wave == 1) {
     // skipped, non-empty clusters only: a quarter routed leaves a quarter fewer centroid tiles
     int at = comp0;
-    if (a < Cq) {
+    if (a < p.Cq) {
       const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
       for (int b0 = 0; b0 < Ck; b0 += 64) {
         const int b = b0 + lane;
@@ -219,6 +188,110 @@ attn_bf16_kernel(AttnArgs p) {
     if (lane < BN - 1) ent1[at + lane] = __float_as_int(-INFINITY);  // the rest of the last tile
     if (lane == 0) slot_s[1] = at - comp0;
   }
+}
+
+// Row of K / V, or of the centroid tables, at position `at` of tile t; cur: the thread's segment cursor.
+// Positions past the last key or centroid repeat it (their bias is -inf).
+__device__ __forceinline__ int key_row(const int32_t* ent0, const int32_t* ent1, int comp0, int nt_r, int n_r, int n_c,
+                                       int t, int at, int& cur) {
+  if (t >= nt_r) return ent0[comp0 + min((t - nt_r) * BN + at, n_c - 1)];
+  const int pos = min(t * BN + at, n_r - 1);
+  while (pos >= ent0[cur + 1]) ++cur;
+  return ent1[cur] + (pos - ent0[cur]);
+}
+
+// 16-byte chunk of a tile row r in LDS: chunk ^ swizzle
+template <int D>
+__device__ __forceinline__ int k_swz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+template <int D>
+__device__ __forceinline__ int v_swz(int r) { return D == 128 ? ((r & 3) << 2) : ((r & 2) << 1); }
+
+// Per-lane LDS byte offsets of the first MFMA operands. K row li of a 32-row block, dims 16s + 8lh .. +7:
+// chunk (2s + lh) ^ swizzle
+template <int D>
+__device__ __forceinline__ int k_operand_offset(int li, int lh) { return li * (D * 2) + ((lh ^ k_swz<D>(li)) << 4); }
+// V, transpose read: group = lane/16 -> (dim half, key half); r = lane%16
+template <int D>
+__device__ __forceinline__ int v_operand_offset(int lane) {
+  const int r = lane & 15, g = lane >> 4, ddhalf = g & 1, khalf = g >> 1, row = 4 * khalf + (r >> 2);
+  return row * (D * 2) + (((2 * ddhalf + ((r & 3) >> 1)) ^ v_swz<D>(row)) << 4) + (r & 1) * 8;
+}
+
+template <int D>
+__device__ __forceinline__ void rescale_to(float m_new, float& m, float& l, f32x16 (&oacc)[D / 32]) {
+  const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
+  l *= alpha;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+  m = m_new;
+}
+
+// One query row's output and log-sum-exp: the lane holds dims 32db + 8g + 4lh + 0..3
+template <int D>
+__device__ __forceinline__ void store_row(const AttnArgs& p, int bh, int qrow, int lh, const f32x16 (&oacc)[D / 32],
+                                          float m, float lt) {
+  const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+  int64_t lse_idx;
+  bf16_t* o = static_cast<bf16_t*>(p.op) + out_row_offset(p, bh, qrow, D, lse_idx);
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      uint2 w;
+      w.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
+      w.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
+      *reinterpret_cast<uint2*>(o + 32 * db + 8 * g + 4 * lh) = w;
+    }
+  if (p.lse && lh == 0) p.lse[lse_idx] = (m + log2f(lt)) * kLn2;
+}
+
+// NW waves of 32 query rows (three per SIMD); NSTAGE K/V tile buffers. The first CW waves of
+// the workgroup (the oldest wave of every SIMD, which finishes its step first) issue the tile
+// copies, after their compute of the step (just before the tile barrier): measured faster
+// than issuing them behind the score MFMAs or from more waves.
+// WIDE: rows by 64-bit addresses instead of 32-bit byte offsets from the head's first one.
+template <int D, int NW, int NSTAGE, int CW, bool WIDE>
+__global__ void __launch_bounds__(64 * NW, 1)
+attn_bf16_kernel(AttnArgs p) {
+  static_assert(D == 64 || D == 128, "swizzles");
+  constexpr int ROWB = D * 2;                       // bytes per K/V row
+  constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
+  constexpr int RPI = 64 / CPR;                     // rows per copy instruction
+  constexpr int KS = D / 16;
+  constexpr int DB = D / 32;
+  constexpr int TILE_BYTES = BN * ROWB;
+  constexpr int INST_PER_TILE = TILE_BYTES / 1024;  // wave-wide 1 KB copies per tensor tile
+  constexpr int LOADS_PER_TILE = 2 * INST_PER_TILE / CW;  // copy instructions per copying wave per tile
+  constexpr int RS = NSTAGE + 1;                    // row-map ring
+  static_assert(INST_PER_TILE % CW == 0 && CW <= NW, "copies must split evenly over the copying waves");
+
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+  unsigned char* Ks = smem;                        // [NSTAGE][64 rows][ROWB], chunk-swizzled
+  unsigned char* Vs = smem + NSTAGE * TILE_BYTES;  // [NSTAGE][64 rows][ROWB], chunk-swizzled
+  int32_t* rowmap = reinterpret_cast<int32_t*>(smem + 2 * NSTAGE * TILE_BYTES);  // [RS][BN]
+  float* rag_bias = reinterpret_cast<float*>(rowmap + RS * BN);  // [BN] bias of the ragged routed tile
+  // the two tables of cluster_tables
+  int32_t* ent0 = reinterpret_cast<int32_t*>(rag_bias + BN);
+  int32_t* ent1 = ent0 + list_entries(p.Ck);
+  int32_t* slot_s = ent1 + list_entries(p.Ck);  // claimed tile, number of compensated clusters
+
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  if (tid == 0) claim_tile(p, 1, slot_s);
+  __syncthreads();
+  const int claimed = __builtin_amdgcn_readfirstlane(slot_s[0]);
+  if (claimed < 0) return;
+  const int bh = p.sched_bh[claimed], a = p.sched_a[claimed], row0 = p.sched_row0[claimed];
+  const int Ck = p.Ck;
+  const int row_end = p.sched_rend[claimed];  // the tile's rows are [row0, row_end), all of query cluster a
+  const int32_t* rp = p.row_ptr + (int64_t)bh * (p.Cq + 2);
+  const int ne = min(rp[a + 1] - rp[a], Ck + 1);
+  const int comp0 = (ne + 1 + 3) & ~3;
+
+  cluster_tables(p, bh, a, ne, comp0, wave, lane, ent0, ent1, slot_s);
   __syncthreads();
   // (part 2 leaves the routed keys out, part 1 the centroid tiles: the two-stage form)
   const int n_r = p.part == 2 ? 0 : __builtin_amdgcn_readfirstlane(ent0[ne]);  // wave-uniform
@@ -235,17 +308,7 @@ attn_bf16_kernel(AttnArgs p) {
 
   int cur = 0;  // segment cursor of threads 0..63 (virtual key position -> permuted row)
   auto map_tile = [&](int t) __attribute__((always_inline)) {
-    if (tid < BN) {
-      int phys;
-      if (t < nt_r) {  // positions past the last key repeat it (masked by rag_bias)
-        const int pos = min(t * BN + tid, n_r - 1);
-        while (pos >= ent0[cur + 1]) ++cur;
-        phys = ent1[cur] + (pos - ent0[cur]);
-      } else {
-        phys = ent0[comp0 + min((t - nt_r) * BN + tid, n_c - 1)];
-      }
-      rowmap[(t % RS) * BN + tid] = phys;
-    }
+    if (tid < BN) rowmap[(t % RS) * BN + tid] = key_row(ent0, ent1, comp0, nt_r, n_r, n_c, t, tid, cur);
   };
 
   // one wave-wide copy moves rows RPI*inst .. of a tile; lane -> (row, LDS chunk slot).
@@ -255,11 +318,9 @@ attn_bf16_kernel(AttnArgs p) {
   static_assert((RPI * CW) % 16 == 0, "copy rows of one lane must share their swizzle phase");
   constexpr int CPW = INST_PER_TILE / CW;  // copies per tensor per wave per tile
   const uint32_t lds_k0 = lds_address(Ks), lds_v0 = lds_address(Vs);
-  auto k_swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
-  auto v_swz = [](int row) { return D == 128 ? ((row & 3) << 2) : ((row & 2) << 1); };
   const int cp_rr = RPI * (wave % CW) + lane / CPR;
-  const uint32_t cp_koff = (uint32_t)(((lane % CPR) ^ k_swz(cp_rr)) << 4);
-  const uint32_t cp_voff = (uint32_t)(((lane % CPR) ^ v_swz(cp_rr)) << 4);
+  const uint32_t cp_koff = (uint32_t)(((lane % CPR) ^ k_swz<D>(cp_rr)) << 4);
+  const uint32_t cp_voff = (uint32_t)(((lane % CPR) ^ v_swz<D>(cp_rr)) << 4);
   // permuted rows (of K/V or of the centroid tables) this lane copies for tile t
   auto fetch_rows = [&](int t, int (&rows)[CPW]) __attribute__((always_inline)) {
     const int32_t* rm = rowmap + (t % RS) * BN + cp_rr;
@@ -290,17 +351,10 @@ attn_bf16_kernel(AttnArgs p) {
     }
   };
 
-  // per-lane LDS byte offsets of the MFMA operands
-  // K row li of a 32-row block, dims 16s + 8lh .. +7: chunk (2s + lh) ^ swizzle
   // (the swizzles are XORs of disjoint bit fields, so operand s / block db is the offset of
   // operand 0 with s << 5 / db << 6 XORed in: one register each instead of a table)
-  const int koff0 = li * ROWB + ((lh ^ k_swz(li)) << 4);
+  const int koff0 = k_operand_offset<D>(li, lh), voff0 = v_operand_offset<D>(lane);
   auto koff = [&](int s) { return koff0 ^ (s << 5); };
-  int voff0;  // transpose read: group = lane/16 -> (dim half, key half); r = lane%16
-  {
-    const int r = lane & 15, g = lane >> 4, ddhalf = g & 1, khalf = g >> 1, row = 4 * khalf + (r >> 2);
-    voff0 = row * ROWB + (((2 * ddhalf + ((r & 3) >> 1)) ^ v_swz(row)) << 4) + (r & 1) * 8;
-  }
   auto voff = [&](int db) { return voff0 ^ (db << 6); };
 
   const bool wave_active = (row0 + 32 * wave) < row_end;
@@ -323,15 +377,7 @@ attn_bf16_kernel(AttnArgs p) {
   float m = -INFINITY, l = 0.f;
   const float c = p.scale * kLog2e;
 
-  auto rescale = [&](float m_new) __attribute__((always_inline)) {
-    const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
-    l *= alpha;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-    m = m_new;
-  };
+  auto rescale = [&](float m_new) __attribute__((always_inline)) { rescale_to<D>(m_new, m, l, oacc); };
 
   // ---- S^T = K Q^T of tile t: 64 keys x 32 queries; register r of block kb is key
   // 32kb + 8(r/4) + 4lh + r%4, query li. The scores of tile t+1 are computed at the end of
@@ -549,19 +595,7 @@ attn_bf16_kernel(AttnArgs p) {
     const float lt = l + swap32(l);
     const int qrow = row0 + 32 * wave + li;
     if (qrow < row_end) {
-      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-      int64_t lse_idx;
-      bf16_t* o = static_cast<bf16_t*>(p.op) + out_row_offset(p, bh, qrow, D, lse_idx);
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 w;
-          w.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
-          w.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
-          *reinterpret_cast<uint2*>(o + 32 * db + 8 * g + 4 * lh) = w;
-        }
-      if (p.lse && lh == 0) p.lse[lse_idx] = (m + log2f(lt)) * kLn2;
+      store_row<D>(p, bh, qrow, lh, oacc, m, lt);
     }
   }
 }
@@ -583,7 +617,6 @@ __global__ void __launch_bounds__(64 * kQuadWaves, 2)
 attn_bf16_quad_kernel(AttnArgs p) {
   constexpr int NW = kQuadWaves, NSTAGE = 2, CW = kQuadWaves;
   static_assert(D == 64 || D == 128, "swizzles");
-  constexpr int NT = 64 * NW;
   constexpr int ROWB = D * 2;                       // bytes per K/V row
   constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;                     // rows per copy instruction
@@ -599,8 +632,7 @@ attn_bf16_quad_kernel(AttnArgs p) {
   unsigned char* Vs = smem + NSTAGE * TILE_BYTES;  // [NSTAGE][64 rows][ROWB], chunk-swizzled
   int32_t* rowmap = reinterpret_cast<int32_t*>(smem + 2 * NSTAGE * TILE_BYTES);  // [RS][BN]
   float* rag_bias = reinterpret_cast<float*>(rowmap + RS * BN);  // [BN] bias of the ragged routed tile
-  // two tables: of the routed clusters e < ne the first virtual position and the first row (then the
-  // end position); from comp0 on, of the compensated ones the index and the bias
+  // the two tables of cluster_tables
   int32_t* ent0 = reinterpret_cast<int32_t*>(rag_bias + BN);
   int32_t* ent1 = ent0 + list_entries(p.Ck);
   int32_t* slot_s = ent1 + list_entries(p.Ck);  // claimed tile, number of compensated clusters
@@ -608,79 +640,20 @@ attn_bf16_quad_kernel(AttnArgs p) {
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // (claimed as in the kernel above; `splits` slots per tile)
   const int splits = p.splits;
-  if (tid == 0) {
-    const int my_xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7;  // XCC_ID
-    int found = -1, part = 0;
-    for (int xk = 0; xk < 8 && found < 0; ++xk) {
-      const int xl = (my_xcd + xk) & 7, slots = p.sched_x[8 + xl] * splits;
-      if (p.sched_x[sched_counter(xl)] >= slots) continue;  // used up (the counter only grows)
-      const int slot = atomicAdd(p.sched_x + sched_counter(xl), 1);
-      if (slot < slots) {
-        found = p.sched_x[xl] + slot / splits;
-        part = slot % splits;
-      }
-    }
-    slot_s[0] = found;
-    slot_s[2] = part;
-  }
+  if (tid == 0) claim_tile(p, splits, slot_s);
   __syncthreads();
   const int claimed = __builtin_amdgcn_readfirstlane(slot_s[0]);
   if (claimed < 0) return;
   const int split = __builtin_amdgcn_readfirstlane(slot_s[2]);
   const int bh = p.sched_bh[claimed], a = p.sched_a[claimed], row0 = p.sched_row0[claimed];
-  const int Cq = p.Cq, Ck = p.Ck, R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
-  const int32_t* ko = p.k_offsets + (int64_t)bh * (Ck + 2);
+  const int Ck = p.Ck;
   const int row_end = p.sched_rend[claimed];  // the tile's rows are [row0, row_end), all of query cluster a
-  const int32_t* rp = p.row_ptr + (int64_t)bh * (R + 1);
-  const int32_t* ci = p.col_idx + (int64_t)bh * R * Cc + rp[a];
-  const int ne = min(rp[a + 1] - rp[a], Cc);
+  const int32_t* rp = p.row_ptr + (int64_t)bh * (p.Cq + 2);
+  const int ne = min(rp[a + 1] - rp[a], Ck + 1);
   const int comp0 = (ne + 1 + 3) & ~3;
 
-  if (wave == 0) {
-    int carry = 0;
-    for (int e0 = 0; e0 < ne; e0 += 64) {
-      const int e = e0 + lane;
-      int sz = 0;
-      if (e < ne) {
-        const int b = ci[e];
-        const int ps = ko[b];
-        sz = ko[b + 1] - ps;
-        sz = sz > 0 ? sz : 0;
-        ent1[e] = ps;
-      }
-      int incl = sz;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-      }
-      if (e < ne) ent0[e] = carry + incl - sz;
-      carry += __shfl(incl, 63);
-    }
-    if (lane == 0) ent0[ne] = carry;
-  } else if (wave == 1) {
-    // skipped, non-empty clusters only: a quarter routed leaves a quarter fewer centroid tiles
-    int at = comp0;
-    if (a < Cq) {
-      const uint32_t* mrow = p.mask_bits + ((int64_t)bh * R + a) * W;
-      for (int b0 = 0; b0 < Ck; b0 += 64) {
-        const int b = b0 + lane;
-        const int sz = b < Ck ? ko[b + 1] - ko[b] : 0;
-        const bool on = sz > 0 && !mask_bit(mrow, b);
-        const unsigned long long votes = __ballot(on);
-        const int slot = at + __popcll(votes & ((1ull << lane) - 1ull));
-        if (on && slot < list_entries(Ck) - (BN - 1)) {
-          ent0[slot] = b;
-          ent1[slot] = __float_as_int(log2f((float)sz));
-        }
-        at += __popcll(votes);
-      }
-    }
-    at = min(at, list_entries(Ck) - (BN - 1));
-    if (lane < BN - 1) ent1[at + lane] = __float_as_int(-INFINITY);  // the rest of the last tile
-    if (lane == 0) slot_s[1] = at - comp0;
-  }
+  cluster_tables(p, bh, a, ne, comp0, wave, lane, ent0, ent1, slot_s);
   __syncthreads();
   // (part 2 leaves the routed keys out, part 1 the centroid tiles: the two-stage form)
   const int n_r = p.part == 2 ? 0 : __builtin_amdgcn_readfirstlane(ent0[ne]);  // wave-uniform
@@ -706,17 +679,7 @@ attn_bf16_quad_kernel(AttnArgs p) {
     else hi = mid;
   }
   auto map_tile = [&](int t) __attribute__((always_inline)) {
-    if (tid < BN) {
-      int phys;
-      if (t < nt_r) {  // positions past the last key repeat it (masked by rag_bias)
-        const int pos = min(t * BN + tid, n_r - 1);
-        while (pos >= ent0[cur + 1]) ++cur;
-        phys = ent1[cur] + (pos - ent0[cur]);
-      } else {
-        phys = ent0[comp0 + min((t - nt_r) * BN + tid, n_c - 1)];
-      }
-      rowmap[(t % RS) * BN + tid] = phys;
-    }
+    if (tid < BN) rowmap[(t % RS) * BN + tid] = key_row(ent0, ent1, comp0, nt_r, n_r, n_c, t, tid, cur);
   };
 
   // one wave-wide copy moves rows RPI*inst .. of a tile; lane -> (row, LDS chunk slot).
@@ -726,11 +689,9 @@ attn_bf16_quad_kernel(AttnArgs p) {
   static_assert((RPI * CW) % 16 == 0, "copy rows of one lane must share their swizzle phase");
   constexpr int CPW = INST_PER_TILE / CW;  // copies per tensor per wave per tile
   const uint32_t lds_k0 = lds_address(Ks), lds_v0 = lds_address(Vs);
-  auto k_swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
-  auto v_swz = [](int row) { return D == 128 ? ((row & 3) << 2) : ((row & 2) << 1); };
   const int cp_rr = RPI * (wave % CW) + lane / CPR;
-  const uint32_t cp_koff = (uint32_t)(((lane % CPR) ^ k_swz(cp_rr)) << 4);
-  const uint32_t cp_voff = (uint32_t)(((lane % CPR) ^ v_swz(cp_rr)) << 4);
+  const uint32_t cp_koff = (uint32_t)(((lane % CPR) ^ k_swz<D>(cp_rr)) << 4);
+  const uint32_t cp_voff = (uint32_t)(((lane % CPR) ^ v_swz<D>(cp_rr)) << 4);
   // permuted rows (of K/V or of the centroid tables) this lane copies for tile t
   auto fetch_rows = [&](int t, int (&rows)[CPW]) __attribute__((always_inline)) {
     const int32_t* rm = rowmap + (t % RS) * BN + cp_rr;
@@ -751,17 +712,10 @@ attn_bf16_quad_kernel(AttnArgs p) {
     }
   };
 
-  // per-lane LDS byte offsets of the MFMA operands
-  // K row li of a 32-row block, dims 16s + 8lh .. +7: chunk (2s + lh) ^ swizzle
   // (the swizzles are XORs of disjoint bit fields, so operand s / block db is the offset of
   // operand 0 with s << 5 / db << 6 XORed in: one register each instead of a table)
-  const int koff0 = li * ROWB + ((lh ^ k_swz(li)) << 4);
+  const int koff0 = k_operand_offset<D>(li, lh), voff0 = v_operand_offset<D>(lane);
   auto koff = [&](int s) { return koff0 ^ (s << 5); };
-  int voff0;  // transpose read: group = lane/16 -> (dim half, key half); r = lane%16
-  {
-    const int r = lane & 15, g = lane >> 4, ddhalf = g & 1, khalf = g >> 1, row = 4 * khalf + (r >> 2);
-    voff0 = row * ROWB + (((2 * ddhalf + ((r & 3) >> 1)) ^ v_swz(row)) << 4) + (r & 1) * 8;
-  }
   auto voff = [&](int db) { return voff0 ^ (db << 6); };
 
   // (the blocks of a partly filled tile rotate over the SIMDs with the tile)
@@ -786,15 +740,7 @@ attn_bf16_quad_kernel(AttnArgs p) {
   float m = -INFINITY, l = 0.f;
   const float c = p.scale * kLog2e;
 
-  auto rescale = [&](float m_new) __attribute__((always_inline)) {
-    const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
-    l *= alpha;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-    m = m_new;
-  };
+  auto rescale = [&](float m_new) __attribute__((always_inline)) { rescale_to<D>(m_new, m, l, oacc); };
 
   f32x16 sA[2], sB[2];
   uint32_t pk[2][8];
@@ -942,19 +888,7 @@ attn_bf16_quad_kernel(AttnArgs p) {
           *reinterpret_cast<float4*>(o + 32 * db + 8 * g + 4 * lh) =
               make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
     } else if (qrow < row_end) {
-      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-      int64_t lse_idx;
-      bf16_t* o = static_cast<bf16_t*>(p.op) + out_row_offset(p, bh, qrow, D, lse_idx);
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 w;
-          w.x = pack_bf16(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv);
-          w.y = pack_bf16(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
-          *reinterpret_cast<uint2*>(o + 32 * db + 8 * g + 4 * lh) = w;
-        }
-      if (p.lse && lh == 0) p.lse[lse_idx] = (m + log2f(lt)) * kLn2;
+      store_row<D>(p, bh, qrow, lh, oacc, m, lt);
     }
   }
 }
@@ -996,7 +930,7 @@ merge_splits_kernel(AttnArgs p) {
 
 // ------------------------------------------------------------------------ work lists
 // Item = (head, query cluster); its tiles all run T = #routed key tiles + #centroid tiles
-// pipeline steps. Items are ranked by T, longest first (ties by index), and dealt to the 8
+// pipeline steps (the latter counted here as if no cluster were routed: the order alone depends on it). Items are ranked by T, longest first (ties by index), and dealt to the 8
 // lists in boustrophedon order, which keeps the lists' totals close; inside a list the
 // longest come first, so a list's tail consists of its shortest tiles.
 // Steps and tiles of item (bh, a), by a whole wave, its lanes over the routed key clusters.
@@ -1083,7 +1017,7 @@ __device__ __forceinline__ int list_of_rank(int r) { return ((r >> 3) & 1) ? 7 -
 
 // The lists from the ranked items (one workgroup of 1024).
 __device__ __forceinline__ void write_lists(const int32_t* q_offsets, const int32_t* item_nt, const int32_t* by_rank,
-                                            int M, int Cq, int BM, int32_t* rank_off, int32_t* sched_bh,
+                                            int M, int Cq, int32_t* rank_off, int32_t* sched_bh,
                                             int32_t* sched_a, int32_t* sched_row0, int32_t* sched_rend,
                                             int32_t* sched_x) {
   __shared__ int32_t total[8], first[8];
@@ -1159,10 +1093,10 @@ __device__ __forceinline__ void write_lists(const int32_t* q_offsets, const int3
 
 __global__ void __launch_bounds__(1024)
 plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ item_nt,
-                  const int32_t* __restrict__ by_rank, int M, int Cq, int BM, int32_t* __restrict__ rank_off,
+                  const int32_t* __restrict__ by_rank, int M, int Cq, int32_t* __restrict__ rank_off,
                   int32_t* __restrict__ sched_bh, int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
                   int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x) {
-  write_lists(q_offsets, item_nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
+  write_lists(q_offsets, item_nt, by_rank, M, Cq, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
 }
 
 // Ranks and lists of up to kRankListItems items in one workgroup: the counting is M^2 / 1024 LDS reads a
@@ -1170,7 +1104,7 @@ plan_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
 constexpr int kRankListItems = 256;
 __global__ void __launch_bounds__(1024)
 plan_rank_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ item_T,
-                       const int32_t* __restrict__ item_nt, int M, int Cq, int BM, int32_t* __restrict__ sched_bh,
+                       const int32_t* __restrict__ item_nt, int M, int Cq, int32_t* __restrict__ sched_bh,
                        int32_t* __restrict__ sched_a, int32_t* __restrict__ sched_row0,
                        int32_t* __restrict__ sched_rend, int32_t* __restrict__ sched_x) {
   __shared__ int32_t T[kRankListItems], nt[kRankListItems], rank[kRankListItems], by_rank[kRankListItems],
@@ -1194,7 +1128,7 @@ plan_rank_lists_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __r
   __syncthreads();
   if (tid < M) by_rank[rank[tid]] = tid;
   __syncthreads();
-  write_lists(q_offsets, nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
+  write_lists(q_offsets, nt, by_rank, M, Cq, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
 }
 
 // The whole plan of a call with up to kPlanItems items in one workgroup (block 0: a small layer is
@@ -1219,7 +1153,7 @@ plan_small_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restri
     by_rank[rank] = i;
   }
   __syncthreads();
-  write_lists(q_offsets, item_nt, by_rank, M, Cq, BM, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
+  write_lists(q_offsets, item_nt, by_rank, M, Cq, rank_off, sched_bh, sched_a, sched_row0, sched_rend, sched_x);
 }
 
 }  // namespace
@@ -1320,14 +1254,14 @@ int plan_bf16(AttnArgs& a, int d, bf16_t* kbar16, bf16_t* vbar16, void* ws, size
       a.q_offsets, a.k_offsets, a.row_ptr, a.col_idx, M, a.Cq, a.Ck, BM, item_T, item_nt, a.kbar, a.vbar, n, kbar16, vbar16);
   SVGEAR_LAUNCH_CHECK();
   if (M <= kRankListItems) {
-    plan_rank_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_T, item_nt, M, a.Cq, BM, sched_bh, sched_a, sched_row0,
+    plan_rank_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_T, item_nt, M, a.Cq, sched_bh, sched_a, sched_row0,
                                               sched_rend, sched_x);
     SVGEAR_LAUNCH_CHECK();
     return SVGEAR_OK;
   }
   plan_rank_kernel<<<(unsigned)ceil_div(M, kRankItems), 256, 0, s>>>(item_T, M, by_rank);
   SVGEAR_LAUNCH_CHECK();
-  plan_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_nt, by_rank, M, a.Cq, BM, rank_off, sched_bh, sched_a, sched_row0,
+  plan_lists_kernel<<<1, 1024, 0, s>>>(a.q_offsets, item_nt, by_rank, M, a.Cq, rank_off, sched_bh, sched_a, sched_row0,
                                       sched_rend, sched_x);
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;

@@ -57,27 +57,6 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
-template <typename T>
-struct Elem;
-template <>
-struct Elem<float> {
-  static __device__ __forceinline__ float load(const float* p) { return *p; }
-  static __device__ __forceinline__ void store(float* p, float v) { *p = v; }
-};
-template <>
-struct Elem<bf16_t> {
-  static __device__ __forceinline__ float load(const bf16_t* p) { return bf16_to_f32(*p); }
-  static __device__ __forceinline__ void store(bf16_t* p, float v) { *p = f32_to_bf16(v); }
-};
-
-// Loads 4 consecutive elements as floats (p must be 16-byte aligned for float, 8 for bf16).
-__device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ float4 load4(const bf16_t* p) {
-  uint2 r = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
-                     __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
-}
-
 // Batch*head decomposition for strided [B,H,N,d] tensors.
 struct Strides {
   int64_t b, h, n;
