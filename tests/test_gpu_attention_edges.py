@@ -180,3 +180,52 @@ def test_the_largest_weight_of_a_row_is_exact(H, rows):
     assert torch.equal(O.cpu(), V[:, :, :1].expand_as(O))
     logits = (Q.double()[..., :1] * K.double()[..., 0][:, :, None, :]) * d ** -0.5
     assert (lse.cpu().double() - torch.logsumexp(logits, -1)).abs().max() <= 2e-5
+
+
+@pytest.mark.parametrize("Nq,Cq", [(300, 3), (208000, 100)])  # keys split over 128-row tiles; tiles of 384 rows
+def test_heads_of_more_than_33_million_keys(Nq, Cq):
+    """bf16 heads of 64 whose K and V rows lie more than 2^32 bytes apart are reached by 64-bit addresses. The
+    cluster that makes up the distance is compensated, so its rows are never read (nor initialised here)."""
+    d, scale = 64, 0.125
+    ks = np.array([90, 2 ** 25 + 77, 130, 64, 200, 0])
+    qs = np.append(np.full(Cq, Nq // Cq), 0)
+    qs[0] += Nq - qs.sum()
+    Ck, Nk, off = len(ks) - 1, int(ks.sum()), np.concatenate([[0], np.cumsum(ks)])
+    g = torch.Generator(device=dev()).manual_seed(4)
+    K, V = (torch.empty(1, 1, Nk, d, dtype=torch.bfloat16, device=dev()) for _ in range(2))
+    near = [0, 2, 3, 4]
+    for b in near:
+        for x in (K, V):
+            x[0, 0, off[b]:off[b + 1]] = torch.randn(int(ks[b]), d, generator=g, device=dev())
+    Q = torch.randn(1, 1, Nq, d, generator=g, device=dev()).to(torch.bfloat16)
+    Q[..., 0] = 8.0
+    kbar, vbar = (torch.randn(1, 1, Ck, d, generator=g, device=dev()).to(torch.bfloat16).float() for _ in range(2))
+    kbar[0, 0, 1, 0] = -17.0  # logit about -17 + ln 2^25
+    mask = np.outer(qs > 0, ks > 0)
+    mask[:, 1] = False
+    mask[: Cq // 2, 3] = False
+    row_ptr, col_idx = csr_from_mask(mask)
+    lists = [torch.from_numpy(x)[None, None].contiguous().to(dev())
+             for x in (mask_to_bits(mask, Cq, Ck).view(np.int32), row_ptr, col_idx)]
+    offs = [torch.from_numpy(np.concatenate([[0], np.cumsum(x)]).astype(np.int32))[None, None].contiguous().to(dev()) for x in (qs, ks)]
+    O, lse = sv.sparse_attn_comp(Q, K, V, kbar, vbar, *offs, *lists, scale, want_lse=True)
+    torch.cuda.synchronize()
+    rows = np.unique(np.linspace(0, Nq - 1, 1500).astype(int))
+    cluster = np.repeat(np.arange(Cq + 1), qs)[rows]
+    q = Q[0, 0, torch.from_numpy(rows).to(dev())].double().cpu()
+    parts, values = [], []
+    for b in range(Ck):
+        on = torch.from_numpy(mask[cluster, b])[:, None]
+        c = (q @ kbar[0, 0, b].double().cpu())[:, None] * scale + float(np.log(ks[b]))
+        if b == 1:
+            parts.append(c)
+            values.append(vbar[0, 0, 1:2].double().cpu())
+            continue
+        s = (q @ K[0, 0, off[b]:off[b + 1]].double().cpu().t()) * scale
+        parts += [s.masked_fill(~on, -np.inf), c.masked_fill(on, -np.inf)]
+        values += [V[0, 0, off[b]:off[b + 1]].double().cpu(), vbar[0, 0, b:b + 1].double().cpu()]
+    logits = torch.cat(parts, 1)
+    ref, ref_lse = torch.softmax(logits, 1) @ torch.cat(values), torch.logsumexp(logits, 1)
+    at = torch.from_numpy(rows).to(dev())
+    assert (O[0, 0, at].double().cpu() - ref).norm() <= TOL[torch.bfloat16] * ref.norm()
+    assert (lse[0, 0, at].double().cpu() - ref_lse).abs().max() <= _lse_tol(torch.bfloat16, d)
