@@ -28,7 +28,7 @@ import torch  # noqa: E402
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA
 HBM_PEAK_GBS = 8000.0
-FP32_VECTOR_PEAK_TFLOPS = 157.3  # 256 CUs x 4 SIMDs x 64 lanes x 2 flop x 2.4 GHz
+FP32_PEAK_TFLOPS = 157.3  # fp32 matrix and vector units alike: 256 CUs x 4 SIMDs x 64 lanes x 2 flop x 2.4 GHz
 # HBM bytes per launch of the fused attention kernel come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs scaled
 # by a 1 GiB copy (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0). They are kept in a tracked text file together with the
 # hash of the kernel sources they were measured on; a figure measured on other sources is not reported.
@@ -43,6 +43,22 @@ def attention_source_hash() -> str:
         with open(os.path.join(ROOT, "paper_2603_08982_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def attention_form(BH: int, Nq: int, Nk: int, Cq: int, d: int):
+    """(kernel, rows per tile, workgroups that share a tile's keys) of a bf16 attention call: the rule of
+    bf16_form in csrc/attention_bf16.hip, which decides from the sizes alone."""
+    ceil = lambda a, b: -(-a // b)
+    quads = BH * (ceil(Nq, 128) + Cq // 2)
+    fill = min((512 + quads // 2) // quads, Nk // 1024)
+    fine = min(ceil(1024, quads), Nk // 4096, 4)
+    spread = min(ceil(2048, quads), Nk // 8192, 4) if quads <= 1536 and Nk >= 16 * quads else 1
+    n = max(fill, fine, spread)
+    if n >= 2:
+        return "attn_bf16_quad_kernel", 128, min(n, 8)
+    if Nq <= 160 * Cq or quads <= (1024 if d == 128 else 64):
+        return "attn_bf16_quad_kernel", 128, 1
+    return "attn_bf16_kernel", 384, 1
 
 
 def vendor_gemm_rate():
@@ -349,11 +365,13 @@ def run_sweep(sv, args, wl, Q, K, V, cq0, ck0):
 
 
 def run_attention_steps(sv):
-    """Kernel-level timing of attn_bf16_kernel on synthetic layouts (bf16, d = 128, 16 heads): every query
-    cluster has 32 k rows (k active waves per tile), every key cluster the same size, each query cluster routes
-    `routed` random key clusters. (1) k = 12, exactly 12 tiles per CU, the routed count varied: a least-squares fit
-    of time per tile against the steps per tile T gives the fixed time per tile and the time per step. (2) a quarter
-    of the key clusters routed, k varied: time per tile-step against the active waves."""
+    """Kernel-level timing of the bf16 attention kernels on synthetic layouts (d = 128, 16 heads): every query
+    cluster has 32 k rows, every key cluster the same size, each query cluster routes `routed` random key clusters.
+    (1) k = 12, exactly 12 tiles of 384 rows per CU, the routed count varied: a least-squares fit of time per tile
+    against the steps per tile T gives the fixed time per tile and the time per step. (2) a quarter of the key
+    clusters routed, k varied from 12 to 6: time per tile-step against the active waves of the 384-row tile. (3) the
+    same from 5 to 1, where clusters are small enough for the 128-row kernel (four waves, two workgroups a CU):
+    time per cluster-step."""
     dev = torch.device("cuda:0")
     H, d, Ck = 16, 128, 512
     gen = torch.Generator(device=dev)
@@ -387,18 +405,25 @@ def run_attention_steps(sv):
         call()
         ms = min(_time_ms(call, reps=1)[0] for _ in range(4))
         steps = float(np.mean([(int(ks[np.nonzero(mask[a, :Ck])[0]].sum()) + 63) // 64 for a in range(Cq)])) + Ck // 64
-        tiles = H * Cq * ((32 * k + 383) // 384)
-        return {"active_waves": k, "query_clusters": Cq, "routed_key_clusters": routed, "steps_per_tile": steps,
-                "tiles_per_cu": tiles / 256.0, "kernel_ms": ms, "us_per_tile": ms * 1e3 / (tiles / 256.0),
-                "ns_per_tile_step": ms * 1e6 / (tiles / 256.0 * steps)}
+        kernel, tile_rows, splits = attention_form(H, N, N, Cq, d)
+        tiles = H * Cq * -(-32 * k // tile_rows)
+        row = {"kernel": kernel, "tile_rows": tile_rows, "splits": splits, "cluster_rows": 32 * k, "query_clusters": Cq,
+               "routed_key_clusters": routed, "steps_per_tile": steps, "tiles_per_cu": tiles / 256.0, "kernel_ms": ms,
+               "ns_per_cluster_step": ms * 1e6 / (H * Cq / 256.0 * steps)}
+        if tile_rows == 384:  # one workgroup a CU: a tile has it to itself
+            row.update(active_waves=k, us_per_tile=ms * 1e3 / (tiles / 256.0), ns_per_tile_step=ms * 1e6 / (tiles / 256.0 * steps))
+        return row
 
     fit_rows = [run_case(12, 192, r) for r in (0, 16, 32, 64, 128, 256)]
     A = np.array([[1.0, r["steps_per_tile"]] for r in fit_rows])
     y = np.array([r["us_per_tile"] for r in fit_rows])
     (a, b), *_ = np.linalg.lstsq(A, y, rcond=None)
-    wave_rows = [run_case(k, 2304 // k, 128) for k in (12, 9, 8, 6, 4, 3, 2, 1)]
-    print(json.dumps({"mode": "attention-steps", "kernel": "attn_bf16_kernel", "heads": H, "key_clusters": Ck,
-                      "fit_us_per_tile": a, "fit_ns_per_step": b * 1e3, "fit_cases": fit_rows, "wave_cases": wave_rows}))
+    wave_rows = [run_case(k, 2304 // k, 128) for k in (12, 9, 8, 6)]
+    small_rows = [run_case(k, 2304 // k, 128) for k in (5, 4, 3, 2, 1)]
+    assert all(r["tile_rows"] == 384 for r in fit_rows + wave_rows) and all(r["tile_rows"] == 128 for r in small_rows)
+    print(json.dumps({"mode": "attention-steps", "heads": H, "key_clusters": Ck, "fit_us_per_tile": a,
+                      "fit_ns_per_step": b * 1e3, "fit_cases": fit_rows, "wave_cases": wave_rows,
+                      "small_cluster_cases": small_rows}))
 
 
 def run_trajectory(sv, args, wl):
@@ -529,8 +554,8 @@ def main():
             comp_pairs += float((qs[:, None] * ((~m) & (ks[None, :] > 0))).sum())
     attn_flops = 4.0 * wl.d * (routed_pairs + comp_pairs)
     attn_ms = stages["attention"]
-    # bf16: matrix cores; fp32 (one query row per lane on the vector ALUs): the fp32 vector peak
-    peak_tflops = MFMA_BF16_PEAK_TFLOPS if wl.dtype == "bf16" else FP32_VECTOR_PEAK_TFLOPS
+    # the matrix cores in either type
+    peak_tflops = MFMA_BF16_PEAK_TFLOPS if wl.dtype == "bf16" else FP32_PEAK_TFLOPS
     achieved = attn_flops / (attn_ms * 1e-3) / 1e12
     density = routed_pairs / (wl.B * wl.H * float(wl.N) ** 2)
 
@@ -556,8 +581,9 @@ def main():
         "worst_sampled_row": {"rel_l2": worst_row[1], "row": worst_row[2]},
         "probe_max_exponent_above_row_stabiliser": {"value": excess, "cap": 40.0, "cap_reached": bool(excess > 40.0)},
         "attention_stage": {"ms": attn_ms, "dense_equiv_tflops": dense_flops / (attn_ms * 1e-3) / 1e12},
-        "roofline": {"bound": "mfma" if wl.dtype == "bf16" else "alu",
-                     "kernel": "attn_bf16_kernel" if wl.dtype == "bf16" else "attn_f32_kernel",
+        "roofline": {"bound": "mfma",
+                     "kernel": attention_form(wl.B * wl.H, wl.N, wl.N, wl.Cq, wl.d)[0] if wl.dtype == "bf16"
+                     else "attn_f32_kernel",
                      "achieved": achieved, "peak": peak_tflops, "unit": "TFLOP/s",
                      "frac": achieved / peak_tflops,
                      "traffic": measured_attention_traffic(wl.name, wl.rho, wl.H),
