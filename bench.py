@@ -404,7 +404,7 @@ def run_attention_steps(sv):
         call = lambda: sv.sparse_attn_comp(Q, K, V, kbar, vbar, *meta, d ** -0.5)
         call()
         ms = min(_time_ms(call, reps=1)[0] for _ in range(4))
-        steps = float(np.mean([(int(ks[np.nonzero(mask[a, :Ck])[0]].sum()) + 63) // 64 for a in range(Cq)])) + Ck // 64
+        steps = float(np.mean([(int(ks[np.nonzero(mask[a, :Ck])[0]].sum()) + 63) // 64 for a in range(Cq)])) + (Ck - routed + 63) // 64
         kernel, tile_rows, splits = attention_form(H, N, N, Cq, d)
         tiles = H * Cq * -(-32 * k // tile_rows)
         row = {"kernel": kernel, "tile_rows": tile_rows, "splits": splits, "cluster_rows": 32 * k, "query_clusters": Cq,
