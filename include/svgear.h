@@ -230,6 +230,11 @@ int svgear_probe_route_top_p(const float* qbar, const float* kbar, const float* 
  * per-key-cluster tables sit in LDS beside the K/V tile buffers (12 bytes per key cluster), which
  * allows Ck up to about 2500 for d = 128 and 8192 for d = 64; for d = 128 the K/V rows of a head are
  * addressed by 32-bit byte offsets, so Nk <= 16,777,215 keys per head.
+ * The workspace serves either dtype (the larger need of the two). Beside lists and bf16 centroids it
+ * holds, where the query tiles of a call are too few for the GPU and their keys are split over n <= 8
+ * workgroups, n partial results: n*B*H*Nq*(4 d + 8) bytes. n follows from the sizes; it is 1 beyond
+ * 1,536 estimated tiles of 128 query rows (B*H*(Nq/128 + Cq/2)), and for fp32 from 512 tiles of 32 rows
+ * on. One head of 118,800 rows of 128: n = 2, 124 MB; 40 heads of 75,600: n = 1, 10 MB in all.
  */
 size_t svgear_sparse_attn_comp_workspace(int B, int H, int64_t Nq, int64_t Nk, int d, int Cq,
                                          int Ck);

@@ -1169,26 +1169,26 @@ struct Bf16Form {
   int rows;    // per tile: 384 (12-wave kernel) or 128 (four waves, two workgroups per CU)
   int splits;  // workgroups that share the keys of a 128-row tile
 };
-// Measured at d = 128 unless stated, 384-row against 128-row tiles, us a call (a quarter routed):
+// Measured at d = 128 unless stated, us a call with a quarter routed (5 % in brackets):
 //  * keys split, for the longest tiles: a cluster may have anything from a dozen keys to all of them routed,
 //    and a launch ends no sooner than its longest tile. As many splits as the largest of three rules:
 //    - fill: workgroups for the 512 that are resident at once, 1,024 keys each or more (fewer, and the
-//      merge costs what it saves). 1 head x 11,970 rows, 8 / 942 clusters 199 -> 80; 1 x 4,096, 32 / 64
-//      63 -> 36. Rounded to the nearest, since a few workgroups beyond 512 wait for a whole tile: 12 x
-//      2,376, 384 tiles in two splits 80, in one 56; 4 x 5,400, 236 tiles in three 76, in two 58;
-//    - fine: two rounds of workgroups at 4,096 keys or more a split: 1 x 37,800, 396 tiles in one split 912,
-//      in two 491, in three 353; 4 x 10,000, 356 tiles in one 172, in two 120;
-//    - spread: up to 1,536 tiles, four rounds at 8,192 keys or more: 1 x 75,600, 641 tiles in one split 1588,
-//      in two 955, in four 860; 1 x 118,800, 1,079 tiles 2817 -> 2085; d = 64, 2 x 75,600, 1,482 tiles
-//      1506 -> 1229. Not where the keys are few for so many tiles (8 x 20,000, 1,456 tiles 597 -> 613) nor
-//      with more tiles, which even out by themselves (3 x 75,600, 1,923 tiles 2240 -> 2279);
-//  * clusters of at most 160 rows, which fill at most five of twelve waves: 12 x 16,200, 81 rows 1047 -> 829;
-//    24 x 10,800, 108 rows 838 -> 725; 24 x 4,000, 20 rows 492 -> 293; d = 64, 8 x 32,400, 162 rows 1008 ->
-//    967, 24 x 1,200, 6 rows 375 -> 229; larger ones want the larger tile (5 x 75,600, 252 rows 4018 -> 4507;
-//    d = 64, 24 x 32,477, 507 rows 2025 -> 2294);
-//  * at most four 128-row tiles a CU, d = 128: 1 x 75,600, 756 rows 1675 -> 1611; 4 x 18,900 497 -> 491; 3 x
-//    2,000, 1,000 rows 51 -> 42. d = 64 at most 64 of them: 1 x 2,000, 667 rows 31 -> 27, but 12 x 7,000
-//    128 -> 133.
+//      merge costs what it saves). 1 head x 11,970 rows, 8 / 942 clusters in one split 176 (84), in five 82
+//      (56); 1 x 4,096, 32 / 64 in one 48 (27), in four 32 (28). Rounded to the nearest, since a few
+//      workgroups beyond 512 wait for a whole tile: 12 x 2,376, 348 tiles in one 61 (33), in two 55 (47);
+//    - fine: two rounds of workgroups at 4,096 keys or more a split: 1 x 37,800, 346 tiles in one split 980
+//      (296), in two 543 (181), in three 389 (140); 4 x 10,000, 436 tiles in one 195 (61), in two 137 (69);
+//    - spread: up to 1,536 tiles, four rounds at 8,192 keys or more: 1 x 75,600, 641 tiles in one split 1655
+//      (487), in two 1010 (285), in four 918 (276); 1 x 118,800, 1,079 tiles in one 2885 (696), in two 2323
+//      (534); d = 64, 2 x 75,600, 1,482 tiles in one 1586 (654), in two 1282 (373). Not where the keys are few
+//      for so many tiles (8 x 20,000, 1,456 tiles of 128 rows in two 568 (230), the 384-row tile 542 (176)) nor
+//      with more tiles, which even out by themselves (3 x 75,600, 1,923 tiles 2406 (631) against 2204 (532));
+//  * clusters of at most 160 rows, which fill at most five of twelve waves, 384-row against 128-row tiles:
+//    12 x 16,200, 81 rows 1091 -> 804 (427 -> 305); 24 x 10,800, 108 rows 795 -> 627; 24 x 4,000, 20 rows 734 ->
+//    437; d = 64, 8 x 32,400, 162 rows 1014 -> 947, 24 x 1,200, 6 rows 386 -> 234 (277 -> 188); larger ones want
+//    the larger tile (5 x 75,600, 252 rows 4022 -> 4449; d = 64, 24 x 32,400, 506 rows 2152 -> 2370);
+//  * at most four 128-row tiles a CU, d = 128: 3 x 2,000, 1,000 rows 51 -> 41 (36 -> 29); 4 x 18,900 550 -> 529.
+//    d = 64 at most 64 of them: 1 x 2,000, 666 rows 35 -> 30; 12 x 7,000 is the same either way (124).
 static Bf16Form bf16_form(int64_t BH, int64_t Nq, int64_t Nk, int Cq, int d) {
   const int64_t quads = BH * (ceil_div(Nq, 32 * kQuadWaves) + Cq / 2);  // a cluster's last tile is half full
   const int64_t fill = std::min((512 + quads / 2) / quads, Nk / 1024);

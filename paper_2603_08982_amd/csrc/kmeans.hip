@@ -13,8 +13,10 @@
 // split exactly into two bf16 pieces plus a residual below 2^-16), with the best and the
 // second-best score tracked per row. A row whose margin exceeds a rigorous bound on
 // |filter score - fixed-order score| keeps the filter's label (the fixed-order argmin is
-// provably the same); the few remaining rows are re-assigned by the fp32 kernel, so the
-// labels are always those of the fixed-order definition.
+// provably the same); for the few remaining rows the fixed-order scores of the centroids that the
+// bound leaves possible are evaluated (of all centroids where those are too many), so the labels
+// are always those of the fixed-order definition. Small bf16 calls skip the filter and score every
+// row exactly, as fp32 inputs do.
 // From the second iteration on only the rows whose distance bounds (Hamerly's: one upper, one
 // lower bound per row, widened by the centroids' moves) do not prove that the fixed-order label
 // stays are assigned again; with many centroids each such row is tested only against the

@@ -11,11 +11,9 @@ from helpers import dev, to_np
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N", [2, 63, 64, 65, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193])
-@pytest.mark.parametrize("C", [1, 2, 63, 1000, 1023, 1024, 2048, 2049])
+@pytest.mark.parametrize("N,C", [(N, C) for C in (1, 2, 63, 1000, 1023, 1024, 2048, 2049)
+                                 for N in (2, 63, 64, 65, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193) if C < N])
 def test_sort_is_the_stable_argsort(N, C):
-    if C > N - 1:
-        pytest.skip("more clusters than tokens")
     rng = np.random.default_rng(N + C)
     H = 3
     for n_tail in (0, 1 if N < 66 else 37):
