@@ -16,7 +16,7 @@
 // provably the same); for the few remaining rows the fixed-order scores of the centroids that the
 // bound leaves possible are evaluated (of all centroids where those are too many), so the labels
 // are always those of the fixed-order definition. Small bf16 calls skip the filter and score every
-// row exactly, as fp32 inputs do.
+// row exactly, as fp32 inputs do; the smallest calls of either type run in one launch (kmeans_small.hip).
 // From the second iteration on only the rows whose distance bounds (Hamerly's: one upper, one
 // lower bound per row, widened by the centroids' moves) do not prove that the fixed-order label
 // stays are assigned again; with many centroids each such row is tested only against the
@@ -27,12 +27,11 @@
 // atomics, so the centroids are run-to-run deterministic.
 #include <atomic>
 
-#include "common.h"
+#include "kmeans.h"
 
 namespace svgear {
 namespace {
 
-constexpr int kCentChunk = 64;                  // centroids per LDS stage (two 32-blocks)
 // per head: [0] rows queued for assign_filter_kernel; as float bits: [1] max |x| of the flagged rows, [2] max |c|^2
 constexpr int kHeadState = 4;
 constexpr int kListMax = 128;                   // longest candidate list of a cluster (longer: every centroid)
@@ -41,15 +40,14 @@ constexpr int kListChunk = 4 * kListTile;       // sorted positions per wave (on
 constexpr int kMaxCentroids = 8192;             // most centroids per head the entry point accepts
 // Candidate lists pay when there are many centroids: with fewer than this, testing every
 // centroid (shared through LDS by 256 rows, streaming) costs no more than the lists' gathers.
-std::atomic<int> g_list_min_centroids{400};
+constexpr int kListDefault = 400;
+std::atomic<int> g_list_min_centroids{kListDefault};
 // (in the second iteration of a cold start the radii still reach every centroid, so no cluster gets
 // a list: the lists start one iteration later)
 #ifndef SVGEAR_LIST_FROM
 #define SVGEAR_LIST_FROM 2
 #endif
 constexpr int kListFromIteration = SVGEAR_LIST_FROM;
-
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 // Prepares the caller's centroids for the matrix cores (later iterations: publish_centroid):
 //  * cn[c] = |c|^2 as ONE fp32 fma chain over t = 0..d-1 (+inf for the padding centroids that
@@ -68,8 +66,10 @@ __global__ void __launch_bounds__(256)
 prep_centroids_kernel(const float* __restrict__ cent, int C, int Cpad, int d, float* __restrict__ cperm,
                       float* __restrict__ cn, bf16_t* __restrict__ chl, bf16_t* __restrict__ crow,
                       int32_t* __restrict__ amb_count, int32_t* __restrict__ head_state, int32_t* __restrict__ rmax,
-                      int32_t* __restrict__ dirty) {
+                      int32_t* __restrict__ dirty, int32_t* __restrict__ small_state, float* __restrict__ small_norms) {
   const int bh = blockIdx.y;
+  if (small_state && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < kSmallState; i += 256) small_state[bh * kSmallState + i] = 0;
   const float* cb = cent + (int64_t)bh * C * d;
   const int64_t n = (int64_t)Cpad * d;
   if (amb_count && blockIdx.x == 0 && threadIdx.x == 0) amb_count[bh] = 0;
@@ -138,31 +138,11 @@ prep_centroids_kernel(const float* __restrict__ cent, int C, int Cpad, int d, fl
         }
       }
     }
-    cn[(int64_t)bh * Cpad + c] = acc;
+    if (small_norms) small_norms[(int64_t)bh * Cpad * 4 + (c >> 3) * 32 + (c & 7)] = acc;
+    else cn[(int64_t)bh * Cpad + c] = acc;
   }
 }
 
-
-// x[row][2s + h] for s = 0..D/2-1 into xb[] (the B operand of k-step s for lane (row, h))
-template <int D>
-__device__ __forceinline__ void load_row_operands(const float* xr, int h, float (&xb)[D / 2]) {
-#pragma unroll
-  for (int t = 0; t < D / 4; ++t) {
-    const float4 v = *reinterpret_cast<const float4*>(xr + 4 * t);
-    xb[2 * t] = h ? v.y : v.x;
-    xb[2 * t + 1] = h ? v.w : v.z;
-  }
-}
-template <int D>
-__device__ __forceinline__ void load_row_operands(const bf16_t* xr, int h, float (&xb)[D / 2]) {
-#pragma unroll
-  for (int t = 0; t < D / 8; ++t) {
-    const uint4 v = *reinterpret_cast<const uint4*>(xr + 8 * t);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) xb[4 * t + i] = __uint_as_float(h ? (w[i] & 0xffff0000u) : (w[i] << 16));
-  }
-}
 
 // Nearest centroid of every row. The score tile is computed transposed (centroids x rows):
 // a lane then holds 16 centroids of ONE row per 32x32 block and keeps a private running
@@ -1408,12 +1388,6 @@ means_finish_kernel(const float* __restrict__ partial, const int32_t* __restrict
   if (next.cperm && on && cnt > 0) publish_centroid<D>(next, row + threadIdx.x / D * D, dim, bh, c, Cpad);
 }
 
-// Parts per cluster of the centroid update: about 128 members per part on average, at most 8.
-static inline int means_parts(int64_t n, int C) {
-  const int64_t p = (n / C + 64) / 128;
-  return (int)(p < 1 ? 1 : (p > 8 ? 8 : p));
-}
-
 template <typename T, int D>
 int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail, Strides st, int C, int iters,
                float* cent, float* cent2, int32_t* labels, int32_t* counts, Workspace& ws, hipStream_t s) {
@@ -1448,6 +1422,8 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   int32_t* nlen = kFilter ? ws.take<int32_t>((size_t)BH * C) : nullptr;
   float* dout = kFilter ? ws.take<float>((size_t)BH * C) : nullptr;
   int4* tiles = kFilter ? ws.take<int4>((size_t)BH * tile_cap) : nullptr;
+  int32_t* small_state = ws.take<int32_t>((size_t)BH * kSmallState);
+  float* small_norms = ws.take<float>((size_t)BH * Cpad * 4);
   if (!ws.ok()) return SVGEAR_ERR_WORKSPACE;
   const size_t lds = 2 * (size_t)kCentChunk * D * 4 + 2 * kCentChunk * sizeof(float);
   // A small bf16 call (rows for one round of workgroups, two chunks of centroids at most) assigns every
@@ -1472,6 +1448,15 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(filter),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_f));
   const dim3 gp((unsigned)ceil_div((int64_t)Cpad * D, 256 * 4), BH);
+  // (a threshold of the caller's own asks for the forms it chooses between)
+  if (g_list_min_centroids.load(std::memory_order_relaxed) == kListDefault && kmeans_small_takes(BH, nv, C)) {
+    prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                             nullptr, small_state, small_norms);
+    SVGEAR_LAUNCH_CHECK();
+    SmallKmeans a{x, x2, st, BH, H, (int)nv, C, Cpad, iters, cent, cent2, labels, counts, cperm, small_norms,
+                  small_state, 0, 0, 0, 0, 0};
+    return launch_kmeans_small(a, D, kFilter, s);
+  }
   const dim3 ga((unsigned)ceil_div(nv, 32 * assign_waves), BH);
   // only_changed: clusters that neither gained nor lost a member in this iteration keep their
   // centroid (flags set by the assignment kernels; null = every cluster)
@@ -1493,7 +1478,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
                                      : NextIteration{cperm, cn, chl, crow, amb_count, head_state, rmax};
   const NextIteration nothing{};
   prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, tables.chl, tables.crow, tables.amb_count,
-                                           tables.head_state, tables.rmax, exact ? nullptr : dirty);
+                                           tables.head_state, tables.rmax, exact ? nullptr : dirty, nullptr, nullptr);
   SVGEAR_LAUNCH_CHECK();
   for (int it = 0; it < iters; ++it) {
     if (exact) {
@@ -1580,7 +1565,8 @@ extern "C" size_t svgear_kmeans_workspace(int B, int H, int64_t N, int d, int C)
          align_up(BH * N * 8, 256) + 4 * align_up(BH * N * 4, 256) +
          align_up(BH * kHeadState * 4, 256) + 3 * align_up(BH * Cpad * 4, 256) +
          align_up(BH * C * kListMax * 4, 256) + 2 * align_up(BH * C * 4, 256) +
-         align_up(BH * (N / kListChunk + C + 1) * 16, 256);
+         align_up(BH * (N / kListChunk + C + 1) * 16, 256) + align_up(BH * kSmallState * 4, 256) +
+         align_up(BH * Cpad * 16, 256);
 }
 
 extern "C" int svgear_kmeans(const void* x, const void* x2, svgear_dtype dt, int B, int H, int64_t N,
