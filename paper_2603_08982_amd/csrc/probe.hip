@@ -105,7 +105,8 @@ sbar_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, cons
 // The same for many centroids: one workgroup per 32 query centroids, whose waves take the 32-blocks of
 // key centroids in turn. The dot products run on fp32 MFMAs, k-step s contracting dims 2s (lanes 0-31) and
 // 2s + 1: every product is the fma chain over the dims in order, bit for bit that of the kernel above,
-// which fetches every key centroid Cq / 4 times. 40 heads, 300 x 1,000 centroids of 128: 240 -> 113 us;
+// which fetches every key centroid Cq / 4 times. 40 heads, 300 x 1,000 centroids of 128: 240 -> 113 us, 86 with half
+// the fetches of a row (the next block's rows fetched ahead cost half the waves: 119);
 // with too few workgroups for the chip the longer chain of each loses (5 heads, 200 x 500: 20 -> 33), so
 // run_sbar asks for one a CU.
 constexpr int kSbarWaves = 8;
@@ -118,6 +119,23 @@ __device__ __forceinline__ void row_operands(const float* row, int h, float (&x)
     const float4 v = *reinterpret_cast<const float4*>(row + 4 * t);
     x[2 * t] = h ? v.y : v.x;
     x[2 * t + 1] = h ? v.w : v.z;
+  }
+}
+
+// The same operands from half the fetches: the lane halves take alternate 16-byte pieces of the row and
+// exchange them (v_permlane32_swap: the high lanes of one register for the low lanes of another).
+template <int D>
+__device__ __forceinline__ void row_operands_swapped(const float* row, int h, float (&x)[D / 2]) {
+  auto swap = [](float a, float b, float& lo, float& hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    lo = __uint_as_float(r[0]);  // a of the low lanes, b of the low lanes
+    hi = __uint_as_float(r[1]);  // a of the high lanes, b of the high lanes
+  };
+#pragma unroll
+  for (int u = 0; u < D / 8; ++u) {
+    const float4 v = *reinterpret_cast<const float4*>(row + 8 * u + 4 * h);
+    swap(v.x, v.y, x[4 * u], x[4 * u + 2]);
+    swap(v.z, v.w, x[4 * u + 1], x[4 * u + 3]);
   }
 }
 
@@ -150,12 +168,12 @@ sbar_mfma_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
   const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
   const int a = a0 + li;
   float q[D / 2];
-  row_operands<D>(qbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * D, lh, q);
+  row_operands_swapped<D>(qbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * D, lh, q);
   float* out = sbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * Ck;
   float mx = -INFINITY;
   for (int b0 = 32 * wave; b0 < Ck; b0 += 32 * kSbarWaves) {
     float kf[D / 2];
-    row_operands<D>(kbar + ((int64_t)bh * Ck + min(b0 + li, Ck - 1)) * D, lh, kf);
+    row_operands_swapped<D>(kbar + ((int64_t)bh * Ck + min(b0 + li, Ck - 1)) * D, lh, kf);
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -189,23 +207,6 @@ sbar_mfma_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
 #pragma unroll
     for (int w = 1; w < kSbarWaves; ++w) m = fmaxf(m, red[w][tid]);
     mrow[(int64_t)bh * Cq + a0 + tid] = m;
-  }
-}
-
-// The same operands from half the fetches: the lane halves take alternate 16-byte pieces of the row and
-// exchange them (v_permlane32_swap: the high lanes of one register for the low lanes of another).
-template <int D>
-__device__ __forceinline__ void row_operands_swapped(const float* row, int h, float (&x)[D / 2]) {
-  auto swap = [](float a, float b, float& lo, float& hi) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    lo = __uint_as_float(r[0]);  // a of the low lanes, b of the low lanes
-    hi = __uint_as_float(r[1]);  // a of the high lanes, b of the high lanes
-  };
-#pragma unroll
-  for (int u = 0; u < D / 8; ++u) {
-    const float4 v = *reinterpret_cast<const float4*>(row + 8 * u + 4 * h);
-    swap(v.x, v.y, x[4 * u], x[4 * u + 2]);
-    swap(v.z, v.w, x[4 * u + 1], x[4 * u + 3]);
   }
 }
 
@@ -403,58 +404,69 @@ value_stats_kernel(const float* __restrict__ vbar, const bf16_t* __restrict__ vp
 
 
 // Block errors with the logits qbar_a . k_j on bf16 MFMAs (qbar in three exact bf16 pieces,
-// so the logits carry fp32-level accuracy). One workgroup per (head, kProbeClusters consecutive
+// so the logits carry fp32-level accuracy). One workgroup per (head, `clusters` consecutive
 // key clusters, group of 128 query centroids); wave w owns query centroids 32w..32w+31 of the
 // group and keeps their operand fragments in registers across those key clusters. The score
 // tile is keys x centroids: a lane holds 16 keys of ONE query centroid per 32-key block, so
 // the block error accumulates lane-locally.
-// The 32-key blocks of the workgroup's key clusters form one sequence. Each block is copied
-// once by the whole workgroup, straight from global memory into a ring of kProbeStages LDS
-// buffers, kProbeStages - 1 blocks ahead of the one being computed (the kernel streams every
-// key once and has few workgroups per CU: without that depth too few bytes are in flight),
-// together with its per-key value statistics; the 16-byte chunks of a row are XOR-swizzled
-// with the row index so that the operand reads of 32 rows do not collide. One barrier per
-// block. A block of a wave is 24 MFMAs (d = 128, 768 cycles of its SIMD) and about as long on the vector
-// ALU for the errors of its 512 pairs, and a SIMD holds two waves: the errors of block k - 1 are written
-// between the MFMAs of block k, and a cluster's last block, a third of them at 75 keys a cluster, selects
-// instead of branching per register (40 heads, 300 x 1,000 centroids: 1.58 -> 1.53 ms; 5 heads,
-// 200 x 500: 129 -> 118 us). What is left is the vector ALU, some 160 to 250 instructions a block, at
-// the two waves that 96 registers of centroid fragments leave room for (three waves spill: 1.85 ms).
+// The 32-key blocks of the workgroup's key clusters form one sequence, worked at in pairs. Each block is copied
+// once by the whole workgroup, straight from global memory into a ring of kProbeStages LDS buffers, two pairs
+// ahead of the one being computed, together with its per-key value statistics; the 16-byte chunks of a row are
+// XOR-swizzled with the row index so that the operand reads of 32 rows do not collide. One barrier per pair.
+// Nothing else is fetched in the loop: a load the compiler waits for would drain the copies.
+// A block of a wave is 24 MFMAs (d = 128, 768 cycles of its SIMD) and as long on the vector ALU for the errors
+// of its 512 pairs, and a SIMD holds two waves (96 registers of centroid fragments; three waves spill): the errors
+// of block k - 1 are written between the MFMAs of block k. Counters: vector ALU busy 53 %, matrix cores 38 %, the
+// two hardly at the same time. 40 heads, 300 x 1,000 centroids, the whole call: 1,870 us with the weights and
+// bounds of a cluster fetched when it begins, 1,660 with all of a workgroup's fetched at its start, 1,605 with a
+// barrier per pair of blocks, 1,490 with the sum of u^2 apart (a multiplication less a pair), no branch per
+// register in a cluster's last block and the groups of query centroids side by side on an XCD. Two waves a workgroup,
+// no wave without centroids at 300 of them, took the same.
 // d = 64 has half the MFMAs and fragments and is bound by the vector ALU and latencies: three waves a SIMD,
 // for which the statistics are read group by group (240 heads x 2,000 keys, 60 clusters, 30 centroids: the
 // whole call 127 us with two waves, 103 with three).
-constexpr int kProbeClusters = 4;  // key clusters per workgroup
-constexpr int kProbeStages = 4;    // LDS ring buffers
+constexpr int kProbeClusters = 8;  // most key clusters per workgroup
+constexpr int kProbeWaves = 4;     // per workgroup, 32 query centroids each
+constexpr int kProbeStages = 6;    // LDS ring buffers: the pair of blocks at work and two pairs in flight
 
 template <int D, bool VALUE_AWARE>
-__global__ void __launch_bounds__(256, D == 64 ? 3 : 2)
+__global__ void __launch_bounds__(64 * kProbeWaves, D == 64 ? 3 : 2)
 block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__ vbar, const bf16_t* __restrict__ kp,
                         const int32_t* __restrict__ k_offsets, const float* __restrict__ sbar,
                         const float* __restrict__ mrow, const float* __restrict__ nd, const float* __restrict__ dd,
-                        int64_t Nk, int64_t stat_stride, int Cq, int Ck, float scale, float* __restrict__ scores) {
+                        int64_t Nk, int64_t stat_stride, int Cq, int Ck, float scale, int clusters, int cgroups, int heads,
+                        float* __restrict__ scores) {
   constexpr int KSN = D / 16;
   constexpr int CPR = D / 8;             // 16-byte chunks per key row
   constexpr int RPI = 64 / CPR;          // key rows per copy instruction of a wave
-  constexpr int NCH = 32 / RPI / 4;      // copy instructions per wave per block
+  constexpr int NCH = 32 / RPI / kProbeWaves;      // copy instructions per wave per block
   constexpr int TILE_B = 32 * D * 2;     // bytes of a block in LDS
   constexpr int LPB = NCH + (VALUE_AWARE ? 1 : 0);  // loads per wave per block
-  constexpr int PF = kProbeStages - 1;   // blocks in flight ahead of the one computed
-  static_assert(32 % (RPI * 4) == 0 && (CPR == 16 || CPR == 8), "tile split / swizzle assume d = 64 or 128");
+  constexpr int PF = kProbeStages - 2;   // blocks copied ahead when a pair starts, besides the pair
+  static_assert(32 % (RPI * kProbeWaves) == 0 && (CPR == 16 || CPR == 8), "tile split / swizzle assume d = 64 or 128");
   __shared__ __attribute__((aligned(1024))) unsigned char ktile[kProbeStages][TILE_B];
   // [|delta|^2 x 32, vbar.delta x 32]; read one block later than the keys, so one buffer more
   __shared__ __attribute__((aligned(256))) float stat[kProbeStages + 1][64];
   // scores of the workgroup's key clusters, per wave [query centroid][key cluster]: a row leaves
   // as ONE 16-byte store at the end instead of kProbeClusters 4-byte stores a score row apart
-  __shared__ __attribute__((aligned(16))) float sc[4][32][kProbeClusters];
-  const int bh = blockIdx.y, tid = threadIdx.x;
+  __shared__ __attribute__((aligned(16))) float sc[kProbeWaves][32][kProbeClusters];
+  // centroid weights W of the wave's query centroids and |vbar|^2 of the key clusters
+  __shared__ float s_w[kProbeWaves][kProbeClusters][32], s_nvb[kProbeClusters];
+  // The groups of query centroids that read the same keys run side by side on one XCD (workgroups go round-robin
+  // over the eight): every eight workgroups take eight sets of clusters, the next eight the same sets again.
+  const int sets = (Ck + clusters - 1) / clusters * heads;
+  const int set = blockIdx.x / (8 * cgroups) * 8 + (blockIdx.x & 7), cgroup = blockIdx.x / 8 % cgroups;
+  if (set >= sets) return;
+  const int per_head = (Ck + clusters - 1) / clusters;
+  const int bh = set / per_head, tid = threadIdx.x;
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ab = blockIdx.z * 4 + wave, nab = (Cq + 31) >> 5;
+  const int ab = cgroup * kProbeWaves + wave, nab = (Cq + 31) >> 5;
   const bool wave_on = ab < nab;  // waves past the last centroid block still help copying
   const int a = 32 * ab + li;
   const bool live = wave_on && a < Cq;
   const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
-  const int b_lo = blockIdx.x * kProbeClusters, b_end = min(b_lo + kProbeClusters, Ck);
+  const int b_lo = set % per_head * clusters, b_end = min(b_lo + clusters, Ck);
   // empty key clusters score 0 (each wave reads and writes its own part of sc only)
   if (lh == 0) {
 #pragma unroll
@@ -463,8 +475,9 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   auto flush = [&]() {  // the wave's scores to global memory
     if (!live || lh != 0) return;
     float* dst = scores + ((int64_t)bh * Cq + a) * Ck + b_lo;
-    if (b_end - b_lo == kProbeClusters && (Ck % 4) == 0) {
-      *reinterpret_cast<float4*>(dst) = *reinterpret_cast<const float4*>(&sc[wave][li][0]);
+    if ((b_end - b_lo) % 4 == 0 && clusters % 4 == 0 && (Ck % 4) == 0) {
+      for (int i = 0; i < b_end - b_lo; i += 4)
+        *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(&sc[wave][li][i]);
     } else {
       for (int i = 0; i < b_end - b_lo; ++i) dst[i] = sc[wave][li][i];
     }
@@ -482,6 +495,29 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   // exponentials as exp2 with the constants folded: e^(x scale - m) = 2^(x scale2 - m2)
   constexpr float kLog2e = 1.4426950408889634f;
   const float scale2 = scale * kLog2e, neg_m2 = -m_a * kLog2e, cap2 = kMaxExponent * kLog2e;
+  // what the loop needs to know about the workgroup's clusters: a fetch in the loop would have to wait for the
+  // block copies in flight before it
+  const int bounds = off[min(b_lo + lane, Ck)];  // lane i: first key of cluster b_lo + i
+  {
+    float w[kProbeClusters];
+#pragma unroll
+    for (int i = 0; i < kProbeClusters; ++i)
+      w[i] = live && i < clusters ? sbar[((int64_t)bh * Cq + a) * Ck + min(b_lo + i, Ck - 1)] : 0.f;
+#pragma unroll
+    for (int i = 0; i < kProbeClusters; ++i)
+      if (lh == 0) s_w[wave][i][li] = live ? __expf(fminf(w[i] - m_a, kMaxExponent)) : 0.f;
+  }
+  if (VALUE_AWARE) {  // |vbar_b|^2: D/64 dims per lane, then across the wave
+    for (int i = wave; i < clusters; i += kProbeWaves) {
+      const float* vb = vbar + ((int64_t)bh * Ck + min(b_lo + i, Ck - 1)) * D;
+      float nvb = 0.f;
+#pragma unroll
+      for (int t = 0; t < D / 64; ++t) nvb = __builtin_fmaf(vb[lane + 64 * t], vb[lane + 64 * t], nvb);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) nvb += __shfl_xor(nvb, o);
+      if (lane == 0) s_nvb[i] = nvb;
+    }
+  }
   SVGEAR_WAIT_VMCNT(0);  // from here on vmcnt counts the block copies only
   const bf16_t* kh = kp + (int64_t)bh * Nk * D;
   const float* ndh = nd + (int64_t)bh * stat_stride;
@@ -493,8 +529,8 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   struct Cursor { int b, start, end, j0; };
   auto seek = [&](Cursor& c) {  // first non-empty cluster at or after c.b
     while (c.b < b_end) {
-      c.start = off[c.b];
-      c.end = off[c.b + 1];
+      c.start = __builtin_amdgcn_readlane(bounds, c.b - b_lo);
+      c.end = __builtin_amdgcn_readlane(bounds, c.b + 1 - b_lo);
       if (c.end > c.start) break;
       ++c.b;
     }
@@ -511,14 +547,14 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   auto swz = [](int r) { return CPR == 16 ? (r & 15) : ((r >> 1) & 7); };
   auto issue = [&](const Cursor& c, int k) {  // block k of the sequence; rows past the cluster's end repeat its last key
     const int buf = k % kProbeStages;
+    const bf16_t* base = kh + (int64_t)c.j0 * D;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int inst = wave * NCH + i;
       const int row = inst * RPI + lane / CPR;
       const int chunk = (lane % CPR) ^ swz(row);
-      const int jr = min(c.j0 + row, c.end - 1);
-      async_copy_16B(kh + (int64_t)jr * D + chunk * 8,
-                     __builtin_amdgcn_readfirstlane(lds_k + buf * TILE_B + inst * 1024));
+      const uint32_t at = (uint32_t)min(row, c.end - 1 - c.j0) * (D * 2) + chunk * 16;
+      async_copy_16B(base, at, __builtin_amdgcn_readfirstlane(lds_k + buf * TILE_B + inst * 1024));
     }
     if (VALUE_AWARE) {  // every wave copies the 64 statistics (same values to the same words)
       const int j = min(c.j0 + li, c.end - 1);
@@ -538,7 +574,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
     issue(fc, issued);
     advance(fc);
   }
-  float E = 0.f, W = 0.f, nvb = 0.f;
+  float E = 0.f, U = 0.f, W = 0.f, nvb = 0.f;
   f32x16 acc_even, acc_odd;  // logits of the even and odd blocks
   // logits of block k (MF) and errors of block k - 1 (RANK: 0 none, 1 a full block, 2 a cluster's last one,
   // whose unused rows do not count)
@@ -580,21 +616,25 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       if (D == 64 && s + 1 < KSN) rd_stats(s + 1);
       if constexpr (RANK != 0) {
         // register r is key j0 + 8(r/4) + 4lh + r%4, query centroid a. Per key, with u = W - w:
-        //   |W vbar - w v_j|^2 = u (u |vbar|^2 - 2 w vbar.delta_j) + w^2 |delta_j|^2
+        //   |W vbar - w v_j|^2 = u^2 |vbar|^2 + w (-2 u vbar.delta_j + w |delta_j|^2),
+        // the u^2 in a sum of their own, which takes its factor at the end of the cluster
 #pragma unroll
         for (int r = s * RPS; r < (s + 1) * RPS; ++r) {
           const float w = __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(acc[r], scale2, neg_m2), cap2));
           const float u = W - w;
-          float e;
-          if (VALUE_AWARE) {
-            e = __builtin_fmaf(u, __builtin_fmaf(w, dl[r], u * nvb), E);
-            e = __builtin_fmaf(w * w, nn[r], e);
-          } else {
-            e = __builtin_fmaf(u, u, E);
+          float uu = __builtin_fmaf(u, u, U), e = E;
+          if (VALUE_AWARE) e = __builtin_fmaf(w, __builtin_fmaf(u, dl[r], w * nn[r]), E);
+          // (an unused row, which repeats the cluster's last key, does not count: a select of the sums, no
+          // product of 0 with a value that has overflowed, and no branch per register: the compiler would
+          // rather make one)
+          if constexpr (RANK == 2) {
+            asm volatile("" : "+v"(uu), "+v"(e));
+            const bool used = pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end;
+            uu = used ? uu : U;
+            e = used ? e : E;
           }
-          // (an unused row, which repeats the cluster's last key, does not count: a select of the sum, no
-          // branch per register, and no product of 0 with a value that has overflowed)
-          E = RANK == 1 || pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end ? e : E;
+          U = uu;
+          E = e;
         }
       }
     }
@@ -605,34 +645,28 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   using Last = std::integral_constant<int, 2>;
   auto iteration = [&](int k, f32x16& acc_new, f32x16& acc) __attribute__((always_inline)) {
     const bool mf = k < issued;  // block k exists
-    if (mf) {
-      // it has landed once at most the copies of the later blocks are outstanding
-      const int ahead = issued - k - 1;
+    if (mf && (k & 1) == 0) {  // blocks k and k + 1 have landed once at most the copies of later ones are outstanding
+      const int ahead = issued - k - 2;
       if (ahead >= 2) SVGEAR_WAIT_VMCNT(2 * LPB);
       else if (ahead == 1) SVGEAR_WAIT_VMCNT(LPB);
       else SVGEAR_WAIT_VMCNT(0);
-      __syncthreads();  // everyone's part of block k is in LDS; everyone is done with iteration k - 1
-      if (fc.b < b_end) {
-        issue(fc, issued);
-        advance(fc);
-        ++issued;
-      }
+      __syncthreads();  // everyone's part of them is in LDS; everyone is done with the pair before
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (fc.b < b_end) {
+          issue(fc, issued);
+          advance(fc);
+          ++issued;
+        }
     }
     if (k == 0) {
       if (wave_on) block(k, acc_new, acc, std::true_type{}, No{});
       return true;
     }
     if (pc.j0 == pc.start) {  // first block of key cluster pc.b
-      E = 0.f;
-      W = live ? __expf(fminf(sbar[((int64_t)bh * Cq + a) * Ck + pc.b] - m_a, kMaxExponent)) : 0.f;
-      nvb = 0.f;
-      if (VALUE_AWARE) {  // |vbar_b|^2: D/64 dims per lane, then across the wave
-        const float* vb = vbar + ((int64_t)bh * Ck + pc.b) * D;
-#pragma unroll
-        for (int t = 0; t < D / 64; ++t) nvb = __builtin_fmaf(vb[lane + 64 * t], vb[lane + 64 * t], nvb);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) nvb += __shfl_xor(nvb, o);
-      }
+      E = U = 0.f;
+      W = s_w[wave][pc.b - b_lo][li];
+      nvb = VALUE_AWARE ? s_nvb[pc.b - b_lo] : 0.f;
     }
     if (wave_on) {
       const bool full = pc.j0 + 32 <= pc.end;
@@ -641,7 +675,9 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       else if (full) block(k, acc_new, acc, std::false_type{}, Full{});
       else block(k, acc_new, acc, std::false_type{}, Last{});
       if (pc.j0 + 32 >= pc.end) {  // last block of the cluster
-        const float Et = E + __shfl_xor(E, 32);
+        // (both lanes' sums first: a lane without a key would multiply 0 by a norm that may have overflowed)
+        float Et = U + __shfl_xor(U, 32);
+        if (VALUE_AWARE) Et = __builtin_fmaf(Et, nvb, E + __shfl_xor(E, 32));
         if (lh == 0) sc[wave][li][pc.b - b_lo] = Et / (float)(pc.end - pc.start);
       }
     }
@@ -684,15 +720,22 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
     const int64_t stat_stride = probe_stat_stride(Nk);
     const bf16_t* k16 = static_cast<const bf16_t*>(kp);
     const bf16_t* v16 = static_cast<const bf16_t*>(vp);
-    const dim3 gs(Ck, BH), gb((unsigned)ceil_div(Ck, kProbeClusters), BH, (unsigned)ceil_div(ceil_div(Cq, 32), 4));
+    const int groups = (int)ceil_div(ceil_div(Cq, 32), kProbeWaves);
+    // key clusters a workgroup: its start (fragments, weights, the first copies) is worth some three clusters of
+    // 75 keys, but a launch wants two rounds of the 512 workgroups that are resident at once. us a call with 1, 2, 4, 8:
+    // 40 heads, 300 x 1,000 centroids 2205, 1840, 1561, 1493; 5 x 200 x 500 247, 231, 225, 234; 8 x 30 x 60 38, 40, 44, 50
+    const int64_t units = (int64_t)BH * Ck * groups;
+    const int clusters = units >= 8192 ? kProbeClusters : units >= 2048 ? 4 : units >= 1024 ? 2 : 1;
+    const dim3 gs(Ck, BH);
+    const unsigned gb = (unsigned)(align_up(ceil_div(Ck, clusters) * BH, 8) * groups);
     if (value_aware) {
       if (d == 64) value_stats_kernel<64><<<gs, 256, 0, s>>>(vbar, v16, k_offsets, Nk, stat_stride, Ck, nd, dd);
       else value_stats_kernel<128><<<gs, 256, 0, s>>>(vbar, v16, k_offsets, Nk, stat_stride, Ck, nd, dd);
       SVGEAR_LAUNCH_CHECK();
     }
 #define SVGEAR_PM(D, VA)                                                                                     \
-  block_error_mfma_kernel<D, VA><<<gb, 256, 0, s>>>(q3, vbar, k16, k_offsets, sbar, mrow, nd, dd, Nk, stat_stride, \
-                                                    Cq, Ck, scale, scores)
+  block_error_mfma_kernel<D, VA><<<gb, 64 * kProbeWaves, 0, s>>>(q3, vbar, k16, k_offsets, sbar, mrow, nd, dd, Nk, stat_stride, \
+                                                    Cq, Ck, scale, clusters, groups, BH, scores)
     if (d == 64) { if (value_aware) SVGEAR_PM(64, true); else SVGEAR_PM(64, false); }
     else { if (value_aware) SVGEAR_PM(128, true); else SVGEAR_PM(128, false); }
 #undef SVGEAR_PM

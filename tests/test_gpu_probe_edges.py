@@ -139,3 +139,25 @@ def test_fp32_scores_of_many_small_clusters(d, Ck, Cq, plain):
         got = to_np(r["scores"][0, h]).astype(np.float64)
         assert not got[:, sizes == 0].any()
         assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Ck,Cq", [(35, 30, 40), (36, 29, 40), (70, 30, 130), (75, 28, 31), (300, 28, 40), (290, 29, 130)])
+def test_scores_do_not_depend_on_the_clusters_a_workgroup_takes(H, Ck, Cq, d):
+    """Few heads give a workgroup one key cluster, many two, four or eight, side by side with the other groups of 128
+    query centroids: every head's scores are those of a call with that head alone, bit for bit."""
+    g = torch.Generator().manual_seed(H + d)
+    sizes = torch.randint(0, 70, (H, Ck), generator=g)
+    sizes[:, 0] = 70 * Ck - sizes[:, 1:].sum(1)  # the same number of keys in every head
+    n = 70 * Ck
+    q, kb, vb = (torch.randn(1, H, c, d, generator=g) for c in (Cq, Ck, Ck))
+    lab = torch.stack([torch.repeat_interleave(torch.arange(Ck), s) for s in sizes])
+    rows = lambda t: (torch.gather(t[0], 1, lab[:, :, None].expand(H, n, d)) + 0.3 * torch.randn(H, n, d, generator=g)).bfloat16()[None]
+    koff = torch.cat([torch.zeros(H, 1, dtype=torch.int64), sizes.cumsum(1), torch.full((H, 1), n)], 1).int()[None]
+    qoff = torch.cat([torch.arange(Cq + 1) * 3, torch.tensor([3 * Cq])]).int().expand(1, H, Cq + 2)
+    a = [t.contiguous().to(dev()) for t in (q, kb, vb, rows(kb), rows(vb), qoff, koff)]
+    got = sv.probe_route(*a, n, d ** -0.5, Nq=3 * Cq)["scores"]
+    for h in (0, 1, H // 2, H - 1):
+        one = sv.probe_route(*(t[:, h:h + 1].contiguous() for t in a), n, d ** -0.5, Nq=3 * Cq)["scores"]
+        torch.cuda.synchronize()
+        assert torch.isfinite(one).all() and torch.equal(got[:, h:h + 1], one)
