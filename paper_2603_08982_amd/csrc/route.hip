@@ -253,22 +253,31 @@ __device__ __forceinline__ int mask_row(const float* sc, const int32_t* qo, cons
   const int Cc = Ck + 1, W = (Cc + 31) / 32, lane = threadIdx.x & 63;
   const int64_t qa = qo[a + 1] - qo[a];
   int cnt = 0;
-  for (int b0 = 0; b0 < W * 32; b0 += 64) {
-    const int b = b0 + lane;
-    bool on = false;
-    if (qa > 0 && b < Cc) {
-      const int64_t kb = ko[b + 1] - ko[b];
-      if (kb > 0) {
-        on = (a == Cq) || (b == Ck);
-        if (!on) on = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b)) > ks;
-        if (on) cost += qa * kb;
-      }
+  constexpr int U = 4;  // steps whose loads are in flight together
+  for (int b00 = 0; b00 < W * 32; b00 += 64 * U) {
+    int32_t size[U];
+    float score[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = min(b00 + 64 * u + lane, Ck);
+      size[u] = ko[b + 1] - ko[b];
+      score[u] = a < Cq && b < Ck ? sc[(int64_t)a * Ck + b] : 0.f;
     }
-    const unsigned long long bits = __ballot(on);
-    cnt += __popcll(bits);
-    if (lane == 0) {
-      words[b0 >> 5] = (uint32_t)bits;
-      if ((b0 >> 5) + 1 < W) words[(b0 >> 5) + 1] = (uint32_t)(bits >> 32);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b0 = b00 + 64 * u, b = b0 + lane;
+      if (b0 >= W * 32) break;
+      bool on = false;
+      if (qa > 0 && b < Cc && size[u] > 0) {
+        on = a == Cq || b == Ck || block_key(score[u], (uint32_t)(a * Ck + b)) > ks;
+        if (on) cost += qa * (int64_t)size[u];
+      }
+      const unsigned long long bits = __ballot(on);
+      cnt += __popcll(bits);
+      if (lane == 0) {
+        words[b0 >> 5] = (uint32_t)bits;
+        if ((b0 >> 5) + 1 < W) words[(b0 >> 5) + 1] = (uint32_t)(bits >> 32);
+      }
     }
   }
   return cnt;
@@ -373,7 +382,7 @@ route_small_kernel(const float* __restrict__ scores, const int32_t* __restrict__
 // build_kernel 0.35 ms on 40 of 256 CUs. From kWideItems blocks a head on the work is spread:
 // two streaming passes over all CUs, after which a single workgroup sees only the blocks of one
 // 12-bit digit (an eighth of an octave of scores, a few thousand blocks). Measured at 300 x 1000
-// x 40 heads: cut, mask and lists 2.04 -> 0.25 ms (of a whole call of 3.74 before and 1.87 now). Small
+// x 40 heads: cut, mask and lists 2.04 -> 0.15 ms (of a whole call of 3.74 before and 1.36 now). Small
 // heads stay with one workgroup, three launches fewer (1,800 blocks 19 us a call from given scores); at
 // the line one head takes 65 us below it and 39 above.
 constexpr int kWideItems = 16384;
@@ -474,19 +483,36 @@ route_collect_kernel(const float* __restrict__ scores, const int32_t* __restrict
   float v[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) v[u] = lo + u * kHistThreads < n_items ? sc[lo + u * kHistThreads] : 0.f;
+  unsigned int mine = 0;  // a bit per block of this thread
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const int i = lo + u * kHistThreads;
-    const bool on = i < n_items && (int)(block_key(v[u], (uint32_t)i) >> (64 - kHistBits)) == digit &&
-                    block_cost(qo, ko, i, Ck) != 0ull;
-    const unsigned long long votes = __ballot(on);
-    if (!votes) continue;
-    const int leader = __ffsll((long long)votes) - 1;
-    unsigned int at = 0;
-    if (lane == leader) at = atomicAdd(&hc.n_cand, (unsigned int)__popcll(votes));
-    at = __shfl(at, leader) + (unsigned int)__popcll(votes & ((1ull << lane) - 1ull));
-    if (on) cand[(int64_t)bh * n_items + at] = (uint32_t)i;
+    if (i < n_items && (int)(block_key(v[u], (uint32_t)i) >> (64 - kHistBits)) == digit && block_cost(qo, ko, i, Ck) != 0ull)
+      mine |= 1u << u;
   }
+  // one addition to the head's counter per workgroup (one per 64 blocks with a hit: 75 us at 300 x 1000 x 40 heads,
+  // additions to a line follow each other at some 57 ns; this way 28)
+  __shared__ int wave_cand[kHistThreads / 64], base_s;
+  const int n_mine = __popc(mine);
+  int upto = n_mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(upto, o);
+    if (lane >= o) upto += t;
+  }
+  if (lane == 63) wave_cand[wave] = upto;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int all = 0;
+    for (int w = 0; w < kHistThreads / 64; ++w) all += wave_cand[w];
+    base_s = all ? (int)atomicAdd(&hc.n_cand, (unsigned int)all) : 0;
+  }
+  __syncthreads();
+  int at = base_s + upto - n_mine;
+  for (int w = 0; w < wave; ++w) at += wave_cand[w];
+#pragma unroll
+  for (int u = 0; u < 16; ++u)
+    if (mine & (1u << u)) cand[(int64_t)bh * n_items + at++] = (uint32_t)(lo + u * kHistThreads);
 }
 
 // grid (BH): the cut among the collected blocks
@@ -520,16 +546,21 @@ route_mask_kernel(const float* __restrict__ scores, const int32_t* __restrict__ 
                   int64_t* __restrict__ routed_cost) {
   const int bh = blockIdx.y, lane = threadIdx.x & 63, a = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int R = Cq + 1, W = (Ck + 1 + 31) / 32;
-  if (a >= R) return;
+  __shared__ long long part[4];
   long long cost = 0;
-  const int cnt = mask_row(scores + (int64_t)bh * Cq * Ck, q_offsets + (int64_t)bh * (Cq + 2),
-                           k_offsets + (int64_t)bh * (Ck + 2), Cq, Ck, a,
-                           a < Cq ? kstar[(int64_t)bh * (per_row ? Cq : 1) + (per_row ? a : 0)] : 0ull,
-                           mask_bits + ((int64_t)bh * R + a) * W, cost);
+  if (a < R) {
+    const int cnt = mask_row(scores + (int64_t)bh * Cq * Ck, q_offsets + (int64_t)bh * (Cq + 2),
+                             k_offsets + (int64_t)bh * (Ck + 2), Cq, Ck, a,
+                             a < Cq ? kstar[(int64_t)bh * (per_row ? Cq : 1) + (per_row ? a : 0)] : 0ull,
+                             mask_bits + ((int64_t)bh * R + a) * W, cost);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
-  if (lane == 0) {
-    row_count[(int64_t)bh * R + a] = cnt;
+    for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
+    if (lane == 0) row_count[(int64_t)bh * R + a] = cnt;
+  }
+  if (lane == 0) part[threadIdx.x >> 6] = cost;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    cost = part[0] + part[1] + part[2] + part[3];
     if (cost) atomicAdd(reinterpret_cast<unsigned long long*>(routed_cost + bh), (unsigned long long)cost);
   }
 }
