@@ -103,10 +103,9 @@ static inline int64_t sort_chunks(int64_t N) { return ceil_div(N, kSortChunk); }
 // tiles of at most tile_len positions that never straddle a cluster: tile
 // t = floor(offsets[c] / tile_len) + c + j is positions offsets[c] + tile_len j .. of cluster c, stored
 // as (c, first position, end position, 0); indices no cluster uses hold c = -1.
-// rank (optional, [BH][N]): the position of every token in the sorted order (perm's inverse).
 int sort_labels(const int32_t* labels, int BH, int64_t N, int64_t n_tail, int C, int32_t* perm,
                 int32_t* offsets, int32_t* chunk_hist, hipStream_t s, int4* tiles = nullptr, int tile_cap = 0,
-                int tile_len = 64, int32_t* rank = nullptr);
+                int tile_len = 64);
 
 
 // Per-head length of the probe's per-key statistic arrays (padded so that 16-byte reads

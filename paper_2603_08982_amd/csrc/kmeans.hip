@@ -32,11 +32,14 @@
 namespace svgear {
 namespace {
 
-// per head: [0] rows queued for assign_filter_kernel; as float bits: [1] max |x| of the flagged rows, [2] max |c|^2
-constexpr int kHeadState = 4;
+// Counters and maxima of a head, in cache lines of their own (additions to one line from all XCDs follow each other at
+// some 57 ns: with the heads' counters of undecided rows side by side 40 heads of 75,600 keys spent 0.2 to 0.5 ms an
+// iteration on them): rows queued for assign_filter_kernel; as float bits max |x| of the flagged rows and max |c|^2;
+// undecided rows.
+constexpr int kQueued = 0, kMaxX = 64, kMaxC = 65, kUndecided = 128;
+constexpr int kHeadState = 192;
 constexpr int kListMax = 128;                   // longest candidate list of a cluster (longer: every centroid)
-constexpr int kListTile = 64;                   // sorted positions per step of a wave of assign_list_kernel
-constexpr int kListChunk = 4 * kListTile;       // sorted positions per wave (one cluster's)
+constexpr int kListChunk = 256;                 // sorted positions per wave of assign_list_kernel (one cluster's)
 constexpr int kMaxCentroids = 8192;             // most centroids per head the entry point accepts
 // Candidate lists pay when there are many centroids: with fewer than this, testing every
 // centroid (shared through LDS by 256 rows, streaming) costs no more than the lists' gathers.
@@ -61,18 +64,17 @@ constexpr int kListFromIteration = SVGEAR_LIST_FROM;
 //    the operand order of v_mfma_f32_32x32x16_bf16 (A[i = lane%32][k = 16s + 8(lane/32) + e]):
 //    [blk][piece][s][lane][e], 16 bytes per lane; crow (with chl): the same two pieces row by row,
 //    [c][piece][d], for the kernel that fetches single centroids;
-//  * amb_count, head_state, rmax, dirty (optional): the per-iteration counters, maxima and flags are reset.
+//  * head_state, rmax, dirty (optional): the per-iteration counters, maxima and flags are reset.
 __global__ void __launch_bounds__(256)
 prep_centroids_kernel(const float* __restrict__ cent, int C, int Cpad, int d, float* __restrict__ cperm,
                       float* __restrict__ cn, bf16_t* __restrict__ chl, bf16_t* __restrict__ crow,
-                      int32_t* __restrict__ amb_count, int32_t* __restrict__ head_state, int32_t* __restrict__ rmax,
-                      int32_t* __restrict__ dirty, int32_t* __restrict__ small_state, float* __restrict__ small_norms) {
+                      int32_t* __restrict__ head_state, int32_t* __restrict__ rmax, int32_t* __restrict__ dirty,
+                      int32_t* __restrict__ small_state, float* __restrict__ small_norms) {
   const int bh = blockIdx.y;
   if (small_state && blockIdx.x == 0)
     for (int i = threadIdx.x; i < kSmallState; i += 256) small_state[bh * kSmallState + i] = 0;
   const float* cb = cent + (int64_t)bh * C * d;
   const int64_t n = (int64_t)Cpad * d;
-  if (amb_count && blockIdx.x == 0 && threadIdx.x == 0) amb_count[bh] = 0;
   if (head_state && blockIdx.x == 0 && threadIdx.x < kHeadState) head_state[bh * kHeadState + threadIdx.x] = 0;
   // both operand tables are written 16 bytes per thread from 32 contiguous bytes of a centroid row
   if (chl) {
@@ -293,7 +295,7 @@ template <int D>
 __device__ __forceinline__ void settle_row(float best, float second, int arg, bool valid, int64_t row, float X,
                                            float Cm, float far_lb, const int32_t* __restrict__ positions, int cur,
                                            int bh, int64_t nv, int Cpad, int32_t* __restrict__ labels,
-                                           int2* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
+                                           int2* __restrict__ amb_rows, int32_t* __restrict__ head_state,
                                            float2* __restrict__ bnd, int32_t* __restrict__ dirty) {
   constexpr float kappa = 1.52587890625e-05f + (2 * D + 1) * 1.1920928955078125e-07f + D * 5.9604644775390625e-08f;
   const int lane = threadIdx.x & 63, lh = lane >> 5;
@@ -319,7 +321,7 @@ __device__ __forceinline__ void settle_row(float best, float second, int arg, bo
       const unsigned long long am = __ballot(1);
       const int leader = __ffsll((long long)am) - 1;
       int slot = 0;
-      if (lane == leader) slot = atomicAdd(&amb_count[bh], __popcll(am));
+      if (lane == leader) slot = atomicAdd(&head_state[bh * kHeadState + kUndecided], __popcll(am));
       slot = __shfl(slot, leader) + __popcll(am & ((1ull << lane) - 1ull));
       // no centroid whose filter score exceeds this can be the fixed-order argmin (rounded up)
       const float limit = __builtin_fmaf(2.0002f, B, lo) + 2.384185791015625e-07f * fabsf(lo);
@@ -347,13 +349,13 @@ __device__ __forceinline__ void settle_row(float best, float second, int arg, bo
 //   B = 2 X Cm kappa + 2^-23 (Cm^2 + 2 X Cm).
 // If second - best > 2B the fixed-order argmin is the filter's argmin; otherwise the row is
 // queued for the exact kernel. With row_list != nullptr only the rows listed there
-// (row_count[kHeadState bh] of them, in any order) are assigned.
+// (as many as the head has queued, in any order) are assigned.
 template <int D, bool RESIDENT>
 __global__ void __launch_bounds__(64 * kFilterWaves) __attribute__((amdgpu_waves_per_eu(2)))
 assign_filter_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, const bf16_t* __restrict__ chl,
                      const float* __restrict__ cn, float* __restrict__ xnorm, int C, int Cpad,
-                     int32_t* __restrict__ labels, int2* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
-                     const int32_t* __restrict__ row_list, const int32_t* __restrict__ row_count,
+                     int32_t* __restrict__ labels, int2* __restrict__ amb_rows, int32_t* __restrict__ head_state,
+                     const int32_t* __restrict__ row_list,
                      float2* __restrict__ bnd, int32_t* __restrict__ dirty) {
   constexpr int KSN = D / 16;
   constexpr int CHUNK_BYTES = kCentChunk * D * 2 * 2;  // 64 centroids, hi and lo pieces
@@ -363,7 +365,7 @@ assign_filter_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv
   float* cns = reinterpret_cast<float*>(smem + 2 * CHUNK_BYTES);  // [Cpad] |c|^2 of every centroid
   float* red = cns + Cpad;                                        // [64 * kFilterWaves]
   const int bh = blockIdx.y;
-  const int64_t n_rows = row_list ? row_count[bh * kHeadState] : nv;
+  const int64_t n_rows = row_list ? head_state[bh * kHeadState + kQueued] : nv;
   if ((int64_t)blockIdx.x * kFilterRows >= n_rows) return;
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -530,7 +532,7 @@ assign_filter_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv
 #pragma unroll
   for (int rs = 0; rs < 2; ++rs)
     settle_row<D>(best[rs], second[rs], arg[rs], valid[rs], rows[rs], xn[rs], Cm, INFINITY, nullptr, cur[rs], bh, nv,
-                  Cpad, labels, amb_rows, amb_count, bnd, dirty);
+                  Cpad, labels, amb_rows, head_state, bnd, dirty);
   grp += gridDim.x;
   } while (RESIDENT && grp * kFilterRows < n_rows);
 }
@@ -564,7 +566,7 @@ __global__ void __launch_bounds__(256, 3)
 assign_few_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, const bf16_t* __restrict__ chl,
                   const float* __restrict__ cent, const float* __restrict__ cperm, const float* __restrict__ cn, int C,
                   int Cpad, int32_t* __restrict__ labels, const int2* __restrict__ amb_rows,
-                  const int32_t* __restrict__ amb_count, int32_t* __restrict__ dirty, int BH, int per_head) {
+                  const int32_t* __restrict__ head_state, int32_t* __restrict__ dirty, int BH, int per_head) {
   constexpr int KSN = D / 16;
   constexpr int QG = D / 8;  // 16-byte fp32 operand groups per 32-block
   __shared__ int s_row[kFewRows];
@@ -579,7 +581,7 @@ assign_few_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, c
   if (bh >= BH) return;
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t n_rows = amb_count[bh];
+  const int64_t n_rows = head_state[bh * kHeadState + kUndecided];
   const float* cnb = cn + (int64_t)bh * Cpad;
   const bf16_t* xh = x + head_base(st, bh, H);
   for (int64_t tile = logical % per_head; tile * kFewRows < n_rows; tile += per_head) {
@@ -727,6 +729,8 @@ assign_few_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, c
 }
 
 constexpr int kBoundRows = 8;  // rows per thread of bounds_update_kernel
+// 64-bit words that hold a bit per row of a head
+__host__ __device__ static inline int64_t flag_words(int64_t nv) { return (nv + 63) / 64; }
 
 // Per head: Cm^2 = max |c|^2, the largest and second largest centroid move, and whose the
 // largest is. Every workgroup of bounds_update_kernel works them out for itself from the
@@ -780,25 +784,34 @@ __device__ __forceinline__ void head_stats(const float* __restrict__ cn, const f
 // label, strictly, so the row is skipped and keeps its label with the widened bounds;
 // otherwise it is flagged. Skipping never changes a label, so the result is the same as
 // assigning every row in every iteration.
-// LISTS = false: the flagged rows are queued (act_rows, counted in head_state[kHeadState bh])
+// LISTS = false: the flagged rows are queued (act_rows, counted in the head's state)
 // for assign_filter_kernel.
-// LISTS = true: they are left to assign_list_kernel: prow, indexed by the row's position in the
-// sorted order of the previous iteration, holds the row's index (-1 for a skipped row); per
+// LISTS = true: they are left to assign_list_kernel: a bit per row in `flags`; per
 // cluster the kernel records rmax = the largest u among its flagged rows (the radius the
 // cluster's candidate list is built for; non-negative floats order like their bit patterns),
 // per head the largest |x| among the flagged rows and max |c|^2.
+// The largest move of a head is that of some centroid far away, as a rule. With the previous iteration's candidate
+// lists (near, from neighbour_drift_kernel: of cluster a the largest move m among the centroids its list names and the
+// distance f from centroid a to the nearest one it leaves out, before the moves) a centroid is either in the list and
+// at least lb - m away or not and at least f - ub - (largest drift among the others): the smaller of the two is a
+// bound as well, and the larger bound counts.
 template <int D, bool LISTS>
 __global__ void __launch_bounds__(256)
 bounds_update_kernel(const int32_t* __restrict__ labels, const float* __restrict__ xnorm,
                      const float* __restrict__ cn, const float* __restrict__ drift, int C, int Cpad, int64_t nv,
-                     float2* __restrict__ bnd, int32_t* __restrict__ act_rows, const int32_t* __restrict__ rank,
-                     int32_t* __restrict__ prow, int32_t* __restrict__ rmax, int32_t* __restrict__ head_state) {
+                     float2* __restrict__ bnd, int32_t* __restrict__ act_rows, uint64_t* __restrict__ flags,
+                     const float2* __restrict__ near, int32_t* __restrict__ rmax, int32_t* __restrict__ head_state) {
   const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float cm2, d1, d2;
   int a1;
   head_stats(cn + (int64_t)bh * Cpad, drift + (int64_t)bh * Cpad, C, cm2, d1, d2, a1);
   const float Cm = sqrtf(cm2) * 1.00002f;
-  if (LISTS && blockIdx.x == 0 && tid == 0) head_state[bh * kHeadState + 2] = __float_as_int(cm2);
+  extern __shared__ int32_t s_rmax[];  // LISTS: the radii of this workgroup's rows (one addition per cluster, not per row)
+  if constexpr (LISTS) {
+    for (int c = tid; c < C; c += 256) s_rmax[c] = 0;
+    __syncthreads();
+  }
+  if (LISTS && blockIdx.x == 0 && tid == 0) head_state[bh * kHeadState + kMaxC] = __float_as_int(cm2);
 
   // kBoundRows rows per thread, 256 apart (a launch of one-row threads is bound by the rate at
   // which workgroups start, not by memory)
@@ -807,31 +820,44 @@ bounds_update_kernel(const int32_t* __restrict__ labels, const float* __restrict
 #pragma unroll
   for (int j = 0; j < kBoundRows; ++j) {
     const int64_t row = ((int64_t)blockIdx.x * kBoundRows + j) * 256 + tid;
+    bool flagged = false;
     if (row < nv) {
       const int a = labels[(int64_t)bh * nv + row];
       const float2 st = bnd[(int64_t)bh * nv + row];
       const float X = xnorm[(int64_t)bh * nv + row];
       const float u = (st.x + drift[(int64_t)bh * Cpad + a]) * 1.000001f;
-      const float l = (st.y - (a == a1 ? d2 : d1)) * 0.999999f;
+      const float others = a == a1 ? d2 : d1;
+      float l = st.y - others;
+      if (LISTS && near) {
+        const float2 nb = near[(int64_t)bh * C + a];
+        l = fmaxf(l, fminf(st.y - nb.x, nb.y * 0.99999f - st.x - others));
+      }
+      l *= 0.999999f;
       const float E = fixed_order_error<D>(X, Cm);
       const bool keep = l > u && (l - u) * (l + u) > 2.002f * E;  // false for NaN
       bnd[(int64_t)bh * nv + row] = make_float2(u, l > 0.f ? l : 0.f);
       if constexpr (LISTS) {
-        prow[(int64_t)bh * nv + rank[(int64_t)bh * nv + row]] = keep ? -1 : (int32_t)row;
+        flagged = !keep;
         if (!keep) {
-          const int ubits = __float_as_int(u);
-          // (the plain read only saves atomics: most rows find a radius that already covers them)
-          if (ubits > rmax[(int64_t)bh * Cpad + a]) atomicMax(&rmax[(int64_t)bh * Cpad + a], ubits);
+          atomicMax(&s_rmax[a], __float_as_int(u));
           xmax = fmaxf(xmax, X);
         }
       }
       if (!LISTS && !keep) qmask |= 1u << j;
     }
+    if constexpr (LISTS) {
+      const uint64_t bits = __ballot(flagged);
+      if (lane == 0 && row < nv) flags[(int64_t)bh * flag_words(nv) + (row >> 6)] = bits;
+    }
   }
   if constexpr (LISTS) {
+    __syncthreads();
+    // (the plain read only saves atomics)
+    for (int c = tid; c < C; c += 256)
+      if (s_rmax[c] > rmax[(int64_t)bh * Cpad + c]) atomicMax(&rmax[(int64_t)bh * Cpad + c], s_rmax[c]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) xmax = fmaxf(xmax, __shfl_xor(xmax, o));
-    if (lane == 0 && xmax > 0.f) atomicMax(&head_state[bh * kHeadState + 1], __float_as_int(xmax));
+    if (lane == 0 && xmax > 0.f) atomicMax(&head_state[bh * kHeadState + kMaxX], __float_as_int(xmax));
   } else {
     // queue the rows of this workgroup with one counter update: exclusive scan of the per-thread
     // counts (wave shuffles, then the four wave totals)
@@ -847,7 +873,7 @@ bounds_update_kernel(const int32_t* __restrict__ labels, const float* __restrict
     __syncthreads();
     if (tid == 0) {
       const int total = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-      s_base = total ? atomicAdd(&head_state[bh * kHeadState], total) : 0;
+      s_base = total ? atomicAdd(&head_state[bh * kHeadState + kQueued], total) : 0;
     }
     __syncthreads();
     int pos = s_base + incl - cnt;
@@ -902,10 +928,14 @@ nlist_kernel(const bf16_t* __restrict__ chl, const float* __restrict__ cn, int C
   }
   const float cna = a < C ? cnb[a] : 0.f;
   const float r2 = a < C ? 2.0f * __int_as_float(rmax[(int64_t)bh * Cpad + a]) * 1.000001f : 0.f;
-  const float Cm = sqrtf(__int_as_float(head_state[bh * kHeadState + 2])) * 1.00002f;
-  const float E2 = 2.002f * fixed_order_error<D>(__int_as_float(head_state[bh * kHeadState + 1]), Cm);
+  const float Cm = sqrtf(__int_as_float(head_state[bh * kHeadState + kMaxC])) * 1.00002f;
+  const float E2 = 2.002f * fixed_order_error<D>(__int_as_float(head_state[bh * kHeadState + kMaxX]), Cm);
+  // d > 2R and d (d - 2R) > 2E as one comparison of d^2 (both roots of a pair took most of the kernel's time): d above
+  // the larger root of d^2 - 2R d - 2E, everything rounded up
+  const float root = 0.5f * (r2 + sqrtf(r2 * r2 + 4.002f * E2)) * 1.00001f;
+  const float apart = root * root * 1.00002f;
   int mine = 0;  // entries of cluster a this lane contributes
-  float dmin = INFINITY;
+  float dmin = INFINITY;  // (squared until the end)
   for (int cb = wave; cb * 32 < C; cb += 4) {
     f32x16 acc;
 #pragma unroll
@@ -930,10 +960,9 @@ nlist_kernel(const bf16_t* __restrict__ chl, const float* __restrict__ cn, int C
         const int c = 32 * cb + 8 * g + 4 * lh + r;
         const float nsum = cna + nn[r];
         const float dd2 = nsum - 2.0f * acc[4 * g + r] - 1.2e-4f * nsum;  // lower bound of |a - c|^2
-        const float d = sqrtf(fmaxf(dd2, 0.f)) * 0.999999f;               // lower bound of |a - c|
-        const bool out_c = d > r2 && d * (d - r2) * 0.9999f > E2;         // false for NaN: kept
+        const bool out_c = dd2 > apart;                                   // false for NaN: kept
         const bool k = c < C && (!out_c || c == a);
-        if (c < C && !k) dmin = fminf(dmin, d);
+        if (c < C && !k) dmin = fminf(dmin, dd2);
         if (k) keep |= 1u << (4 * g + r);
       }
     }
@@ -944,7 +973,7 @@ nlist_kernel(const bf16_t* __restrict__ chl, const float* __restrict__ cn, int C
   dmin = fminf(dmin, __shfl_xor(dmin, 32));
   if (lh == 0) {
     s_cnt[wave][li] = mine;
-    s_dmin[wave][li] = dmin;
+    s_dmin[wave][li] = sqrtf(fmaxf(dmin, 0.f)) * 0.999999f;  // lower bound of the distance
   }
   __syncthreads();
   int run = 0, total = 0;
@@ -952,7 +981,7 @@ nlist_kernel(const bf16_t* __restrict__ chl, const float* __restrict__ cn, int C
   for (int w = 0; w < 4; ++w) {
     if (w < wave) run += s_cnt[w][li];
     total += s_cnt[w][li];
-    dmin = fminf(dmin, s_dmin[w][li]);
+    dmin = w == 0 ? s_dmin[0][li] : fminf(dmin, s_dmin[w][li]);
   }
   if (a < C && total <= kListMax) {  // (a list that is dropped is not written either)
     int32_t* out = nlist + ((int64_t)bh * C + a) * kListMax;
@@ -980,34 +1009,53 @@ nlist_kernel(const bf16_t* __restrict__ chl, const float* __restrict__ cn, int C
   }
 }
 
+// What bounds_update_kernel needs of the lists once the centroids have moved: half a wave per cluster.
+__global__ void __launch_bounds__(256)
+neighbour_drift_kernel(const float* __restrict__ drift, int C, int Cpad, const int32_t* __restrict__ nlist,
+                       const int32_t* __restrict__ nlen, const float* __restrict__ dout, float2* __restrict__ near) {
+  const int bh = blockIdx.y, a = blockIdx.x * 8 + (int)(threadIdx.x >> 5), li = threadIdx.x & 31;
+  if (a >= C) return;
+  const int n = nlen[(int64_t)bh * C + a];
+  const int32_t* lst = nlist + ((int64_t)bh * C + a) * kListMax;
+  float m = 0.f;
+  for (int e = li; e < n; e += 32) {
+    const int c = lst[e];
+    if (c != a) m = fmaxf(m, drift[(int64_t)bh * Cpad + c]);
+  }
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  if (li == 0) near[(int64_t)bh * C + a] = n >= 0 ? make_float2(m, dout[(int64_t)bh * C + a]) : make_float2(INFINITY, 0.f);
+}
+
 // Later iterations: the flagged rows against the candidate list of the cluster they are in -- a
 // centroid outside the list provably has a larger fixed-order score than the row's old
 // centroid, so the argmin over the list is the argmin over all centroids. A few clusters (wide
 // ones, whose radius reaches most centroids) have no list (nlen < 0): their flagged rows are
 // only queued here, for assign_filter_kernel, which tests every centroid and shares the
 // centroids among 256 rows. One wave takes a chunk of at most kListChunk positions of ONE cluster in
-// the sorted order (chunk table of sort_labels), 64 positions per step. Lists are short (a
-// handful to a few dozen centroids once the clustering settles), so there is nothing to share
-// between waves: no LDS, no barrier. What bounds the kernel is the number of cache lines its
-// fetches touch (every row and every candidate lies somewhere else), so
-//  * a list of at most 32 candidates is fetched once per wave and stays in registers;
+// the sorted order (chunk table of sort_labels), picks the flagged rows out of it and tests them 32 at a time. Lists are
+// short (a handful to a few dozen centroids once the clustering settles), so there is nothing to share
+// between waves: no barrier. What bounds the kernel is the number of cache lines its
+// fetches touch (every row and every candidate lies somewhere else) and the chain of dependent fetches, so
+//  * a list of at most 32 candidates is fetched once per wave and stays in registers, and the next rows are fetched
+//    while the present ones are tested;
 //  * a lane reads half a row / half a piece of "its" candidate (position lane % 32 of the list's
 //    32-block) as whole cache lines: the contraction index is permuted (the filter's scores are
 //    approximate and their error bound holds for any order of the additions), in k-step s lane
 //    (i, h) holds dims D/2 h + 8 s .. + 7 of centroid / row i;
-//  * rows that are not flagged are not fetched, and nothing of a flagged row's state is read:
+//  * rows that are not flagged are not fetched (their flags are a bit each, 9 KB a head of 75,600 rows, where a table
+//    in sorted order cost the bounds pass a scattered store a row), and nothing of a flagged row's state is read:
 //    every 4 bytes read or written at a row's index cost a whole memory transaction, as much as
 //    a quarter of the row itself. |x| is computed again from the row, the row's old upper bound
-//    is replaced by the cluster's radius, and which rows are flagged comes in position order;
-//  * the chain of dependent fetches is three long (tile -> rows and list -> operands), and the
-//    rows of the next step are looked up while this step's are ranked.
+//    is replaced by the cluster's radius.
+// 40 heads of 75,600 keys, 1,000 centroids, 8 iterations: 2,790 us; 2,560 with fewer rows flagged (neighbour_drift_kernel);
+// 1,750 with the counters of undecided rows in lines of their own. Rows 64 at a time, two to four waves a SIMD: the same.
 template <int D>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64, 3)
 assign_list_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, const bf16_t* __restrict__ crow,
                    const float* __restrict__ cn, int C, int Cpad, int32_t* __restrict__ labels,
-                   int2* __restrict__ amb_rows, int32_t* __restrict__ amb_count,
-                   const int32_t* __restrict__ prow, const int4* __restrict__ tiles, int tile_cap,
-                   const int32_t* __restrict__ rmax, const int32_t* __restrict__ nlist,
+                   int2* __restrict__ amb_rows, const int32_t* __restrict__ perm, const uint64_t* __restrict__ flags,
+                   const int4* __restrict__ tiles, int tile_cap, const int32_t* __restrict__ rmax, const int32_t* __restrict__ nlist,
                    const int32_t* __restrict__ nlen, const float* __restrict__ dout,
                    int32_t* __restrict__ head_state, int32_t* __restrict__ act_rows, float2* __restrict__ bnd,
                    int32_t* __restrict__ dirty) {
@@ -1017,37 +1065,40 @@ assign_list_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, 
   const int a_old = tile.x, p_begin = tile.y, p_end = tile.z;
   if (a_old < 0) return;
   const int n_list = nlen[(int64_t)bh * C + a_old];
-  if (n_list < 0) {  // no list: queue the flagged rows (all fetches first, then one counter update)
-    int r[kListChunk / 64];
+  // the flagged rows of the tile, in order: all fetches first
+  __shared__ int s_rows[kListChunk];
+  int n_rows = 0;
+  {
+    constexpr int J = kListChunk / 64;
+    const uint32_t* fw = reinterpret_cast<const uint32_t*>(flags + (int64_t)bh * flag_words(nv));
+    int r[J];
+    uint32_t word[J];
 #pragma unroll
-    for (int j = 0; j < kListChunk / 64; ++j) {
-      const int p = p_begin + 64 * j + lane;
-      r[j] = p < p_end ? prow[(int64_t)bh * nv + p] : -1;
+    for (int j = 0; j < J; ++j) r[j] = perm[(int64_t)bh * nv + min(p_begin + 64 * j + lane, p_end - 1)];
+#pragma unroll
+    for (int j = 0; j < J; ++j) word[j] = fw[r[j] >> 5];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const bool on = p_begin + 64 * j + lane < p_end && (word[j] >> (r[j] & 31) & 1u);
+      const uint64_t votes = __ballot(on);
+      if (on) s_rows[n_rows + __popcll(votes & ((1ull << lane) - 1ull))] = r[j];
+      n_rows += __popcll(votes);
     }
-    int mine = 0;
-#pragma unroll
-    for (int j = 0; j < kListChunk / 64; ++j) mine += r[j] >= 0;
-    int incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
-    }
-    const int total = __shfl(incl, 63);
-    if (total == 0) return;
+  }
+  if (n_rows == 0) return;
+  __builtin_amdgcn_wave_barrier();
+  if (n_list < 0) {  // no list: queue them
     int base = 0;
-    if (lane == 0) base = atomicAdd(&head_state[bh * kHeadState], total);
-    int slot = __shfl(base, 0) + incl - mine;
-#pragma unroll
-    for (int j = 0; j < kListChunk / 64; ++j)
-      if (r[j] >= 0) act_rows[(int64_t)bh * nv + slot++] = r[j];
+    if (lane == 0) base = atomicAdd(&head_state[bh * kHeadState + kQueued], n_rows);
+    base = __shfl(base, 0);
+    for (int i = lane; i < n_rows; i += 64) act_rows[(int64_t)bh * nv + base + i] = s_rows[i];
     return;
   }
   // a centroid outside the list is at least |a_old - c| - |x - a_old| away from a flagged row x of
   // the cluster, and the list was built for |x - a_old| <= rmax
   const float far = dout[(int64_t)bh * C + a_old] * 0.99999f -
                     __int_as_float(rmax[(int64_t)bh * Cpad + a_old]) * 1.000001f;
-  const float Cm = sqrtf(__int_as_float(head_state[bh * kHeadState + 2])) * 1.00002f;
+  const float Cm = sqrtf(__int_as_float(head_state[bh * kHeadState + kMaxC])) * 1.00002f;
   const int nblk = (n_list + 31) / 32;
   const int32_t* lst = nlist + ((int64_t)bh * C + a_old) * kListMax;
   const bf16_t* tab = crow + (int64_t)bh * 2 * Cpad * D;
@@ -1068,93 +1119,58 @@ assign_list_kernel(const bf16_t* __restrict__ x, Strides st, int H, int64_t nv, 
     for (int i = 0; i < 2 * KSN; ++i)  // hi piece (k-steps 0 .. KSN-1), then lo piece
       av[i] = as_bf16x8(*reinterpret_cast<const uint4*>(src + (i / KSN) * D + 8 * (i % KSN)));
   };
-  // rows of the step at positions p .. p + 63 (row set rs, lane li: position p + 32 rs + li) and
-  // whether they are flagged
-  auto fetch_rows = [&](int p, int64_t (&rows)[2], int (&flag)[2]) {
+  // 32 rows at a time, the next ones fetched while these are tested
+  const bf16_t* xh = x + head_base(st, bh, H) + (D / 2) * lh;
+  bf16x8 bx[KSN], bnext[KSN];
+  auto fetch_set = [&](int p) {
+    const bf16_t* xr = xh + (int64_t)s_rows[min(p + li, n_rows - 1)] * st.n;
 #pragma unroll
-    for (int rs = 0; rs < 2; ++rs) {
-      const int pos = p + 32 * rs + li;
-      const int r = pos < p_end ? prow[(int64_t)bh * nv + pos] : -1;
-      rows[rs] = r < 0 ? 0 : r;
-      flag[rs] = r >= 0;
-    }
+    for (int s = 0; s < KSN; ++s) bnext[s] = as_bf16x8(*reinterpret_cast<const uint4*>(xr + 8 * s));
   };
-
-  int64_t rows[2], rows_next[2];
-  int flag[2], flag_next[2];
-  fetch_rows(p_begin, rows, flag);
+  fetch_set(0);
   fetch_candidates(0);
-  for (int p = p_begin; p < p_end; p += kListTile) {
-    const bool more = p + kListTile < p_end;
-    if (more) fetch_rows(p + kListTile, rows_next, flag_next);
-    const bool valid[2] = {flag[0] != 0, flag[1] != 0};
-    if (__any(valid[0] || valid[1])) {  // else nothing flagged in this step (whole wave)
-      bf16x8 bx[2][KSN];
-      float xn[2];
+  for (int p = 0; p < n_rows; p += 32) {
+    const bool valid = p + li < n_rows;
+    const int64_t row = s_rows[valid ? p + li : n_rows - 1];
 #pragma unroll
-      for (int rs = 0; rs < 2; ++rs) {
+    for (int s = 0; s < KSN; ++s) bx[s] = bnext[s];
+    if (p + 32 < n_rows) fetch_set(p + 32);
+    // |x|_2 rounded up, as in assign_filter_kernel
+    float x2 = 0.f;
 #pragma unroll
-        for (int s = 0; s < KSN; ++s) bx[rs][s] = as_bf16x8(uint4{0u, 0u, 0u, 0u});
-        if (valid[rs]) {
-          const bf16_t* xr = x + head_base(st, bh, H) + rows[rs] * st.n + (D / 2) * lh;
+    for (int s = 0; s < KSN; ++s) {
+      union { bf16x8 b; uint4 u; } c;
+      c.b = bx[s];
+      const uint32_t w[4] = {c.u.x, c.u.y, c.u.z, c.u.w};
 #pragma unroll
-          for (int s = 0; s < KSN; ++s) bx[rs][s] = as_bf16x8(*reinterpret_cast<const uint4*>(xr + 8 * s));
-        }
-        // |x|_2 rounded up, as in assign_filter_kernel
-        float acc = 0.f;
-#pragma unroll
-        for (int s = 0; s < KSN; ++s) {
-          union { bf16x8 b; uint4 u; } c;
-          c.b = bx[rs][s];
-          const uint32_t w[4] = {c.u.x, c.u.y, c.u.z, c.u.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float lo = __uint_as_float(w[i] << 16), hi = __uint_as_float(w[i] & 0xffff0000u);
-            acc = __builtin_fmaf(lo, lo, acc);
-            acc = __builtin_fmaf(hi, hi, acc);
-          }
-        }
-        acc += __shfl_xor(acc, 32);
-        xn[rs] = sqrtf(acc) * 1.00002f;
-      }
-      float best[2] = {INFINITY, INFINITY}, second[2] = {INFINITY, INFINITY};
-      int arg[2] = {0, 0};
-      for (int g = 0; g < nblk; ++g) {
-        if (nblk > 1) fetch_candidates(g);  // (a single block is already in registers)
-        f32x16 acc0, acc1;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 2 * KSN; ++i) {
-          acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bx[0][i % KSN], acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bx[1][i % KSN], acc1, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          // register r is the candidate at position 32 g + 8(r/4) + 4 lh + r%4 of the list
-          const int k = 8 * (r >> 2) + 4 * lh + (r & 3);
-          const float nn = __shfl(cnv, k);
-          const int idx = 32 * g + k;
-          const float s0 = __builtin_fmaf(-2.0f, acc0[r], nn);
-          const float s1 = __builtin_fmaf(-2.0f, acc1[r], nn);
-          second[0] = __builtin_amdgcn_fmed3f(s0, best[0], second[0]);
-          second[1] = __builtin_amdgcn_fmed3f(s1, best[1], second[1]);
-          if (s0 < best[0]) { best[0] = s0; arg[0] = idx; }
-          if (s1 < best[1]) { best[1] = s1; arg[1] = idx; }
-        }
-      }
-#pragma unroll
-      for (int rs = 0; rs < 2; ++rs)
-        settle_row<D>(best[rs], second[rs], arg[rs], valid[rs], rows[rs], xn[rs], Cm, far, lst, a_old, bh, nv, Cpad,
-                      labels, amb_rows, amb_count, bnd, dirty);
-    }
-    if (more) {
-#pragma unroll
-      for (int rs = 0; rs < 2; ++rs) {
-        rows[rs] = rows_next[rs];
-        flag[rs] = flag_next[rs];
+      for (int i = 0; i < 4; ++i) {
+        const float lo = __uint_as_float(w[i] << 16), hi = __uint_as_float(w[i] & 0xffff0000u);
+        x2 = __builtin_fmaf(lo, lo, x2);
+        x2 = __builtin_fmaf(hi, hi, x2);
       }
     }
+    x2 += __shfl_xor(x2, 32);
+    const float xn = sqrtf(x2) * 1.00002f;
+    float best = INFINITY, second = INFINITY;
+    int arg = 0;
+    for (int g = 0; g < nblk; ++g) {
+      if (nblk > 1) fetch_candidates(g);  // (a single block is already in registers)
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 2 * KSN; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bx[i % KSN], acc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        // register r is the candidate at position 32 g + 8(r/4) + 4 lh + r%4 of the list
+        const int k = 8 * (r >> 2) + 4 * lh + (r & 3);
+        const float score = __builtin_fmaf(-2.0f, acc[r], __shfl(cnv, k));
+        second = __builtin_amdgcn_fmed3f(score, best, second);
+        if (score < best) { best = score; arg = 32 * g + k; }
+      }
+    }
+    settle_row<D>(best, second, arg, valid, row, xn, Cm, far, lst, a_old, bh, nv, Cpad, labels, amb_rows, head_state,
+                  bnd, dirty);
   }
 }
 
@@ -1166,7 +1182,6 @@ struct NextIteration {
   float* cn;
   bf16_t* chl;
   bf16_t* crow;
-  int32_t* amb_count;
   int32_t* head_state;
   int32_t* rmax;
 };
@@ -1222,11 +1237,10 @@ __device__ __forceinline__ void publish_centroid(const NextIteration& nx, const 
 
 // The next iteration's counters: those of cluster c, and with the first cluster those of the head.
 __device__ __forceinline__ void clear_counters(const NextIteration& nx, int bh, int c, int Cpad) {
-  if (!nx.cperm || !nx.amb_count) return;
+  if (!nx.cperm || !nx.head_state) return;
   nx.rmax[(int64_t)bh * Cpad + c] = 0;
   if (c == 0) {
-    nx.amb_count[bh] = 0;
-    for (int k = 0; k < kHeadState; ++k) nx.head_state[bh * kHeadState + k] = 0;
+    for (int k : {kQueued, kMaxX, kMaxC, kUndecided}) nx.head_state[bh * kHeadState + k] = 0;
   }
 }
 
@@ -1402,7 +1416,6 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   bf16_t* chl = kFilter ? ws.take<bf16_t>((size_t)BH * 2 * Cpad * D) : nullptr;
   bf16_t* crow = kFilter ? ws.take<bf16_t>((size_t)BH * 2 * Cpad * D) : nullptr;
   int2* amb_rows = kFilter ? ws.take<int2>((size_t)BH * nv) : nullptr;
-  int32_t* amb_count = kFilter ? ws.take<int32_t>((size_t)BH) : nullptr;
   const int P = means_parts(nv, C);
   float* partial = P > 1 ? ws.take<float>((size_t)BH * C * P * D) : nullptr;
   // row skipping between iterations (bf16 input): distance bounds and flags per row, centroid
@@ -1411,8 +1424,8 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   const int tile_cap = (int)(nv / kListChunk) + C + 1;
   float2* bnd = kFilter ? ws.take<float2>((size_t)BH * nv) : nullptr;
   float* xnorm = kFilter ? ws.take<float>((size_t)BH * nv) : nullptr;
-  int32_t* rank = kFilter ? ws.take<int32_t>((size_t)BH * nv) : nullptr;
-  int32_t* prow = kFilter ? ws.take<int32_t>((size_t)BH * nv) : nullptr;
+  uint64_t* flags = kFilter ? ws.take<uint64_t>((size_t)BH * flag_words(nv)) : nullptr;
+  float2* near = kFilter ? ws.take<float2>((size_t)BH * C) : nullptr;
   int32_t* act_rows = kFilter ? ws.take<int32_t>((size_t)BH * nv) : nullptr;
   int32_t* head_state = kFilter ? ws.take<int32_t>((size_t)BH * kHeadState) : nullptr;
   float* drift = kFilter ? ws.take<float>((size_t)BH * Cpad) : nullptr;
@@ -1451,7 +1464,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   // (a threshold of the caller's own asks for the forms it chooses between)
   if (g_list_min_centroids.load(std::memory_order_relaxed) == kListDefault && kmeans_small_takes(BH, nv, C)) {
     prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                             nullptr, small_state, small_norms);
+                                             small_state, small_norms);
     SVGEAR_LAUNCH_CHECK();
     SmallKmeans a{x, x2, st, BH, H, (int)nv, C, Cpad, iters, cent, cent2, labels, counts, cperm, small_norms,
                   small_state, 0, 0, 0, 0, 0};
@@ -1474,10 +1487,10 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     }
     return SVGEAR_OK;
   };
-  const NextIteration tables = exact ? NextIteration{cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr}
-                                     : NextIteration{cperm, cn, chl, crow, amb_count, head_state, rmax};
+  const NextIteration tables = exact ? NextIteration{cperm, cn, nullptr, nullptr, nullptr, nullptr}
+                                     : NextIteration{cperm, cn, chl, crow, head_state, rmax};
   const NextIteration nothing{};
-  prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, tables.chl, tables.crow, tables.amb_count,
+  prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, tables.chl, tables.crow,
                                            tables.head_state, tables.rmax, exact ? nullptr : dirty, nullptr, nullptr);
   SVGEAR_LAUNCH_CHECK();
   for (int it = 0; it < iters; ++it) {
@@ -1489,21 +1502,26 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
       const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
       if (it == 0) {
         // every row against every centroid
-        filter<<<gf, 64 * kFilterWaves, lds_f, s>>>(xb, st, H, nv, chl, cn, xnorm, C, Cpad, labels, amb_rows, amb_count,
-                                                    nullptr, nullptr, bnd, nullptr);
+        filter<<<gf, 64 * kFilterWaves, lds_f, s>>>(xb, st, H, nv, chl, cn, xnorm, C, Cpad, labels, amb_rows,
+                                                    head_state, nullptr, bnd, nullptr);
         SVGEAR_LAUNCH_CHECK();
       } else {
         // only the rows whose bounds do not prove that their label stays
         if (use_lists && it >= kListFromIteration) {
           // ... each against the centroids near its cluster
-          bounds_update_kernel<D, true><<<gb, 256, 0, s>>>(labels, xnorm, cn, drift, C, Cpad, nv, bnd, act_rows, rank,
-                                                           prow, rmax, head_state);
+          const bool had_lists = it > kListFromIteration;
+          if (had_lists) {
+            neighbour_drift_kernel<<<dim3((unsigned)ceil_div(C, 8), BH), 256, 0, s>>>(drift, C, Cpad, nlist, nlen, dout, near);
+            SVGEAR_LAUNCH_CHECK();
+          }
+          bounds_update_kernel<D, true><<<gb, 256, C * sizeof(int32_t), s>>>(labels, xnorm, cn, drift, C, Cpad, nv, bnd, act_rows, flags,
+                                                           had_lists ? near : nullptr, rmax, head_state);
           SVGEAR_LAUNCH_CHECK();
           nlist_kernel<D><<<dim3((unsigned)ceil_div(C, 32), BH), 256, 0, s>>>(chl, cn, C, Cpad, rmax, head_state,
                                                                                nlist, nlen, dout);
           SVGEAR_LAUNCH_CHECK();
           assign_list_kernel<D><<<dim3((unsigned)tile_cap, BH), 64, 0, s>>>(
-              xb, st, H, nv, crow, cn, C, Cpad, labels, amb_rows, amb_count, prow, tiles, tile_cap, rmax, nlist, nlen,
+              xb, st, H, nv, crow, cn, C, Cpad, labels, amb_rows, perm, flags, tiles, tile_cap, rmax, nlist, nlen,
               dout, head_state, act_rows, bnd, dirty);
           SVGEAR_LAUNCH_CHECK();
         } else {
@@ -1514,8 +1532,8 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
         // the queued rows (all flagged rows, or those of the clusters without a list) against
         // every centroid; the grid covers every row, workgroups beyond the queue's length leave
         // at once
-        filter<<<gf, 64 * kFilterWaves, lds_f, s>>>(xb, st, H, nv, chl, cn, xnorm, C, Cpad, labels, amb_rows, amb_count,
-                                                    act_rows, head_state, bnd, dirty);
+        filter<<<gf, 64 * kFilterWaves, lds_f, s>>>(xb, st, H, nv, chl, cn, xnorm, C, Cpad, labels, amb_rows,
+                                                    head_state, act_rows, bnd, dirty);
         SVGEAR_LAUNCH_CHECK();
       }
       // workgroups per head: enough for 1,024 in all (two rounds of the chip) or, where every row is
@@ -1523,11 +1541,11 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
       const int64_t few_tiles = ceil_div(nv, kFewRows), few_spread = ceil_div(1024, BH), few_least = ceil_div(few_tiles, 64);
       const int few = (int)(few_tiles < few_spread ? few_tiles : (few_spread > few_least ? few_spread : few_least));
       assign_few_kernel<D><<<(unsigned)align_up((size_t)few * BH, 8), 256, 0, s>>>(
-          xb, st, H, nv, chl, cent, cperm, cn, C, Cpad, labels, amb_rows, amb_count, it > 0 ? dirty : nullptr, BH, few);
+          xb, st, H, nv, chl, cent, cperm, cn, C, Cpad, labels, amb_rows, head_state, it > 0 ? dirty : nullptr, BH, few);
     }
     SVGEAR_LAUNCH_CHECK();
     int rc = sort_labels(labels, BH, nv, 0, C, perm, offsets, chunk_hist, s, use_lists ? tiles : nullptr, tile_cap,
-                         kListChunk, use_lists ? rank : nullptr);
+                         kListChunk);
     if (rc != SVGEAR_OK) return rc;
     rc = update(x, cent, counts, (!exact && it > 0) ? dirty : nullptr, exact ? nullptr : drift, it + 1 < iters ? tables : nothing);
     if (rc != SVGEAR_OK) return rc;
@@ -1556,13 +1574,14 @@ extern "C" size_t svgear_kmeans_workspace(int B, int H, int64_t N, int d, int C)
   return align_up(BH * sort_chunks(N) * (C + 1) * 4, 256) + align_up(BH * N * 4, 256) +
          align_up(BH * (C + 2) * 4, 256) + align_up(BH * Cpad * 4, 256) + align_up(BH * Cpad * d * 4, 256) +
          // bf16 filter: hi/lo operand tables (two layouts), ambiguous-row list and counter
-         2 * align_up(BH * 2 * Cpad * d * 2, 256) + align_up(BH * N * 8, 256) + align_up(BH * 4, 256) +
+         2 * align_up(BH * 2 * Cpad * d * 2, 256) + align_up(BH * N * 8, 256) +
          // partial sums of the split centroid update
          (means_parts(N, C) > 1 ? align_up(BH * C * means_parts(N, C) * d * 4, 256) : 0) +
          // row skipping: per row two bounds, the norm, the sorted position, the flagged-row table and
          // the queue; per-head maxima, centroid moves, radii,
          // membership-changed flags, candidate lists with their lengths and outer distances, chunk table
-         align_up(BH * N * 8, 256) + 4 * align_up(BH * N * 4, 256) +
+         align_up(BH * N * 8, 256) + 2 * align_up(BH * N * 4, 256) + align_up(BH * flag_words(N) * 8, 256) +
+         align_up(BH * C * 8, 256) +
          align_up(BH * kHeadState * 4, 256) + 3 * align_up(BH * Cpad * 4, 256) +
          align_up(BH * C * kListMax * 4, 256) + 2 * align_up(BH * C * 4, 256) +
          align_up(BH * (N / kListChunk + C + 1) * 16, 256) + align_up(BH * kSmallState * 4, 256) +

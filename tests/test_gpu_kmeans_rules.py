@@ -51,3 +51,29 @@ def test_forms_agree(H, N, tail, C, d, dtype, strided):
         if iters == 1:
             for h in range(H):
                 assert np.array_equal(to_np(got[0][0][0, h]), orc.kmeans_assign(to_np(x[0, h])[: N - tail], to_np(start[0, h])))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,N,C", [(1, 63, 9), (2, 65, 40), (3, 2049, 33), (2, 4096, 130), (1, 6001, 700), (2, 3000, 5)])
+@pytest.mark.parametrize("spread", [0.3, 3.0])
+def test_candidate_lists_over_many_iterations(H, N, C, d, spread):
+    """Rows tested against candidate lists only where moved neighbours do not prove their label (a bit per row, words of
+    64; clusters of more than the 256 positions a wave takes; lists of one to more than 128 centroids): after every
+    number of iterations the same labels and centroids as testing every centroid."""
+    g = torch.Generator().manual_seed(N + C)
+    mu = torch.randn(max(2, C // 4), d, generator=g)
+    x = (mu[torch.randint(0, len(mu), (H, N), generator=g)] + spread * torch.randn(H, N, d, generator=g)).bfloat16()[None].to(dev())
+    start = x[:, :, torch.randperm(N, generator=g)[:C].to(dev())].float().contiguous()
+    for iters in (3, 4, 5, 9, 14):
+        got = []
+        for threshold in (1, 2**31 - 1):
+            before = kmeans_list_threshold(threshold)
+            try:
+                c = start.clone()
+                labels, counts, _ = sv.kmeans(x, c, iters)
+                torch.cuda.synchronize()
+            finally:
+                kmeans_list_threshold(before)
+            got.append((labels, counts, c))
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
