@@ -22,6 +22,70 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr float kMaxExponent = 40.0f;  // e^40 squared still fits fp32
 
+// |delta_j|^2 and -2 vbar . delta_j of every clustered key (delta_j = v_j - vbar of its cluster), bf16 inputs: what the
+// block errors need of the values. 256 threads per (head, key cluster): 16 key slots x 16 lanes of 8 dims (d = 64: 32 x 8).
+// They depend on nothing the centroid logits compute, so both share a launch, the logits' workgroups first: 5 heads,
+// 200 x 500 centroids 20 + 29 us apart, 38 together; 8 x 2,000 keys, 30 x 60: the whole call 39 -> 33. (Not with the
+// matrix-core form of the logits, whose registers cost the streaming half its waves: 40 heads, 300 x 1,000 centroids
+// 85 + 168 apart, 300 together.)
+struct ValueStats {
+  const float* vbar;
+  const bf16_t* vp;
+  int64_t Nk, stride;  // of nd and dd
+  float* nd;
+  float* dd;
+  int clusters;  // of all heads; 0: none wanted
+};
+
+template <int D>
+__device__ __forceinline__ void value_stats(const ValueStats& p, const int32_t* k_offsets, int Ck, int cluster, int tid) {
+  constexpr int LPK = D / 8;  // lanes per key
+  constexpr int SLOTS = 256 / LPK;
+  if (cluster >= p.clusters) return;
+  const int b = cluster % Ck, bh = cluster / Ck;
+  const int slot = tid / LPK, lane = tid % LPK;
+  const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
+  const int start = off[b], end = off[b + 1];
+  const float* vb = p.vbar + ((int64_t)bh * Ck + b) * D + lane * 8;
+  float vbl[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) vbl[k] = vb[k];
+  const bf16_t* vh = p.vp + (int64_t)bh * p.Nk * D + lane * 8;
+  constexpr int INFLIGHT = 4;  // independent key fetches per lane group
+  for (int j0 = start + slot; j0 < end; j0 += INFLIGHT * SLOTS) {
+    uint4 raw[INFLIGHT];
+#pragma unroll
+    for (int u = 0; u < INFLIGHT; ++u) {
+      const int j = j0 + u * SLOTS;
+      raw[u] = j < end ? *reinterpret_cast<const uint4*>(vh + (int64_t)j * D) : uint4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int u = 0; u < INFLIGHT; ++u) {
+      const int j = j0 + u * SLOTS;
+      const uint32_t w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+      float p_nd = 0.f, p_dd = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float d0 = __uint_as_float(w[i] << 16) - vbl[2 * i];
+        const float d1 = __uint_as_float(w[i] & 0xffff0000u) - vbl[2 * i + 1];
+        p_nd = __builtin_fmaf(d0, d0, p_nd);
+        p_dd = __builtin_fmaf(d0, vbl[2 * i], p_dd);
+        p_nd = __builtin_fmaf(d1, d1, p_nd);
+        p_dd = __builtin_fmaf(d1, vbl[2 * i + 1], p_dd);
+      }
+#pragma unroll
+      for (int o = LPK / 2; o > 0; o >>= 1) {
+        p_nd += __shfl_xor(p_nd, o);
+        p_dd += __shfl_xor(p_dd, o);
+      }
+      if (lane == 0 && j < end) {
+        p.nd[(int64_t)bh * p.stride + j] = p_nd;
+        p.dd[(int64_t)bh * p.stride + j] = -2.0f * p_dd;
+      }
+    }
+  }
+}
+
 // Sbar[a][b] = qbar_a . kbar_b * scale; mrow[a] = max over non-empty b.
 // With q3 != nullptr (grid.x = Cq rounded up to 32) it also writes qbar split into three bf16
 // pieces q = hi + mid + lo (exact: 3 x 8 significant bits), laid out as B operands of
@@ -33,10 +97,12 @@ template <int D>
 __global__ void __launch_bounds__(256)
 sbar_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, const int32_t* __restrict__ k_offsets,
             int Cq, int Ck, float scale, float* __restrict__ sbar, float* __restrict__ mrow,
-            bf16_t* __restrict__ q3) {
+            bf16_t* __restrict__ q3, int groups, int logit_blocks, ValueStats stats) {
   __shared__ float q[kSbarRows][D];
   __shared__ float red[kSbarRows][4];
-  const int a0 = blockIdx.x * kSbarRows, bh = blockIdx.y;
+  const int block = blockIdx.x;
+  if (block >= logit_blocks) return value_stats<D>(stats, k_offsets, Ck, block - logit_blocks, threadIdx.x);
+  const int a0 = block % groups * kSbarRows, bh = block / groups;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = threadIdx.x; i < kSbarRows * D; i += 256) {
     const int a = a0 + i / D;
@@ -349,60 +415,6 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
   return c.b;
 }
 
-// |delta_j|^2 and -2 vbar . delta_j of every clustered key (delta_j = v_j - vbar of its cluster).
-// One workgroup per (head, key cluster): 16 key slots x 16 lanes of 8 dims.
-template <int D>
-__global__ void __launch_bounds__(256)
-value_stats_kernel(const float* __restrict__ vbar, const bf16_t* __restrict__ vp,
-                   const int32_t* __restrict__ k_offsets, int64_t Nk, int64_t stat_stride, int Ck,
-                   float* __restrict__ nd, float* __restrict__ dd) {
-  constexpr int LPK = D / 8;  // lanes per key
-  constexpr int SLOTS = 256 / LPK;
-  const int b = blockIdx.x, bh = blockIdx.y;
-  const int slot = threadIdx.x / LPK, lane = threadIdx.x % LPK;
-  const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
-  const int start = off[b], end = off[b + 1];
-  const float* vb = vbar + ((int64_t)bh * Ck + b) * D + lane * 8;
-  float vbl[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) vbl[k] = vb[k];
-  const bf16_t* vh = vp + (int64_t)bh * Nk * D + lane * 8;
-  constexpr int INFLIGHT = 4;  // independent key fetches per lane group
-  for (int j0 = start + slot; j0 < end; j0 += INFLIGHT * SLOTS) {
-    uint4 raw[INFLIGHT];
-#pragma unroll
-    for (int u = 0; u < INFLIGHT; ++u) {
-      const int j = j0 + u * SLOTS;
-      raw[u] = j < end ? *reinterpret_cast<const uint4*>(vh + (int64_t)j * D) : uint4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int u = 0; u < INFLIGHT; ++u) {
-      const int j = j0 + u * SLOTS;
-      const uint32_t w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
-      float p_nd = 0.f, p_dd = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float d0 = __uint_as_float(w[i] << 16) - vbl[2 * i];
-        const float d1 = __uint_as_float(w[i] & 0xffff0000u) - vbl[2 * i + 1];
-        p_nd = __builtin_fmaf(d0, d0, p_nd);
-        p_dd = __builtin_fmaf(d0, vbl[2 * i], p_dd);
-        p_nd = __builtin_fmaf(d1, d1, p_nd);
-        p_dd = __builtin_fmaf(d1, vbl[2 * i + 1], p_dd);
-      }
-#pragma unroll
-      for (int o = LPK / 2; o > 0; o >>= 1) {
-        p_nd += __shfl_xor(p_nd, o);
-        p_dd += __shfl_xor(p_dd, o);
-      }
-      if (lane == 0 && j < end) {
-        nd[(int64_t)bh * stat_stride + j] = p_nd;
-        dd[(int64_t)bh * stat_stride + j] = -2.0f * p_dd;
-      }
-    }
-  }
-}
-
-
 // Block errors with the logits qbar_a . k_j on bf16 MFMAs (qbar in three exact bf16 pieces,
 // so the logits carry fp32-level accuracy). One workgroup per (head, `clusters` consecutive
 // key clusters, group of 128 query centroids); wave w owns query centroids 32w..32w+31 of the
@@ -693,20 +705,29 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
 
 }  // namespace
 
-// Centroid logits and their row maxima alone (no block errors); q3: see sbar_kernel.
+// Centroid logits and their row maxima (q3: see sbar_kernel), and beside them the statistics of the values.
+static int run_logits(const float* qbar, const float* kbar, const int32_t* k_offsets, int BH, int d, int Cq, int Ck,
+                      float scale, float* sbar, float* mrow, bf16_t* q3, const ValueStats& stats, hipStream_t s) {
+  int groups = 1, blocks = 0;
+  if (ceil_div(Cq, 32) * BH >= 256) {
+    auto kern = d == 64 ? sbar_mfma_kernel<64> : sbar_mfma_kernel<128>;
+    kern<<<dim3((unsigned)ceil_div(Cq, 32), BH), 64 * kSbarWaves, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3);
+    SVGEAR_LAUNCH_CHECK();
+  } else {
+    groups = (int)ceil_div(q3 ? align_up(Cq, 32) : Cq, kSbarRows);
+    blocks = groups * BH;
+  }
+  if (blocks + stats.clusters > 0) {
+    auto kern = d == 64 ? sbar_kernel<64> : sbar_kernel<128>;
+    kern<<<blocks + stats.clusters, 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3, groups, blocks, stats);
+    SVGEAR_LAUNCH_CHECK();
+  }
+  return SVGEAR_OK;
+}
+
 int run_sbar(const float* qbar, const float* kbar, const int32_t* k_offsets, int BH, int d, int Cq, int Ck,
              float scale, float* sbar, float* mrow, bf16_t* q3, hipStream_t s) {
-  const int64_t blocks = ceil_div(Cq, 32);
-  if (blocks * BH >= 256) {
-    auto kern = d == 64 ? sbar_mfma_kernel<64> : sbar_mfma_kernel<128>;
-    kern<<<dim3((unsigned)blocks, BH), 64 * kSbarWaves, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3);
-  } else {
-    const int64_t rows = q3 ? align_up(Cq, 32) : Cq;
-    auto kern = d == 64 ? sbar_kernel<64> : sbar_kernel<128>;
-    kern<<<dim3((unsigned)ceil_div(rows, kSbarRows), BH), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3);
-  }
-  SVGEAR_LAUNCH_CHECK();
-  return SVGEAR_OK;
+  return run_logits(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, q3, ValueStats{}, s);
 }
 
 int run_probe(const float* qbar, const float* kbar, const float* vbar, const void* kp, const void* vp,
@@ -714,25 +735,20 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
               bool value_aware, float* scores, float* sbar, float* mrow, bf16_t* q3, float* nd, float* dd,
               hipStream_t s) {
   const bool mfma = dt == SVGEAR_BF16;
-  const int rc = run_sbar(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, mfma ? q3 : nullptr, s);
+  const int64_t stat_stride = probe_stat_stride(Nk);
+  ValueStats stats{};
+  if (mfma && value_aware) stats = ValueStats{vbar, static_cast<const bf16_t*>(vp), Nk, stat_stride, nd, dd, BH * Ck};
+  const int rc = run_logits(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, mfma ? q3 : nullptr, stats, s);
   if (rc != SVGEAR_OK) return rc;
   if (mfma) {
-    const int64_t stat_stride = probe_stat_stride(Nk);
     const bf16_t* k16 = static_cast<const bf16_t*>(kp);
-    const bf16_t* v16 = static_cast<const bf16_t*>(vp);
     const int groups = (int)ceil_div(ceil_div(Cq, 32), kProbeWaves);
     // key clusters a workgroup: its start (fragments, weights, the first copies) is worth some three clusters of
     // 75 keys, but a launch wants two rounds of the 512 workgroups that are resident at once. us a call with 1, 2, 4, 8:
     // 40 heads, 300 x 1,000 centroids 2205, 1840, 1561, 1493; 5 x 200 x 500 247, 231, 225, 234; 8 x 30 x 60 38, 40, 44, 50
     const int64_t units = (int64_t)BH * Ck * groups;
     const int clusters = units >= 8192 ? kProbeClusters : units >= 2048 ? 4 : units >= 1024 ? 2 : 1;
-    const dim3 gs(Ck, BH);
     const unsigned gb = (unsigned)(align_up(ceil_div(Ck, clusters) * BH, 8) * groups);
-    if (value_aware) {
-      if (d == 64) value_stats_kernel<64><<<gs, 256, 0, s>>>(vbar, v16, k_offsets, Nk, stat_stride, Ck, nd, dd);
-      else value_stats_kernel<128><<<gs, 256, 0, s>>>(vbar, v16, k_offsets, Nk, stat_stride, Ck, nd, dd);
-      SVGEAR_LAUNCH_CHECK();
-    }
 #define SVGEAR_PM(D, VA)                                                                                     \
   block_error_mfma_kernel<D, VA><<<gb, 64 * kProbeWaves, 0, s>>>(q3, vbar, k16, k_offsets, sbar, mrow, nd, dd, Nk, stat_stride, \
                                                     Cq, Ck, scale, clusters, groups, BH, scores)
