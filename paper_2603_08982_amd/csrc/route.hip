@@ -28,7 +28,7 @@ int run_sbar(const float* qbar, const float* kbar, const int32_t* k_offsets, int
 namespace {
 
 constexpr int kSelThreads = 1024;
-constexpr int kTopPThreads = 256;
+constexpr int kRowThreads = 256;
 constexpr int kTopPWeightBits = 20;  // masses are counted in units of 2^-20
 constexpr int kTopPIndexBits = 13;   // Ck <= 8192
 
@@ -159,63 +159,26 @@ __device__ __forceinline__ long long head_budget(const int32_t* qo, const int32_
   return budget - (tq * Nk + (Nq - tq) * tk);
 }
 
-// grid (Cq, BH): the cut of every query cluster (row_budget, if given, holds each cluster's budget for
-// its clustered blocks, the tail column on top; otherwise its share of the head's).
-__global__ void __launch_bounds__(kSelThreads)
-select_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
-              const int32_t* __restrict__ k_offsets, int Cq, int Ck, int64_t budget,
-              const int64_t* __restrict__ row_budget, uint64_t* __restrict__ kstar) {
-  __shared__ CutState st;
-  const int a = blockIdx.x, bh = blockIdx.y;
-  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
-  const float* sc = scores + (int64_t)bh * Cq * Ck;
-  const int64_t Nq = qo[Cq + 1], qa = qo[a + 1] - qo[a];
-  const long long rem = row_budget ? row_budget[(int64_t)bh * Cq + a]
-                                   : (budget * qa) / (Nq > 0 ? Nq : 1) - qa * (ko[Ck + 1] - ko[Ck]);
-  const unsigned long long cut = radix_cut<kSelThreads>(st, rem, Ck, [&](int b, uint64_t& key,
-                                                                         unsigned long long& weight) {
-    weight = block_cost(qo, ko, a * Ck + b, Ck);
-    if (weight == 0ull) return false;
-    key = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b));
-    return true;
-  });
-  if (threadIdx.x == 0) kstar[(int64_t)bh * Cq + a] = cut;
-}
-
-// Adaptive budget of query cluster a (grid (Cq, BH)): the non-empty key clusters carry the
+// Adaptive budget of query cluster a: the non-empty key clusters carry the
 // centroid attention mass |k_b| exp(Sbar_ab - m_a), counted in integer units of 2^-20 so that
 // sums are exact in any order; ordered by weight descending (ties: lower b first), the
 // shortest prefix whose weight reaches ceil(top_p * total) is kept, and the budget is the
-// cost |q_a| * sum |k_b| of exact attention over it.
-__global__ void __launch_bounds__(kTopPThreads)
-top_p_budget_kernel(const float* __restrict__ sbar, const float* __restrict__ mrow,
-                    const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets, int Cq, int Ck,
-                    float top_p, int64_t* __restrict__ row_budget) {
-  extern __shared__ unsigned long long wgt[];  // Ck
-  __shared__ CutState st;
+// cost |q_a| * sum |k_b| of exact attention over it. Called by all kRowThreads threads; wgt: Ck entries of LDS.
+__device__ __forceinline__ int64_t top_p_budget(const float* sbar_row, float m, const int32_t* ko, int64_t qa, int Ck,
+                                                float top_p, unsigned long long* wgt, CutState& st) {
   __shared__ unsigned long long sh_total, sh_keys;
-  const int a = blockIdx.x, bh = blockIdx.y;
-  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
-  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
-  const int64_t qa = qo[a + 1] - qo[a];
-  if (qa <= 0) {
-    if (threadIdx.x == 0) row_budget[(int64_t)bh * Cq + a] = 0;
-    return;
-  }
+  if (qa <= 0) return 0;
   if (threadIdx.x == 0) {
     sh_total = 0ull;
     sh_keys = 0ull;
   }
   __syncthreads();
-  const float* sr = sbar + ((int64_t)bh * Cq + a) * Ck;
-  const float m = mrow[(int64_t)bh * Cq + a];
   unsigned long long part = 0ull;
-  for (int b = threadIdx.x; b < Ck; b += kTopPThreads) {
+  for (int b = threadIdx.x; b < Ck; b += kRowThreads) {
     const int32_t kb = ko[b + 1] - ko[b];
     unsigned long long w = 0ull;
     if (kb > 0) {
-      const float mass = (float)kb * expf(sr[b] - m) * (float)(1 << kTopPWeightBits);
+      const float mass = (float)kb * expf(sbar_row[b] - m) * (float)(1 << kTopPWeightBits);
       if (mass >= 1.f) w = (unsigned long long)mass;  // also drops NaN
     }
     wgt[b] = w;
@@ -227,8 +190,8 @@ top_p_budget_kernel(const float* __restrict__ sbar, const float* __restrict__ mr
   const double want = ceil((double)top_p * (double)total);
   const long long need = want >= 1.0 ? (long long)want : 1ll;
   auto key_of = [&](int b) { return (wgt[b] << kTopPIndexBits) | (unsigned long long)((1 << kTopPIndexBits) - 1 - b); };
-  const unsigned long long cut = radix_cut<kTopPThreads>(st, need - 1, Ck, [&](int it, uint64_t& key,
-                                                                               unsigned long long& weight) {
+  const unsigned long long cut = radix_cut<kRowThreads>(st, need - 1, Ck, [&](int it, uint64_t& key,
+                                                                              unsigned long long& weight) {
     const int b = it;
     if (ko[b + 1] <= ko[b]) return false;
     key = key_of(b);
@@ -236,25 +199,25 @@ top_p_budget_kernel(const float* __restrict__ sbar, const float* __restrict__ mr
     return true;
   });
   unsigned long long keys = 0ull;
-  for (int b = threadIdx.x; b < Ck; b += kTopPThreads) {
+  for (int b = threadIdx.x; b < Ck; b += kRowThreads) {
     const int32_t kb = ko[b + 1] - ko[b];
     if (kb > 0 && key_of(b) >= cut) keys += (unsigned long long)kb;
   }
   if (keys) atomicAdd(&sh_keys, keys);
   __syncthreads();
-  if (threadIdx.x == 0) row_budget[(int64_t)bh * Cq + a] = qa * (int64_t)sh_keys;
+  return qa * (int64_t)sh_keys;
 }
 
 // Mask words and routed blocks of row a of a head (a whole wave): returns the count and adds the
 // lane's share of the cost. 64 consecutive key clusters per step (coalesced score loads), two mask
-// words per ballot.
+// words per ballot, four steps at a time; share s of `shares` waves takes every shares-th four.
 __device__ __forceinline__ int mask_row(const float* sc, const int32_t* qo, const int32_t* ko, int Cq, int Ck, int a,
-                                        uint64_t ks, uint32_t* words, long long& cost) {
+                                        uint64_t ks, uint32_t* words, long long& cost, int share = 0, int shares = 1) {
   const int Cc = Ck + 1, W = (Cc + 31) / 32, lane = threadIdx.x & 63;
   const int64_t qa = qo[a + 1] - qo[a];
   int cnt = 0;
   constexpr int U = 4;  // steps whose loads are in flight together
-  for (int b00 = 0; b00 < W * 32; b00 += 64 * U) {
+  for (int b00 = 64 * U * share; b00 < W * 32; b00 += 64 * U * shares) {
     int32_t size[U];
     float score[U];
 #pragma unroll
@@ -335,19 +298,61 @@ __device__ __forceinline__ void build_head(const float* sc, const int32_t* qo, c
   for (int a = wave; a < R; a += NWAVES) list_row(mb + (int64_t)a * W, W, rowcnt[a], ci);
 }
 
-// grid (BH): mask, lists and cost of heads of fewer than kWideItems blocks whose rows have budgets of
-// their own
-__global__ void __launch_bounds__(kSelThreads)
-build_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
-             const int32_t* __restrict__ k_offsets, int Cq, int Ck, const uint64_t* __restrict__ kstar,
-             uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
-             int64_t* __restrict__ routed_cost) {
-  extern __shared__ int32_t rowcnt[];  // Cq+2
-  __shared__ unsigned long long cost_sum;
-  const int bh = blockIdx.x;
-  const uint64_t* ks = kstar + (int64_t)bh * Cq;
-  build_head(scores + (int64_t)bh * Cq * Ck, q_offsets + (int64_t)bh * (Cq + 2), k_offsets + (int64_t)bh * (Ck + 2), Cq,
-             Ck, bh, [&](int a) { return ks[a]; }, rowcnt, &cost_sum, mask_bits, row_ptr, col_idx, routed_cost);
+// grid (Cq + 1, BH): rows with budgets of their own: the row's budget (its share of the head's, or with top_p >= 0 the
+// adaptive one, for its clustered blocks, the tail column on top), its cut, mask words, routed blocks and cost. One
+// launch instead of three or four dependent ones: 5 heads, 200 x 500 centroids 28 + 16 + 8 us, and 5 to clear a counter,
+// in 39.
+__global__ void __launch_bounds__(kRowThreads)
+route_rows_kernel(const float* __restrict__ scores, const float* __restrict__ sbar, const float* __restrict__ mrow,
+                  const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets, int Cq, int Ck,
+                  int64_t budget, float top_p, int64_t* __restrict__ row_budget, uint32_t* __restrict__ mask_bits,
+                  int32_t* __restrict__ row_count, int64_t* __restrict__ row_cost) {
+  extern __shared__ unsigned long long wgt[];  // Ck, with top_p
+  __shared__ CutState st;
+  __shared__ int s_cnt[kRowThreads / 64];
+  __shared__ long long s_cost[kRowThreads / 64];
+  const int a = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int R = Cq + 1, W = (Ck + 1 + 31) / 32;
+  const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
+  const int32_t* ko = k_offsets + (int64_t)bh * (Ck + 2);
+  const float* sc = scores + (int64_t)bh * Cq * Ck;
+  unsigned long long cut = 0ull;
+  if (a < Cq) {
+    const int64_t Nq = qo[Cq + 1], qa = qo[a + 1] - qo[a], at = (int64_t)bh * Cq + a;
+    long long rem;
+    if (top_p >= 0.f) {
+      rem = top_p_budget(sbar + at * Ck, mrow[at], ko, qa, Ck, top_p, wgt, st);
+      if (threadIdx.x == 0) row_budget[at] = rem;
+      __syncthreads();
+    } else {
+      rem = (budget * qa) / (Nq > 0 ? Nq : 1) - qa * (ko[Ck + 1] - ko[Ck]);
+    }
+    cut = radix_cut<kRowThreads>(st, rem, Ck, [&](int b, uint64_t& key, unsigned long long& weight) {
+      weight = block_cost(qo, ko, a * Ck + b, Ck);
+      if (weight == 0ull) return false;
+      key = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b));
+      return true;
+    });
+  }
+  long long cost = 0;
+  const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, cut, mask_bits + ((int64_t)bh * R + a) * W, cost, wave, kRowThreads / 64);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
+  if (lane == 0) {
+    s_cnt[wave] = cnt;
+    s_cost[wave] = cost;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int n = 0;
+    long long sum = 0;
+    for (int w = 0; w < kRowThreads / 64; ++w) {
+      n += s_cnt[w];
+      sum += s_cost[w];
+    }
+    row_count[(int64_t)bh * R + a] = n;
+    row_cost[(int64_t)bh * R + a] = sum;
+  }
 }
 
 // grid (BH): cut, mask, lists and cost of heads of fewer than kWideItems blocks with one budget: a
@@ -541,8 +546,8 @@ route_cut_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q
 // grid (ceil((Cq + 1) / 4), BH): mask words, routed blocks and routed cost, a wave per row of blocks
 __global__ void __launch_bounds__(256)
 route_mask_kernel(const float* __restrict__ scores, const int32_t* __restrict__ q_offsets,
-                  const int32_t* __restrict__ k_offsets, int Cq, int Ck, int per_row,
-                  const uint64_t* __restrict__ kstar, uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_count,
+                  const int32_t* __restrict__ k_offsets, int Cq, int Ck, const uint64_t* __restrict__ kstar,
+                  uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_count,
                   int64_t* __restrict__ routed_cost) {
   const int bh = blockIdx.y, lane = threadIdx.x & 63, a = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int R = Cq + 1, W = (Ck + 1 + 31) / 32;
@@ -551,7 +556,7 @@ route_mask_kernel(const float* __restrict__ scores, const int32_t* __restrict__ 
   if (a < R) {
     const int cnt = mask_row(scores + (int64_t)bh * Cq * Ck, q_offsets + (int64_t)bh * (Cq + 2),
                              k_offsets + (int64_t)bh * (Ck + 2), Cq, Ck, a,
-                             a < Cq ? kstar[(int64_t)bh * (per_row ? Cq : 1) + (per_row ? a : 0)] : 0ull,
+                             a < Cq ? kstar[bh] : 0ull,
                              mask_bits + ((int64_t)bh * R + a) * W, cost);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
@@ -566,11 +571,13 @@ route_mask_kernel(const float* __restrict__ scores, const int32_t* __restrict__ 
 }
 
 // grid (ceil((Cq + 1) / kListRows), BH): row_ptr and col_idx of kListRows rows; the routed blocks of
-// the rows before them are summed by the workgroup itself
+// the rows before them are summed by the workgroup itself, and with row_cost the head's cost by its first one
 constexpr int kListRows = 16;
 __global__ void __launch_bounds__(256)
 route_lists_kernel(int Cq, int Ck, const uint32_t* __restrict__ mask_bits, const int32_t* __restrict__ row_count,
-                   int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx) {
+                   const int64_t* __restrict__ row_cost, int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+                   int64_t* __restrict__ routed_cost) {
+  __shared__ long long cost_part[4];
   __shared__ int32_t part[4], start[kListRows + 1];
   const int bh = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int R = Cq + 1, Cc = Ck + 1, W = (Cc + 31) / 32;
@@ -591,6 +598,15 @@ route_lists_kernel(int Cq, int Ck, const uint32_t* __restrict__ mask_bits, const
     start[n] = run;
   }
   __syncthreads();
+  if (row_cost && blockIdx.x == 0) {
+    long long cost = 0;
+    for (int a = threadIdx.x; a < R; a += 256) cost += row_cost[(int64_t)bh * R + a];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
+    if (lane == 0) cost_part[wave] = cost;
+    __syncthreads();
+    if (threadIdx.x == 0) routed_cost[bh] = cost_part[0] + cost_part[1] + cost_part[2] + cost_part[3];
+  }
   if ((int)threadIdx.x < n || ((int)threadIdx.x == n && a0 + n == R))
     row_ptr[(int64_t)bh * (R + 1) + a0 + threadIdx.x] = start[threadIdx.x];
   int32_t* ci = col_idx + (int64_t)bh * R * Cc;
@@ -659,23 +675,22 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
     int rc = run_sbar(qbar, kbar, k_offsets, BH, d, Cq, Ck, scale, sbar, mrow, nullptr, s);
     if (rc != SVGEAR_OK) return rc;
   }
-  const int per_row = (adaptive || (flags & SVGEAR_ROUTE_PER_ROW)) ? 1 : 0;
-  if (adaptive) {
-    // up to 64 KB of weights for the largest Ck, beside the kernel's static LDS
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(top_p_budget_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)((size_t)Ck * sizeof(unsigned long long))));
-    top_p_budget_kernel<<<dim3(Cq, BH), kTopPThreads, (size_t)Ck * sizeof(unsigned long long), s>>>(
-        sbar, mrow, q_offsets, k_offsets, Cq, Ck, top_p, row_budget);
-    SVGEAR_LAUNCH_CHECK();
-  }
   const int64_t n_items = (int64_t)Cq * Ck;
-  const bool wide = n_items >= kWideItems;
-  if (wide) {
+  const dim3 list_grid((unsigned)ceil_div(Cq + 1, kListRows), BH);
+  if (adaptive || (flags & SVGEAR_ROUTE_PER_ROW)) {
+    // up to 64 KB of weights for the largest Ck, beside the kernel's static LDS
+    const size_t lds = adaptive ? (size_t)Ck * sizeof(unsigned long long) : 0;
+    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(route_rows_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    int64_t* row_cost = reinterpret_cast<int64_t*>(kstar);  // (no cut leaves that kernel)
+    route_rows_kernel<<<dim3(Cq + 1, BH), kRowThreads, lds, s>>>(scores, sbar, mrow, q_offsets, k_offsets, Cq, Ck,
+                                                                 budget_cost, adaptive ? top_p : -1.f, row_budget,
+                                                                 mask_bits, row_count, row_cost);
+    SVGEAR_LAUNCH_CHECK();
+    route_lists_kernel<<<list_grid, 256, 0, s>>>(Cq, Ck, mask_bits, row_count, row_cost, row_ptr, col_idx, routed_cost);
+  } else if (n_items >= kWideItems) {
     route_clear_kernel<<<dim3(kHistBins / 256, BH), 256, 0, s>>>(cuts, routed_cost);
     SVGEAR_LAUNCH_CHECK();
-  }
-  if (wide && !per_row) {
     const dim3 grid((unsigned)ceil_div(n_items, kHistItems), BH);
     uint32_t* cand = reinterpret_cast<uint32_t*>(sbar);  // the probe is done with the centroid logits
     route_hist_kernel<<<grid, kHistThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, cuts);
@@ -684,25 +699,14 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
     SVGEAR_LAUNCH_CHECK();
     route_cut_kernel<<<BH, kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, cuts, cand, kstar);
     SVGEAR_LAUNCH_CHECK();
-  } else if (per_row) {  // a workgroup walks the blocks of a row
-    select_kernel<<<dim3(Cq, BH), kSelThreads, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost,
-                                                      adaptive ? row_budget : nullptr, kstar);
+    route_mask_kernel<<<dim3((unsigned)ceil_div(Cq + 1, 4), BH), 256, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck, kstar,
+                                                                             mask_bits, row_count, routed_cost);
     SVGEAR_LAUNCH_CHECK();
-  }
-  const size_t rows_lds = (Cq + 2) * sizeof(int32_t);
-  if (wide) {
-    route_mask_kernel<<<dim3((unsigned)ceil_div(Cq + 1, 4), BH), 256, 0, s>>>(scores, q_offsets, k_offsets, Cq, Ck,
-                                                                             per_row, kstar, mask_bits, row_count,
-                                                                             routed_cost);
-    SVGEAR_LAUNCH_CHECK();
-    route_lists_kernel<<<dim3((unsigned)ceil_div(Cq + 1, kListRows), BH), 256, 0, s>>>(Cq, Ck, mask_bits, row_count,
-                                                                                      row_ptr, col_idx);
-  } else if (per_row) {
-    build_kernel<<<BH, kSelThreads, rows_lds, s>>>(scores, q_offsets, k_offsets, Cq, Ck, kstar, mask_bits, row_ptr,
-                                                  col_idx, routed_cost);
+    route_lists_kernel<<<list_grid, 256, 0, s>>>(Cq, Ck, mask_bits, row_count, nullptr, row_ptr, col_idx, routed_cost);
   } else {
-    route_small_kernel<<<BH, kSelThreads, rows_lds, s>>>(scores, q_offsets, k_offsets, Cq, Ck, budget_cost, mask_bits,
-                                                        row_ptr, col_idx, routed_cost);
+    route_small_kernel<<<BH, kSelThreads, (Cq + 2) * sizeof(int32_t), s>>>(scores, q_offsets, k_offsets, Cq, Ck,
+                                                                          budget_cost, mask_bits, row_ptr, col_idx,
+                                                                          routed_cost);
   }
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
