@@ -114,8 +114,10 @@ plan_kernel(const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k
   }
 }
 
+// (two waves a SIMD asked for at d = 64: without a bound the accumulators go to AGPRs, and every score through a move;
+// 8 heads x 5,957 rows 244 -> 235 us. d = 128 needs more registers than two waves have.)
 template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1)
 attn_f32_kernel(AttnArgs p) {
   constexpr int CPR = D / 4;                // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;             // rows per copy instruction

@@ -26,6 +26,7 @@
 // in a fixed order (interleaved partial sums per cluster, combined in slot order) -- no float
 // atomics, so the centroids are run-to-run deterministic.
 #include <atomic>
+#include <type_traits>
 
 #include "kmeans.h"
 
@@ -152,10 +153,12 @@ prep_centroids_kernel(const float* __restrict__ cent, int C, int Cpad, int d, fl
 // Centroid chunks (64 centroids, in operand order) stream through two LDS stages with
 // asynchronous global-to-LDS copies shared by the NW waves (32 rows each) of the workgroup.
 // (fp32 inputs and small bf16 ones; other bf16 inputs go through the filter below.)
+// (Waves a SIMD are asked for: without a bound the accumulators go to AGPRs, and every score through a move. With it, and
+// the padding half of a last chunk left out, 8 x 18,135 rows, 200 centroids: d = 128 753 -> 643 us, d = 64 419 -> 400.)
 template <typename T, int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, D == 64 ? 4 : 3)
 assign_mfma_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const float* __restrict__ cperm,
-                   const float* __restrict__ cn, int Cpad, int32_t* __restrict__ labels) {
+                   const float* __restrict__ cn, int C, int Cpad, int32_t* __restrict__ labels) {
   constexpr int QG = D / 8;                        // 16-byte operand groups per block
   constexpr int CHUNK_BYTES = kCentChunk * D * 4;  // one LDS stage of centroids
   constexpr int COPIES = CHUNK_BYTES / 1024 / NW;
@@ -199,45 +202,44 @@ assign_mfma_kernel(const T* __restrict__ x, Strides st, int H, int64_t nv, const
     }
     const unsigned char* cb = smem + (ch & 1) * CHUNK_BYTES + lane * 16;
     const float* cnc = cns + (ch & 1) * kCentChunk;
-    f32x16 acc0, acc1;
+    auto test = [&](auto both_tag) __attribute__((always_inline)) {  // the chunk's two blocks, or the first alone
+      constexpr bool BOTH = decltype(both_tag)::value;
+      f32x16 acc0, acc1;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.f;
 #pragma unroll
-    for (int q = 0; q < QG; ++q) {
-      const float4 a0 = *reinterpret_cast<const float4*>(cb + q * 1024);
-      const float4 a1 = *reinterpret_cast<const float4*>(cb + (QG + q) * 1024);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, xb[4 * q + 0], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, xb[4 * q + 0], acc1, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, xb[4 * q + 1], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, xb[4 * q + 1], acc1, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, xb[4 * q + 2], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, xb[4 * q + 2], acc1, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, xb[4 * q + 3], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, xb[4 * q + 3], acc1, 0, 0, 0);
-    }
-    // register r of a block is centroid 8(r/4) + 4 lh + r%4 of the block, row li
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 n4 = *reinterpret_cast<const float4*>(cnc + 8 * g + 4 * lh);
-      const float nn[4] = {n4.x, n4.y, n4.z, n4.w};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float score = __builtin_fmaf(-2.0f, acc0[4 * g + r], nn[r]);
-        const int idx = ch * kCentChunk + 8 * g + 4 * lh + r;
-        if (score < best) { best = score; arg = idx; }
+      for (int q = 0; q < QG; ++q) {
+        const float4 a0 = *reinterpret_cast<const float4*>(cb + q * 1024);
+        float4 a1;
+        if (BOTH) a1 = *reinterpret_cast<const float4*>(cb + (QG + q) * 1024);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, xb[4 * q + 0], acc0, 0, 0, 0);
+        if (BOTH) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, xb[4 * q + 0], acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, xb[4 * q + 1], acc0, 0, 0, 0);
+        if (BOTH) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, xb[4 * q + 1], acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, xb[4 * q + 2], acc0, 0, 0, 0);
+        if (BOTH) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, xb[4 * q + 2], acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, xb[4 * q + 3], acc0, 0, 0, 0);
+        if (BOTH) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, xb[4 * q + 3], acc1, 0, 0, 0);
       }
-    }
+      // register r of a block is centroid 8(r/4) + 4 lh + r%4 of the block, row li
+      auto rank = [&](int block, const f32x16& acc) __attribute__((always_inline)) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 n4 = *reinterpret_cast<const float4*>(cnc + 32 + 8 * g + 4 * lh);
-      const float nn[4] = {n4.x, n4.y, n4.z, n4.w};
+        for (int g = 0; g < 4; ++g) {
+          const float4 n4 = *reinterpret_cast<const float4*>(cnc + 32 * block + 8 * g + 4 * lh);
+          const float nn[4] = {n4.x, n4.y, n4.z, n4.w};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float score = __builtin_fmaf(-2.0f, acc1[4 * g + r], nn[r]);
-        const int idx = ch * kCentChunk + 32 + 8 * g + 4 * lh + r;
-        if (score < best) { best = score; arg = idx; }
-      }
-    }
+          for (int r = 0; r < 4; ++r) {
+            const float score = __builtin_fmaf(-2.0f, acc[4 * g + r], nn[r]);
+            const int idx = ch * kCentChunk + 32 * block + 8 * g + 4 * lh + r;
+            if (score < best) { best = score; arg = idx; }
+          }
+        }
+      };
+      rank(0, acc0);
+      if (BOTH) rank(1, acc1);
+    };
+    if (C - ch * kCentChunk > 32) test(std::true_type{});
+    else test(std::false_type{});  // (the rest of the last chunk is padding)
     if (ch + 1 < nchunks && tid < kCentChunk) cns[((ch + 1) & 1) * kCentChunk + tid] = cn_next;
     SVGEAR_WAIT_VMCNT(0);
     __syncthreads();
@@ -1495,7 +1497,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
   SVGEAR_LAUNCH_CHECK();
   for (int it = 0; it < iters; ++it) {
     if (exact) {
-      assign<<<ga, 64 * assign_waves, lds, s>>>(x, st, H, nv, cperm, cn, Cpad, labels);
+      assign<<<ga, 64 * assign_waves, lds, s>>>(x, st, H, nv, cperm, cn, C, Cpad, labels);
     } else {
       const dim3 gf((unsigned)ceil_div(ceil_div(nv, kFilterRows), resident ? kFilterGroups : 1), BH);
       const dim3 gb((unsigned)ceil_div(nv, 256 * kBoundRows), BH);
