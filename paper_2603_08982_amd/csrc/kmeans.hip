@@ -1579,9 +1579,9 @@ extern "C" size_t svgear_kmeans_workspace(int B, int H, int64_t N, int d, int C)
          2 * align_up(BH * 2 * Cpad * d * 2, 256) + align_up(BH * N * 8, 256) +
          // partial sums of the split centroid update
          (means_parts(N, C) > 1 ? align_up(BH * C * means_parts(N, C) * d * 4, 256) : 0) +
-         // row skipping: per row two bounds, the norm, the sorted position, the flagged-row table and
-         // the queue; per-head maxima, centroid moves, radii,
-         // membership-changed flags, candidate lists with their lengths and outer distances, chunk table
+         // row skipping: per row two bounds, the norm, the queue and a flag bit; per-head maxima, centroid
+         // moves, radii, membership-changed flags, candidate lists with their lengths and outer distances,
+         // chunk table, state of the one-launch form, moves near each cluster
          align_up(BH * N * 8, 256) + 2 * align_up(BH * N * 4, 256) + align_up(BH * flag_words(N) * 8, 256) +
          align_up(BH * C * 8, 256) +
          align_up(BH * kHeadState * 4, 256) + 3 * align_up(BH * Cpad * 4, 256) +

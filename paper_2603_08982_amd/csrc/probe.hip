@@ -461,8 +461,8 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   __shared__ __attribute__((aligned(1024))) unsigned char ktile[kProbeStages][TILE_B];
   // [|delta|^2 x 32, vbar.delta x 32]; read one block later than the keys, so one buffer more
   __shared__ __attribute__((aligned(256))) float stat[kProbeStages + 1][64];
-  // scores of the workgroup's key clusters, per wave [query centroid][key cluster]: a row leaves
-  // as ONE 16-byte store at the end instead of kProbeClusters 4-byte stores a score row apart
+  // scores of the workgroup's key clusters, per wave [query centroid][key cluster]: they leave together at the
+  // end, 16 bytes at a time, instead of each by itself a score row apart
   __shared__ __attribute__((aligned(16))) float sc[kProbeWaves][32][kProbeClusters];
   // centroid weights W of the wave's query centroids and |vbar|^2 of the key clusters
   __shared__ float s_w[kProbeWaves][kProbeClusters][32], s_nvb[kProbeClusters];

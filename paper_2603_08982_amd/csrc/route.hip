@@ -382,9 +382,9 @@ route_small_kernel(const float* __restrict__ scores, const int32_t* __restrict__
 
 // ---- one budget over many blocks ---------------------------------------------------------
 // What bounds the cut of a head is reading its scores and, with one workgroup per head, the one
-// CU that does it: 300 x 1000 blocks of 40 heads took select_kernel 1.69 ms (four to five walks
+// CU that does it: 300 x 1000 blocks of 40 heads took such a cut 1.69 ms (four to five walks
 // over 1.2 MB, LDS atomics on the dozen exponents that an 8-bit digit tells apart) and
-// build_kernel 0.35 ms on 40 of 256 CUs. From kWideItems blocks a head on the work is spread:
+// the mask and lists 0.35 ms on 40 of 256 CUs. From kWideItems blocks a head on the work is spread:
 // two streaming passes over all CUs, after which a single workgroup sees only the blocks of one
 // 12-bit digit (an eighth of an octave of scores, a few thousand blocks). Measured at 300 x 1000
 // x 40 heads: cut, mask and lists 2.04 -> 0.15 ms (of a whole call of 3.74 before and 1.36 now). Small
