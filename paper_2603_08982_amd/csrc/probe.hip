@@ -291,10 +291,11 @@ sbar_mfma_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
 // 32 centroids x 64 clusters of one head of 4,096 keys, d = 64: 112 -> 12 us.
 constexpr int kF32Cents = 128;
 
-// (Waves a SIMD are asked for: without a bound the logits go to AGPRs, and each through a move: 40 x 4,000 keys of 64,
-// 30 x 60 clusters 73 -> 63 us, 8 x 6,000 of 128, 100 x 200 231 -> 209.)
+// (d = 64 asks for waves: without a bound the logits go to AGPRs, and each through a move: 40 x 4,000 keys of 64, 30 x 60
+// clusters 72 -> 61 us. d = 128 does not: 8 x 6,000, 100 x 200 213 -> 208 with two waves, but 8 x 4,640, 156 x 53, too
+// few workgroups for the chip, 154 -> 162.)
 template <int D, bool VALUE_AWARE, int CW>
-__global__ void __launch_bounds__(256, VALUE_AWARE ? 2 : 3)
+__global__ void __launch_bounds__(256, D == 128 ? 1 : VALUE_AWARE ? 2 : 3)
 block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__ vbar, const float* __restrict__ kp,
                        const float* __restrict__ vp, const int32_t* __restrict__ k_offsets,
                        const float* __restrict__ sbar, const float* __restrict__ mrow, int64_t Nk, int Cq, int Ck,
