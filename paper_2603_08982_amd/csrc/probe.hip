@@ -434,9 +434,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
 // of block k - 1 are written between the MFMAs of block k. Counters: vector ALU busy 53 %, matrix cores 38 %, the
 // two hardly at the same time. 40 heads, 300 x 1,000 centroids, the whole call: 1,870 us with the weights and
 // bounds of a cluster fetched when it begins, 1,660 with all of a workgroup's fetched at its start, 1,605 with a
-// barrier per pair of blocks, 1,490 with the sum of u^2 apart (a multiplication less a pair), no branch per
-// register in a cluster's last block and the groups of query centroids side by side on an XCD. Two waves a workgroup,
-// no wave without centroids at 300 of them, took the same.
+// barrier per pair of blocks, some 1,500 with no branch per register in a cluster's last block and the groups of query
+// centroids side by side on an XCD. Two waves a workgroup, no wave without centroids at 300 of them, took the same.
 // d = 64 has half the MFMAs and fragments and is bound by the vector ALU and latencies: three waves a SIMD,
 // for which the statistics are read group by group (240 heads x 2,000 keys, 60 clusters, 30 centroids: the
 // whole call 127 us with two waves, 103 with three).
@@ -589,7 +588,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
     issue(fc, issued);
     advance(fc);
   }
-  float E = 0.f, U = 0.f, W = 0.f, nvb = 0.f;
+  float E = 0.f, W = 0.f, nvb = 0.f;
   f32x16 acc_even, acc_odd;  // logits of the even and odd blocks
   // logits of block k (MF) and errors of block k - 1 (RANK: 0 none, 1 a full block, 2 a cluster's last one,
   // whose unused rows do not count)
@@ -631,24 +630,27 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       if (D == 64 && s + 1 < KSN) rd_stats(s + 1);
       if constexpr (RANK != 0) {
         // register r is key j0 + 8(r/4) + 4lh + r%4, query centroid a. Per key, with u = W - w:
-        //   |W vbar - w v_j|^2 = u^2 |vbar|^2 + w (-2 u vbar.delta_j + w |delta_j|^2),
-        // the u^2 in a sum of their own, which takes its factor at the end of the cluster
+        //   |W vbar - w v_j|^2 = u (u |vbar|^2 - 2 w vbar.delta_j) + w (w |delta_j|^2)
+        // (the norm inside the term: a sum of u^2 alone, a multiplication less a pair and 1 % of the call above, would
+        // leave the range of a float where the errors do not: 6,200 keys at the cap, weights below e^-44)
 #pragma unroll
         for (int r = s * RPS; r < (s + 1) * RPS; ++r) {
           const float w = __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(acc[r], scale2, neg_m2), cap2));
           const float u = W - w;
-          float uu = __builtin_fmaf(u, u, U), e = E;
-          if (VALUE_AWARE) e = __builtin_fmaf(w, __builtin_fmaf(u, dl[r], w * nn[r]), E);
-          // (an unused row, which repeats the cluster's last key, does not count: a select of the sums, no
+          float e;
+          if (VALUE_AWARE) {
+            e = __builtin_fmaf(u, __builtin_fmaf(w, dl[r], u * nvb), E);
+            e = __builtin_fmaf(w, w * nn[r], e);
+          } else {
+            e = __builtin_fmaf(u, u, E);
+          }
+          // (an unused row, which repeats the cluster's last key, does not count: a select of the sum, no
           // product of 0 with a value that has overflowed, and no branch per register: the compiler would
           // rather make one)
           if constexpr (RANK == 2) {
-            asm volatile("" : "+v"(uu), "+v"(e));
-            const bool used = pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end;
-            uu = used ? uu : U;
-            e = used ? e : E;
+            asm volatile("" : "+v"(e));
+            e = pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end ? e : E;
           }
-          U = uu;
           E = e;
         }
       }
@@ -679,7 +681,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       return true;
     }
     if (pc.j0 == pc.start) {  // first block of key cluster pc.b
-      E = U = 0.f;
+      E = 0.f;
       W = s_w[wave][pc.b - b_lo][li];
       nvb = VALUE_AWARE ? s_nvb[pc.b - b_lo] : 0.f;
     }
@@ -690,9 +692,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       else if (full) block(k, acc_new, acc, std::false_type{}, Full{});
       else block(k, acc_new, acc, std::false_type{}, Last{});
       if (pc.j0 + 32 >= pc.end) {  // last block of the cluster
-        // (both lanes' sums first: a lane without a key would multiply 0 by a norm that may have overflowed)
-        float Et = U + __shfl_xor(U, 32);
-        if (VALUE_AWARE) Et = __builtin_fmaf(Et, nvb, E + __shfl_xor(E, 32));
+        const float Et = E + __shfl_xor(E, 32);
         if (lh == 0) sc[wave][li][pc.b - b_lo] = Et / (float)(pc.end - pc.start);
       }
     }

@@ -161,3 +161,42 @@ def test_scores_do_not_depend_on_the_clusters_a_workgroup_takes(H, Ck, Cq, d):
         one = sv.probe_route(*(t[:, h:h + 1].contiguous() for t in a), n, d ** -0.5, Nq=3 * Cq)["scores"]
         torch.cuda.synchronize()
         assert torch.isfinite(one).all() and torch.equal(got[:, h:h + 1], one)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("case,value", [("cap", 0.0), ("cap", 1e-3), ("low", 1e4)])
+def test_scores_at_both_ends_of_the_weights(case, value, d):
+    """bf16 errors that a float holds although the weights' squares alone, summed over the cluster or not, would leave its
+    range: thousands of keys at the cap of e^40 with values of (almost) nothing, and weights below e^-50 with large
+    values. Keys and query have one dim that is not 0, so a logit is one product."""
+    n0, n1 = 16400, 300
+    g = torch.Generator().manual_seed(d)
+    step = 0.25 * d ** 0.5  # a logit of 1/4
+    k = torch.zeros(n0 + n1, d)
+    if case == "cap":
+        k[:n0, 0] = torch.where(torch.arange(n0) % 2 == 0, 200.0, -200.0) * step  # logits +-50 around a centroid at 0
+    else:
+        k[:n0, 0] = -206.0 * step + step * torch.randint(-4, 5, (n0,), generator=g)  # around -51.5
+    k = k.bfloat16().float()
+    v = torch.randn(n0 + n1, d, generator=g)
+    if case == "low":
+        v = 1.0 + 0.1 * v
+    v = (value * v).bfloat16().float()
+    if case == "cap":
+        v[:n0] = v[0]
+    kb, vb = (torch.stack([t[:n0].double().mean(0), t[n0:].double().mean(0)]).float() for t in (k, v))
+    q = torch.zeros(1, d)
+    q[0, 0] = 1.0
+    scale = d ** -0.5
+    logits = (k.double() @ q[0].double()) * scale
+    lb = (kb.double() @ q[0].double()) * scale
+    ref = []
+    for b, (lo, hi) in enumerate(((0, n0), (n0, n0 + n1))):
+        W, w = (torch.clamp(x - lb.max(), max=40.0).exp() for x in (lb[b], logits[lo:hi]))
+        ref.append(float(((W * vb[b].double() - w[:, None] * v[lo:hi].double()) ** 2).sum() / (hi - lo)))
+    at = lambda t, ty=torch.float32: t[None, None].to(ty).contiguous().to(dev())
+    koff = at(torch.tensor([0, n0, n0 + n1, n0 + n1]), torch.int32)
+    qoff = at(torch.tensor([0, 5, 5]), torch.int32)
+    got = to_np(sv.probe_route(at(q), at(kb), at(vb), at(k, torch.bfloat16), at(v, torch.bfloat16), qoff, koff, 1, scale, Nq=5)["scores"][0, 0, 0])
+    # a weight's error is its logit's (50 x a few 2^-24) and the exponential's; squares double it
+    assert np.isfinite(got).all() and np.allclose(got.astype(np.float64), ref, rtol=1e-4, atol=0), (got, ref)
