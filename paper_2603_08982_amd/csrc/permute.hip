@@ -14,6 +14,7 @@ namespace svgear {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxLabels = 8192;  // most labels the entry points accept
 
 __device__ __forceinline__ int token_label(const int32_t* labels, int64_t i, int64_t nv, int C) {
   if (i >= nv) return C;  // tail pseudo-cluster
@@ -383,11 +384,15 @@ int sort_labels(const int32_t* labels, int BH, int64_t N, int64_t n_tail, int C,
   scan_kernel<<<BH, kScanThreads, 2 * (C + 1) * sizeof(int32_t), s>>>(chunk_hist, N, C, nchunks, offsets, tiles, tile_cap,
                                                                   tile_len);
   SVGEAR_LAUNCH_CHECK();
-  // C + 1 positions and four counters of 16 bits a label
-  const size_t lds = (size_t)(C + 1) * (sizeof(int32_t) + kThreads / 64 * sizeof(uint16_t));
-  if (lds > 65536)
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(scatter_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  // C + 1 positions and four counters of 16 bits a label. (The limit is raised in every call and to what the most labels
+  // take: the kernel's static 8 KB count too, so that the default is passed from some 4,800 labels on, and a call of
+  // another thread never finds it below its own need.)
+  const auto scatter_lds = [](int labels) {
+    return (size_t)(labels + 1) * (sizeof(int32_t) + kThreads / 64 * sizeof(uint16_t));
+  };
+  const size_t lds = scatter_lds(C);
+  SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(scatter_kernel),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)scatter_lds(kMaxLabels)));
   scatter_kernel<<<grid, kThreads, lds, s>>>(labels, N, nv, C, nchunks, chunk_hist, perm);
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
@@ -454,7 +459,7 @@ extern "C" int svgear_permute(const int32_t* labels, int B, int H, int64_t N, in
                               const int64_t (*sstride)[3], void* const* dst, svgear_dtype dt, int d,
                               void* ws, size_t ws_bytes, void* stream) {
   if (!labels || !perm || !offsets || B <= 0 || H <= 0 || N <= 0 || n_tail < 0 || n_tail >= N || C <= 0 ||
-      C > N - n_tail || N > INT32_MAX / 2 || n_tensors < 0 || n_tensors > 4 || C > 8192)
+      C > N - n_tail || N > INT32_MAX / 2 || n_tensors < 0 || n_tensors > 4 || C > kMaxLabels)
     return SVGEAR_ERR_INVALID;
   if (dt != SVGEAR_F32 && dt != SVGEAR_BF16) return SVGEAR_ERR_INVALID;
   if (n_tensors > 0) {
