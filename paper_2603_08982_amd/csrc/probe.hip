@@ -22,6 +22,14 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr float kMaxExponent = 40.0f;  // e^40 squared still fits fp32
 
+// A one-dimensional launch in two dimensions (2^24 workgroups of 256 threads are too many for one): where a workgroup
+// stands in it. Rows are a multiple of 8 long, so that workgroups go round the XCDs as they would in one.
+constexpr int64_t kGridRow = 1 << 20;
+static inline dim3 long_grid(int64_t blocks) {
+  return blocks <= kGridRow ? dim3((unsigned)blocks) : dim3((unsigned)kGridRow, (unsigned)ceil_div(blocks, kGridRow));
+}
+__device__ __forceinline__ int long_grid_index() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+
 // |delta_j|^2 and -2 vbar . delta_j of every clustered key (delta_j = v_j - vbar of its cluster), bf16 inputs: what the
 // block errors need of the values. 256 threads per (head, key cluster): 16 key slots x 16 lanes of 8 dims (d = 64: 32 x 8).
 // They depend on nothing the centroid logits compute, so both share a launch, the logits' workgroups first: 5 heads,
@@ -100,7 +108,7 @@ sbar_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, cons
             bf16_t* __restrict__ q3, int groups, int logit_blocks, ValueStats stats) {
   __shared__ float q[kSbarRows][D];
   __shared__ float red[kSbarRows][4];
-  const int block = blockIdx.x;
+  const int block = long_grid_index();
   if (block >= logit_blocks) return value_stats<D>(stats, k_offsets, Ck, block - logit_blocks, threadIdx.x);
   const int a0 = block % groups * kSbarRows, bh = block / groups;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -469,7 +477,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   // The groups of query centroids that read the same keys run side by side on one XCD (workgroups go round-robin
   // over the eight): every eight workgroups take eight sets of clusters, the next eight the same sets again.
   const int sets = (Ck + clusters - 1) / clusters * heads;
-  const int set = blockIdx.x / (8 * cgroups) * 8 + (blockIdx.x & 7), cgroup = blockIdx.x / 8 % cgroups;
+  const int wg = long_grid_index(), set = wg / (8 * cgroups) * 8 + (wg & 7), cgroup = wg / 8 % cgroups;
   if (set >= sets) return;
   const int per_head = (Ck + clusters - 1) / clusters;
   const int bh = set / per_head, tid = threadIdx.x;
@@ -722,7 +730,7 @@ static int run_logits(const float* qbar, const float* kbar, const int32_t* k_off
   }
   if (blocks + stats.clusters > 0) {
     auto kern = d == 64 ? sbar_kernel<64> : sbar_kernel<128>;
-    kern<<<blocks + stats.clusters, 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3, groups, blocks, stats);
+    kern<<<long_grid((int64_t)blocks + stats.clusters), 256, 0, s>>>(qbar, kbar, k_offsets, Cq, Ck, scale, sbar, mrow, q3, groups, blocks, stats);
     SVGEAR_LAUNCH_CHECK();
   }
   return SVGEAR_OK;
@@ -751,7 +759,7 @@ int run_probe(const float* qbar, const float* kbar, const float* vbar, const voi
     // 40 heads, 300 x 1,000 centroids 2205, 1840, 1561, 1493; 5 x 200 x 500 247, 231, 225, 234; 8 x 30 x 60 38, 40, 44, 50
     const int64_t units = (int64_t)BH * Ck * groups;
     const int clusters = units >= 8192 ? kProbeClusters : units >= 2048 ? 4 : units >= 1024 ? 2 : 1;
-    const unsigned gb = (unsigned)(align_up(ceil_div(Ck, clusters) * BH, 8) * groups);
+    const dim3 gb = long_grid((int64_t)align_up(ceil_div(Ck, clusters) * BH, 8) * groups);
 #define SVGEAR_PM(D, VA)                                                                                     \
   block_error_mfma_kernel<D, VA><<<gb, 64 * kProbeWaves, 0, s>>>(q3, vbar, k16, k_offsets, sbar, mrow, nd, dd, Nk, stat_stride, \
                                                     Cq, Ck, scale, clusters, groups, BH, scores)

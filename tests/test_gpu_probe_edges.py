@@ -200,3 +200,21 @@ def test_scores_at_both_ends_of_the_weights(case, value, d):
     got = to_np(sv.probe_route(at(q), at(kb), at(vb), at(k, torch.bfloat16), at(v, torch.bfloat16), qoff, koff, 1, scale, Nq=5)["scores"][0, 0, 0])
     # a weight's error is its logit's (50 x a few 2^-24) and the exponential's; squares double it
     assert np.isfinite(got).all() and np.allclose(got.astype(np.float64), ref, rtol=1e-4, atol=0), (got, ref)
+
+
+def test_more_key_clusters_than_one_grid_dimension_holds():
+    """2,050 heads of 8,192 key clusters, 2^24 and more in one launch: heads of few keys, nearly all clusters empty; the
+    last head's scores are those of a call with that head alone."""
+    H, Ck, d, n = 2050, 8192, 64, 40
+    g = torch.Generator(device=dev()).manual_seed(0)
+    r = lambda *s: torch.randn(1, H, *s, d, generator=g, device=dev())
+    q, kb, vb, k, v = r(1), r(Ck), r(Ck), r(n).bfloat16(), r(n).bfloat16()
+    koff = torch.zeros(1, H, Ck + 2, dtype=torch.int32, device=dev())
+    koff[..., 1:100] = 7
+    koff[..., 100:] = n - 3
+    koff[..., -1] = n
+    qoff = torch.tensor([0, 5, 5], dtype=torch.int32, device=dev()).expand(1, H, 3).contiguous()
+    got = sv.probe_route(q, kb, vb, k, v, qoff, koff, 100, 0.125, Nq=5)["scores"]
+    for h in (0, H - 1):
+        one = sv.probe_route(*(t[:, h:h + 1].contiguous() for t in (q, kb, vb, k, v, qoff, koff)), 100, 0.125, Nq=5)["scores"]
+        assert int((one != 0).sum()) == 2 and torch.equal(got[:, h:h + 1], one)
