@@ -46,6 +46,7 @@ struct SmallKmeans {
   float* cent;
   float* cent2;
   int32_t* labels;
+  int32_t* labels2;  // [BH][n] scratch: the labels of every second iteration
   int32_t* counts;
   float* cperm;
   float* norms;    // [BH][4 Cpad]: |c|^2, eight to a line; padding +inf
@@ -60,6 +61,7 @@ constexpr int kSmallLine = 64, kSmallSpread = 8;
 constexpr int kSmallState = kSmallLine * (1 + 2 * kSmallSpread);
 
 constexpr int kSmallRows = 16384;  // most rows a head (the member lists of a group lie in LDS, two bytes a row)
+
 
 // Whether a call of these sizes takes the small path.
 bool kmeans_small_takes(int64_t BH, int64_t nv, int C);

@@ -1468,7 +1468,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr,
                                              small_state, small_norms);
     SVGEAR_LAUNCH_CHECK();
-    SmallKmeans a{x, x2, st, BH, H, (int)nv, C, Cpad, iters, cent, cent2, labels, counts, cperm, small_norms,
+    SmallKmeans a{x, x2, st, BH, H, (int)nv, C, Cpad, iters, cent, cent2, labels, perm, counts, cperm, small_norms,
                   small_state, 0, 0, 0, 0, 0};
     return launch_kmeans_small(a, D, kFilter, s);
   }

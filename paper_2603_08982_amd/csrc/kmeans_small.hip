@@ -14,6 +14,7 @@
 #include "kmeans.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace svgear {
 namespace {
@@ -46,6 +47,8 @@ __device__ __forceinline__ void store_shared(__amdgpu_buffer_rsrc_t t, int byte,
 // Eight waves a workgroup, one workgroup a CU (some 220 to 250 registers a lane: the row operands, two sets of
 // centroid fragments, 16 rows in flight).
 constexpr int kWaves = 8;
+constexpr int kMaxParts = 4;      // most parts a cluster is summed in (means_parts)
+constexpr int kLongCluster = 256;  // rows from which a cluster is summed by four waves wherever it lies
 __host__ __device__ static inline int small_share(int n) { return ((n + kWaves - 1) / kWaves + 255) & ~255; }
 // |c|^2 of eight centroids to a cache line
 __device__ __forceinline__ int norm_at(int c) { return (c >> 3) * 32 + (c & 7); }
@@ -53,20 +56,21 @@ __device__ __forceinline__ int norm_at(int c) { return (c >> 3) * 32 + (c & 7); 
 template <typename T, int D, int kShareWaves>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 kmeans_small_kernel(SmallKmeans p) {
+  using Share = std::integral_constant<int, kShareWaves>;
   constexpr int kUnits = kWaves / kShareWaves;  // clusters (or parts of one) at work at the same time
   constexpr int VEC = 16 / sizeof(T);   // elements per 16 bytes
   constexpr int LPR = D / VEC;          // lanes per row
   constexpr int SLOTS = 256 / LPR;      // member slots of a cluster's sum
-  constexpr int RPL = 64 / LPR, J = 4 / kShareWaves;  // a wave fetches RPL rows at once: slots RPL j + lane / LPR of J j
+  constexpr int RPL = 64 / LPR;         // rows a wave fetches at once, for slots RPL j + lane / LPR of its 4 / waves j
   constexpr int HALVES = D / 64;        // a 32-centroid block's operands come in pieces of 64 dims
-  static_assert(SLOTS == J * kShareWaves * RPL, "slots");
+  static_assert(SLOTS == 4 * RPL, "slots");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_task, s_cnt[kWaves][kWaves], s_count[kUnits];
+  __shared__ int s_task, s_cnt[kWaves][kWaves], s_live[kUnits], s_moved[kWaves];
   __shared__ float s_norm[kUnits];
   __shared__ float s_best[4][256];
   __shared__ int s_arg[4][256];
   __shared__ __attribute__((aligned(16))) float s_red[kUnits][SLOTS][D], s_mean[kUnits][D];
-  __shared__ __attribute__((aligned(16))) float s_part[8][D];
+  __shared__ __attribute__((aligned(16))) float s_part[kMaxParts][D];
   const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = p.n, C = p.C;
@@ -78,11 +82,11 @@ kmeans_small_kernel(SmallKmeans p) {
   int32_t* groups_done = tiles_done + kSmallLine * kSmallSpread;
   const T* xh = static_cast<const T*>(p.x) + head_base(p.st, bh, p.H);
   const T* x2h = p.x2 ? static_cast<const T*>(p.x2) + head_base(p.st, bh, p.H) : nullptr;
-  int32_t* lab = p.labels + (int64_t)bh * n;
+  // labels of iteration it: the two buffers in turn, the last iteration's in the caller's
+  auto label_rows = [&](int it) { return ((p.iters - 1 - it) & 1 ? p.labels2 : p.labels) + (int64_t)bh * n; };
   const __amdgpu_buffer_rsrc_t tab = shared_table(p.cperm + (int64_t)bh * p.Cpad * D, (int64_t)p.Cpad * D * 4);
   float* cnb = p.norms + (int64_t)bh * p.Cpad * 4;
   const __amdgpu_buffer_rsrc_t norms = shared_table(cnb, (int64_t)p.Cpad * 16);
-  const __amdgpu_buffer_rsrc_t labels = shared_table(lab, (int64_t)n * 4);
   const uint64_t below = (1ull << lane) - 1ull;
 
   auto wait_for = [&](const int32_t* counters, int target) {
@@ -164,13 +168,15 @@ kmeans_small_kernel(SmallKmeans p) {
         const int a2 = s_arg[w][tid];
         if (b2 < b || (b2 == b && a2 < a)) { b = b2; a = a2; }
       }
-      store_shared(lab + at, a);
+      store_shared(label_rows(it) + at, a);
     }
   };
 
-  // the rows members[from, to) added up by kShareWaves waves: a lane's 16 bytes of its slots, to s_red[unit]
-  const int unit = wave / kShareWaves, j0 = (wave % kShareWaves) * J;
-  auto sum_rows = [&](const T* src, int from, int to) {
+  // the rows members[from, to) added up by a team of WAVES waves: a lane's 16 bytes of its slots, to s_red[u]
+  const int unit = wave / kShareWaves;
+  auto sum_rows = [&](auto waves_tag, const T* src, int from, int to, int u) {
+    constexpr int WAVES = decltype(waves_tag)::value, J = 4 / WAVES;
+    const int j0 = (wave % WAVES) * J;
     float acc[J][VEC];
 #pragma unroll
     for (int j = 0; j < J; ++j)
@@ -209,7 +215,7 @@ kmeans_small_kernel(SmallKmeans p) {
     for (int j = 0; j < J; ++j)
 #pragma unroll
       for (int e = 0; e < VEC; e += 4)
-        *reinterpret_cast<float4*>(&s_red[unit][slot0 + RPL * j][(lane % LPR) * VEC + e]) =
+        *reinterpret_cast<float4*>(&s_red[u][slot0 + RPL * j][(lane % LPR) * VEC + e]) =
             make_float4(acc[j][e], acc[j][e + 1], acc[j][e + 2], acc[j][e + 3]);
   };
   // dims lane and lane + 64 of unit u's sum: its slots in order
@@ -230,7 +236,7 @@ kmeans_small_kernel(SmallKmeans p) {
     const __amdgpu_buffer_rsrc_t out = shared_table(dst + (int64_t)bh * C * D, (int64_t)C * D * 4);
     for (int u = tid; u < rows * (D / 4); u += 64 * kWaves) {
       const int j = u / (D / 4), d = 4 * (u % (D / 4));
-      if (s_count[j] > 0)  // (a cluster without members keeps its centroid)
+      if (s_live[j])  // (a cluster without members keeps its centroid)
         store_shared(out, ((c0 + j) * D + d) * 4, *reinterpret_cast<const float4*>(&s_mean[j][d]));
     }
     if (!tables) return;
@@ -238,11 +244,11 @@ kmeans_small_kernel(SmallKmeans p) {
       const int j = u % rows, q = u / rows >> 1, h = u / rows & 1, c = c0 + j;
       const float4 v0 = *reinterpret_cast<const float4*>(&s_mean[j][8 * q]);
       const float4 v1 = *reinterpret_cast<const float4*>(&s_mean[j][8 * q + 4]);
-      if (s_count[j] > 0)
+      if (s_live[j])
         store_shared(tab, (((c >> 5) * (D / 8) + q) * 64 + (c & 31) + 32 * h) * 16,
                      h ? make_float4(v0.y, v0.w, v1.y, v1.w) : make_float4(v0.x, v0.z, v1.x, v1.z));
     }
-    if (tid < rows && s_count[tid] > 0) store_shared(cnb + norm_at(c0 + tid), s_norm[tid]);
+    if (tid < rows && s_live[tid]) store_shared(cnb + norm_at(c0 + tid), s_norm[tid]);
   };
   // one cluster's mean by one wave into s_mean[u], and |mean|^2, one chain over the dims in order
   auto finish = [&](int u, const float (&sum)[HALVES], int cnt) {
@@ -270,11 +276,19 @@ kmeans_small_kernel(SmallKmeans p) {
     const int lo = wave * share, hi = min(lo + share, n);
     uint16_t* mine = near + lo;
     int kept = 0;
+    // a bit per cluster of the group that rows came to or left in this iteration: the others keep their means, which
+    // would be the same sums again (9,600 bf16 rows of 128, 200 centroids, one with nine rows in ten, 10 iterations:
+    // 706 -> 326 us)
+    uint32_t moved = it == 0 ? ~0u : 0u;
+    const __amdgpu_buffer_rsrc_t labels = shared_table(label_rows(it), (int64_t)n * 4);
+    const __amdgpu_buffer_rsrc_t labels_before = shared_table(label_rows(it > 0 ? it - 1 : it), (int64_t)n * 4);
     constexpr int U = 4;
     for (int i0 = lo; i0 < hi; i0 += 256 * U) {
-      u32x4 l[U];  // (rows past the end read as label 0)
+      u32x4 l[U], b[U];  // (rows past the end read as label 0)
 #pragma unroll
       for (int u = 0; u < U; ++u) l[u] = __builtin_amdgcn_raw_buffer_load_b128(labels, (i0 + 256 * u + 4 * lane) * 4, 0, 16);
+#pragma unroll
+      for (int u = 0; u < U; ++u) b[u] = __builtin_amdgcn_raw_buffer_load_b128(labels_before, (i0 + 256 * u + 4 * lane) * 4, 0, 16);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = i0 + 256 * u + 4 * lane;
@@ -285,6 +299,8 @@ kmeans_small_kernel(SmallKmeans p) {
           votes[e] = __ballot(l[u][e] - (unsigned)c0 < (unsigned)G && i + e < hi);
           to += __popcll(votes[e] & below);
           kept += __popcll(votes[e]);
+          const unsigned to_c = l[u][e] - (unsigned)c0, from_c = b[u][e] - (unsigned)c0;
+          if (to_c != from_c) moved |= (to_c < (unsigned)G ? 1u << to_c : 0u) | (from_c < (unsigned)G ? 1u << from_c : 0u);
         }
         if (votes[0] | votes[1] | votes[2] | votes[3]) {
 #pragma unroll
@@ -293,10 +309,17 @@ kmeans_small_kernel(SmallKmeans p) {
         }
       }
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) moved |= __shfl_xor(moved, o);
+    if (lane == 0) s_moved[wave] = (int)moved;
     __builtin_amdgcn_wave_barrier();
     if (lane < kWaves) s_cnt[wave][lane] = 0;
     for (int e = lane; e < kept; e += 64) atomicAdd(&s_cnt[wave][mine[e] & 7], 1);
     __syncthreads();
+    const bool last = it + 1 == p.iters;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) moved |= (uint32_t)s_moved[w];
+    if (moved == 0 && !last) return;
     // lane 8 k + w: where wave w's members of cluster k begin
     const int here = s_cnt[lane & 7][lane >> 3];
     int upto = here;
@@ -308,7 +331,12 @@ kmeans_small_kernel(SmallKmeans p) {
     int next = upto - here;
     const int own = P == 1 ? unit : 0, begin = __shfl(next, 8 * own), count = __shfl(upto, 8 * own + 7) - begin;
     const bool lead = wave % kShareWaves == 0;
-    if (lane == 0 && lead) s_count[unit] = count;
+    int longest = upto - __shfl_up(upto, 8);  // (lanes 8 k + 7 hold a cluster's rows)
+    if (lane < 8) longest = upto;
+    longest = lane % 8 == 7 ? longest : 0;
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) longest = max(longest, __shfl_xor(longest, o));
+    longest = __shfl(longest, 7);
     for (int e = 0; e < kept; e += 64) {
       const int v = e + lane < kept ? mine[e + lane] : -1, c = v < 0 ? -1 : v & 7;
       int to = __shfl(next, 8 * (c & 7) + wave);
@@ -321,23 +349,38 @@ kmeans_small_kernel(SmallKmeans p) {
       if (c >= 0) members[to] = (uint16_t)(lo + (v >> 3));
     }
     __syncthreads();
-    const bool last = it + 1 == p.iters;
     if (last && lane == 0 && lead && c0 + unit < C && unit < G) p.counts[(int64_t)bh * C + c0 + unit] = count;
     const int len = (((count + P - 1) / P) + SLOTS - 1) / SLOTS * SLOTS;
     for (int t = 0; t < (last && x2h ? 2 : 1); ++t) {
       const T* src = t ? x2h : xh;
+      const bool live = count > 0 && (t == 1 || (moved >> own & 1u));
+      if (lane == 0 && lead) s_live[unit] = live;
       float s[HALVES];
       if (P == 1) {
-        if (count > 0) sum_rows(src, begin, begin + count);
+        // (a long cluster would keep its one or two waves busy for all the others: four take it)
+        const bool alone = kShareWaves == 4 || count <= kLongCluster;
+        if (live && alone) sum_rows(Share{}, src, begin, begin + count, unit);
         __syncthreads();
-        if (lead && count > 0) {
+        if (lead && live && alone) {
           unit_sum(unit, s);
           finish(unit, s, count);
         }
-      } else {
-        for (int p0 = 0; p0 < P; p0 += kUnits) {  // (P parts of the members; an empty one adds a zero)
+        if (kShareWaves < 4 && longest > kLongCluster) {
+          for (int k = 0; k < kUnits; k += 2) {
+            const int c = k + wave / 4, from = __shfl(upto - here, 8 * c), n_c = __shfl(upto, 8 * c + 7) - from;
+            const bool on = n_c > kLongCluster && (t == 1 || (moved >> c & 1u));
+            if (on) sum_rows(std::integral_constant<int, 4>{}, src, from, from + n_c, c);
+            __syncthreads();
+            if (on && wave % 4 == 0) {
+              unit_sum(c, s);
+              finish(c, s, n_c);
+            }
+          }
+        }
+      } else if constexpr (kShareWaves == 4) {
+        for (int p0 = 0; live && p0 < P; p0 += kUnits) {  // (P parts of the members; an empty one adds a zero)
           const int from = min((p0 + unit) * len, count), to = min(from + len, count);
-          sum_rows(src, from, to);
+          sum_rows(Share{}, src, from, to, unit);
           __syncthreads();
           if (lead && p0 + unit < P) {
             unit_sum(unit, s);
@@ -346,7 +389,7 @@ kmeans_small_kernel(SmallKmeans p) {
           }
           __syncthreads();
         }
-        if (wave == 0 && count > 0) {
+        if (wave == 0 && live) {
 #pragma unroll
           for (int h = 0; h < HALVES; ++h) {
             s[h] = s_part[0][lane + 64 * h];
@@ -385,15 +428,14 @@ kmeans_small_kernel(SmallKmeans p) {
 }
 
 template <typename T, int D, int SHARE>
-int launch_share(SmallKmeans a, hipStream_t s) {
-  a.groups = a.parts == 1 ? (int)ceil_div(a.C, kWaves / SHARE) : a.C;
+int launch_share(const SmallKmeans& a, hipStream_t s) {
   const size_t lds = (kWaves * (size_t)small_share(a.n) + align_up(a.n, 8)) * 2;
   auto kern = kmeans_small_kernel<T, D, SHARE>;
   SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds));
   // at most a workgroup a CU: with more, the first heads' workgroups fill the chip and the last heads run after them
   // (5 x 600 rows, 100 centroids: 110 us with 512, 68 with 256)
-  kern<<<dim3(std::min(a.tiles + a.groups, std::max(1, 256 / a.BH)), a.BH), 64 * kWaves, lds, s>>>(a);
+  kern<<<dim3(std::min(a.tiles + a.groups, 256 / a.BH), a.BH), 64 * kWaves, lds, s>>>(a);
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
 }
@@ -402,21 +444,8 @@ int launch_shape(const SmallKmeans& a, int share, hipStream_t s) {
   return share == 1 ? launch_share<T, D, 1>(a, s) : share == 2 ? launch_share<T, D, 2>(a, s) : launch_share<T, D, 4>(a, s);
 }
 
-}  // namespace
-
-// Measured against the launch-by-launch paths over 1 to 40 heads of 600 to 19,200 rows, 10 to 1,000 centroids, both
-// types and head sizes, four iterations (us a call, before and here):
-//  * up to 64 centroids nearly always faster: 1 x 600, 10 centroids 76 -> 59; 2 x 2,400, 30 94 -> 67; 8 x 9,600, 30
-//    355 -> 150; 40 x 4,800, 10 328 -> 242; at 19,200 rows a head even or slower (3 heads, 10 centroids 206 -> 226);
-//  * more centroids: while tiles and groups fit about one round of the CUs. 640 blocks of 64 rows: 1 x 9,600, 300
-//    centroids 245 -> 131, 5 x 2,400, 300 172 -> 124, 8 x 1,200, 100 102 -> 82; 12 x 4,800, 100 178 -> 210. 256
-//    groups of 8 centroids: 12 x 1,200, 100 104 -> 85; 24 x 1,200, 100 125 -> 149; 8 x 2,400, 300 196 -> 210.
-bool kmeans_small_takes(int64_t BH, int64_t nv, int C) {
-  if (nv > kSmallRows || BH * nv > 200000) return false;
-  return C <= 64 || (BH * ceil_div(nv, 64) <= 640 && BH * ceil_div(C, 8) <= 256);
-}
-
-int launch_kmeans_small(SmallKmeans a, int d, bool bf16, hipStream_t s) {
+// The shape of a call's work (waves a cluster as the result).
+int set_shape(SmallKmeans& a) {
   // four waves, one a SIMD, share a tile's rows and centroid blocks; all eight where the tiles outnumber the CUs
   const int nblk = (a.C + 31) / 32;
   a.col_waves = nblk >= 4 ? 4 : nblk >= 2 ? 2 : 1;
@@ -428,6 +457,39 @@ int launch_kmeans_small(SmallKmeans a, int d, bool bf16, hipStream_t s) {
   // with one, 128 with two, 124 with four; 12 x 1,200 rows, 100 centroids: 317, 309, 408)
   int share = 4;
   if (a.parts == 1 && a.BH * ceil_div(a.C, 2) > 256) share = a.BH * ceil_div(a.C, 4) > 256 ? 1 : 2;
+  a.groups = a.parts == 1 ? (int)ceil_div(a.C, kWaves / share) : a.C;
+  return share;
+}
+
+}  // namespace
+
+// While groups are one round of the CUs, tiles one or (four waves a cluster, one block of centroids a wave) two, and no
+// cluster is many workgroups' work on the other path, which gives every part of a cluster its own. Measured against that
+// path over 1 to 300 heads of 130 to 16,384 rows, 1 to 2,000 centroids, both types and head sizes, 2, 4 and 10
+// iterations, rows spread evenly over 128 components or nine in ten of them in one cluster:
+//  * inside: 1.46 times as fast on average, two to five times where an fp32 call has a dominant cluster, 0.93 to 1 in
+//    the least favourable variants: two iterations of a few hundred rows (36 -> 38 us, in a layer ten launches less),
+//    and bf16 calls of 10 iterations with a dominant cluster, most of whose rows the other path stops assigning
+//    (2 x 4,800, 300 centroids 282 -> 302 us; 16 x 4,800, 10 centroids 270 -> 292; with 4 iterations as fast or faster);
+//  * more groups: 40 x 300, 64 centroids 0.84, 100 x 300, 48 0.63, 300 x 300, 5 0.46;
+//  * more tiles: 12 x 2,400, 100 centroids 0.80, 5 x 4,800, 200 0.73, 24 x 4,800, 48 0.59;
+//  * more parts: 1 x 16,384 rows in 16 clusters (8 parts) 0.56, 12 x 2,400 in 2 (8) 0.75, 1 x 2,400 in 4 (5) 0.89;
+//    3 and 4 parts of long heads that leave CUs idle: 1 x 16,384 in 32 0.67, 3 x 8,100 in 20 0.84, 1 x 6,300 in 16 0.72;
+//  * one or two workgroups a head: 100 x 630, 2 centroids 0.85.
+bool kmeans_small_takes(int64_t BH, int64_t nv, int C) {
+  if (BH > 64 || nv > kSmallRows) return false;
+  SmallKmeans a{};
+  a.BH = (int)BH;
+  a.n = (int)nv;
+  a.C = C;
+  const int share = set_shape(a);
+  const int64_t tiles = BH * a.tiles, groups = BH * a.groups;
+  if (a.parts > 2 && (a.parts > kMaxParts || (BH < 8 && nv > 5000))) return false;
+  return groups <= 256 && (tiles <= 256 || (tiles <= 512 && share == 4 && C <= 128));
+}
+
+int launch_kmeans_small(SmallKmeans a, int d, bool bf16, hipStream_t s) {
+  const int share = set_shape(a);
   if (bf16) return d == 64 ? launch_shape<bf16_t, 64>(a, share, s) : launch_shape<bf16_t, 128>(a, share, s);
   return d == 64 ? launch_shape<float, 64>(a, share, s) : launch_shape<float, 128>(a, share, s);
 }

@@ -1,7 +1,7 @@
 """GPU k-means of small calls (all iterations in one launch) against the paths that launch every step: labels, counts,
 centroids and the second tensor's means are the same bits, at the edges of blocks of centroids (32), groups of clusters
-(2, 4, 8), tiles, clusters summed in parts, with text rows, strides, empty and lopsided clusters and rows without a
-finite score."""
+(2, 4, 8), tiles, clusters summed in parts, with text rows, strides, empty and lopsided clusters, iterations that leave
+clusters as they are and rows without a finite score."""
 import pytest
 import torch
 
@@ -38,7 +38,7 @@ def _rows(H, N, d, dtype, seed, spread=40):
 @pytest.mark.parametrize("H,N,tail,C", [
     (1, 2, 1, 1), (1, 33, 0, 33), (2, 257, 5, 2), (3, 640, 7, 31), (2, 667, 37, 32), (2, 700, 0, 33), (1, 4096, 0, 64),
     (1, 900, 3, 65), (5, 1000, 0, 129), (1, 2049, 1, 8), (2, 5000, 0, 3), (12, 1200, 0, 100), (17, 650, 9, 90),
-    (1, 16384, 0, 20), (1, 16385, 0, 20), (1, 9000, 0, 1000), (40, 600, 0, 10), (300, 64, 0, 5),
+    (1, 16384, 0, 80), (1, 16385, 0, 80), (8, 9600, 0, 24), (1, 4999, 0, 10), (2, 9600, 0, 100), (1, 9000, 0, 1000), (40, 600, 0, 10), (300, 64, 0, 5),
 ])
 def test_small_calls_agree_with_the_step_by_step_paths(H, N, tail, C, d, dtype):
     x, x2 = _rows(H, N, d, dtype, 1), _rows(H, N, d, dtype, 2)
@@ -46,14 +46,13 @@ def test_small_calls_agree_with_the_step_by_step_paths(H, N, tail, C, d, dtype):
     start = torch.stack([x[0, h, torch.randperm(N - tail, generator=g)[:C].to(dev())].float() for h in range(H)])[None].contiguous()
     if C > 2:
         start[0, 0, 1] = 1e6  # a cluster without rows
-    for iters in (1, 2, 5):
+    for iters in (1, 2, 5, 12):
         _both(x, start, iters, tail, x2 if iters != 2 else None)
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("C", [6, 40])
-def test_lopsided_clusters_strided_and_nonfinite_rows(C, d):
-    H, N = 2, 3000
+@pytest.mark.parametrize("H,N,C", [(2, 3000, 6), (2, 3000, 40), (16, 1200, 40), (24, 1200, 48)])  # 4, 4, 2, 1 waves a cluster
+def test_lopsided_clusters_strided_and_nonfinite_rows(H, N, C, d):
     x = _rows(H, N, d, torch.bfloat16, 5, spread=1)  # one blob: nearly all rows go to the centroid in its middle
     start = x[:, :, :C].float() * 3.0
     start[:, :, C // 2] = x.float().mean(2)
