@@ -62,9 +62,10 @@ constexpr int kSmallState = kSmallLine * (1 + 2 * kSmallSpread);
 
 constexpr int kSmallRows = 16384;  // most rows a head (the member lists of a group lie in LDS, two bytes a row)
 
+constexpr int kSmallIterations = 1 << 16;  // most iterations (tasks are counted in 32 bits)
 
 // Whether a call of these sizes takes the small path.
-bool kmeans_small_takes(int64_t BH, int64_t nv, int C);
+bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters);
 int launch_kmeans_small(SmallKmeans a, int d, bool bf16, hipStream_t s);
 
 }  // namespace svgear

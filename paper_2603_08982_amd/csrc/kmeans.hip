@@ -1464,7 +1464,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_f));
   const dim3 gp((unsigned)ceil_div((int64_t)Cpad * D, 256 * 4), BH);
   // (a threshold of the caller's own asks for the forms it chooses between)
-  if (g_list_min_centroids.load(std::memory_order_relaxed) == kListDefault && kmeans_small_takes(BH, nv, C)) {
+  if (g_list_min_centroids.load(std::memory_order_relaxed) == kListDefault && kmeans_small_takes(BH, nv, C, iters)) {
     prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr,
                                              small_state, small_norms);
     SVGEAR_LAUNCH_CHECK();

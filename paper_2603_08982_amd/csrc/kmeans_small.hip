@@ -476,8 +476,8 @@ int set_shape(SmallKmeans& a) {
 //  * more parts: 1 x 16,384 rows in 16 clusters (8 parts) 0.56, 12 x 2,400 in 2 (8) 0.75, 1 x 2,400 in 4 (5) 0.89;
 //    3 and 4 parts of long heads that leave CUs idle: 1 x 16,384 in 32 0.67, 3 x 8,100 in 20 0.84, 1 x 6,300 in 16 0.72;
 //  * one or two workgroups a head: 100 x 630, 2 centroids 0.85.
-bool kmeans_small_takes(int64_t BH, int64_t nv, int C) {
-  if (BH > 64 || nv > kSmallRows) return false;
+bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters) {
+  if (BH > 64 || nv > kSmallRows || iters > kSmallIterations) return false;
   SmallKmeans a{};
   a.BH = (int)BH;
   a.n = (int)nv;

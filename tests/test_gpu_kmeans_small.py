@@ -60,3 +60,16 @@ def test_lopsided_clusters_strided_and_nonfinite_rows(H, N, C, d):
     _both(x, start.contiguous(), 4, 11, x)
     x[0, 0, 100, 3], x[0, 1, 200, 5] = float("nan"), float("inf")
     _both(x, start.contiguous(), 1, 0, None)
+
+
+def test_more_iterations_than_the_one_launch_counts():
+    """65,537 iterations, past the last of which the tasks of a launch are no longer sure to be counted in 32 bits."""
+    x = _rows(1, 64, 64, torch.float32, 8)
+    start = x[:, :, :3].contiguous()
+    got = []
+    for iters in (65537, 100):
+        c = start.clone()
+        labels, counts, _ = sv.kmeans(x, c, iters)
+        got.append((labels, counts, c))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
