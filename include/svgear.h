@@ -91,13 +91,21 @@ int svgear_kmeans(const void* x, const void* x2, svgear_dtype dt, int B, int H, 
                   float* centroids, float* centroids2, int32_t* labels, int32_t* counts,
                   void* ws, size_t ws_bytes, void* stream);
 
+/* svgear_kmeans with launches of its own for every step, small calls too: the same arguments, the
+ * same results bit for bit. For comparing and timing the two ways. */
+int svgear_kmeans_stepwise(const void* x, const void* x2, svgear_dtype dt, int B, int H, int64_t N,
+                           int64_t n_tail, int d, const int64_t xstride[3], int C, int iters,
+                           float* centroids, float* centroids2, int32_t* labels, int32_t* counts,
+                           void* ws, size_t ws_bytes, void* stream);
+
 /* Tuning (host only; results never depend on it). From the second iteration on, a bf16 call
  * re-assigns only the rows whose distance bounds do not prove that their label stays. With
  * C >= the value set here each such row is tested against the centroids near its cluster only
  * (candidate lists from centroid-to-centroid distances); with fewer centroids against all of
- * them (small calls, which assign every row in every iteration, do so too while the value is
- * another than the default). min_centroids >= 1 sets the threshold for later calls of this process (INT_MAX: never
- * use lists); min_centroids <= 0 only queries. Returns the previous value (default 400). */
+ * them. (Small calls, whose iterations all run in one launch, test every row against every centroid in
+ * every iteration, whatever the value.) min_centroids >= 1 sets the threshold for later calls of this
+ * process (INT_MAX: never use lists); min_centroids <= 0 only queries. Returns the previous value
+ * (default 400). */
 int svgear_kmeans_list_threshold(int min_centroids);
 
 /* ---------------------------------------------------------------------------------------

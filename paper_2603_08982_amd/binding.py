@@ -21,7 +21,7 @@ USE_GIVEN_SCORES = 4
 
 EXPORTED_SYMBOLS = [
     "svgear_version", "svgear_last_hip_error",
-    "svgear_kmeans_workspace", "svgear_kmeans", "svgear_kmeans_list_threshold",
+    "svgear_kmeans_workspace", "svgear_kmeans", "svgear_kmeans_stepwise", "svgear_kmeans_list_threshold",
     "svgear_permute_workspace", "svgear_permute", "svgear_permute_rows",
     "svgear_permute_static_capacity", "svgear_permute_static",
     "svgear_probe_route_workspace", "svgear_probe_route", "svgear_probe_route_top_p",
@@ -61,6 +61,8 @@ def load_library():
     lib.svgear_kmeans.restype = _i
     lib.svgear_kmeans.argtypes = [_vp, _vp, _i, _i, _i, _i64, _i64, _i, _c.POINTER(_c.c_int64), _i, _i,
                                   _vp, _vp, _vp, _vp, _vp, _sz, _vp]
+    lib.svgear_kmeans_stepwise.restype = _i
+    lib.svgear_kmeans_stepwise.argtypes = lib.svgear_kmeans.argtypes
     lib.svgear_permute_workspace.restype = _sz
     lib.svgear_permute_workspace.argtypes = [_i, _i, _i64, _i]
     lib.svgear_permute.restype = _i
@@ -150,8 +152,9 @@ def kmeans_list_threshold(min_centroids: int = 0) -> int:
 
 
 def kmeans(x: torch.Tensor, centroids: torch.Tensor, iters: int, n_tail: int = 0,
-           x2: Optional[torch.Tensor] = None):
-    """svgear_kmeans. x [B,H,N,d]; centroids [B,H,C,d] fp32 (updated in place).
+           x2: Optional[torch.Tensor] = None, one_launch: bool = True):
+    """svgear_kmeans (one_launch=False: svgear_kmeans_stepwise, the same results with launches of its own for
+    every step of a small call too). x [B,H,N,d]; centroids [B,H,C,d] fp32 (updated in place).
     Returns (labels [B,H,N-n_tail] i32, counts [B,H,C] i32, centroids2 or None)."""
     _need_gpu(x, centroids, x2)
     lib = load_library()
@@ -165,9 +168,10 @@ def kmeans(x: torch.Tensor, centroids: torch.Tensor, iters: int, n_tail: int = 0
     c2 = torch.zeros(B, H, C, d, dtype=torch.float32, device=x.device) if x2 is not None else None
     ws = _ws(lib.svgear_kmeans_workspace(B, H, N, d, C), x.device)
     st = _strides4(x)
-    rc = lib.svgear_kmeans(_ptr(x), _ptr(x2), _dt(x), B, H, N, n_tail, d, st, C, iters, _ptr(centroids),
-                           _ptr(c2), _ptr(labels), _ptr(counts), _ptr(ws), ws.numel(), _stream())
-    _check(rc, "svgear_kmeans")
+    fn = lib.svgear_kmeans if one_launch else lib.svgear_kmeans_stepwise
+    rc = fn(_ptr(x), _ptr(x2), _dt(x), B, H, N, n_tail, d, st, C, iters, _ptr(centroids), _ptr(c2), _ptr(labels),
+            _ptr(counts), _ptr(ws), ws.numel(), _stream())
+    _check(rc, "svgear_kmeans" if one_launch else "svgear_kmeans_stepwise")
     return labels, counts, c2
 
 

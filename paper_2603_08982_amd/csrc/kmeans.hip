@@ -44,8 +44,7 @@ constexpr int kListChunk = 256;                 // sorted positions per wave of 
 constexpr int kMaxCentroids = 8192;             // most centroids per head the entry point accepts
 // Candidate lists pay when there are many centroids: with fewer than this, testing every
 // centroid (shared through LDS by 256 rows, streaming) costs no more than the lists' gathers.
-constexpr int kListDefault = 400;
-std::atomic<int> g_list_min_centroids{kListDefault};
+std::atomic<int> g_list_min_centroids{400};
 // (in the second iteration of a cold start the radii still reach every centroid, so no cluster gets
 // a list: the lists start one iteration later)
 #ifndef SVGEAR_LIST_FROM
@@ -1406,7 +1405,7 @@ means_finish_kernel(const float* __restrict__ partial, const int32_t* __restrict
 
 template <typename T, int D>
 int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail, Strides st, int C, int iters,
-               float* cent, float* cent2, int32_t* labels, int32_t* counts, Workspace& ws, hipStream_t s) {
+               float* cent, float* cent2, int32_t* labels, int32_t* counts, bool one_launch, Workspace& ws, hipStream_t s) {
   const int64_t nv = N - n_tail;
   const int Cpad = (int)align_up(C, kCentChunk);
   int32_t* chunk_hist = ws.take<int32_t>((size_t)BH * sort_chunks(nv) * (C + 1));
@@ -1463,8 +1462,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(filter),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_f));
   const dim3 gp((unsigned)ceil_div((int64_t)Cpad * D, 256 * 4), BH);
-  // (a threshold of the caller's own asks for the forms it chooses between)
-  if (g_list_min_centroids.load(std::memory_order_relaxed) == kListDefault && kmeans_small_takes(BH, nv, C, iters)) {
+  if (one_launch && kmeans_small_takes(BH, nv, C, iters)) {
     prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr,
                                              small_state, small_norms);
     SVGEAR_LAUNCH_CHECK();
@@ -1590,10 +1588,10 @@ extern "C" size_t svgear_kmeans_workspace(int B, int H, int64_t N, int d, int C)
          align_up(BH * Cpad * 16, 256);
 }
 
-extern "C" int svgear_kmeans(const void* x, const void* x2, svgear_dtype dt, int B, int H, int64_t N,
-                             int64_t n_tail, int d, const int64_t xstride[3], int C, int iters, float* centroids,
-                             float* centroids2, int32_t* labels, int32_t* counts, void* ws, size_t ws_bytes,
-                             void* stream) {
+namespace {
+int kmeans_impl(const void* x, const void* x2, svgear_dtype dt, int B, int H, int64_t N, int64_t n_tail,
+                int d, const int64_t xstride[3], int C, int iters, float* centroids, float* centroids2,
+                int32_t* labels, int32_t* counts, bool one_launch, void* ws, size_t ws_bytes, void* stream) {
   if (!x || !xstride || !centroids || !labels || !counts || B <= 0 || H <= 0 || N <= 0 || n_tail < 0 ||
       n_tail >= N || C <= 0 || C > N - n_tail || C > kMaxCentroids || iters < 1 || N > INT32_MAX / 2 ||
       (d != 64 && d != 128) || (dt != SVGEAR_F32 && dt != SVGEAR_BF16) || ((x2 == nullptr) != (centroids2 == nullptr)))
@@ -1609,7 +1607,7 @@ extern "C" int svgear_kmeans(const void* x, const void* x2, svgear_dtype dt, int
   const int BH = B * H;
 #define SVGEAR_KM(T, D)                                                                                   \
   return run_kmeans<T, D>(static_cast<const T*>(x), static_cast<const T*>(x2), BH, H, N, n_tail, st, C, iters, \
-                          centroids, centroids2, labels, counts, w, s)
+                          centroids, centroids2, labels, counts, one_launch, w, s)
   if (dt == SVGEAR_F32) {
     if (d == 64) SVGEAR_KM(float, 64);
     SVGEAR_KM(float, 128);
@@ -1618,4 +1616,21 @@ extern "C" int svgear_kmeans(const void* x, const void* x2, svgear_dtype dt, int
     SVGEAR_KM(bf16_t, 128);
   }
 #undef SVGEAR_KM
+}
+}  // namespace
+
+extern "C" int svgear_kmeans(const void* x, const void* x2, svgear_dtype dt, int B, int H, int64_t N,
+                             int64_t n_tail, int d, const int64_t xstride[3], int C, int iters, float* centroids,
+                             float* centroids2, int32_t* labels, int32_t* counts, void* ws, size_t ws_bytes,
+                             void* stream) {
+  return kmeans_impl(x, x2, dt, B, H, N, n_tail, d, xstride, C, iters, centroids, centroids2, labels, counts, true, ws,
+                     ws_bytes, stream);
+}
+
+extern "C" int svgear_kmeans_stepwise(const void* x, const void* x2, svgear_dtype dt, int B, int H, int64_t N,
+                                      int64_t n_tail, int d, const int64_t xstride[3], int C, int iters,
+                                      float* centroids, float* centroids2, int32_t* labels, int32_t* counts, void* ws,
+                                      size_t ws_bytes, void* stream) {
+  return kmeans_impl(x, x2, dt, B, H, N, n_tail, d, xstride, C, iters, centroids, centroids2, labels, counts, false, ws,
+                     ws_bytes, stream);
 }

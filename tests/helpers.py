@@ -3,6 +3,7 @@ import numpy as np
 import torch
 
 from oracle import svgear_oracle as orc
+from paper_2603_08982_amd.binding import kmeans, kmeans_list_threshold
 from workloads import kmeans_init_indices, structural_rows
 
 
@@ -13,6 +14,19 @@ def dev():
 def to_np(t: torch.Tensor) -> np.ndarray:
     t = t.detach().cpu()
     return t.float().numpy() if t.dtype == torch.bfloat16 else t.numpy()
+
+
+KMEANS_FORMS = ("one launch", "steps", "lists")
+
+
+def kmeans_as(form, *args, **kw):
+    """The library's k-means in one of its forms: all iterations in one launch (where the call's sizes take it), a launch or more per
+    step without candidate lists, and the same with lists whatever the number of centroids (bf16)."""
+    before = kmeans_list_threshold({"one launch": 0, "steps": 2**31 - 1, "lists": 1}[form])
+    try:
+        return kmeans(*args, one_launch=form == "one launch", **kw)
+    finally:
+        kmeans_list_threshold(before)
 
 
 def init_centroids(X: torch.Tensor, C: int, seed: int, tensor_id: int, n_tail: int = 0) -> torch.Tensor:

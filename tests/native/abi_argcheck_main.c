@@ -51,6 +51,8 @@ int main(void) {
          svgear_kmeans(fake, NULL, SVGEAR_F32, 1, 1, 16, 0, 64, st64, 2, 0, fake, NULL, fake, fake, fake, big, NULL), -1);
   expect("kmeans: null strides",
          svgear_kmeans(fake, NULL, SVGEAR_F32, 1, 1, 16, 0, 64, NULL, 2, 1, fake, NULL, fake, fake, fake, big, NULL), -1);
+  expect("kmeans_stepwise: C > N - n_tail",
+         svgear_kmeans_stepwise(fake, NULL, SVGEAR_F32, 1, 1, 16, 0, 64, st64, 17, 1, fake, NULL, fake, fake, fake, big, NULL), -1);
   expect("kmeans: workspace too small",
          svgear_kmeans(fake, NULL, SVGEAR_F32, 1, 1, 16, 0, 64, st64, 2, 1, fake, NULL, fake, fake, fake, 8, NULL), -2);
 

@@ -3,24 +3,26 @@ sequence of kernel launches on the caller's stream (no host synchronisation, no 
 the work-list counters are cleared by kernels), so a caller may capture a layer and replay it
 per denoising step. Each replay is checked bit for bit against the eager result, with eager
 runs of the same path between the replays."""
+from functools import partial
+
 import pytest
 import torch
 
 import paper_2603_08982_amd as sv
+from paper_2603_08982_amd import binding
 from workloads import budget_pairs, get_workload, make_qkv
-from helpers import dev, init_centroids
+from helpers import dev, init_centroids, kmeans_as
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(params=["default", "candidate_lists"])
-def kmeans_mode(request):
-    """The library's default, and the later k-means iterations forced onto candidate lists (more
-    kernels, queues filled through atomics) whatever the number of centroids."""
-    from paper_2603_08982_amd.binding import kmeans_list_threshold
-    before = kmeans_list_threshold(1) if request.param == "candidate_lists" else kmeans_list_threshold(0)
+@pytest.fixture(params=["default", "steps", "lists"])
+def kmeans_mode(request, monkeypatch):
+    """The library's default (these sizes: one launch), k-means step by step, and its later iterations forced onto
+    candidate lists (more kernels, queues filled through atomics) whatever the number of centroids."""
+    if request.param != "default":
+        monkeypatch.setattr(binding, "kmeans", partial(kmeans_as, request.param))
     yield request.param
-    kmeans_list_threshold(before)
 
 
 @pytest.mark.parametrize("overlap", [False, True])

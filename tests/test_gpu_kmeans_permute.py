@@ -1,4 +1,6 @@
 """GPU parity: svgear_kmeans / svgear_permute / svgear_unpermute against the CPU oracle."""
+from functools import partial
+
 import numpy as np
 import pytest
 import torch
@@ -6,21 +8,18 @@ import torch
 import paper_2603_08982_amd as sv
 from oracle import svgear_oracle as orc
 from workloads import get_workload, make_qkv
-from helpers import dev, to_np, init_centroids
+from helpers import dev, to_np, init_centroids, kmeans_as
 
 pytestmark = pytest.mark.gpu
 
-NEVER = 2**31 - 1
-
 
 @pytest.fixture(params=["lists", "every_centroid"])
-def later_iterations_mode(request):
-    """Both ways the library re-assigns rows after the first iteration, whatever the number of
-    centroids: against candidate lists (threshold 1) and against every centroid."""
-    from paper_2603_08982_amd.binding import kmeans_list_threshold
-    before = kmeans_list_threshold(1 if request.param == "lists" else NEVER)
+def later_iterations_mode(request, monkeypatch):
+    """Both ways the library, launching step by step, re-assigns rows after the first iteration, whatever the number
+    of centroids: against candidate lists and against every centroid."""
+    form = "lists" if request.param == "lists" else "steps"
+    monkeypatch.setattr(sv, "kmeans", partial(kmeans_as, form))
     yield request.param
-    kmeans_list_threshold(before)
 
 
 def _lockstep(X, C, iters, n_tail=0, seed=0, tensor_id=0, X2=None):

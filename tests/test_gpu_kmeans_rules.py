@@ -1,15 +1,13 @@
-"""GPU k-means on both sides of the lines between its forms: small bf16 calls assign every row exactly in
-one launch, larger ones filter first (and, with the list threshold at 1, small ones too); workgroups of two
-or four waves. The forms give the same labels, counts and centroids bit for bit, also for strided rows and
+"""GPU k-means on both sides of the lines between its forms: the smallest calls run in one launch; launched step by
+step, small bf16 calls assign every row exactly, larger ones filter first (and, with the list threshold at 1, small
+ones too), in workgroups of two or four waves. The forms give the same labels, counts and centroids bit for bit, also for strided rows and
 with text rows, and the labels are the oracle's."""
 import numpy as np
 import pytest
 import torch
 
-import paper_2603_08982_amd as sv
 from oracle import svgear_oracle as orc
-from paper_2603_08982_amd.binding import kmeans_list_threshold
-from helpers import dev, to_np
+from helpers import KMEANS_FORMS, dev, kmeans_as, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -37,17 +35,13 @@ def test_forms_agree(H, N, tail, C, d, dtype, strided):
                          for h in range(H)])[None].float().contiguous()
     for iters in (1, 4):
         got = []
-        for threshold in (400, 1):
-            before = kmeans_list_threshold(threshold)
-            try:
-                c = start.clone()
-                labels, counts, c2 = sv.kmeans(x, c, iters, tail, x2=x2)
-                torch.cuda.synchronize()
-            finally:
-                kmeans_list_threshold(before)
+        for form in KMEANS_FORMS:
+            c = start.clone()
+            labels, counts, c2 = kmeans_as(form, x, c, iters, tail, x2=x2)
+            torch.cuda.synchronize()
             got.append((labels, counts, c, c2))
-        for a, b in zip(*got):
-            assert torch.equal(a, b)
+        for a, b, e in zip(*got):
+            assert torch.equal(a, b) and torch.equal(a, e)
         if iters == 1:
             for h in range(H):
                 assert np.array_equal(to_np(got[0][0][0, h]), orc.kmeans_assign(to_np(x[0, h])[: N - tail], to_np(start[0, h])))
@@ -66,14 +60,10 @@ def test_candidate_lists_over_many_iterations(H, N, C, d, spread):
     start = x[:, :, torch.randperm(N, generator=g)[:C].to(dev())].float().contiguous()
     for iters in (3, 4, 5, 9, 14):
         got = []
-        for threshold in (1, 2**31 - 1):
-            before = kmeans_list_threshold(threshold)
-            try:
-                c = start.clone()
-                labels, counts, _ = sv.kmeans(x, c, iters)
-                torch.cuda.synchronize()
-            finally:
-                kmeans_list_threshold(before)
+        for form in ("lists", "steps"):
+            c = start.clone()
+            labels, counts, _ = kmeans_as(form, x, c, iters)
+            torch.cuda.synchronize()
             got.append((labels, counts, c))
         for a, b in zip(*got):
             assert torch.equal(a, b)

@@ -6,22 +6,17 @@ import pytest
 import torch
 
 import paper_2603_08982_amd as sv
-from paper_2603_08982_amd.binding import kmeans_list_threshold
-from helpers import dev
+from helpers import dev, kmeans_as
 
 pytestmark = pytest.mark.gpu
 
 
 def _both(x, start, iters, tail, x2):
     got = []
-    for threshold in (400, 2**31 - 1):  # the default; another value: step by step
-        before = kmeans_list_threshold(threshold)
-        try:
-            c = start.clone()
-            labels, counts, c2 = sv.kmeans(x, c, iters, tail, x2=x2)
-            torch.cuda.synchronize()
-        finally:
-            kmeans_list_threshold(before)
+    for form in ("one launch", "steps"):
+        c = start.clone()
+        labels, counts, c2 = kmeans_as(form, x, c, iters, tail, x2=x2)
+        torch.cuda.synchronize()
         got.append((labels, counts, c) + ((c2,) if x2 is not None else ()))
     for a, b in zip(*got):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
