@@ -16,8 +16,8 @@ import numpy as np
 import pytest
 import torch
 
-import paper_2603_08982_amd as sv
 from oracle import svgear_oracle as orc
+from helpers import KMEANS_FORMS, kmeans_as
 
 ORDERS = ("pair swapped", "pair fused", "unfused", "quad fused", "quad reversed", "fully reversed", "exact")
 
@@ -124,8 +124,9 @@ def test_tie_cases_separate_the_fixed_order_from_other_orders(d):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("form", KMEANS_FORMS)  # one launch, the exact kernel, and (bf16) the filter with exact scores of few
 @pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.float32), (128, torch.bfloat16), (64, torch.bfloat16)])
-def test_kmeans_labels_follow_the_sequential_fma_chain_on_exact_ties(d, dtype):
+def test_kmeans_labels_follow_the_sequential_fma_chain_on_exact_ties(d, dtype, form):
     X, C = tie_case(d, seed=1 + d, bf16_rows=dtype == torch.bfloat16)
     ref = orc.kmeans_assign(X, C)
     others = {k: _labels_from_dots(v, C) for k, v in _dots_in_other_orders(X, C).items()}
@@ -134,8 +135,8 @@ def test_kmeans_labels_follow_the_sequential_fma_chain_on_exact_ties(d, dtype):
     x = torch.from_numpy(X).to(dtype)[None, None].cuda().contiguous()
     assert torch.equal(x.float().cpu()[0, 0], torch.from_numpy(X))  # the rows are exact in this dtype
     cent = torch.from_numpy(C)[None, None].cuda().contiguous()
-    print(f"tie case d={d} {dtype} rows={len(X)} centroids={len(C)}", flush=True)
-    labels, counts, _ = sv.kmeans(x, cent, 1)
+    print(f"tie case d={d} {dtype} {form} rows={len(X)} centroids={len(C)}", flush=True)
+    labels, counts, _ = kmeans_as(form, x, cent, 1)
     torch.cuda.synchronize()
     got = labels[0, 0].cpu().numpy()
     if not np.array_equal(got, ref):
