@@ -28,7 +28,8 @@ int run_sbar(const float* qbar, const float* kbar, const int32_t* k_offsets, int
 namespace {
 
 constexpr int kSelThreads = 1024;
-constexpr int kRowThreads = 256;
+constexpr int kRowThreads = 256, kLongRowThreads = 512;
+constexpr int kLongRow = 4000;  // key clusters from which a row with a budget of its own takes the latter
 constexpr int kTopPWeightBits = 20;  // masses are counted in units of 2^-20
 constexpr int kTopPIndexBits = 13;   // Ck <= 8192
 
@@ -164,6 +165,7 @@ __device__ __forceinline__ long long head_budget(const int32_t* qo, const int32_
 // sums are exact in any order; ordered by weight descending (ties: lower b first), the
 // shortest prefix whose weight reaches ceil(top_p * total) is kept, and the budget is the
 // cost |q_a| * sum |k_b| of exact attention over it. Called by all kRowThreads threads; wgt: Ck entries of LDS.
+template <int THREADS>
 __device__ __forceinline__ int64_t top_p_budget(const float* sbar_row, float m, const int32_t* ko, int64_t qa, int Ck,
                                                 float top_p, unsigned long long* wgt, CutState& st) {
   __shared__ unsigned long long sh_total, sh_keys;
@@ -174,7 +176,7 @@ __device__ __forceinline__ int64_t top_p_budget(const float* sbar_row, float m, 
   }
   __syncthreads();
   unsigned long long part = 0ull;
-  for (int b = threadIdx.x; b < Ck; b += kRowThreads) {
+  for (int b = threadIdx.x; b < Ck; b += THREADS) {
     const int32_t kb = ko[b + 1] - ko[b];
     unsigned long long w = 0ull;
     if (kb > 0) {
@@ -190,7 +192,7 @@ __device__ __forceinline__ int64_t top_p_budget(const float* sbar_row, float m, 
   const double want = ceil((double)top_p * (double)total);
   const long long need = want >= 1.0 ? (long long)want : 1ll;
   auto key_of = [&](int b) { return (wgt[b] << kTopPIndexBits) | (unsigned long long)((1 << kTopPIndexBits) - 1 - b); };
-  const unsigned long long cut = radix_cut<kRowThreads>(st, need - 1, Ck, [&](int it, uint64_t& key,
+  const unsigned long long cut = radix_cut<THREADS>(st, need - 1, Ck, [&](int it, uint64_t& key,
                                                                               unsigned long long& weight) {
     const int b = it;
     if (ko[b + 1] <= ko[b]) return false;
@@ -199,7 +201,7 @@ __device__ __forceinline__ int64_t top_p_budget(const float* sbar_row, float m, 
     return true;
   });
   unsigned long long keys = 0ull;
-  for (int b = threadIdx.x; b < Ck; b += kRowThreads) {
+  for (int b = threadIdx.x; b < Ck; b += THREADS) {
     const int32_t kb = ko[b + 1] - ko[b];
     if (kb > 0 && key_of(b) >= cut) keys += (unsigned long long)kb;
   }
@@ -301,16 +303,20 @@ __device__ __forceinline__ void build_head(const float* sc, const int32_t* qo, c
 // grid (Cq + 1, BH): rows with budgets of their own: the row's budget (its share of the head's, or with top_p >= 0 the
 // adaptive one, for its clustered blocks, the tail column on top), its cut, mask words, routed blocks and cost. One
 // launch instead of three or four dependent ones: 5 heads, 200 x 500 centroids 28 + 16 + 8 us, and 5 to clear a counter,
-// in 39.
-__global__ void __launch_bounds__(kRowThreads)
+// in 39. A row of thousands of blocks takes twice the threads: its adaptive weights fill so much LDS that two
+// workgroups a CU are left of it (24 heads, 400 x 6,000: 3,404 us with 256 threads, 2,581 with 512, 3,205 with 1,024; three
+// launches as before 3,070; fixed budgets 795, 752, 1,029, 802), while shorter rows wait for one another in wider ones
+// (8 heads, 1,000 x 3,000: 304 with 256, 326 with 512, 486 with 1,024; 2 heads, 1,000 x 4,000: 174, 161, 211).
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
 route_rows_kernel(const float* __restrict__ scores, const float* __restrict__ sbar, const float* __restrict__ mrow,
                   const int32_t* __restrict__ q_offsets, const int32_t* __restrict__ k_offsets, int Cq, int Ck,
                   int64_t budget, float top_p, int64_t* __restrict__ row_budget, uint32_t* __restrict__ mask_bits,
                   int32_t* __restrict__ row_count, int64_t* __restrict__ row_cost) {
   extern __shared__ unsigned long long wgt[];  // Ck, with top_p
   __shared__ CutState st;
-  __shared__ int s_cnt[kRowThreads / 64];
-  __shared__ long long s_cost[kRowThreads / 64];
+  __shared__ int s_cnt[THREADS / 64];
+  __shared__ long long s_cost[THREADS / 64];
   const int a = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int R = Cq + 1, W = (Ck + 1 + 31) / 32;
   const int32_t* qo = q_offsets + (int64_t)bh * (Cq + 2);
@@ -321,13 +327,13 @@ route_rows_kernel(const float* __restrict__ scores, const float* __restrict__ sb
     const int64_t Nq = qo[Cq + 1], qa = qo[a + 1] - qo[a], at = (int64_t)bh * Cq + a;
     long long rem;
     if (top_p >= 0.f) {
-      rem = top_p_budget(sbar + at * Ck, mrow[at], ko, qa, Ck, top_p, wgt, st);
+      rem = top_p_budget<THREADS>(sbar + at * Ck, mrow[at], ko, qa, Ck, top_p, wgt, st);
       if (threadIdx.x == 0) row_budget[at] = rem;
       __syncthreads();
     } else {
       rem = (budget * qa) / (Nq > 0 ? Nq : 1) - qa * (ko[Ck + 1] - ko[Ck]);
     }
-    cut = radix_cut<kRowThreads>(st, rem, Ck, [&](int b, uint64_t& key, unsigned long long& weight) {
+    cut = radix_cut<THREADS>(st, rem, Ck, [&](int b, uint64_t& key, unsigned long long& weight) {
       weight = block_cost(qo, ko, a * Ck + b, Ck);
       if (weight == 0ull) return false;
       key = block_key(sc[(int64_t)a * Ck + b], (uint32_t)(a * Ck + b));
@@ -335,7 +341,7 @@ route_rows_kernel(const float* __restrict__ scores, const float* __restrict__ sb
     });
   }
   long long cost = 0;
-  const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, cut, mask_bits + ((int64_t)bh * R + a) * W, cost, wave, kRowThreads / 64);
+  const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, cut, mask_bits + ((int64_t)bh * R + a) * W, cost, wave, THREADS / 64);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o);
   if (lane == 0) {
@@ -346,7 +352,7 @@ route_rows_kernel(const float* __restrict__ scores, const float* __restrict__ sb
   if (threadIdx.x == 0) {
     int n = 0;
     long long sum = 0;
-    for (int w = 0; w < kRowThreads / 64; ++w) {
+    for (int w = 0; w < THREADS / 64; ++w) {
       n += s_cnt[w];
       sum += s_cost[w];
     }
@@ -680,12 +686,14 @@ int probe_route_impl(const float* qbar, const float* kbar, const float* vbar, co
   if (adaptive || (flags & SVGEAR_ROUTE_PER_ROW)) {
     // up to 64 KB of weights for the largest Ck, beside the kernel's static LDS
     const size_t lds = adaptive ? (size_t)Ck * sizeof(unsigned long long) : 0;
-    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(route_rows_kernel),
+    const bool long_row = Ck >= kLongRow;
+    auto rows = long_row ? route_rows_kernel<kLongRowThreads> : route_rows_kernel<kRowThreads>;
+    SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(rows),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int64_t* row_cost = reinterpret_cast<int64_t*>(kstar);  // (no cut leaves that kernel)
-    route_rows_kernel<<<dim3(Cq + 1, BH), kRowThreads, lds, s>>>(scores, sbar, mrow, q_offsets, k_offsets, Cq, Ck,
-                                                                 budget_cost, adaptive ? top_p : -1.f, row_budget,
-                                                                 mask_bits, row_count, row_cost);
+    rows<<<dim3(Cq + 1, BH), long_row ? kLongRowThreads : kRowThreads, lds, s>>>(
+        scores, sbar, mrow, q_offsets, k_offsets, Cq, Ck, budget_cost, adaptive ? top_p : -1.f, row_budget, mask_bits,
+        row_count, row_cost);
     SVGEAR_LAUNCH_CHECK();
     route_lists_kernel<<<list_grid, 256, 0, s>>>(Cq, Ck, mask_bits, row_count, row_cost, row_ptr, col_idx, routed_cost);
   } else if (n_items >= kWideItems) {

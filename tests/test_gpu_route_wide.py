@@ -27,7 +27,7 @@ def _scores(kind, rng, H, Cq, Ck):
     return s
 
 
-@pytest.mark.parametrize("Cq,Ck", [(127, 129), (128, 128), (1, 8192), (300, 1000), (8, 2049), (2050, 8)])
+@pytest.mark.parametrize("Cq,Ck", [(127, 129), (128, 128), (1, 8192), (300, 1000), (8, 2049), (2050, 8), (5, 3999), (5, 4000)])
 @pytest.mark.parametrize("kind", ["plain", "equal", "odd", "close"])
 def test_cut_and_lists_of_many_blocks(Cq, Ck, kind):
     rng = np.random.default_rng(Cq * 7 + Ck)
