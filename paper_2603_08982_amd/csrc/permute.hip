@@ -15,6 +15,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxLabels = 8192;  // most labels the entry points accept
+constexpr int kManyLabels = 3700;  // labels from which scatter_kernel keeps neither positions nor an order in LDS
 
 __device__ __forceinline__ int token_label(const int32_t* labels, int64_t i, int64_t nv, int C) {
   if (i >= nv) return C;  // tail pseudo-cluster
@@ -138,12 +139,17 @@ scan_kernel(int32_t* __restrict__ chunk_hist, int64_t N, int C, int nchunks,
 // side by side, and the chunk's tokens are put in order in LDS first, so that a store writes runs of positions. 40 heads
 // of 75,600 random labels of 1,000 / 100: 38 / 16 us with waves that claimed their positions one after the other and
 // stored from there, 25 / 19 stored from the tokens' own order, 23 / 15 now; one head 8.5 -> 6.7.
+// MANY labels leave a chunk no runs to store, and the table of positions and the order leave two workgroups a CU from
+// 3,700 labels on, one from 6,000: there tokens are stored from their own order, each by its label's first position
+// from global memory. The whole sort of 100 heads of 75,600, us (positions claimed wave by wave, in order, this): 3,000
+// labels 186, 136, 145; 4,000 212, 245, 151; 8,192 329, 419, 207; 8 heads of 20,000: 40, 29, 24; 49, 36, 26; 77, 48, 37.
+template <bool MANY>
 __global__ void __launch_bounds__(kThreads)
 scatter_kernel(const int32_t* __restrict__ labels, int64_t N, int64_t nv, int C, int nchunks,
                const int32_t* __restrict__ chunk_hist, int32_t* __restrict__ perm) {
   constexpr int WAVES = kThreads / 64, ITERS = kSortChunk / kThreads;
-  extern __shared__ int32_t base[];                         // C + 1 first positions of the chunk's labels
-  uint16_t* cnt = reinterpret_cast<uint16_t*>(base + C + 1);  // [wave][C + 1]: counts, then of the waves before
+  extern __shared__ int32_t base[];  // C + 1 first positions of the chunk's labels (MANY: only what follows)
+  uint16_t* cnt = reinterpret_cast<uint16_t*>(base + (MANY ? 0 : C + 1));  // [wave][C + 1]: counts, then of the waves before
   const int bh = blockIdx.y, chunk = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int32_t* hist = chunk_hist + ((int64_t)bh * nchunks + chunk) * (C + 1);
@@ -158,8 +164,11 @@ scatter_kernel(const int32_t* __restrict__ labels, int64_t N, int64_t nv, int C,
     const int64_t i = first + 64 * it;
     my[it] = i < N ? token_label(lab, i, nv, C) : C + 1;
   }
+  int at[ITERS];  // MANY: first position of the token's label
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) at[it] = MANY && my[it] <= C ? hist[my[it]] : 0;
   for (int c = threadIdx.x; c <= C; c += kThreads) {
-    base[c] = hist[c];
+    if constexpr (!MANY) base[c] = hist[c];
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) cnt[w * (C + 1) + c] = 0;
   }
@@ -184,6 +193,15 @@ scatter_kernel(const int32_t* __restrict__ labels, int64_t N, int64_t nv, int C,
     __builtin_amdgcn_wave_barrier();  // the next step reads what other lanes wrote
   }
   __syncthreads();
+  if constexpr (MANY) {
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      if (my[it] > C) continue;
+      for (int w = 0; w < wave; ++w) rank[it] += cnt[w * (C + 1) + my[it]];
+      out[at[it] + rank[it]] = (int32_t)(first + 64 * it);
+    }
+    return;
+  }
   // first place of every (label, wave) in the chunk's order: each thread takes a contiguous run of labels
   __shared__ int wave_sum[WAVES];
   const int per = (C + kThreads) / kThreads, c_lo = threadIdx.x * per, c_hi = min(C + 1, c_lo + per);
@@ -384,16 +402,16 @@ int sort_labels(const int32_t* labels, int BH, int64_t N, int64_t n_tail, int C,
   scan_kernel<<<BH, kScanThreads, 2 * (C + 1) * sizeof(int32_t), s>>>(chunk_hist, N, C, nchunks, offsets, tiles, tile_cap,
                                                                   tile_len);
   SVGEAR_LAUNCH_CHECK();
-  // C + 1 positions and four counters of 16 bits a label. (The limit is raised in every call and to what the most labels
-  // take: the kernel's static 8 KB count too, so that the default is passed from some 4,800 labels on, and a call of
-  // another thread never finds it below its own need.)
-  const auto scatter_lds = [](int labels) {
-    return (size_t)(labels + 1) * (sizeof(int32_t) + kThreads / 64 * sizeof(uint16_t));
+  // four counters of 16 bits a label and, below kManyLabels, C + 1 positions. (The limit is raised in every call and to
+  // what the most labels take: static LDS counts too, and a call of another thread never finds it below its own need.)
+  const bool many = C >= kManyLabels;
+  const auto scatter_lds = [=](int labels) {
+    return (size_t)(labels + 1) * ((many ? 0 : sizeof(int32_t)) + kThreads / 64 * sizeof(uint16_t));
   };
-  const size_t lds = scatter_lds(C);
-  SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(scatter_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)scatter_lds(kMaxLabels)));
-  scatter_kernel<<<grid, kThreads, lds, s>>>(labels, N, nv, C, nchunks, chunk_hist, perm);
+  auto scatter = many ? scatter_kernel<true> : scatter_kernel<false>;
+  SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(scatter), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)scatter_lds(many ? kMaxLabels : kManyLabels)));
+  scatter<<<grid, kThreads, scatter_lds(C), s>>>(labels, N, nv, C, nchunks, chunk_hist, perm);
   SVGEAR_LAUNCH_CHECK();
   return SVGEAR_OK;
 }
