@@ -47,10 +47,7 @@ constexpr int kMaxCentroids = 8192;             // most centroids per head the e
 std::atomic<int> g_list_min_centroids{400};
 // (in the second iteration of a cold start the radii still reach every centroid, so no cluster gets
 // a list: the lists start one iteration later)
-#ifndef SVGEAR_LIST_FROM
-#define SVGEAR_LIST_FROM 2
-#endif
-constexpr int kListFromIteration = SVGEAR_LIST_FROM;
+constexpr int kListFromIteration = 2;
 
 // Prepares the caller's centroids for the matrix cores (later iterations: publish_centroid):
 //  * cn[c] = |c|^2 as ONE fp32 fma chain over t = 0..d-1 (+inf for the padding centroids that

@@ -185,21 +185,11 @@ sbar_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, cons
 // run_sbar asks for one a CU.
 constexpr int kSbarWaves = 8;
 
-// dims h, 2 + h, 4 + h ... of a row: the operands of steps 0 .. D/2 - 1 for lane half h
+// dims h, 2 + h, 4 + h ... of a row: the operands of steps 0 .. D/2 - 1 for lane half h. The lane halves fetch
+// alternate 16-byte pieces of the row, each piece once, and exchange them (v_permlane32_swap: the high lanes of one
+// register for the low lanes of another).
 template <int D>
 __device__ __forceinline__ void row_operands(const float* row, int h, float (&x)[D / 2]) {
-#pragma unroll
-  for (int t = 0; t < D / 4; ++t) {
-    const float4 v = *reinterpret_cast<const float4*>(row + 4 * t);
-    x[2 * t] = h ? v.y : v.x;
-    x[2 * t + 1] = h ? v.w : v.z;
-  }
-}
-
-// The same operands from half the fetches: the lane halves take alternate 16-byte pieces of the row and
-// exchange them (v_permlane32_swap: the high lanes of one register for the low lanes of another).
-template <int D>
-__device__ __forceinline__ void row_operands_swapped(const float* row, int h, float (&x)[D / 2]) {
   auto swap = [](float a, float b, float& lo, float& hi) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     lo = __uint_as_float(r[0]);  // a of the low lanes, b of the low lanes
@@ -242,12 +232,12 @@ sbar_mfma_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
   const int32_t* off = k_offsets + (int64_t)bh * (Ck + 2);
   const int a = a0 + li;
   float q[D / 2];
-  row_operands_swapped<D>(qbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * D, lh, q);
+  row_operands<D>(qbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * D, lh, q);
   float* out = sbar + ((int64_t)bh * Cq + min(a, Cq - 1)) * Ck;
   float mx = -INFINITY;
   for (int b0 = 32 * wave; b0 < Ck; b0 += 32 * kSbarWaves) {
     float kf[D / 2];
-    row_operands_swapped<D>(kbar + ((int64_t)bh * Ck + min(b0 + li, Ck - 1)) * D, lh, kf);
+    row_operands<D>(kbar + ((int64_t)bh * Ck + min(b0 + li, Ck - 1)) * D, lh, kf);
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -349,7 +339,7 @@ block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__
     for (int j0 = start + 32 * quarter; j0 < end; j0 += 128) {
       const int j = min(j0 + li, end - 1);  // (rows past the cluster's end are not counted below)
       float kf[QS];
-      row_operands_swapped<D>(kh + (int64_t)j * D, lh, kf);
+      row_operands<D>(kh + (int64_t)j * D, lh, kf);
       float nd = 0.f, dd = 0.f;
       if (VALUE_AWARE) {
         const float4* vr = reinterpret_cast<const float4*>(vh + (int64_t)j * D + lh * QS);
@@ -377,7 +367,7 @@ block_error_f32_kernel(const float* __restrict__ qbar, const float* __restrict__
       for (int i = 0; i < NB; ++i) {
         if (i >= nb) break;
         float q[QS];
-        row_operands_swapped<D>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D, lh, q);
+        row_operands<D>(qbar + ((int64_t)bh * Cq + min(a0 + 32 * i + li, Cq - 1)) * D, lh, q);
         f32x16 acc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.f;

@@ -260,10 +260,9 @@ __device__ __forceinline__ void list_row(const uint32_t* words, int W, int32_t p
 }
 
 // Bit mask, CSR lists and routed cost of one head (all threads of a workgroup of kSelThreads), a wave
-// per row of blocks; key_of(a): the cut of row a. rowcnt: Cq + 2 ints of LDS.
-template <class KeyOf>
+// per row of blocks. rowcnt: Cq + 2 ints of LDS.
 __device__ __forceinline__ void build_head(const float* sc, const int32_t* qo, const int32_t* ko, int Cq, int Ck, int bh,
-                                           KeyOf key_of, int32_t* rowcnt, unsigned long long* cost_sum,
+                                           uint64_t cut, int32_t* rowcnt, unsigned long long* cost_sum,
                                            uint32_t* mask_bits, int32_t* row_ptr, int32_t* col_idx,
                                            int64_t* routed_cost) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -274,7 +273,7 @@ __device__ __forceinline__ void build_head(const float* sc, const int32_t* qo, c
   __syncthreads();
   long long my_cost = 0;
   for (int a = wave; a < R; a += NWAVES) {
-    const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, a < Cq ? key_of(a) : 0ull, mb + (int64_t)a * W, my_cost);
+    const int cnt = mask_row(sc, qo, ko, Cq, Ck, a, a < Cq ? cut : 0ull, mb + (int64_t)a * W, my_cost);
     if (lane == 0) rowcnt[a] = cnt;
   }
 #pragma unroll
@@ -382,8 +381,7 @@ route_small_kernel(const float* __restrict__ scores, const int32_t* __restrict__
     key = block_key(sc[it], (uint32_t)it);
     return true;
   });
-  build_head(sc, qo, ko, Cq, Ck, bh, [&](int) { return cut; }, rowcnt, &cost_sum, mask_bits, row_ptr, col_idx,
-             routed_cost);
+  build_head(sc, qo, ko, Cq, Ck, bh, cut, rowcnt, &cost_sum, mask_bits, row_ptr, col_idx, routed_cost);
 }
 
 // ---- one budget over many blocks ---------------------------------------------------------
