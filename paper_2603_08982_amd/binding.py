@@ -379,19 +379,18 @@ def attention_layer(Q, K, V, init_q, init_k, iters: int, budget_cost: int, n_tai
     overlap=True uses a second stream of default priority for Q's side of the k-means and
     permutation stages (they do not depend on K's and V's; the small kernels of one stream fill
     the gaps of the other), joined before the probe, which needs the queries' offsets. (One fork and
-    one join for both stages: each pair costs the host 37 us, a fifth of a layer of 667 tokens.)
+    one join for both stages, since a pair costs the host 37 us of the 245 that a layer of 667 tokens takes;
+    with mark, which tells the stages apart, a pair for each.)
 
     init_q [B,H,Cq,d], init_k [B,H,Ck,d] fp32 are the starting centroids (updated in place,
     so a caller can carry them to the next denoising step). With top_p the routing budget is
     the adaptive per-query-cluster one and budget_cost is ignored. mark(name), if given, is
     called on the current stream after each stage ("kmeans", "permute", "probe_route",
-    "attention", "unpermute"; with overlap, "kmeans" and "permute" mark K's and V's side, and the
-    join with Q's falls into "permute"). Returns (O, intermediates)."""
+    "attention", "unpermute"). Returns (O, intermediates)."""
     B, H, N, d = Q.shape
     if scale is None:
         scale = float(d) ** -0.5
     Cq, Ck = init_q.shape[2], init_k.shape[2]
-    mark = mark or (lambda name: None)
     km_q, km_k = lambda: kmeans(Q, init_q, iters, n_tail), lambda: kmeans(K, init_k, iters, n_tail, x2=V)
     pm_q = lambda lab: permute(lab, Cq, [] if token_order else [Q], n_tail)
     pm_k = lambda lab: permute(lab, Ck, [K, V], n_tail)
@@ -402,15 +401,17 @@ def attention_layer(Q, K, V, init_q, init_k, iters: int, budget_cost: int, n_tai
 
     def k_side():
         r = km_k()
-        mark("kmeans")
         return r, pm_k(r[0])
 
-    if overlap:
+    one_pair = overlap and mark is None
+    mark = mark or (lambda name: None)
+    if one_pair:
         (q, q_rows), (k, k_rows) = run_pair(q_side, k_side)
     else:
-        q, k = km_q(), km_k()
+        pair = run_pair if overlap else (lambda f, g: (f(), g()))
+        q, k = pair(km_q, km_k)
         mark("kmeans")
-        q_rows, k_rows = pm_q(q[0]), pm_k(k[0])
+        q_rows, k_rows = pair(lambda: pm_q(q[0]), lambda: pm_k(k[0]))
     (lab_q, qcnt, _), (lab_k, kcnt, vbar) = q, k
     (perm_q, qoff, q_rows), (perm_k, koff, (Kp, Vp)) = q_rows, k_rows
     mark("permute")
