@@ -30,8 +30,17 @@ static inline dim3 long_grid(int64_t blocks) {
 }
 __device__ __forceinline__ int long_grid_index() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
 
-// |delta_j|^2 and -2 vbar . delta_j of every clustered key (delta_j = v_j - vbar of its cluster), bf16 inputs: what the
-// block errors need of the values. 256 threads per (head, key cluster): 16 key slots x 16 lanes of 8 dims (d = 64: 32 x 8).
+// A power of two near the largest component of a cluster's mean value (bf16 inputs): the block errors take their
+// weights' differences times it, so that squares summed before they meet |vbar|^2 stay as far from the ends of a
+// float's range as the errors themselves do.
+__device__ __forceinline__ float value_scale(float largest) {
+  const int e = (int)(__float_as_uint(largest) >> 23 & 255u);
+  return __uint_as_float((uint32_t)min(max(e, 127 - 60), 127 + 62) << 23);
+}
+__device__ __forceinline__ float inverse_scale(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
+
+// |delta_j|^2 and -2 vbar . delta_j / value_scale of every clustered key (delta_j = v_j - vbar of its cluster), bf16
+// inputs: what the block errors need of the values. 256 threads per (head, key cluster): 16 key slots x 16 lanes of 8 dims (d = 64: 32 x 8).
 // They depend on nothing the centroid logits compute, so both share a launch, the logits' workgroups first: 5 heads,
 // 200 x 500 centroids 20 + 29 us apart, 38 together; 8 x 2,000 keys, 30 x 60: the whole call 39 -> 33. (Not with the
 // matrix-core form of the logits, whose registers cost the streaming half its waves: 40 heads, 300 x 1,000 centroids
@@ -58,6 +67,12 @@ __device__ __forceinline__ void value_stats(const ValueStats& p, const int32_t* 
   float vbl[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) vbl[k] = vb[k];
+  float largest = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) largest = fmaxf(largest, fabsf(vbl[k]));
+#pragma unroll
+  for (int o = LPK / 2; o > 0; o >>= 1) largest = fmaxf(largest, __shfl_xor(largest, o));
+  const float dd_scale = -2.0f * inverse_scale(value_scale(largest));
   const bf16_t* vh = p.vp + (int64_t)bh * p.Nk * D + lane * 8;
   constexpr int INFLIGHT = 4;  // independent key fetches per lane group
   for (int j0 = start + slot; j0 < end; j0 += INFLIGHT * SLOTS) {
@@ -88,7 +103,7 @@ __device__ __forceinline__ void value_stats(const ValueStats& p, const int32_t* 
       }
       if (lane == 0 && j < end) {
         p.nd[(int64_t)bh * p.stride + j] = p_nd;
-        p.dd[(int64_t)bh * p.stride + j] = -2.0f * p_dd;
+        p.dd[(int64_t)bh * p.stride + j] = dd_scale * p_dd;
       }
     }
   }
@@ -462,8 +477,8 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   // scores of the workgroup's key clusters, per wave [query centroid][key cluster]: they leave together at the
   // end, 16 bytes at a time, instead of each by itself a score row apart
   __shared__ __attribute__((aligned(16))) float sc[kProbeWaves][32][kProbeClusters];
-  // centroid weights W of the wave's query centroids and |vbar|^2 of the key clusters
-  __shared__ float s_w[kProbeWaves][kProbeClusters][32], s_nvb[kProbeClusters];
+  // centroid weights W of the wave's query centroids; value_scale and |vbar|^2 over its square of the key clusters
+  __shared__ float s_w[kProbeWaves][kProbeClusters][32], s_scale[kProbeClusters], s_nvb[kProbeClusters];
   // The groups of query centroids that read the same keys run side by side on one XCD (workgroups go round-robin
   // over the eight): every eight workgroups take eight sets of clusters, the next eight the same sets again.
   const int sets = (Ck + clusters - 1) / clusters * heads;
@@ -522,12 +537,22 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
   if (VALUE_AWARE) {  // |vbar_b|^2: D/64 dims per lane, then across the wave
     for (int i = wave; i < clusters; i += kProbeWaves) {
       const float* vb = vbar + ((int64_t)bh * Ck + min(b_lo + i, Ck - 1)) * D;
-      float nvb = 0.f;
+      float nvb = 0.f, largest = 0.f;
 #pragma unroll
-      for (int t = 0; t < D / 64; ++t) nvb = __builtin_fmaf(vb[lane + 64 * t], vb[lane + 64 * t], nvb);
+      for (int t = 0; t < D / 64; ++t) {
+        nvb = __builtin_fmaf(vb[lane + 64 * t], vb[lane + 64 * t], nvb);
+        largest = fmaxf(largest, fabsf(vb[lane + 64 * t]));
+      }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) nvb += __shfl_xor(nvb, o);
-      if (lane == 0) s_nvb[i] = nvb;
+      for (int o = 32; o > 0; o >>= 1) {
+        nvb += __shfl_xor(nvb, o);
+        largest = fmaxf(largest, __shfl_xor(largest, o));
+      }
+      if (lane == 0) {
+        const float scale_b = value_scale(largest), inv = inverse_scale(scale_b);
+        s_scale[i] = scale_b;
+        s_nvb[i] = nvb * inv * inv;
+      }
     }
   }
   SVGEAR_WAIT_VMCNT(0);  // from here on vmcnt counts the block copies only
@@ -586,7 +611,7 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
     issue(fc, issued);
     advance(fc);
   }
-  float E = 0.f, W = 0.f, nvb = 0.f;
+  float E = 0.f, U = 0.f, W = 0.f, vs = 1.f, nvb = 0.f;
   f32x16 acc_even, acc_odd;  // logits of the even and odd blocks
   // logits of block k (MF) and errors of block k - 1 (RANK: 0 none, 1 a full block, 2 a cluster's last one,
   // whose unused rows do not count)
@@ -628,27 +653,27 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       if (D == 64 && s + 1 < KSN) rd_stats(s + 1);
       if constexpr (RANK != 0) {
         // register r is key j0 + 8(r/4) + 4lh + r%4, query centroid a. Per key, with u = W - w:
-        //   |W vbar - w v_j|^2 = u (u |vbar|^2 - 2 w vbar.delta_j) + w (w |delta_j|^2)
-        // (the norm inside the term: a sum of u^2 alone, a multiplication less a pair and 1 % of the call above, would
-        // leave the range of a float where the errors do not: 6,200 keys at the cap, weights below e^-44)
+        //   |W vbar - w v_j|^2 = u^2 |vbar|^2 + w (-2 u vbar.delta_j + w |delta_j|^2),
+        // the u^2 in a sum of their own, which takes its factor at the end of the cluster; u comes times value_scale,
+        // its other factors over it (unscaled, 6,200 keys at the cap overflowed the sum whatever the values were, and
+        // weights below e^-44 lost digits; with |vbar|^2 in the term instead, a multiplication more a pair: 2 % of
+        // the call above)
 #pragma unroll
         for (int r = s * RPS; r < (s + 1) * RPS; ++r) {
           const float w = __builtin_amdgcn_exp2f(fminf(__builtin_fmaf(acc[r], scale2, neg_m2), cap2));
-          const float u = W - w;
-          float e;
-          if (VALUE_AWARE) {
-            e = __builtin_fmaf(u, __builtin_fmaf(w, dl[r], u * nvb), E);
-            e = __builtin_fmaf(w, w * nn[r], e);
-          } else {
-            e = __builtin_fmaf(u, u, E);
-          }
-          // (an unused row, which repeats the cluster's last key, does not count: a select of the sum, no
+          const float u = VALUE_AWARE ? __builtin_fmaf(-vs, w, W) : W - w;
+          float uu = __builtin_fmaf(u, u, U), e = E;
+          if (VALUE_AWARE) e = __builtin_fmaf(w, __builtin_fmaf(u, dl[r], w * nn[r]), E);
+          // (an unused row, which repeats the cluster's last key, does not count: a select of the sums, no
           // product of 0 with a value that has overflowed, and no branch per register: the compiler would
           // rather make one)
           if constexpr (RANK == 2) {
-            asm volatile("" : "+v"(e));
-            e = pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end ? e : E;
+            asm volatile("" : "+v"(uu), "+v"(e));
+            const bool used = pc.j0 + 8 * (r >> 2) + 4 * lh + (r & 3) < pc.end;
+            uu = used ? uu : U;
+            e = used ? e : E;
           }
+          U = uu;
           E = e;
         }
       }
@@ -679,9 +704,13 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       return true;
     }
     if (pc.j0 == pc.start) {  // first block of key cluster pc.b
-      E = 0.f;
+      E = U = 0.f;
       W = s_w[wave][pc.b - b_lo][li];
-      nvb = VALUE_AWARE ? s_nvb[pc.b - b_lo] : 0.f;
+      if (VALUE_AWARE) {
+        vs = s_scale[pc.b - b_lo];
+        nvb = s_nvb[pc.b - b_lo];
+        W *= vs;
+      }
     }
     if (wave_on) {
       const bool full = pc.j0 + 32 <= pc.end;
@@ -690,7 +719,9 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
       else if (full) block(k, acc_new, acc, std::false_type{}, Full{});
       else block(k, acc_new, acc, std::false_type{}, Last{});
       if (pc.j0 + 32 >= pc.end) {  // last block of the cluster
-        const float Et = E + __shfl_xor(E, 32);
+        // (both lanes' sums first: a lane without a key would multiply 0 by a norm that may have overflowed)
+        float Et = U + __shfl_xor(U, 32);
+        if (VALUE_AWARE) Et = __builtin_fmaf(Et, nvb, E + __shfl_xor(E, 32));
         if (lh == 0) sc[wave][li][pc.b - b_lo] = Et / (float)(pc.end - pc.start);
       }
     }
