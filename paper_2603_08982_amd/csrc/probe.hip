@@ -534,24 +534,34 @@ block_error_mfma_kernel(const bf16_t* __restrict__ q3, const float* __restrict__
     for (int i = 0; i < kProbeClusters; ++i)
       if (lh == 0) s_w[wave][i][li] = live ? __expf(fminf(w[i] - m_a, kMaxExponent)) : 0.f;
   }
-  if (VALUE_AWARE) {  // |vbar_b|^2: D/64 dims per lane, then across the wave
-    for (int i = wave; i < clusters; i += kProbeWaves) {
-      const float* vb = vbar + ((int64_t)bh * Ck + min(b_lo + i, Ck - 1)) * D;
-      float nvb = 0.f, largest = 0.f;
+  if (VALUE_AWARE) {  // |vbar_b|^2 and value_scale: D/64 dims per lane, then across the wave, its clusters side by side
+    constexpr int PER = kProbeClusters / kProbeWaves;
+    float nvb[PER], largest[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const float* vb = vbar + ((int64_t)bh * Ck + min(b_lo + wave + u * kProbeWaves, Ck - 1)) * D;
+      nvb[u] = largest[u] = 0.f;
 #pragma unroll
       for (int t = 0; t < D / 64; ++t) {
-        nvb = __builtin_fmaf(vb[lane + 64 * t], vb[lane + 64 * t], nvb);
-        largest = fmaxf(largest, fabsf(vb[lane + 64 * t]));
+        const float v = vb[lane + 64 * t];
+        nvb[u] = __builtin_fmaf(v, v, nvb[u]);
+        largest[u] = fmaxf(largest[u], fabsf(v));
       }
+    }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        nvb += __shfl_xor(nvb, o);
-        largest = fmaxf(largest, __shfl_xor(largest, o));
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        nvb[u] += __shfl_xor(nvb[u], o);
+        largest[u] = fmaxf(largest[u], __shfl_xor(largest[u], o));
       }
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const float scale_b = value_scale(largest[u]), inv = inverse_scale(scale_b);
       if (lane == 0) {
-        const float scale_b = value_scale(largest), inv = inverse_scale(scale_b);
-        s_scale[i] = scale_b;
-        s_nvb[i] = nvb * inv * inv;
+        s_scale[wave + u * kProbeWaves] = scale_b;
+        s_nvb[wave + u * kProbeWaves] = nvb[u] * inv * inv;
       }
     }
   }
