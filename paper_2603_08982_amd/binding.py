@@ -379,8 +379,8 @@ def attention_layer(Q, K, V, init_q, init_k, iters: int, budget_cost: int, n_tai
     overlap=True uses a second stream of default priority for Q's side of the k-means and
     permutation stages (they do not depend on K's and V's; the small kernels of one stream fill
     the gaps of the other), joined before the probe, which needs the queries' offsets. (One fork and
-    one join for both stages, since a pair costs the host 37 us of the 245 that a layer of 667 tokens takes;
-    with mark, which tells the stages apart, a pair for each.)
+    one join for both stages, since a pair costs the host some 40 us: 2 heads of 667 tokens take 192 us with one pair,
+    231 with two; with mark, which tells the stages apart, a pair for each.)
 
     init_q [B,H,Cq,d], init_k [B,H,Ck,d] fp32 are the starting centroids (updated in place,
     so a caller can carry them to the next denoising step). With top_p the routing budget is

@@ -444,11 +444,11 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
 // Nothing else is fetched in the loop: a load the compiler waits for would drain the copies.
 // A block of a wave is 24 MFMAs (d = 128, 768 cycles of its SIMD) and as long on the vector ALU for the errors
 // of its 512 pairs, and a SIMD holds two waves (96 registers of centroid fragments; three waves spill): the errors
-// of block k - 1 are written between the MFMAs of block k. Counters: vector ALU busy 53 %, matrix cores 38 %, the
-// two hardly at the same time. 40 heads, 300 x 1,000 centroids, the whole call: 1,870 us with the weights and
-// bounds of a cluster fetched when it begins, 1,660 with all of a workgroup's fetched at its start, 1,605 with a
-// barrier per pair of blocks, some 1,500 with no branch per register in a cluster's last block and the groups of query
-// centroids side by side on an XCD. Two waves a workgroup, no wave without centroids at 300 of them, took the same.
+// of block k - 1 are written between the MFMAs of block k. At 40 heads, 300 x 1,000 centroids vector issue is busy 54 % of
+// the launch, the matrix cores 41 %, with 233 vector and 105 scalar instructions a block of a wave. The whole call: 1,870 us
+// with the weights and bounds of a cluster fetched when it begins, 1,660 with all of a workgroup's fetched at its start,
+// 1,605 with a barrier per pair of blocks, some 1,500 with no branch per register in a cluster's last block and the groups
+// of query centroids side by side on an XCD. Two waves a workgroup, no wave without centroids at 300 of them, took the same.
 // d = 64 has half the MFMAs and fragments and is bound by the vector ALU and latencies: three waves a SIMD,
 // for which the statistics are read group by group (240 heads x 2,000 keys, 60 clusters, 30 centroids: the
 // whole call 127 us with two waves, 103 with three).
