@@ -65,7 +65,7 @@ constexpr int kSmallRows = 16384;  // most rows a head (the member lists of a gr
 constexpr int kSmallIterations = 1 << 16;  // most iterations (tasks are counted in 32 bits)
 
 // Whether a call of these sizes takes the small path.
-bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters);
+bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters, bool bf16);
 int launch_kmeans_small(SmallKmeans a, int d, bool bf16, hipStream_t s);
 
 }  // namespace svgear

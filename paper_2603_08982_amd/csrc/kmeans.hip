@@ -1459,7 +1459,7 @@ int run_kmeans(const T* x, const T* x2, int BH, int H, int64_t N, int64_t n_tail
     SVGEAR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(filter),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_f));
   const dim3 gp((unsigned)ceil_div((int64_t)Cpad * D, 256 * 4), BH);
-  if (one_launch && kmeans_small_takes(BH, nv, C, iters)) {
+  if (one_launch && kmeans_small_takes(BH, nv, C, iters, kFilter)) {
     prep_centroids_kernel<<<gp, 256, 0, s>>>(cent, C, Cpad, D, cperm, cn, nullptr, nullptr, nullptr, nullptr, nullptr,
                                              small_state, small_norms);
     SVGEAR_LAUNCH_CHECK();

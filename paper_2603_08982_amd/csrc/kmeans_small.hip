@@ -47,7 +47,7 @@ __device__ __forceinline__ void store_shared(__amdgpu_buffer_rsrc_t t, int byte,
 // Eight waves a workgroup, one workgroup a CU (some 220 to 250 registers a lane: the row operands, two sets of
 // centroid fragments, 16 rows in flight).
 constexpr int kWaves = 8;
-constexpr int kMaxParts = 4;      // most parts a cluster is summed in (means_parts)
+constexpr int kMaxParts = 8;      // most parts a cluster is summed in (means_parts)
 constexpr int kLongCluster = 256;  // rows from which a cluster is summed by four waves wherever it lies
 __host__ __device__ static inline int small_share(int n) { return ((n + kWaves - 1) / kWaves + 255) & ~255; }
 // |c|^2 of eight centroids to a cache line
@@ -463,20 +463,24 @@ int set_shape(SmallKmeans& a) {
 
 }  // namespace
 
-// While groups are one round of the CUs, tiles one or (four waves a cluster, one block of centroids a wave) two, and no
-// cluster is many workgroups' work on the other path, which gives every part of a cluster its own. Measured against that
-// path over 1 to 300 heads of 130 to 16,384 rows, 1 to 2,000 centroids, both types and head sizes, 2, 4 and 10
-// iterations, rows spread evenly over 128 components or nine in ten of them in one cluster:
-//  * inside: 1.46 times as fast on average, two to five times where an fp32 call has a dominant cluster, 0.93 to 1 in
-//    the least favourable variants: two iterations of a few hundred rows (36 -> 38 us, in a layer ten launches less),
-//    and bf16 calls of 10 iterations with a dominant cluster, most of whose rows the other path stops assigning
-//    (2 x 4,800, 300 centroids 282 -> 302 us; 16 x 4,800, 10 centroids 270 -> 292; with 4 iterations as fast or faster);
-//  * more groups: 40 x 300, 64 centroids 0.84, 100 x 300, 48 0.63, 300 x 300, 5 0.46;
-//  * more tiles: 12 x 2,400, 100 centroids 0.80, 5 x 4,800, 200 0.73, 24 x 4,800, 48 0.59;
-//  * more parts: 1 x 16,384 rows in 16 clusters (8 parts) 0.56, 12 x 2,400 in 2 (8) 0.75, 1 x 2,400 in 4 (5) 0.89;
-//    3 and 4 parts of long heads that leave CUs idle: 1 x 16,384 in 32 0.67, 3 x 8,100 in 20 0.84, 1 x 6,300 in 16 0.72;
-//  * one or two workgroups a head: 100 x 630, 2 centroids 0.85.
-bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters) {
+// Two lines, since which way is faster depends on the rows. Measured against the launches of their own, which give every
+// part of a cluster a workgroup but wait for the longest one and assign undecided rows again; 2, 4 and 10 iterations.
+//  * One round: groups within a round of the CUs, tiles within one or (four waves a cluster, one block of centroids a
+//    wave) two, no cluster many workgroups' work. Faster whatever the rows: over 1 to 300 heads of 130 to 16,384 rows in
+//    1 to 2,000 clusters, spread evenly over 128 components or nine in ten in one cluster, 1.46 times on average, 0.93 to 1
+//    in the least favourable variants (two iterations of a few hundred rows 36 -> 38 us; bf16, 10 iterations, a dominant
+//    cluster: 2 x 4,800, 300 centroids 282 -> 302, 16 x 4,800, 10 centroids 270 -> 292).
+//  * Some rounds more: faster for rows as a video model has them (32 to 256 components that follow the position, a fifth of
+//    the rows strayed, centroids started at rows, so that some clusters hold several components), slower for even ones.
+//    Of 149 calls and layers of such rows between the lines, single calls, us step by step and here: bf16 5 x 13,230, 31
+//    centroids 153 -> 73; 24 x 3,528, 24 151 -> 76; 40 x 2,592, 31 420 -> 212; 8 x 2,376, 226 82 -> 66; fp32 2 x 11,200, 31
+//    302 -> 174; 12 x 8,316, 31 610 -> 392; layers of 1 x 13,300, 20 / 28 622 -> 316, 5 x 7,000, 13 / 33 780 -> 598. With the
+//    wider line none of them is more than 1 % slower than where it lay before the first line was drawn. Even rows lose
+//    there: 12 x 2,400 fp32 rows, 100 centroids 0.80, 24 x 4,800, 48 0.59, 1 x 16,384 in 16 0.56.
+//    Past it: 40 x 4,180 bf16 rows, 43 centroids (1,320 tiles) 278 -> 292; fp32 layers, whose tiles take longer, 40 x
+//    1,650, 56 key clusters 947 -> 1,189, 12 x 12,720, 11 / 34 2,166 -> 2,270; more than 64 centroids of many heads, 24 x
+//    1,680 to 3,400 rows 1.1 times as long.
+bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters, bool bf16) {
   if (BH > 64 || nv > kSmallRows || iters > kSmallIterations) return false;
   SmallKmeans a{};
   a.BH = (int)BH;
@@ -484,8 +488,10 @@ bool kmeans_small_takes(int64_t BH, int64_t nv, int C, int iters) {
   a.C = C;
   const int share = set_shape(a);
   const int64_t tiles = BH * a.tiles, groups = BH * a.groups;
-  if (a.parts > 2 && (a.parts > kMaxParts || (BH < 8 && nv > 5000))) return false;
-  return groups <= 256 && (tiles <= 256 || (tiles <= 512 && share == 4 && C <= 128));
+  const bool long_clusters = a.parts > 2 && (a.parts > 4 || (BH < 8 && nv > 5000));
+  if (groups <= 256 && (tiles <= 256 || (tiles <= 512 && share == 4 && C <= 128)) && !long_clusters) return true;
+  if (BH * nv > 200000 || groups > (bf16 ? 576 : 400) || tiles > (bf16 ? 1024 : 448)) return false;
+  return C <= 64 || (BH <= 12 && BH * ceil_div(nv, 64) <= 640 && BH * ceil_div(C, 8) <= 256);
 }
 
 int launch_kmeans_small(SmallKmeans a, int d, bool bf16, hipStream_t s) {

@@ -34,6 +34,7 @@ def _rows(H, N, d, dtype, seed, spread=40):
     (1, 2, 1, 1), (1, 33, 0, 33), (2, 257, 5, 2), (3, 640, 7, 31), (2, 667, 37, 32), (2, 700, 0, 33), (1, 4096, 0, 64),
     (1, 900, 3, 65), (5, 1000, 0, 129), (1, 2049, 1, 8), (2, 5000, 0, 3), (12, 1200, 0, 100), (17, 650, 9, 90),
     (1, 16384, 0, 80), (1, 16385, 0, 80), (8, 9600, 0, 24), (1, 4999, 0, 10), (2, 9600, 0, 100), (1, 9000, 0, 1000), (40, 600, 0, 10), (300, 64, 0, 5),
+    (24, 3528, 0, 24), (8, 2376, 0, 226), (1, 13300, 0, 20), (5, 6000, 1, 9),
 ])
 def test_small_calls_agree_with_the_step_by_step_paths(H, N, tail, C, d, dtype):
     x, x2 = _rows(H, N, d, dtype, 1), _rows(H, N, d, dtype, 2)
