@@ -278,17 +278,29 @@ kmeans_small_kernel(SmallKmeans p) {
     int kept = 0;
     // a bit per cluster of the group that rows came to or left in this iteration: the others keep their means, which
     // would be the same sums again (9,600 bf16 rows of 128, 200 centroids, one with nine rows in ten, 10 iterations:
-    // 706 -> 326 us)
-    uint32_t moved = it == 0 ? ~0u : 0u;
+    // 706 -> 326 us). From the third iteration on: in the second nearly every cluster has moved, and to look costs 1 us.
+    const bool compare = it >= 2;
+    uint32_t moved = compare ? 0u : ~0u;
     const __amdgpu_buffer_rsrc_t labels = shared_table(label_rows(it), (int64_t)n * 4);
-    const __amdgpu_buffer_rsrc_t labels_before = shared_table(label_rows(it > 0 ? it - 1 : it), (int64_t)n * 4);
+    const __amdgpu_buffer_rsrc_t labels_before = shared_table(label_rows(compare ? it - 1 : it), (int64_t)n * 4);
     constexpr int U = 4;
     for (int i0 = lo; i0 < hi; i0 += 256 * U) {
-      u32x4 l[U], b[U];  // (rows past the end read as label 0)
+      u32x4 l[U];  // (rows past the end read as label 0)
 #pragma unroll
       for (int u = 0; u < U; ++u) l[u] = __builtin_amdgcn_raw_buffer_load_b128(labels, (i0 + 256 * u + 4 * lane) * 4, 0, 16);
+      if (compare) {
+        u32x4 b[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) b[u] = __builtin_amdgcn_raw_buffer_load_b128(labels_before, (i0 + 256 * u + 4 * lane) * 4, 0, 16);
+        for (int u = 0; u < U; ++u)
+          b[u] = __builtin_amdgcn_raw_buffer_load_b128(labels_before, (i0 + 256 * u + 4 * lane) * 4, 0, 16);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const unsigned to_c = l[u][e] - (unsigned)c0, from_c = b[u][e] - (unsigned)c0;
+            if (to_c != from_c) moved |= (to_c < (unsigned)G ? 1u << to_c : 0u) | (from_c < (unsigned)G ? 1u << from_c : 0u);
+          }
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = i0 + 256 * u + 4 * lane;
@@ -299,8 +311,6 @@ kmeans_small_kernel(SmallKmeans p) {
           votes[e] = __ballot(l[u][e] - (unsigned)c0 < (unsigned)G && i + e < hi);
           to += __popcll(votes[e] & below);
           kept += __popcll(votes[e]);
-          const unsigned to_c = l[u][e] - (unsigned)c0, from_c = b[u][e] - (unsigned)c0;
-          if (to_c != from_c) moved |= (to_c < (unsigned)G ? 1u << to_c : 0u) | (from_c < (unsigned)G ? 1u << from_c : 0u);
         }
         if (votes[0] | votes[1] | votes[2] | votes[3]) {
 #pragma unroll
@@ -309,16 +319,20 @@ kmeans_small_kernel(SmallKmeans p) {
         }
       }
     }
+    if (compare) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) moved |= __shfl_xor(moved, o);
-    if (lane == 0) s_moved[wave] = (int)moved;
+      for (int o = 32; o > 0; o >>= 1) moved |= __shfl_xor(moved, o);
+      if (lane == 0) s_moved[wave] = (int)moved;
+    }
     __builtin_amdgcn_wave_barrier();
     if (lane < kWaves) s_cnt[wave][lane] = 0;
     for (int e = lane; e < kept; e += 64) atomicAdd(&s_cnt[wave][mine[e] & 7], 1);
     __syncthreads();
     const bool last = it + 1 == p.iters;
+    if (compare) {
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) moved |= (uint32_t)s_moved[w];
+      for (int w = 0; w < kWaves; ++w) moved |= (uint32_t)s_moved[w];
+    }
     if (moved == 0 && !last) return;
     // lane 8 k + w: where wave w's members of cluster k begin
     const int here = s_cnt[lane & 7][lane >> 3];
