@@ -486,12 +486,15 @@ int set_shape(SmallKmeans& a) {
 //    in the least favourable variants (two iterations of a few hundred rows 36 -> 38 us; bf16, 10 iterations, a dominant
 //    cluster: 2 x 4,800, 300 centroids 282 -> 302, 16 x 4,800, 10 centroids 270 -> 292).
 //  * Some rounds more: faster for rows as a video model has them (32 to 256 components that follow the position, a fifth of
-//    the rows strayed, centroids started at rows, so that some clusters hold several components), slower for even ones.
+//    the rows strayed, centroids started at rows, so that some clusters hold several components).
 //    Of 149 calls and layers of such rows between the lines, single calls, us step by step and here: bf16 5 x 13,230, 31
 //    centroids 153 -> 73; 24 x 3,528, 24 151 -> 76; 40 x 2,592, 31 420 -> 212; 8 x 2,376, 226 82 -> 66; fp32 2 x 11,200, 31
 //    302 -> 174; 12 x 8,316, 31 610 -> 392; layers of 1 x 13,300, 20 / 28 622 -> 316, 5 x 7,000, 13 / 33 780 -> 598. With the
-//    wider line none of them is more than 1.2 % slower than by sizes alone (200,000 rows, 64 centroids), 15 are over 5 % faster. Even rows lose
-//    there: 12 x 2,400 fp32 rows, 100 centroids 0.80, 24 x 4,800, 48 0.59, 1 x 16,384 in 16 0.56.
+//    wider line none of them is more than 1.2 % slower than by sizes alone (200,000 rows, 64 centroids), 15 are over 5 % faster.
+//    Rows spread evenly over 128 components, 2 and 10 iterations, step by step and here: bf16 24 x 4,800, 48 centroids
+//    158 -> 128 and 617 -> 521; 5 x 4,800, 200 97 -> 84 and 418 -> 341; fp32 12 x 8,316, 31 136 -> 98 and 641 -> 382; slower with
+//    2 and 4 iterations of one head's long clusters, 1 x 16,384 in 16 67 -> 73 (fp32 78 -> 90), or of many short ones,
+//    bf16 12 x 2,400, 100 61 -> 67; 40 x 300, 64 49 -> 53 (10: 214 -> 161).
 //    Past it: 40 x 4,180 bf16 rows, 43 centroids (1,320 tiles) 278 -> 292; fp32 layers, whose tiles take longer, 40 x
 //    1,650, 56 key clusters 947 -> 1,189, 12 x 12,720, 11 / 34 2,166 -> 2,270; more than 64 centroids of many heads, 24 x
 //    1,680 to 3,400 rows 1.1 times as long.
